@@ -303,7 +303,7 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * map an input is shared by up to 8 outputs and the sum is gathered per input through the inverse map
  * (a tiled map of its own, built on the first such call and kept with km; no atomics, fixed order).
  * MFMA paths: FX_F16 / FX_BF16 with C_in % 64 == 0 and C_out % 64 == 0 (bwd_data: C_in % 64 == 0
- * and C_out % 32 == 0; bwd_weight: C_in % 32 == 0 and C_out % 64 == 0) on tiled maps; everything
+ * and C_out % 32 == 0; bwd_weight: C_in % 8 == 0 and C_out % 8 == 0) on tiled maps; everything
  * else takes scalar kernels.  In the MFMA weight-gradient kernel a tile whose input rows do not all
  * fit the kernel's local memory has its operand transposed by a multiplication with the identity; on
  * such a tile a non-finite value in feat makes the whole 32-channel block of gw that it touches NaN

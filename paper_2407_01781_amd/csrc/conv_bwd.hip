@@ -373,8 +373,9 @@ __global__ void k_conv_transpose_scalar(const int32_t* __restrict__ nbmap, int64
 }
 
 // ---------------------------------------------------------------------------------- weight gradient, MFMA
-// A workgroup owns a block of 32 input channels x 64 output channels of every gw[kappa] and a
-// contiguous range of tiles; its 8 waves split the offsets (wave w: kappa = w, w+8, w+16, w+24), so a wave
+// A workgroup owns a block of 32 input channels x 64 output channels of every gw[kappa] (the last block of a channel
+// count that is not a multiple holds fewer: 16-byte pieces beyond the rows are not staged, and what the operands then
+// hold in those channels only reaches elements of gw that do not exist) and a contiguous range of tiles; its 8 waves split the offsets (wave w: kappa = w, w+8, w+16, w+24), so a wave
 // keeps up to 4 offsets x 2 accumulator tiles (32 ci x 32 co) in registers over the whole range, and two
 // waves per SIMD hide each other's LDS and matrix latencies (16 waves with two offsets each have 128 registers
 // per wave, which the loop does not fit without spilling: 261 us against 208 on a 1 M-voxel LiDAR grid; 4 waves 279).  Per tile the workgroup stages,
@@ -427,7 +428,13 @@ static_assert(kGroupsPerWave == 4 && kTileWaves == 4, "id blocks of four column 
 // Either way a partial sum is made of the same terms in a fixed order.
 enum WgradMode { kWgAll = 0, kWgStaged = 1, kWgOthers = 2 };
 
-template <typename T, int W, int MODE>
+//
+// SHAPE: kWgFull when both channel counts are whole blocks (no masks: with them the sixteen-wave kernel spills 16
+// registers instead of 4), kWgPartial otherwise, kWgNarrow for up to 32 output channels (one accumulator tile per
+// offset instead of two, of which the second would multiply nothing).
+enum WgradShape { kWgFull = 0, kWgPartial = 1, kWgNarrow = 2 };
+
+template <typename T, int W, int MODE, int SHAPE>
 __global__ void __launch_bounds__(64 * W, 1)
 k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
              const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
@@ -437,13 +444,15 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     constexpr int kWgWaves = W;
     constexpr int kGoutSlabsPerWave = kGoutSlabs / kWgWaves;
     constexpr int kWgOffsetsPerWave = (kMaxK3Tiled + kWgWaves - 1) / kWgWaves;
+    constexpr bool kMasked = SHAPE != kWgFull;
+    constexpr int kHalves = SHAPE == kWgNarrow ? 1 : 2;      // 32-channel halves of the block's output channels
     static_assert(kGoutSlabs % kWgWaves == 0, "gout slabs per wave");
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     WgradLds& L = *reinterpret_cast<WgradLds*>(lds_raw);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, h = lane >> 5;
-    const int n_cib = C_in / kWgCi, n_cblk = n_cib * (C_out / kWgCo);
+    const int n_cib = (C_in + kWgCi - 1) / kWgCi, n_cblk = n_cib * ((C_out + kWgCo - 1) / kWgCo);
     // Workgroup b runs on XCD b % 8.  The channel blocks of one tile range read the same gout tiles and
     // id blocks: with the number of ranges a multiple of 8 they get block indices 8 apart, so they share
     // an XCD and its L2 and run side by side.
@@ -453,6 +462,8 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         range = (int)(blockIdx.x / (8 * n_cblk)) * 8 + (blockIdx.x & 7);
     }
     const int cib = blk % n_cib, cob = blk / n_cib;
+    // channels from the block's first to the row's end
+    const int ci_n = kMasked ? C_in - cib * kWgCi : kWgCi, co_n = kMasked ? C_out - cob * kWgCo : kWgCo;
     const int64_t t0 = MODE == kWgOthers ? 0 : n_tiles * range / n_ranges, t1 = MODE == kWgOthers ? n_listed : n_tiles * (range + 1) / n_ranges;
 
     if (tid < kRowBytes / 16) reinterpret_cast<u32x4*>(L.rows + kRowCap * kRowBytes)[tid] = u32x4{0, 0, 0, 0};
@@ -473,11 +484,11 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         ident[1] = vec8_from_words<T>(wds[1]);
     }
 
-    f32x16 acc[kWgOffsetsPerWave][2];
+    f32x16 acc[kWgOffsetsPerWave][kHalves];
 #pragma unroll
     for (int j = 0; j < kWgOffsetsPerWave; ++j)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
+        for (int cb = 0; cb < kHalves; ++cb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][cb][v] = 0.f;
 
@@ -543,7 +554,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
             for (int j = 0; j < kGoutSlabsPerWave; ++j) local[j] = nx_local[j];
 #pragma unroll
             for (int j = 0; j < kWgSlabs; ++j) {
-                if (gr[j] >= 0) {
+                if (gr[j] >= 0 && piece * 8 < ci_n) {
                     const uint16_t* src = feat + (int64_t)gr[j] * C_in + cib * kWgCi + piece * 8;
                     __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(L.rows + (wave + kWgWaves * j) * 1024), 16, 0, 0);
                 }
@@ -555,7 +566,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 const int gpiece = (lane & 7) ^ (((slot >> 1) & 1) << 2);        // the piece stored at position lane & 7
                 if (local[j] < n_valid) {
                     const uint16_t* src = gout + (tile * kTileT + local[j]) * (int64_t)C_out + cob * kWgCo + gpiece * 8;
-                    __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(L.gt + slab * 1024), 16, 0, 0);
+                    if (gpiece * 8 < co_n) __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(L.gt + slab * 1024), 16, 0, 0);
                 } else {
                     *reinterpret_cast<u32x4*>(L.gt + slab * 1024 + lane * 16) = u32x4{0, 0, 0, 0};
                 }
@@ -606,13 +617,16 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                             const uint32_t id = (ids[gj >> 1] >> (16 * (gj & 1))) & 0xFFFFu;
                             const bool staged = id < (uint32_t)n_staged;
                             const int row = staged ? (int)id : kRowCap;
-                            ga[gj & 1][0] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(row, h));
-                            ga[gj & 1][1] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(row, h + 2));
+                            // pieces h and h + 2 of the row; a piece beyond the row's end is zero (the identity product
+                            // below sums over all 32 channels)
+                            const bool has0 = h * 8 < ci_n, has1 = h * 8 + 16 < ci_n;
+                            ga[gj & 1][0] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has0 ? row : kRowCap, h));
+                            ga[gj & 1][1] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has1 ? row : kRowCap, h + 2));
                             if (!staged && id != kNoRow) {
                                 const int64_t gr = id < (uint32_t)win_n ? (int64_t)win_lo + id : (int64_t)my_rows[id - win_n];
                                 const uint16_t* src = feat + gr * C_in + cib * kWgCi + h * 8;
-                                ga[gj & 1][0] = *reinterpret_cast<const vec8*>(src);
-                                ga[gj & 1][1] = *reinterpret_cast<const vec8*>(src + 16);
+                                if (has0) ga[gj & 1][0] = *reinterpret_cast<const vec8*>(src);
+                                if (has1) ga[gj & 1][1] = *reinterpret_cast<const vec8*>(src + 16);
                             }
                         }
                     }
@@ -641,7 +655,8 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                         fT[1] = pack8<T>(t, 8);
                     }
 #pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
+                    for (int cb = 0; cb < kHalves; ++cb) {
+                        if (kMasked && cb == 1 && co_n <= 32) continue;
 #pragma unroll
                         for (int ks = 0; ks < 2; ++ks) {
                             // slots 32g + 16ks + 8h + jv (+ 4), channels 32cb + 16g1 + 4q .. + 3: piece 4cb + 2g1 + q/2
@@ -653,6 +668,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                             const u32x2 hi = tr_read4(src + (general ? 8 : 4) * kGoutRowBytes);
                             acc[j][cb] = Elem<T>::mfma(fT[ks], vec8_from_words<T>(u32x4{lo[0], lo[1], hi[0], hi[1]}), acc[j][cb]);
                         }
+                    }
                 }
             }
         }
@@ -668,9 +684,12 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         if (kappa >= K3) continue;
         float* dst = part + (((int64_t)range_out * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
+        for (int cb = 0; cb < kHalves; ++cb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) dst[(int64_t)(8 * (v >> 2) + 4 * h + (v & 3)) * C_out + cb * 32] = acc[j][cb][v];
+            for (int v = 0; v < 16; ++v) {
+                const int ci = 8 * (v >> 2) + 4 * h + (v & 3);
+                if (ci < ci_n && cb * 32 + n < co_n) dst[(int64_t)ci * C_out + cb * 32] = acc[j][cb][v];
+            }
     }
 }
 
@@ -973,7 +992,11 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
             return leaf_wgrad("sparse convolution weight gradient (leaf-window kernel)", km->gin, d_feat, d_gout, dt, C_in,
                               C_out, d_gw, out_dt, st);
     }
-    bool mfma = dt != FX_F32 && km->n_tiles > 0 && C_in % kWgCi == 0 && C_out % kWgCo == 0 && !force_scalar();
+    // The tile kernel takes rows in whole 16-byte pieces: channel counts that are multiples of 8, in partial blocks
+    // where they are not whole ones (f16, 32 -> 32 on 347 k voxels of an indoor scene: 35 us in place of 2760 in the
+    // scalar kernel, which is left with the other channel counts and fp32).
+    bool mfma = dt != FX_F32 && km->n_tiles > 0 && C_in % 8 == 0 && C_out % 8 == 0 &&
+                ((reinterpret_cast<uintptr_t>(d_feat) | reinterpret_cast<uintptr_t>(d_gout)) & 15) == 0 && !force_scalar();
     // Per-leaf dispatch, as in the forward pass: on a grid that mixes locally dense leaves with sparse ones the pairs
     // of the dense leaves' outputs are summed by the leaf-window kernel (over the list of those leaves) and all
     // others by the tile kernel over the copy of the map that leaves those outputs out; both write partial sums of
@@ -996,7 +1019,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     if (mfma) {
         const fx_kmap* km_all = km;
         km = kmt;
-        const int n_cblk = (C_in / kWgCi) * (C_out / kWgCo);
+        const int n_cblk = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
         n_ranges = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles, compute_units() / n_cblk));
         if (n_ranges > 8) n_ranges -= n_ranges % 8;   // see the block-to-XCD mapping in the kernel
         // Sparse submanifold maps with at most a few tiles that are not staged in LDS: the sixteen-wave launch for the
@@ -1019,29 +1042,36 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         }
         const size_t lds = sizeof(WgradLds);
         ProfScope ps(kProfWgrad, st);
-#define FX_WGRAD_ONE(T, W, MODE, NWG)                                                                                  \
+#define FX_WGRAD_ONE(T, W, MODE, SHAPE, NWG)                                                                           \
     do {                                                                                                               \
         if (e == hipSuccess)                                                                                           \
-            e = hipFuncSetAttribute((const void*)k_wgrad_mfma<T, W, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                    (int)lds);                                                                         \
+            e = hipFuncSetAttribute((const void*)k_wgrad_mfma<T, W, MODE, SHAPE>,                                      \
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                             \
         if (e == hipSuccess) {                                                                                         \
-            k_wgrad_mfma<T, W, MODE><<<(unsigned)(n_cblk * (NWG)), 64 * W, lds, st>>>(                                 \
+            k_wgrad_mfma<T, W, MODE, SHAPE><<<(unsigned)(n_cblk * (NWG)), 64 * W, lds, st>>>(                          \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride, \
                 km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, km->K3, part,    \
                 km->d_unstaged_list, n_listed);                                                                        \
             e = hipGetLastError();                                                                                     \
         }                                                                                                              \
     } while (0)
-#define FX_WGRAD(T)                                                                                                    \
+#define FX_WGRAD_SHAPE(T, SHAPE)                                                                                       \
     do {                                                                                                               \
         if (split) {                                                                                                   \
-            FX_WGRAD_ONE(T, 16, kWgStaged, n_ranges);                                                                  \
-            if (n_listed > 0) FX_WGRAD_ONE(T, 8, kWgOthers, kGroupsPerTile);                                           \
-        } else FX_WGRAD_ONE(T, 8, kWgAll, n_ranges);                                                                   \
+            FX_WGRAD_ONE(T, 16, kWgStaged, SHAPE, n_ranges);                                                           \
+            if (n_listed > 0) FX_WGRAD_ONE(T, 8, kWgOthers, SHAPE, kGroupsPerTile);                                    \
+        } else FX_WGRAD_ONE(T, 8, kWgAll, SHAPE, n_ranges);                                                            \
+    } while (0)
+#define FX_WGRAD(T)                                                                                                    \
+    do {                                                                                                               \
+        if (C_in % kWgCi == 0 && C_out % kWgCo == 0) FX_WGRAD_SHAPE(T, kWgFull);                                       \
+        else if (C_out <= 32) FX_WGRAD_SHAPE(T, kWgNarrow);                                                            \
+        else FX_WGRAD_SHAPE(T, kWgPartial);                                                                            \
     } while (0)
         if (dt == FX_BF16) FX_WGRAD(__bf16); else FX_WGRAD(_Float16);
         n_ranges += list_ranges;      // what the reduction adds up
 #undef FX_WGRAD
+#undef FX_WGRAD_SHAPE
 #undef FX_WGRAD_ONE
         if (e == hipSuccess) e = hipGetLastError();
     } else {

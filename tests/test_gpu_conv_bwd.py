@@ -279,3 +279,26 @@ def test_many_work_items_per_workgroup_backward(c_in, c_out):
     gw = gw.cpu().numpy()
     assert np.isfinite(gw).all()
     _wgrad_check(gw, O.conv_bwd_weight(og, ogo, 3, 1, feat, gy, threads=H.ORACLE_THREADS), 2e-3)
+
+
+@pytest.mark.parametrize("dims", [(40, 24, 8), (26, 26, 26)])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 32, 32), ("bf16", 8, 24), ("bf16", 40, 96), ("f16", 72, 136), ("bf16", 96, 40)])
+def test_weight_gradient_of_partial_channel_blocks(dims, dtype, c_in, c_out, fx_opt):
+    # channel counts that are not whole 32 x 64 blocks (one accumulator half up to 32 output channels, masked pieces
+    # otherwise), over staged tiles, a few listed ones (40 x 24 x 8) and the launch that takes every tile (26^3).
+    # Every element is written, matches the oracle at the file's bar, and comes out with the same bits twice.
+    fx_opt("leaf_dispatch", "0")
+    rng = np.random.default_rng(190 + dims[0])
+    cloud = rng.integers(-60, 60, size=(6000, 3)).astype(np.int32)
+    ax = [np.arange(d, dtype=np.int32) + 200 for d in dims]
+    block = np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.concatenate([cloud, block])[rng.permutation(6000 + block.shape[0])]
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, _ = G.features_and_weights(15, og.num_voxels, c_in, c_out, 27, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(16).standard_normal((og.num_voxels, c_out)).astype(np.float32), dtype)
+    d_x, d_gy = H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype)
+    gw = H.nan_filled((27, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
+    _wgrad_check(gw.cpu().numpy(), O.conv_bwd_weight(og, og, 3, 1, feat, gy), 2e-3)
+    assert torch.equal(gw, fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32))
