@@ -982,6 +982,11 @@ extern "C" fx_status fx_build_kernel_map_onto(fx_grid* g_in, fx_grid* g_out, int
 
 void fx::enqueue_leaf_links(fx_grid* g, hipStream_t st, const fx_grid* g_in, int K, int stride) {
     if (option(kOptLeafLinks) == 0 || g->d_leaf_links || (K != 2 && K != 3)) return;
+    // Worth it while it hides behind the read-back (some 12 us; 10 us for the 38 k leaves of 1 M LiDAR rows, whose
+    // capacity is 127 k).  On large grids it would only delay whatever the caller does next (376 k leaves: 105 us of a
+    // point cloud's 0.8 ms) and hold 28 words per leaf of capacity for a map that may never come.
+    constexpr int kMaxShadowLeaves = 1 << 18;
+    if (g->cap_leaf > kMaxShadowLeaves) return;
     void* p = nullptr;
     const size_t n_links = 27 * (size_t)g->cap_leaf, n_first = (size_t)g->cap_leaf + 2;     // runs of 512 voxels <= leaves + 1
     if (dev_alloc(&p, sizeof(int32_t) * (n_links + n_first), st) != FX_OK) return;

@@ -141,3 +141,28 @@ def test_released_device_blocks_are_reused_and_can_be_returned():
     B.release_cached_memory()
     g2, _ = H.both_grids(pts, jo)
     assert g2.leaf_table().tobytes() == t1 == og.leaf_table().tobytes()
+
+
+@pytest.mark.parametrize("n_leaves", [1, 7, 8, 9, 31, 33])
+def test_coordinates_of_leaf_counts_around_the_listing_kernel_s_wave(n_leaves):
+    # the listing takes eight leaves per wave and 32 per workgroup: full leaves, one-voxel leaves and in between
+    rng = np.random.default_rng(300 + n_leaves)
+    parts = []
+    for f in range(n_leaves):
+        full = np.stack(np.meshgrid(*[np.arange(8)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+        keep = {0: 512, 1: 1}.get(f % 3, int(rng.integers(2, 500)))
+        parts.append(full[rng.permutation(512)[:keep]] + 8 * np.array([f % 4 - 2, f // 4 - 3, -f]))
+    pts = np.concatenate(parts).astype(np.int32)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    assert g.counts()[0] == n_leaves
+    H.check_grid(g, og)
+
+
+@pytest.mark.parametrize("B", [1, 2, 3])
+def test_grids_around_the_origin_have_eight_upper_nodes_each(B):
+    # one, two (more than the upper nodes collected in LDS) and three grids (a second attempt with the exact counts)
+    pts = [G.gaussian_points(400 + b, 30000, sigma=60.0) for b in range(B)]
+    ijk, jo = G.make_jagged(pts)
+    g, og = H.both_grids(ijk, jo)
+    assert g.counts()[2] == 8 * B
+    H.check_grid(g, og)
