@@ -86,7 +86,8 @@ struct GridHeader {
     int32_t n_leaf;
     int32_t overflow;     // bit0: upper capacity, bit1: lower, bit2: leaf, bit3: tile limit, bit4: voxel count, bit5: leaf table full, bit6: a bucket's LDS table full, bit7: a scan's bounded wait expired
     int32_t n_leaf_raw;   // distinct leaves found by the voxel pass (may exceed capacity)
-    int32_t pad[2];
+    int32_t n_bad;        // points whose cell is not representable (grids built from points)
+    int32_t wide_rows;    // some input row does not fit the build's packed 8-byte record
     int64_t n_voxels;
     int64_t n_voxels_dense;   // voxels in leaves that hold at least kDenseLeafVoxels of them (what the convolution's per-leaf dispatch goes by)
 };

@@ -35,16 +35,23 @@ struct GridPtrs {
     int32_t cap_upper, cap_lower, cap_leaf, B;
 };
 
-// Row ranges of the grids of a batch, as the build's kernels take them: a single grid travels in the kernel
-// arguments (no upload, no dependent load per row), more grids in a device array of (begin, end) pairs.
+// Row ranges of the grids of a batch, as the build's kernels take them: up to eight grids travel in the kernel
+// arguments (no upload, no dependent load per row), more in a device array of (begin, end) pairs.
+constexpr int kInlineRanges = 8;
 struct BatchRanges {
     const int64_t* d;
-    int64_t begin0, end0;
+    int64_t begin[kInlineRanges], end[kInlineRanges];
 };
 
 // grid that owns row r (ranges sorted, non-overlapping), or -1
 __device__ __forceinline__ int find_batch(const BatchRanges& J, int B, int64_t r) {
-    if (B == 1) return (r >= J.begin0 && r < J.end0) ? 0 : -1;
+    if (B <= kInlineRanges) {
+        int b = -1;
+#pragma unroll
+        for (int q = 0; q < kInlineRanges; ++q)
+            if (q < B && r >= J.begin[q] && r < J.end[q]) b = q;
+        return b;
+    }
     const int64_t* __restrict__ joff = J.d;
     int lo = 0, hi = B;  // last b with start_b <= r
     while (lo < hi) {
@@ -54,6 +61,56 @@ __device__ __forceinline__ int find_batch(const BatchRanges& J, int B, int64_t r
     int b = lo - 1;
     if (b < 0 || r >= joff[2 * b + 1]) return -1;
     return b;
+}
+
+// What the build's rows are: voxel coordinates, or points that are turned into the cells they lie in as they are read
+// (each of the two row passes reads the points; a pass of its own that writes the cells cost 85 us for 10 M points).
+struct RowSource {
+    const int32_t* ijk;
+    const float* xyz;          // kPoints only
+    float o[3], s[3];
+};
+
+// Cell of a coordinate.  Subtraction and division are the correctly rounded single-precision ones (no reciprocal, no
+// contraction), so that the cell of a point near a face is the same on every implementation.
+__device__ __forceinline__ int cell_of(float x, float o, float s, int& bad) {
+    const float t = floorf(__fdiv_rn(__fsub_rn(x, o), s));
+    const bool ok = isfinite(t) && t >= -1073741824.0f && t < 1073741824.0f;
+    bad += ok ? 0 : 1;
+    return ok ? (int32_t)t : 0;
+}
+
+template <bool kPoints>
+__device__ __forceinline__ int3 row_from_words(const RowSource& R, uint32_t w0, uint32_t w1, uint32_t w2, int& bad) {
+    if (!kPoints) return make_int3((int)w0, (int)w1, (int)w2);
+    return make_int3(cell_of(__uint_as_float(w0), R.o[0], R.s[0], bad), cell_of(__uint_as_float(w1), R.o[1], R.s[1], bad),
+                     cell_of(__uint_as_float(w2), R.o[2], R.s[2], bad));
+}
+
+template <bool kPoints>
+__device__ __forceinline__ int3 load_row(const RowSource& R, int64_t r, int& bad) {
+    const uint32_t* p = (kPoints ? reinterpret_cast<const uint32_t*>(R.xyz) : reinterpret_cast<const uint32_t*>(R.ijk)) + 3 * r;
+    return row_from_words<kPoints>(R, p[0], p[1], p[2], bad);
+}
+
+// Four consecutive rows starting at r in three 16-byte loads (the tail row by row); returns how many exist.
+typedef __attribute__((ext_vector_type(4), aligned(4))) uint32_t u32x4_u;
+template <bool kPoints>
+__device__ __forceinline__ int load_four_rows(const RowSource& R, int64_t n_rows, int64_t r, int3 (&v)[4], int& bad) {
+    const uint32_t* p = (kPoints ? reinterpret_cast<const uint32_t*>(R.xyz) : reinterpret_cast<const uint32_t*>(R.ijk)) + 3 * r;
+    if (r + 4 <= n_rows) {
+        const u32x4_u a = *reinterpret_cast<const u32x4_u*>(p), b = *reinterpret_cast<const u32x4_u*>(p + 4),
+                      c = *reinterpret_cast<const u32x4_u*>(p + 8);
+        v[0] = row_from_words<kPoints>(R, a.x, a.y, a.z, bad);
+        v[1] = row_from_words<kPoints>(R, a.w, b.x, b.y, bad);
+        v[2] = row_from_words<kPoints>(R, b.z, b.w, c.x, bad);
+        v[3] = row_from_words<kPoints>(R, c.y, c.z, c.w, bad);
+        return 4;
+    }
+    const int n = r < n_rows ? (int)(n_rows - r) : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = q < n ? load_row<kPoints>(R, r + q, bad) : make_int3(0, 0, 0);
+    return n;
 }
 
 __device__ __forceinline__ uint32_t mix32(uint32_t h, uint32_t v) {
@@ -116,57 +173,71 @@ struct LeafList {
     int32_t cap;
 };
 
+// Positions for the items of one workgroup in the list: rank inside the wave, the wave's place inside the
+// workgroup, the workgroup's place -- one counter update per workgroup.  Called by all threads; -1 for threads without.
+__device__ __forceinline__ int append_positions(bool claimed, int32_t* counter) {
+    __shared__ int in_block, base;
+    if (threadIdx.x == 0) in_block = 0;
+    __syncthreads();
+    const uint64_t cl = __ballot(claimed);
+    const int lane = threadIdx.x & 63;
+    int wave_base = 0;
+    if (lane == 0 && cl) wave_base = atomicAdd(&in_block, __popcll(cl));
+    wave_base = __shfl(wave_base, 0);
+    __syncthreads();
+    if (threadIdx.x == 0) base = in_block ? atomicAdd(counter, in_block) : 0;
+    __syncthreads();
+    return claimed ? base + wave_base + __popcll(cl & ((1ull << lane) - 1)) : -1;
+}
+
 __device__ __forceinline__ uint32_t leaf_hash(int b, int li, int lj, int lk) {
     return mix32(mix32(mix32(mix32(0x811C9DC5u, (uint32_t)b), (uint32_t)li), (uint32_t)lj), (uint32_t)lk);
 }
 
 // ---- direct path
-__global__ void __launch_bounds__(256)
-k_voxels_to_leaves(const int32_t* __restrict__ ijk, int64_t n_rows, const BatchRanges joff, int B,
+constexpr int kDirectThreads = 256;
+template <bool kPoints>
+__global__ void __launch_bounds__(kDirectThreads)
+k_voxels_to_leaves(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B,
                    int32_t* __restrict__ slots, uint32_t slot_mask, LeafList L, GridHeader* hdr) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = r < n_rows ? find_batch(joff, B, r) : -1;
-    int li = 0, lj = 0, lk = 0;
+    const int64_t r = (int64_t)blockIdx.x * kDirectThreads + threadIdx.x;
+    int li = 0, lj = 0, lk = 0, b = -1;
     uint32_t h = 0;
     bool claimed = false;
-    if (b >= 0) {
-        const int i = ijk[3 * r], j = ijk[3 * r + 1], k = ijk[3 * r + 2];
-        li = i >> 3; lj = j >> 3; lk = k >> 3;
-        h = leaf_hash(b, li, lj, lk) & slot_mask;
-        bool found = false;
-        for (uint32_t probe = 0; probe <= slot_mask; ++probe) {
-            // slots hold a representative input row + 1 (0 = empty); device-coherent read: a slot
-            // claimed from another XCD must be seen
-            int32_t s = __hip_atomic_load(&slots[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (s == 0) {
-                const int32_t old = atomicCAS(&slots[h], 0, (int32_t)r + 1);
-                if (old == 0) { found = claimed = true; break; }
-                s = old;
+    if (r < n_rows) {
+        int bad = 0, ignored = 0;
+        const int3 v = load_row<kPoints>(rows, r, bad);
+        if (bad) atomicAdd(&hdr->n_bad, bad);
+        b = find_batch(joff, B, r);
+        if (b >= 0) {
+            li = v.x >> 3; lj = v.y >> 3; lk = v.z >> 3;
+            h = leaf_hash(b, li, lj, lk) & slot_mask;
+            bool found = false;
+            for (uint32_t probe = 0; probe <= slot_mask; ++probe) {
+                // slots hold a representative input row + 1 (0 = empty); device-coherent read: a slot
+                // claimed from another XCD must be seen
+                int32_t s = __hip_atomic_load(&slots[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (s == 0) {
+                    const int32_t old = atomicCAS(&slots[h], 0, (int32_t)r + 1);
+                    if (old == 0) { found = claimed = true; break; }
+                    s = old;
+                }
+                const int64_t q = s - 1;
+                const int3 o = load_row<kPoints>(rows, q, ignored);
+                if ((o.x >> 3) == li && (o.y >> 3) == lj && (o.z >> 3) == lk && find_batch(joff, B, q) == b) {
+                    found = true;
+                    break;
+                }
+                h = (h + 1) & slot_mask;
             }
-            const int64_t q = s - 1;
-            if ((ijk[3 * q] >> 3) == li && (ijk[3 * q + 1] >> 3) == lj && (ijk[3 * q + 2] >> 3) == lk &&
-                find_batch(joff, B, q) == b) {
-                found = true;
-                break;
-            }
-            h = (h + 1) & slot_mask;
+            if (!found) atomicOr(&hdr->overflow, 4 | 32);   // table full: the leaf count is incomplete
+            else atomicOr((unsigned long long*)&L.mask[(size_t)h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
         }
-        if (!found) atomicOr(&hdr->overflow, 4 | 32);   // table full: the leaf count is incomplete
-        else atomicOr((unsigned long long*)&L.mask[(size_t)h * 8 + (i & 7)], 1ull << (((j & 7) << 3) | (k & 7)));
     }
-    // list the newly claimed leaves: one counter update per wave, not per leaf
-    const uint64_t cl = __ballot(claimed);
-    if (cl) {
-        const int lane = threadIdx.x & 63;
-        const int leader = __ffsll((long long)cl) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&hdr->n_leaf_raw, __popcll(cl));
-        base = __shfl(base, leader);
-        if (claimed) {
-            const int pos = base + __popcll(cl & ((1ull << lane) - 1));
-            if (pos < L.cap) { L.key[pos] = make_int4(li, lj, lk, b); L.mask_idx[pos] = (int32_t)h; }
-            else atomicOr(&hdr->overflow, 4);
-        }
+    const int pos = append_positions(claimed, &hdr->n_leaf_raw);
+    if (pos >= 0) {
+        if (pos < L.cap) { L.key[pos] = make_int4(li, lj, lk, b); L.mask_idx[pos] = (int32_t)h; }
+        else atomicOr(&hdr->overflow, 4);
     }
 }
 
@@ -175,7 +246,8 @@ k_voxels_to_leaves(const int32_t* __restrict__ ijk, int64_t n_rows, const BatchR
 // when any of its 8 children is), 16 bits in each of four words of the coarse leaf's mask.  One thread per fine
 // leaf claims the coarse leaf in the table of the direct path (slots hold a representative fine leaf + 1) and ORs
 // its four words in -- tens of thousands of items instead of a row per fine voxel through the whole voxel pass.
-__global__ void __launch_bounds__(256)
+constexpr int kCoarseThreads = 512;
+__global__ void __launch_bounds__(kCoarseThreads)
 k_coarse_leaves(TreeView fine, int32_t* __restrict__ slots, uint32_t slot_mask, LeafList L, GridHeader* hdr) {
     const int f = (int)((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
     const bool has = f < fine.n_leaf;
@@ -224,19 +296,11 @@ k_coarse_leaves(TreeView fine, int32_t* __restrict__ slots, uint32_t slot_mask, 
                 if (word[a]) atomicOr((unsigned long long*)&L.mask[(size_t)h * 8 + bi + a], (unsigned long long)word[a]);
         }
     }
-    // list the newly claimed coarse leaves: one counter update per wave
-    const uint64_t cl = __ballot(claimed);
-    if (cl) {
-        const int lane = threadIdx.x & 63;
-        const int leader = __ffsll((long long)cl) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&hdr->n_leaf_raw, __popcll(cl));
-        base = __shfl(base, leader);
-        if (claimed) {
-            const int pos = base + __popcll(cl & ((1ull << lane) - 1));
-            if (pos < L.cap) { L.key[pos] = make_int4(li, lj, lk, b); L.mask_idx[pos] = (int32_t)h; }
-            else atomicOr(&hdr->overflow, 4);
-        }
+    // (with an update of the list's counter per wave, 590 of them for 38 k fine leaves, this launch took 14 us)
+    const int pos = append_positions(claimed, &hdr->n_leaf_raw);
+    if (pos >= 0) {
+        if (pos < L.cap) { L.key[pos] = make_int4(li, lj, lk, b); L.mask_idx[pos] = (int32_t)h; }
+        else atomicOr(&hdr->overflow, 4);
     }
 }
 
@@ -473,27 +537,36 @@ k_subdivide_leaves(TreeView coarse, LeafList L, GridHeader* hdr, int32_t* __rest
 
 // ---- partitioned path
 constexpr int kPartThreads = 1024;
-constexpr int kPartRowsPerThread = 4;
-constexpr int kPartChunk = kPartThreads * kPartRowsPerThread;   // rows per workgroup of the two row passes
 constexpr int kMaxBuckets = 2048;
 constexpr int kRowsPerBucket = 3072;                             // upper bound of the mean while the bucket count is below its cap
 constexpr int kBucketSlots = 1024;                               // LDS leaf table of one bucket
 
-struct PartRow { int i, j, k, b; uint32_t bucket; };
+// A row on its way through the buckets is one 8-byte record when every coordinate of the input lies in [-2^19, 2^19)
+// and there are at most 16 grids (grid, i, j, k in 4 + 3 x 20 bits): half the bytes of four 32-bit words in the
+// scatter's writes and the leaf pass's reads.  Otherwise (GridHeader::wide_rows) it is two words, (i, j) and (k, grid).
+__device__ __forceinline__ bool row_is_wide(const int3& v) {
+    constexpr uint32_t half = 1u << 19;
+    return (((uint32_t)v.x + half) | ((uint32_t)v.y + half) | ((uint32_t)v.z + half)) >= 2 * half;
+}
+__device__ __forceinline__ uint64_t pack_row(const int3& v, int b) {
+    constexpr uint32_t half = 1u << 19;
+    return ((uint64_t)(uint32_t)b << 60) | ((uint64_t)((uint32_t)v.x + half) << 40) | ((uint64_t)((uint32_t)v.y + half) << 20) |
+           (uint64_t)((uint32_t)v.z + half);
+}
+__device__ __forceinline__ int4 unpack_row(uint64_t r) {
+    constexpr int half = 1 << 19;
+    constexpr uint32_t m = (1u << 20) - 1;
+    return make_int4((int)((uint32_t)(r >> 40) & m) - half, (int)((uint32_t)(r >> 20) & m) - half, (int)((uint32_t)r & m) - half, (int)(r >> 60));
+}
+__device__ __forceinline__ uint64_t two_words(int a, int b) { return (uint64_t)(uint32_t)a | ((uint64_t)(uint32_t)b << 32); }
 
-__device__ __forceinline__ PartRow load_part_row(const int32_t* __restrict__ ijk, int64_t n_rows,
-                                                 const BatchRanges& joff, int B, int64_t r, uint32_t bucket_mask) {
-    PartRow p;
-    p.b = r < n_rows ? find_batch(joff, B, r) : -1;
-    p.i = p.j = p.k = 0; p.bucket = 0;
-    if (p.b >= 0) {
-        p.i = ijk[3 * r]; p.j = ijk[3 * r + 1]; p.k = ijk[3 * r + 2];
-        p.bucket = leaf_hash(p.b, p.i >> 3, p.j >> 3, p.k >> 3) & bucket_mask;
-    }
-    return p;
+// Workgroup b runs on XCD b % 8: consecutive pieces of the input go to one XCD, so that their adjacent runs of a
+// bucket meet in its L2 and leave as whole lines.
+__device__ __forceinline__ int part_piece() {
+    const int n = (int)gridDim.x, per = n >> 3, rest = n & 7, x = (int)blockIdx.x & 7;
+    return x * per + (x < rest ? x : rest) + ((int)blockIdx.x >> 3);
 }
 
-// rows per (bucket, workgroup): hist[bucket * n_wg + wg]
 // What the first kernel of a build clears besides its own work: the head of the grid buffer (header, bases,
 // root table, child masks) and the head of the scratch buffer (scan tickets and block sums, root-tile table).
 // Nothing reads or updates either before the next launch.
@@ -502,9 +575,11 @@ struct ClearRanges {
     uint32_t n16[2];   // 16-byte units
 };
 
+// rows per (piece, bucket): hist[piece * n_buckets + bucket]; whether a row of the piece does not fit a packed record
+template <bool kPoints, int QUADS>
 __global__ void __launch_bounds__(kPartThreads)
-k_bucket_count(const int32_t* __restrict__ ijk, int64_t n_rows, const BatchRanges joff, int B,
-               uint32_t bucket_mask, uint32_t* __restrict__ hist, ClearRanges clr) {
+k_bucket_count(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B,
+               uint32_t bucket_mask, uint32_t* __restrict__ hist, int32_t* __restrict__ wide, ClearRanges clr) {
     __shared__ uint32_t cnt[kMaxBuckets];
 #pragma unroll
     for (int c = 0; c < 2; ++c)
@@ -512,161 +587,257 @@ k_bucket_count(const int32_t* __restrict__ ijk, int64_t n_rows, const BatchRange
             clr.p[c][e] = make_uint4(0u, 0u, 0u, 0u);
     for (uint32_t e = threadIdx.x; e <= bucket_mask; e += kPartThreads) cnt[e] = 0;
     __syncthreads();
-    const int64_t r0 = (int64_t)blockIdx.x * kPartChunk + threadIdx.x;
+    const int piece = part_piece();
+    bool is_wide = B > 16;
+    int ignored = 0;
 #pragma unroll
-    for (int q = 0; q < kPartRowsPerThread; ++q) {
-        const PartRow p = load_part_row(ijk, n_rows, joff, B, r0 + q * kPartThreads, bucket_mask);
-        if (p.b >= 0) atomicAdd(&cnt[p.bucket], 1u);
-    }
-    __syncthreads();
-    for (uint32_t e = threadIdx.x; e <= bucket_mask; e += kPartThreads) hist[(size_t)e * gridDim.x + blockIdx.x] = cnt[e];
-}
-
-// one wave per bucket: exclusive prefix over the workgroups' counts (in place) and the bucket total
-__global__ void __launch_bounds__(256) k_bucket_scan(uint32_t* __restrict__ hist, int n_wg, int n_buckets,
-                                                     uint32_t* __restrict__ totals) {
-    const int bucket = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
-    if (bucket >= n_buckets) return;
-    uint32_t* row = hist + (size_t)bucket * n_wg;
-    uint32_t carry = 0;
-    for (int base = 0; base < n_wg; base += 64) {
-        const int e = base + lane;
-        const uint32_t v = e < n_wg ? row[e] : 0u;
-        uint32_t incl = v;
+    for (int c = 0; c < QUADS; ++c) {
+        const int64_t r = ((int64_t)piece * QUADS + c) * (4 * kPartThreads) + 4 * threadIdx.x;
+        int3 v[4];
+        const int n = load_four_rows<kPoints>(rows, n_rows, r, v, ignored);
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = __shfl_up(incl, d);
-            if (lane >= d) incl += o;
+        for (int q = 0; q < 4; ++q) {
+            const int b = q < n ? find_batch(joff, B, r + q) : -1;
+            if (b < 0) continue;
+            is_wide |= row_is_wide(v[q]);
+            atomicAdd(&cnt[leaf_hash(b, v[q].x >> 3, v[q].y >> 3, v[q].z >> 3) & bucket_mask], 1u);
         }
-        if (e < n_wg) row[e] = carry + incl - v;
-        carry += __shfl(incl, 63);
     }
-    if (lane == 0) totals[bucket] = carry;
+    const int any_wide = __syncthreads_or(is_wide);
+    if (threadIdx.x == 0) wide[piece] = any_wide;
+    for (uint32_t e = threadIdx.x; e <= bucket_mask; e += kPartThreads) hist[(size_t)piece * (bucket_mask + 1) + e] = cnt[e];
 }
 
-// scatter the rows into their buckets as (i, j, k, grid) records; the records of one workgroup
-// are ordered by bucket in LDS first so that each bucket receives one contiguous run
+// 64 buckets per workgroup, lane = bucket, the pieces cut into one run per wave: exclusive prefix over the pieces'
+// counts (in place) and the bucket totals.  Eight rows of counts in flight per wave; a wave reads 256 consecutive bytes.
+constexpr int kBucketScanThreads = 1024;
+__global__ void __launch_bounds__(kBucketScanThreads) k_bucket_scan(uint32_t* __restrict__ hist, int n_pieces, int n_buckets,
+                                                                    uint32_t* __restrict__ totals, const int32_t* __restrict__ wide,
+                                                                    GridHeader* hdr) {
+    constexpr int kWaves = kBucketScanThreads / 64;
+    __shared__ uint32_t run_sum[kWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0) {
+        int w = 0;
+        for (int e = threadIdx.x; e < n_pieces; e += kBucketScanThreads) w |= wide[e];
+        w = __syncthreads_or(w);
+        if (threadIdx.x == 0) hdr->wide_rows = w;
+    }
+    const int p0 = (int)((int64_t)n_pieces * wave / kWaves), p1 = (int)((int64_t)n_pieces * (wave + 1) / kWaves);
+    uint32_t* col = hist + blockIdx.x * 64 + lane;
+    uint32_t sum = 0;
+    int p = p0;
+    for (; p + 8 <= p1; p += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = col[(size_t)(p + u) * n_buckets];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += v[u];
+    }
+    for (; p < p1; ++p) sum += col[(size_t)p * n_buckets];
+    run_sum[wave][lane] = sum;
+    __syncthreads();
+    uint32_t run = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w == wave) run = all;
+        all += run_sum[w][lane];
+    }
+    p = p0;
+    for (; p + 8 <= p1; p += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = col[(size_t)(p + u) * n_buckets];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { col[(size_t)(p + u) * n_buckets] = run; run += v[u]; }
+    }
+    for (; p < p1; ++p) { const uint32_t v = col[(size_t)p * n_buckets]; col[(size_t)p * n_buckets] = run; run += v; }
+    if (wave == 0) totals[blockIdx.x * 64 + lane] = all;
+}
+
+// scatter the rows into their buckets as records; the records of one workgroup are ordered by bucket in LDS first so
+// that each bucket receives one contiguous run
+template <bool kPoints, int QUADS>
 __global__ void __launch_bounds__(kPartThreads)
-k_bucket_scatter(const int32_t* __restrict__ ijk, int64_t n_rows, const BatchRanges joff, int B,
+k_bucket_scatter(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B,
                  uint32_t bucket_mask, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals,
-                 uint32_t* __restrict__ bucket_start, int4* __restrict__ records) {
+                 uint32_t* __restrict__ bucket_start, uint64_t* __restrict__ records, GridHeader* hdr) {
     extern __shared__ __align__(16) unsigned char part_lds[];
-    int4* rec = reinterpret_cast<int4*>(part_lds);                          // [kPartChunk]
-    uint32_t* dest = reinterpret_cast<uint32_t*>(rec + kPartChunk);         // [kPartChunk]
-    uint32_t* cnt = dest + kPartChunk;                                      // [kMaxBuckets] rows of this workgroup
-    uint32_t* lstart = cnt + kMaxBuckets;                                   // [kMaxBuckets] first LDS slot
-    uint32_t* gbase = lstart + kMaxBuckets;                                 // [kMaxBuckets] first global record
+    constexpr int kRows = 4 * QUADS * kPartThreads;
     const uint32_t n_buckets = bucket_mask + 1;
+    uint64_t* rec = reinterpret_cast<uint64_t*>(part_lds);                  // [kRows]
+    uint32_t* dest = reinterpret_cast<uint32_t*>(rec + kRows);              // [kRows]
+    uint32_t* cnt = dest + kRows;                                           // [n_buckets] rows of this workgroup
+    uint32_t* lstart = cnt + n_buckets;                                     // [n_buckets] first LDS slot
+    uint32_t* gbase = lstart + n_buckets;                                   // [n_buckets] first global record
     const int tid = threadIdx.x;
+    const int piece = part_piece();
+    // the rows are requested before the scan below waits for the totals
+    int3 v[4 * QUADS];
+    int b[4 * QUADS];
+    int bad = 0;
+#pragma unroll
+    for (int c = 0; c < QUADS; ++c) {
+        const int64_t r = ((int64_t)piece * QUADS + c) * (4 * kPartThreads) + 4 * tid;
+        int3 w[4];
+        const int n = load_four_rows<kPoints>(rows, n_rows, r, w, bad);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[4 * c + q] = w[q];
+            b[4 * c + q] = q < n ? find_batch(joff, B, r + q) : -1;
+        }
+    }
+    if (kPoints && bad) atomicAdd(&hdr->n_bad, bad);
     // bucket starts = exclusive scan of the totals (every workgroup repeats it; the first one publishes it)
     {
-        uint32_t v[2], sum = 0;
+        uint32_t t[2], sum = 0;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; v[q] = e < n_buckets ? totals[e] : 0u; sum += v[q]; }
+        for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; t[q] = e < n_buckets ? totals[e] : 0u; sum += t[q]; }
         uint32_t total;
         uint32_t run = block_exclusive_scan(sum, &total);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const uint32_t e = tid * 2 + q;
             if (e < n_buckets) {
-                gbase[e] = run + hist[(size_t)e * gridDim.x + blockIdx.x];
+                gbase[e] = run + hist[(size_t)piece * n_buckets + e];
                 if (blockIdx.x == 0) bucket_start[e] = run;
             }
-            run += v[q];
+            run += t[q];
         }
         if (blockIdx.x == 0 && tid == 0) bucket_start[n_buckets] = total;
     }
     for (uint32_t e = tid; e < n_buckets; e += kPartThreads) cnt[e] = 0;
     __syncthreads();
-    PartRow p[kPartRowsPerThread];
-    uint32_t rank[kPartRowsPerThread];
-    const int64_t r0 = (int64_t)blockIdx.x * kPartChunk + tid;
+    uint32_t bucket[4 * QUADS], rank[4 * QUADS];
 #pragma unroll
-    for (int q = 0; q < kPartRowsPerThread; ++q) {
-        p[q] = load_part_row(ijk, n_rows, joff, B, r0 + q * kPartThreads, bucket_mask);
-        rank[q] = p[q].b >= 0 ? atomicAdd(&cnt[p[q].bucket], 1u) : 0u;
+    for (int q = 0; q < 4 * QUADS; ++q) {
+        bucket[q] = leaf_hash(b[q], v[q].x >> 3, v[q].y >> 3, v[q].z >> 3) & bucket_mask;
+        rank[q] = b[q] >= 0 ? atomicAdd(&cnt[bucket[q]], 1u) : 0u;
     }
     __syncthreads();
     // first LDS slot of every bucket = exclusive scan of this workgroup's counts
     {
-        uint32_t v[2], sum = 0;
+        uint32_t t[2], sum = 0;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; v[q] = e < n_buckets ? cnt[e] : 0u; sum += v[q]; }
+        for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; t[q] = e < n_buckets ? cnt[e] : 0u; sum += t[q]; }
         uint32_t total;
         uint32_t run = block_exclusive_scan(sum, &total);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const uint32_t e = tid * 2 + q;
             if (e < n_buckets) lstart[e] = run;
-            run += v[q];
+            run += t[q];
         }
     }
     __syncthreads();
+    const bool is_wide = hdr->wide_rows != 0;
 #pragma unroll
-    for (int q = 0; q < kPartRowsPerThread; ++q) {
-        if (p[q].b < 0) continue;
-        const uint32_t s = lstart[p[q].bucket] + rank[q];
-        rec[s] = make_int4(p[q].i, p[q].j, p[q].k, p[q].b);
-        dest[s] = gbase[p[q].bucket] + rank[q];
+    for (int q = 0; q < 4 * QUADS; ++q) {
+        if (b[q] < 0) continue;
+        const uint32_t s = lstart[bucket[q]] + rank[q];
+        rec[s] = is_wide ? two_words(v[q].x, v[q].y) : pack_row(v[q], b[q]);
+        dest[s] = gbase[bucket[q]] + rank[q];
     }
     __syncthreads();
     // number of valid rows of this workgroup = last bucket's start + count
     const uint32_t n_local = lstart[bucket_mask] + cnt[bucket_mask];
     for (uint32_t s = tid; s < n_local; s += kPartThreads) records[dest[s]] = rec[s];
+    if (!is_wide) return;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4 * QUADS; ++q)
+        if (b[q] >= 0) rec[lstart[bucket[q]] + rank[q]] = two_words(v[q].z, b[q]);
+    __syncthreads();
+    for (uint32_t s = tid; s < n_local; s += kPartThreads) records[n_rows + dest[s]] = rec[s];
 }
 
-// one workgroup per bucket: the bucket's distinct leaves and their masks, built in LDS
+// One workgroup per bucket: the bucket's distinct leaves and their masks, built in LDS.  The table's slots hold the
+// leaf itself when the rows are packed records (17 bits per leaf coordinate, so a probe is one LDS read), a
+// representative row + 1 otherwise.  A bucket with more leaves than slots (very sparse points) is walked in rounds, each
+// of which takes the leaves of one class by further bits of their hash: 4, then 16 of them.
 constexpr int kBucketThreads = 1024;
 __global__ void __launch_bounds__(kBucketThreads)
-k_bucket_leaves(const int4* __restrict__ records, const uint32_t* __restrict__ bucket_start, LeafList L, GridHeader* hdr) {
-    __shared__ int32_t rep[kBucketSlots];                 // representative record + 1 (0 = empty)
+k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint32_t* __restrict__ bucket_start, LeafList L, GridHeader* hdr) {
+    __shared__ unsigned long long slot[kBucketSlots];     // 0 = empty
     __shared__ __align__(16) unsigned long long mask[kBucketSlots * 8];
     __shared__ int32_t list_base;
     static_assert(kBucketSlots == kBucketThreads, "one table slot per thread in the listing step");
     const int tid = threadIdx.x;
-    rep[tid] = 0;
-    for (int e = tid; e < kBucketSlots * 4; e += kBucketThreads) reinterpret_cast<ulonglong2*>(mask)[e] = make_ulonglong2(0ull, 0ull);
-    __syncthreads();
     const uint32_t begin = bucket_start[blockIdx.x], end = bucket_start[blockIdx.x + 1];
-    bool full = false;
-    for (uint32_t r = begin + tid; r < end; r += kBucketThreads) {
-        const int4 v = records[r];
-        const int li = v.x >> 3, lj = v.y >> 3, lk = v.z >> 3;
-        uint32_t h = (leaf_hash(v.w, li, lj, lk) >> 12) & (kBucketSlots - 1);   // other bits than the bucket's
-        bool found = false;
-        for (int probe = 0; probe < kBucketSlots; ++probe) {
-            int32_t s = rep[h];
-            if (s == 0) {
-                const int32_t old = atomicCAS(&rep[h], 0, (int32_t)(r - begin) + 1);
-                if (old == 0) { found = true; break; }
-                s = old;
+    const bool is_wide = hdr->wide_rows != 0;
+    auto row_at = [&](uint32_t r) {
+        const uint64_t a = records[r];
+        if (!is_wide) return unpack_row(a);
+        const uint64_t c = records[n_rows + r];
+        return make_int4((int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)c, (int)(uint32_t)(c >> 32));
+    };
+    int classes = 1;
+    for (int round = 0; round < classes; ++round) {
+        slot[tid] = 0ull;
+        for (int e = tid; e < kBucketSlots * 4; e += kBucketThreads) reinterpret_cast<ulonglong2*>(mask)[e] = make_ulonglong2(0ull, 0ull);
+        __syncthreads();
+        bool full = false;
+        for (uint32_t r = begin + tid; r < end; r += kBucketThreads) {
+            const int4 v = row_at(r);
+            const int li = v.x >> 3, lj = v.y >> 3, lk = v.z >> 3;
+            const uint32_t hash = leaf_hash(v.w, li, lj, lk);
+            if ((int)((hash >> 24) & (classes - 1)) != round) continue;
+            uint32_t h = (hash >> 12) & (kBucketSlots - 1);   // other bits than the bucket's
+            // the leaf as a nonzero word: biased coordinates of 17 bits, grid, a set top bit
+            const unsigned long long self = is_wide ? (unsigned long long)(r - begin) + 1ull
+                : (1ull << 63) | ((unsigned long long)(uint32_t)v.w << 51) | ((unsigned long long)(uint32_t)(li + (1 << 16)) << 34) |
+                  ((unsigned long long)(uint32_t)(lj + (1 << 16)) << 17) | (unsigned long long)(uint32_t)(lk + (1 << 16));
+            bool found = false;
+            for (int probe = 0; probe < kBucketSlots; ++probe) {
+                unsigned long long s = __hip_atomic_load(&slot[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (s == 0ull) {
+                    s = atomicCAS(&slot[h], 0ull, self);
+                    if (s == 0ull) { found = true; break; }
+                }
+                if (!is_wide) {
+                    if (s == self) { found = true; break; }
+                } else {
+                    const int4 o = row_at(begin + (uint32_t)(s - 1ull));
+                    if ((o.x >> 3) == li && (o.y >> 3) == lj && (o.z >> 3) == lk && o.w == v.w) { found = true; break; }
+                }
+                h = (h + 1) & (kBucketSlots - 1);
             }
-            const int4 o = records[begin + (uint32_t)(s - 1)];
-            if ((o.x >> 3) == li && (o.y >> 3) == lj && (o.z >> 3) == lk && o.w == v.w) { found = true; break; }
-            h = (h + 1) & (kBucketSlots - 1);
+            if (found) atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
+            else full = true;
         }
-        if (found) atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
-        else full = true;
-    }
-    if (full) atomicOr(&hdr->overflow, 64);   // more leaves than the table holds: the build falls back to the direct path
-    __syncthreads();
-    // append the bucket's leaves to the global list (thread = table slot)
-    const int32_t s = rep[tid];
-    uint32_t total;
-    const uint32_t before = block_exclusive_scan(s != 0 ? 1u : 0u, &total);
-    if (tid == 0) list_base = total ? atomicAdd(&hdr->n_leaf_raw, (int)total) : 0;
-    __syncthreads();
-    if (s == 0) return;
-    const int pos = list_base + (int)before;
-    if (pos < L.cap) {
-        const int4 v = records[begin + (uint32_t)(s - 1)];
-        L.key[pos] = make_int4(v.x >> 3, v.y >> 3, v.z >> 3, v.w);
-        L.mask_idx[pos] = pos;
+        if (__syncthreads_or(full)) {
+            // nothing of the first round has been listed yet: start over with more classes.  A later round that still
+            // fills up (or a class of 16) leaves it to the path without buckets.
+            if (round > 0 || classes == 16) { if (tid == 0) atomicOr(&hdr->overflow, 64); return; }
+            classes = classes == 1 ? 4 : 16;
+            round = -1;
+            continue;
+        }
+        // append the leaves to the list (thread = table slot)
+        const unsigned long long s = slot[tid];
+        uint32_t total;
+        const uint32_t before = block_exclusive_scan(s != 0ull ? 1u : 0u, &total);
+        if (tid == 0) list_base = total ? atomicAdd(&hdr->n_leaf_raw, (int)total) : 0;
+        __syncthreads();
+        const int pos = list_base + (int)before;
+        if (s != 0ull && pos < L.cap) {
+            if (is_wide) {
+                const int4 v = row_at(begin + (uint32_t)(s - 1ull));
+                L.key[pos] = make_int4(v.x >> 3, v.y >> 3, v.z >> 3, v.w);
+            } else {
+                constexpr uint32_t m = (1u << 17) - 1;
+                constexpr int half = 1 << 16;
+                L.key[pos] = make_int4((int)((uint32_t)(s >> 34) & m) - half, (int)((uint32_t)(s >> 17) & m) - half,
+                                       (int)((uint32_t)s & m) - half, (int)((uint32_t)(s >> 51) & 15u));
+            }
+            L.mask_idx[pos] = pos;
 #pragma unroll
-        for (int w = 0; w < 8; w += 2)
-            *reinterpret_cast<ulonglong2*>(&L.mask[(size_t)pos * 8 + w]) = *reinterpret_cast<const ulonglong2*>(&mask[tid * 8 + w]);
-    } else {
-        atomicOr(&hdr->overflow, 4);
+            for (int w = 0; w < 8; w += 2)
+                *reinterpret_cast<ulonglong2*>(&L.mask[(size_t)pos * 8 + w]) = *reinterpret_cast<const ulonglong2*>(&mask[tid * 8 + w]);
+        } else if (s != 0ull) {
+            atomicOr(&hdr->overflow, 4);
+        }
+        __syncthreads();
     }
 }
 
@@ -776,54 +947,65 @@ __global__ void k_rank_tiles(LeafList L, const int32_t* __restrict__ rep_leaves,
 }
 
 // ---------------------------------------------------------------------------------- leaves -> tree
-// One thread per distinct leaf.
-// LEVEL 0: lower-node bit in the upper node's child mask   (step 11.2)
-// LEVEL 1: leaf bit in the lower node's child mask         (step 11.3)
-// LEVEL 2: the leaf's final id is known: move its mask into the leaf record
-template <int LEVEL>
-__device__ __forceinline__ void insert_item(const LeafList& L, const GridPtrs& g, int idx, const int4& key) {
-    const int b = key.w;
+// The launches below are sized for the leaf capacity, which the leaves of a dense grid fill to a fifth: the number of
+// workgroups is capped and they stride, because workgroups that only find out that there is nothing for them still
+// cost some 0.3 us a thousand.
+constexpr int kInsertMaxBlocks = 1024;
+
+// lower node of a leaf, or -1
+__device__ __forceinline__ int lower_of(const GridPtrs& g, const int4& key) {
     const int i = key.x << 3, j = key.y << 3, k = key.z << 3;   // the leaf's origin
-    const int u = find_upper_short(g.root_key, g.root_batch, g.hdr->n_upper, b, tile_key(i, j, k));
-    if (u < 0) return;
-    if (LEVEL == 0) {
-        const int off = upper_off(i, j, k);
-        uint64_t* word = g.upper_mask + (size_t)u * kUpperWords + (off >> 6);
-        const uint64_t bit = 1ull << (off & 63);
-        // thousands of leaves share each of these bits: look before the atomic (a stale read only
-        // costs a redundant one)
-        if (!(*word & bit)) atomicOr((unsigned long long*)word, (unsigned long long)bit);
-        return;
-    }
-    const int l = child_of(g.upper_mask + (size_t)u * kUpperWords, g.upper_prefix + (size_t)u * kUpperWords,
-                           upper_off(i, j, k));
-    if (l < 0 || l >= g.cap_lower) return;
-    if (LEVEL == 1) {
-        const int off = lower_off(i, j, k);
-        uint64_t* word = g.lower_mask + (size_t)l * kLowerWords + (off >> 6);
-        atomicOr((unsigned long long*)word, 1ull << (off & 63));
-        return;
-    }
-    const int f = child_of(g.lower_mask + (size_t)l * kLowerWords, g.lower_prefix + (size_t)l * kLowerWords,
-                           lower_off(i, j, k));
-    if (f < 0 || f >= g.cap_leaf) return;
-    fx_leaf* lf = &g.leaf[f];
-    const uint64_t* src = L.mask + (size_t)L.mask_idx[idx] * 8;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) lf->mask[w] = src[w];
-    lf->origin[0] = i;
-    lf->origin[1] = j;
-    lf->origin[2] = k;
-    lf->batch = b;
+    const int u = find_upper_short(g.root_key, g.root_batch, g.hdr->n_upper, key.w, tile_key(i, j, k));
+    if (u < 0) return -1;
+    const int l = child_of(g.upper_mask + (size_t)u * kUpperWords, g.upper_prefix + (size_t)u * kUpperWords, upper_off(i, j, k));
+    return l < g.cap_lower ? l : -1;
 }
 
-template <int LEVEL>
-__global__ void k_insert(LeafList L, GridPtrs g) {
+// One thread per distinct leaf: its bit in the lower node's child mask (step 11.3)
+__global__ void k_insert_lower(LeafList L, GridPtrs g) {
     if (g.hdr->overflow) return;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int4 key;
-    if (!leaf_at(L, g.hdr, idx, &key)) return;
-    insert_item<LEVEL>(L, g, (int)idx, key);
+    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;; idx += (int64_t)gridDim.x * blockDim.x) {
+        int4 key;
+        if (!leaf_at(L, g.hdr, idx, &key)) return;
+        const int l = lower_of(g, key);
+        if (l < 0) continue;
+        const int off = lower_off(key.x << 3, key.y << 3, key.z << 3);
+        atomicOr((unsigned long long*)(g.lower_mask + (size_t)l * kLowerWords + (off >> 6)), 1ull << (off & 63));
+    }
+}
+
+// The leaf's final id is known: its mask moves into the leaf record, with the seven 9-bit inclusive word prefixes of
+// Listing 1, origin and grid; its voxel count goes to a compact array for the scan that follows.  Eight threads per
+// leaf, one per mask word, so that a leaf is read and written as 64 consecutive bytes (one thread per leaf: 64 lines
+// touched by every one of 12 store instructions of a wave; 376 k leaves 51 us here and 23 in the scan that re-read them).
+__global__ void k_place_leaves(LeafList L, GridPtrs g, uint32_t* __restrict__ leaf_count) {
+    if (g.hdr->overflow) return;
+    const int w = threadIdx.x & 7;
+    for (int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;; idx += ((int64_t)gridDim.x * blockDim.x) >> 3) {
+        int4 key;
+        if (!leaf_at(L, g.hdr, idx, &key)) return;           // the same for the eight threads of a leaf
+        const uint64_t m = L.mask[(size_t)L.mask_idx[idx] * 8 + w];
+        const int l = lower_of(g, key);
+        int f = -1;
+        if (l >= 0)
+            f = child_of(g.lower_mask + (size_t)l * kLowerWords, g.lower_prefix + (size_t)l * kLowerWords,
+                         lower_off(key.x << 3, key.y << 3, key.z << 3));
+        uint32_t incl = (uint32_t)__popcll(m);
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+            const uint32_t o = __shfl_up(incl, d, 8);
+            if (w >= d) incl += o;
+        }
+        uint64_t pre = w < 7 ? (uint64_t)incl << (9 * w) : 0ull;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) pre |= (uint64_t)__shfl_xor((unsigned long long)pre, d, 8);
+        if (f < 0 || f >= g.cap_leaf) continue;
+        fx_leaf* lf = &g.leaf[f];
+        lf->mask[w] = m;
+        if (w < 4) reinterpret_cast<int32_t*>(lf->origin)[w] = w == 0 ? key.x << 3 : w == 1 ? key.y << 3 : w == 2 ? key.z << 3 : key.w;
+        if (w == 4) lf->prefix = pre;
+        if (w == 7) leaf_count[f] = incl;
+    }
 }
 
 // LEVEL 0 for all leaves: thousands of leaves share every lower node, and atomics on one address queue up at
@@ -837,7 +1019,7 @@ constexpr int kAggUpper = 12;
 // With at most kRankInBlock root tiles possible (the capacity of the upper level says so) the launch that ranks the
 // tiles is dropped: every workgroup ranks them itself into LDS (a handful of comparisons) and looks its leaves up
 // there; the first workgroup also writes the root table and the count for the launches that follow.
-constexpr int kRankInBlock = 16;
+constexpr int kRankInBlock = 72;
 __global__ void __launch_bounds__(kInsertUpperThreads) k_insert_upper(LeafList L, GridPtrs g,
                                                                        const int32_t* __restrict__ rep_leaves, int rank_here) {
     __shared__ unsigned long long bits[kAggUpper * kUpperWords];
@@ -926,9 +1108,12 @@ struct ScanSync {
 };
 constexpr int kScanSpinLimit = 1 << 20;
 
-// the workgroup's chunk, or -1 when an earlier step of the build has failed (one thread decides for all)
-__device__ __forceinline__ int ordered_chunk(uint32_t* ticket, const GridHeader* hdr) {
+// the workgroup's chunk, or -1 when an earlier step of the build has failed (one thread decides for all) or when the
+// launch, sized for the capacity, has more workgroups than there are chunks: those leave without a ticket, whose
+// updates run one after the other at memory (20 ns each: 1222 of them were most of the leaf scan of 376 k leaves)
+__device__ __forceinline__ int ordered_chunk(uint32_t* ticket, const GridHeader* hdr, int64_t n_chunks) {
     __shared__ int chunk;
+    if (blockIdx.x >= (n_chunks > 0 ? n_chunks : 1)) return -1;
     if (threadIdx.x == 0) chunk = hdr->overflow ? -1 : (int)atomicAdd(ticket, 1u);
     __syncthreads();
     return chunk;
@@ -964,9 +1149,9 @@ __device__ __forceinline__ uint64_t publish_and_sum_before(const ScanSync& y, in
 
 // exclusive popcount prefix per mask word over all nodes of a level; the last chunk writes the number of children
 __global__ void __launch_bounds__(kScanThreads) k_scan_words(LevelScan s, GridHeader* hdr, ScanSync y) {
-    const int chunk = ordered_chunk(y.ticket, hdr);
-    if (chunk < 0) return;
     const int64_t n_words = (int64_t)(*s.n_nodes) * s.words_per_node;
+    const int chunk = ordered_chunk(y.ticket, hdr, (n_words + kWordChunk - 1) / kWordChunk);
+    if (chunk < 0) return;
     const int64_t base = (int64_t)chunk * kWordChunk;
     if (base >= n_words && chunk != 0) return;
     const int64_t w0 = base + (int64_t)threadIdx.x * kWordsPerThread;
@@ -1009,13 +1194,13 @@ __device__ __forceinline__ void note_vox_base(const fx_leaf* __restrict__ leaf, 
         for (int b = bcur + 1; b <= B; ++b) vox_base[b] = n_voxels;
 }
 
-// Leaf level: mOffset = exclusive scan of the leaves' active-voxel counts; mPrefixSum = the
-// seven 9-bit inclusive word prefixes of Listing 1.
-__global__ void __launch_bounds__(kScanThreads) k_scan_leaves(fx_leaf* __restrict__ leaf, GridHeader* hdr, ScanSync y,
+// Leaf level: mOffset = exclusive scan of the leaves' active-voxel counts.
+__global__ void __launch_bounds__(kScanThreads) k_scan_leaves(fx_leaf* __restrict__ leaf, const uint32_t* __restrict__ leaf_count,
+                                                               GridHeader* hdr, ScanSync y,
                                                                int64_t* __restrict__ vox_base, int B) {
-    const int chunk = ordered_chunk(y.ticket, hdr);
-    if (chunk < 0) return;
     const int64_t n_leaf = hdr->n_leaf;
+    const int chunk = ordered_chunk(y.ticket, hdr, (n_leaf + kLeafChunk - 1) / kLeafChunk);
+    if (chunk < 0) return;
     const int64_t base = (int64_t)chunk * kLeafChunk;
     if (base >= n_leaf && chunk != 0) return;
     const int64_t l0 = base + (int64_t)threadIdx.x * kLeavesPerThread;
@@ -1023,18 +1208,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_leaves(fx_leaf* __restric
     uint32_t sum = 0;
 #pragma unroll
     for (int q = 0; q < kLeavesPerThread; ++q) {
-        cnt[q] = 0;
-        if (l0 + q < n_leaf) {
-            uint64_t pre = 0;
-            uint32_t acc = 0;
-#pragma unroll
-            for (int w = 0; w < 8; ++w) {
-                acc += (uint32_t)__popcll(leaf[l0 + q].mask[w]);
-                if (w < 7) pre |= (uint64_t)acc << (9 * w);
-            }
-            leaf[l0 + q].prefix = pre;
-            cnt[q] = acc;
-        }
+        cnt[q] = l0 + q < n_leaf ? leaf_count[l0 + q] : 0u;
         sum += cnt[q];
     }
     {   // voxels that sit in locally dense leaves, summed over the grid
@@ -1199,7 +1373,7 @@ struct LeafSource {
     int link_K = 0;               // kCoarsen: the grid becomes the output of a (link_K, 2) kernel map from `grid` (0: no)
 };
 
-static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const BatchRanges& d_joff, int32_t B,
+static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const BatchRanges& d_joff, int32_t B,
                                int cap_upper, int cap_lower, int cap_leaf, bool direct, hipStream_t st, fx_grid** out,
                                const LeafSource& from = LeafSource()) {
     fx_grid* g = new (std::nothrow) fx_grid();
@@ -1217,10 +1391,10 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     //   cleared by the direct one [leaf table slots | leaf masks]
     //   not cleared:              [leaf keys | mask indices | tile representatives |
     //                              partitioned path: leaf masks, bucket records, histogram, totals, bucket starts]
+    const bool partition = !direct && n_rows >= kPartitionMinRows;
     const int64_t max_items = std::max<int64_t>((int64_t)g->cap_lower * kLowerWords / kWordChunk,
                                                 std::max<int64_t>((int64_t)g->cap_upper * kUpperWords / kWordChunk,
                                                                   (int64_t)g->cap_leaf / kLeafChunk)) + 2;
-    const bool partition = !direct && n_rows >= kPartitionMinRows;
     size_t n_slots = 0;                       // direct path: table slots, masks indexed by slot
     const bool no_table = from.kind == LeafSource::kSubdivide;       // every leaf has one source: masks by (leaf, octant)
     if (!partition) { n_slots = 1024; while (n_slots < 2 * (size_t)g->cap_leaf) n_slots <<= 1; }
@@ -1232,11 +1406,14 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     // Buckets of 1500 to 3000 rows: fewer, fuller buckets give the scatter pass longer runs per bucket and the
     // leaf pass fewer workgroups that each clear a 64 KB table (1 M rows: 98 us with ~1000 rows per bucket, 90 with
     // ~2000, 91 with ~4000, 107 with ~8000, which leaves half the compute units without a bucket; four grids of
-    // 1.07 M rows: 140 / 123 / 117 / 111 us for ~500 / 1000 / 2000 / 4000).  A bucket's table holds 1024 leaves, so
-    // rows that average fewer than three per leaf overflow it and take the path without buckets.
+    // 1.07 M rows: 140 / 123 / 117 / 111 us for ~500 / 1000 / 2000 / 4000).
     int n_buckets = 64;
     while (n_buckets < kMaxBuckets && (int64_t)n_buckets * kRowsPerBucket < n_rows) n_buckets <<= 1;
-    const int n_part_wg = (int)((n_rows + kPartChunk - 1) / kPartChunk);
+    // Rows per workgroup of the two row passes: 4096, or 8192 once that still makes two workgroups per compute unit
+    // (longer runs per bucket, half the histogram).
+    const int quads = n_rows >= (int64_t)2 * 8192 * compute_units() ? 2 : 1;
+    const int part_chunk = kPartThreads * 4 * quads;
+    const int n_part_wg = (int)((n_rows + part_chunk - 1) / part_chunk);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t o_sync = take(sizeof(uint32_t) * 3 * (64 + (size_t)max_items));   // three scans: a ticket, then the words
@@ -1250,9 +1427,11 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     const size_t clear_bytes = partition ? clear_bytes_head : (whole_masks ? clear_bytes_slots : off);
     const size_t o_key = take(sizeof(int4) * (size_t)g->cap_leaf);
     const size_t o_midx = take(sizeof(int32_t) * (size_t)g->cap_leaf);
+    const size_t o_lcnt = take(sizeof(uint32_t) * (size_t)g->cap_leaf);
     const size_t o_rep = take(sizeof(int32_t) * kMaxTiles);
     const size_t o_rec = take(partition ? sizeof(int4) * (size_t)n_rows : 0);
     const size_t o_hist = take(partition ? sizeof(uint32_t) * (size_t)n_buckets * n_part_wg : 0);
+    const size_t o_wide = take(partition ? sizeof(int32_t) * (size_t)n_part_wg : 0);
     const size_t o_tot = take(partition ? sizeof(uint32_t) * n_buckets : 0);
     const size_t o_bst = take(partition ? sizeof(uint32_t) * (n_buckets + 1) : 0);
     void* scratch = nullptr;
@@ -1267,12 +1446,14 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     int32_t* d_tile_slots = (int32_t*)(sp + o_tslot);
     int32_t* d_slots = (int32_t*)(sp + o_slots);
     int32_t* d_rep = (int32_t*)(sp + o_rep);
+    uint32_t* d_leaf_count = (uint32_t*)(sp + o_lcnt);
     auto scan_sync = [&](int which) {
         uint32_t* base = (uint32_t*)(sp + o_sync) + (size_t)which * (64 + (size_t)max_items);
         return ScanSync{base, base + 64};
     };
-    int4* d_records = (int4*)(sp + o_rec);
+    uint64_t* d_records = (uint64_t*)(sp + o_rec);         // two words per row (the second: wide rows only)
     uint32_t* d_hist = (uint32_t*)(sp + o_hist);
+    int32_t* d_wide = (int32_t*)(sp + o_wide);
     uint32_t* d_totals = (uint32_t*)(sp + o_tot);
     uint32_t* d_bucket_start = (uint32_t*)(sp + o_bst);
 
@@ -1292,29 +1473,39 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     }
     const GridPtrs q = ptrs_of(g);
     if (n_rows > 0 && B > 0) {
-        const unsigned nb_leaf = (unsigned)((g->cap_leaf + 255) / 256);
+        const unsigned nb_leaf = (unsigned)std::min<int64_t>(((int64_t)g->cap_leaf + 255) / 256, kInsertMaxBlocks);
+        const unsigned nb_place = (unsigned)std::min<int64_t>(((int64_t)g->cap_leaf + 31) / 32, 4 * kInsertMaxBlocks);
+        const unsigned nb_leaf_1024 = (unsigned)(((int64_t)g->cap_leaf + 1023) / 1024);
         if (partition) {
             const uint32_t bucket_mask = (uint32_t)n_buckets - 1;
-            const size_t lds = (sizeof(int4) + sizeof(uint32_t)) * kPartChunk + 3 * sizeof(uint32_t) * kMaxBuckets;
-            FX_TRY_OR_FAIL(hipFuncSetAttribute((const void*)k_bucket_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds));
+            const size_t lds = (sizeof(uint64_t) + sizeof(uint32_t)) * part_chunk + 3 * sizeof(uint32_t) * n_buckets;
+            ClearRanges clr;
+            clr.p[0] = (uint4*)g->buf; clr.n16[0] = (uint32_t)(grid_clear_bytes / 16);
+            clr.p[1] = (uint4*)scratch; clr.n16[1] = (uint32_t)(clear_bytes / 16);
+#define FX_ROW_PASS(KERNEL, LDS, ...)                                                                                  \
+    do {                                                                                                               \
+        const void* f = rows.xyz ? (quads == 2 ? (const void*)KERNEL<true, 2> : (const void*)KERNEL<true, 1>)          \
+                                 : (quads == 2 ? (const void*)KERNEL<false, 2> : (const void*)KERNEL<false, 1>);       \
+        if ((LDS) > 64 * 1024) FX_TRY_OR_FAIL(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS))); \
+        if (rows.xyz && quads == 2) KERNEL<true, 2><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);              \
+        else if (rows.xyz) KERNEL<true, 1><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                       \
+        else if (quads == 2) KERNEL<false, 2><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                    \
+        else KERNEL<false, 1><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                                    \
+    } while (0)
             { ProfScope ps(kProfBucketCount, st);
-              ClearRanges clr;
-              clr.p[0] = (uint4*)g->buf; clr.n16[0] = (uint32_t)(grid_clear_bytes / 16);
-              clr.p[1] = (uint4*)scratch; clr.n16[1] = (uint32_t)(clear_bytes / 16);
-              k_bucket_count<<<n_part_wg, kPartThreads, 0, st>>>(d_ijk, n_rows, d_joff, B, bucket_mask, d_hist, clr); }
+              FX_ROW_PASS(k_bucket_count, (size_t)0, rows, n_rows, d_joff, B, bucket_mask, d_hist, d_wide, clr); }
             { ProfScope ps(kProfBucketScan, st);
-              k_bucket_scan<<<(n_buckets * 64 + 255) / 256, 256, 0, st>>>(d_hist, n_part_wg, n_buckets, d_totals); }
+              k_bucket_scan<<<n_buckets / 64, kBucketScanThreads, 0, st>>>(d_hist, n_part_wg, n_buckets, d_totals, d_wide, g->d_hdr); }
             { ProfScope ps(kProfBucketScatter, st);
-              k_bucket_scatter<<<n_part_wg, kPartThreads, lds, st>>>(d_ijk, n_rows, d_joff, B, bucket_mask, d_hist, d_totals,
-                                                                     d_bucket_start, d_records); }
+              FX_ROW_PASS(k_bucket_scatter, lds, rows, n_rows, d_joff, B, bucket_mask, d_hist, d_totals, d_bucket_start, d_records, g->d_hdr); }
             { ProfScope ps(kProfBucketLeaves, st);
-              k_bucket_leaves<<<n_buckets, kBucketThreads, 0, st>>>(d_records, d_bucket_start, L, g->d_hdr); }
+              k_bucket_leaves<<<n_buckets, kBucketThreads, 0, st>>>(d_records, n_rows, d_bucket_start, L, g->d_hdr); }
+#undef FX_ROW_PASS
         } else {
-            const unsigned nb_rows = (unsigned)((n_rows + 255) / 256);
+            const unsigned nb_rows = (unsigned)((n_rows + kDirectThreads - 1) / kDirectThreads);
             ProfScope ps(kProfVoxelsToLeaves, st);
             if (from.kind == LeafSource::kCoarsen)
-                k_coarse_leaves<<<nb_rows, 256, 0, st>>>(from.grid->view(), d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
+                k_coarse_leaves<<<(unsigned)((n_rows + kCoarseThreads - 1) / kCoarseThreads), kCoarseThreads, 0, st>>>(from.grid->view(), d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
             else if (from.kind == LeafSource::kPad) {
                 k_pad_claim<<<(unsigned)((n_rows * 32 + kPadClaimThreads - 1) / kPadClaimThreads), kPadClaimThreads, 0, st>>>(
                     from.grid->view(), from.r, d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr, from.d_bad);
@@ -1323,26 +1514,28 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
             } else if (from.kind == LeafSource::kSubdivide)
                 k_subdivide_leaves<<<(unsigned)((n_rows * 8 + kSubdivideThreads - 1) / kSubdivideThreads), kSubdivideThreads, 0, st>>>(
                     from.grid->view(), L, g->d_hdr, from.d_bad);
+            else if (rows.xyz)
+                k_voxels_to_leaves<true><<<nb_rows, kDirectThreads, 0, st>>>(rows, n_rows, d_joff, B, d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
             else
-                k_voxels_to_leaves<<<nb_rows, 256, 0, st>>>(d_ijk, n_rows, d_joff, B, d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
+                k_voxels_to_leaves<false><<<nb_rows, kDirectThreads, 0, st>>>(rows, n_rows, d_joff, B, d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
         }
-        { ProfScope ps(kProfFindTiles, st); k_find_tiles<<<(unsigned)((g->cap_leaf + kFindTilesThreads - 1) / kFindTilesThreads), kFindTilesThreads, 0, st>>>(L, d_tile_slots, d_rep, g->d_hdr); }
+        { ProfScope ps(kProfFindTiles, st); k_find_tiles<<<nb_leaf_1024, kFindTilesThreads, 0, st>>>(L, d_tile_slots, d_rep, g->d_hdr); }
         const bool rank_in_block = g->cap_upper <= kRankInBlock;
         if (!rank_in_block) { ProfScope ps(kProfRankTiles, st); k_rank_tiles<<<kMaxTiles / 256, 256, 0, st>>>(L, d_rep, q); }
         { ProfScope ps(kProfInsertUpper, st);
-          k_insert_upper<<<(unsigned)((g->cap_leaf + kInsertUpperThreads - 1) / kInsertUpperThreads), kInsertUpperThreads, 0, st>>>(
+          k_insert_upper<<<nb_leaf_1024, kInsertUpperThreads, 0, st>>>(
               L, q, d_rep, rank_in_block ? 1 : 0); }
         LevelScan su{g->d_upper_mask, g->d_upper_prefix, &g->d_hdr->n_upper, kUpperWords, &g->d_hdr->n_lower,
                      g->cap_lower, 2};
         { ProfScope ps(kProfScanUpper, st); if (scan_level(g, su, g->cap_upper, scan_sync(0), st) != FX_OK) return fail(FX_EDEVICE); }
-        { ProfScope ps(kProfInsertLower, st); k_insert<1><<<nb_leaf, 256, 0, st>>>(L, q); }
+        { ProfScope ps(kProfInsertLower, st); k_insert_lower<<<nb_leaf, 256, 0, st>>>(L, q); }
         LevelScan sl{g->d_lower_mask, g->d_lower_prefix, &g->d_hdr->n_lower, kLowerWords, &g->d_hdr->n_leaf,
                      g->cap_leaf, 4};
         { ProfScope ps(kProfScanLower, st); if (scan_level(g, sl, g->cap_lower, scan_sync(1), st) != FX_OK) return fail(FX_EDEVICE); }
-        { ProfScope ps(kProfInsertLeaf, st); k_insert<2><<<nb_leaf, 256, 0, st>>>(L, q); }
+        { ProfScope ps(kProfInsertLeaf, st); k_place_leaves<<<nb_place, 256, 0, st>>>(L, q, d_leaf_count); }
         const int lb = std::max(1, (g->cap_leaf + kLeafChunk - 1) / kLeafChunk);
         { ProfScope ps(kProfScanLeaf, st);
-          k_scan_leaves<<<lb, kScanThreads, 0, st>>>(g->d_leaf, g->d_hdr, scan_sync(2), g->d_vox_base, B); }
+          k_scan_leaves<<<lb, kScanThreads, 0, st>>>(g->d_leaf, d_leaf_count, g->d_hdr, scan_sync(2), g->d_vox_base, B); }
         FX_TRY_OR_FAIL(hipGetLastError());
     }
     // one read-back: counts + per-grid ranges (Sec. 3.3 step 10)
@@ -1380,17 +1573,19 @@ static fx_status build_attempt(const int32_t* d_ijk, int64_t n_rows, const Batch
     return FX_OK;
 }
 
-static fx_status build_with_ranges(const int32_t* d_ijk, int64_t n_rows, const BatchRanges& d_joff, int32_t B,
+static fx_status build_with_ranges(const RowSource& rows, int64_t n_rows, const BatchRanges& d_joff, int32_t B,
                                     hipStream_t st, fx_grid** out) {
-    // First attempt with capacities that fit typical occupancy; an attempt that overflows has
+    // First attempt with capacities that fit typical occupancy -- for up to some 70 k rows with any: a leaf per row --
+    // and up to eight root tiles per grid (a scene around the origin); an attempt that overflows has
     // (almost always) counted the nodes of the overflowing level exactly and is repeated with those.
-    int cap_upper = B + 8;
-    int cap_lower = (int)std::min<int64_t>(std::max<int64_t>(n_rows, 1), 64 * (int64_t)std::max(B, 1) + n_rows / 256);
-    int cap_leaf = (int)std::min<int64_t>(std::max<int64_t>(n_rows, 1), 1024 + n_rows / 8);
+    const int64_t some = std::max<int64_t>(n_rows, 1);
+    int cap_upper = (int)std::min<int64_t>(some, B <= 8 ? 8 * (int64_t)B + 8 : (int64_t)B + 64);
+    int cap_lower = (int)std::min<int64_t>(some, 64 * (int64_t)std::max(B, 1) + 512 + n_rows / 256);
+    int cap_leaf = (int)std::min<int64_t>(some, 65536 + n_rows / 8);
     bool direct = option(kOptGridDirect) == 1;
     for (int attempt = 0; attempt < 9; ++attempt) {
         fx_grid* g = nullptr;
-        FX_TRY(build_attempt(d_ijk, n_rows, d_joff, B, cap_upper, cap_lower, cap_leaf, direct, st, &g));
+        FX_TRY(build_attempt(rows, n_rows, d_joff, B, cap_upper, cap_lower, cap_leaf, direct, st, &g));
         const int ov = g->hdr.overflow;
         if (!ov) { *out = g; return FX_OK; }
         if (ov & 8) {
@@ -1408,14 +1603,14 @@ static fx_status build_with_ranges(const int32_t* d_ijk, int64_t n_rows, const B
             set_error("grid build: a workgroup of a scan waited for its predecessors beyond the limit");
             return FX_EDEVICE;
         }
-        if (ov & 64) direct = true;   // a bucket held more leaves than its LDS table
+        if (ov & 64) direct = true;   // a bucket held more leaves than its workgroup walks in rounds
         if (ov & 1) cap_upper = g->hdr.n_upper;
         if (ov & 2) { cap_upper = g->hdr.n_upper; cap_lower = g->hdr.n_lower; }
         if (ov & 4) {
             // The voxel pass counts every distinct leaf it can put in its table (twice the
             // capacity); only when the table itself filled up is the count a lower bound, and
             // the capacity grows geometrically instead (at most one leaf per input row exists).
-            if ((ov & 32) || (ov & 64)) cap_leaf = (int)std::min<int64_t>(std::max<int64_t>(n_rows, 1), 4 * (int64_t)cap_leaf);
+            if (ov & 32) cap_leaf = (int)std::min<int64_t>(std::max<int64_t>(n_rows, 1), 4 * (int64_t)cap_leaf);
             else cap_leaf = g->hdr.n_leaf_raw;
         }
         fx_grid_destroy(g);
@@ -1425,14 +1620,15 @@ static fx_status build_with_ranges(const int32_t* d_ijk, int64_t n_rows, const B
 }
 
 // The build from rows already on the device; h_pairs = (begin, end) rows of every grid of the batch, on the host.
-// One grid needs no upload at all; more go through pinned staging into a device array that lives until the build
+// Up to eight grids need no upload at all; more go through pinned staging into a device array that lives until the build
 // has synchronised the stream.
-fx_status build_index_grid_device(const int32_t* d_ijk, int64_t n_rows, const int64_t* h_pairs, int32_t B,
+static fx_status build_index_grid_device(const RowSource& rows, int64_t n_rows, const int64_t* h_pairs, int32_t B,
                                   hipStream_t st, fx_grid** out) {
-    BatchRanges J{nullptr, 0, 0};
+    BatchRanges J{};
     int64_t* d_pairs = nullptr;
-    if (B >= 1) { J.begin0 = h_pairs[0]; J.end0 = h_pairs[1]; }
-    if (B > 1) {
+    if (B <= kInlineRanges) {
+        for (int b = 0; b < B; ++b) { J.begin[b] = h_pairs[2 * b]; J.end[b] = h_pairs[2 * b + 1]; }
+    } else {
         const size_t jb = sizeof(int64_t) * 2 * (size_t)B;
         FX_TRY(dev_alloc((void**)&d_pairs, jb, st));
         void* stage = nullptr;
@@ -1443,7 +1639,7 @@ fx_status build_index_grid_device(const int32_t* d_ijk, int64_t n_rows, const in
         if (e != hipSuccess) { dev_free(d_pairs, st); set_error("joffsets upload failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
         J.d = d_pairs;
     }
-    const fx_status rc = build_with_ranges(d_ijk, n_rows, J, B, st, out);
+    const fx_status rc = build_with_ranges(rows, n_rows, J, B, st, out);
     if (d_pairs) dev_free(d_pairs, st);
     return rc;
 }
@@ -1453,9 +1649,9 @@ fx_status build_index_grid_device(const int32_t* d_ijk, int64_t n_rows, const in
 // ====================================================================================== C ABI
 using namespace fx;
 
-extern "C" fx_status fx_build_index_grid(const int32_t* d_ijk, int64_t n_rows, const int64_t* h_joffsets,
-                                         int32_t B, void* stream, fx_grid** out) {
-    if (!out || B < 0 || n_rows < 0 || (B > 0 && !h_joffsets) || (n_rows > 0 && !d_ijk)) {
+static fx_status build_index_grid_checked(const RowSource& rows, int64_t n_rows, const int64_t* h_joffsets, int32_t B, void* stream,
+                                          fx_grid** out) {
+    if (!out || B < 0 || n_rows < 0 || (B > 0 && !h_joffsets) || (n_rows > 0 && !rows.ijk && !rows.xyz)) {
         set_error("fx_build_index_grid: null pointer or negative size");
         return FX_EINVAL;
     }
@@ -1470,7 +1666,14 @@ extern "C" fx_status fx_build_index_grid(const int32_t* d_ijk, int64_t n_rows, c
         }
         prev_end = e;
     }
-    return build_index_grid_device(d_ijk, n_rows, h_joffsets, B, (hipStream_t)stream, out);
+    return build_index_grid_device(rows, n_rows, h_joffsets, B, (hipStream_t)stream, out);
+}
+
+extern "C" fx_status fx_build_index_grid(const int32_t* d_ijk, int64_t n_rows, const int64_t* h_joffsets,
+                                         int32_t B, void* stream, fx_grid** out) {
+    RowSource rows{};
+    rows.ijk = d_ijk;
+    return build_index_grid_checked(rows, n_rows, h_joffsets, B, stream, out);
 }
 
 extern "C" fx_status fx_grid_info(const fx_grid* g, int64_t* n_voxels, int32_t* B, int64_t* h_voxel_joffsets,
@@ -1520,22 +1723,6 @@ extern "C" fx_status fx_grid_leaf_table(const fx_grid* g, fx_leaf* h_out, size_t
     return FX_OK;
 }
 
-// Voxel coordinates of points (Sec. 3.6.2: grids from point clouds): element e = 3 * point + axis.
-// Subtraction and division are the correctly rounded single-precision ones (no reciprocal, no
-// contraction), so that the cell of a point near a face is the same on every implementation.
-__global__ void k_points_to_ijk(const float* __restrict__ xyz, int64_t n3, float ox, float oy, float oz, float sx,
-                                float sy, float sz, int32_t* __restrict__ ijk, int32_t* __restrict__ n_bad) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n3) return;
-    const int axis = (int)(e % 3);
-    const float o = axis == 0 ? ox : axis == 1 ? oy : oz;
-    const float s = axis == 0 ? sx : axis == 1 ? sy : sz;
-    const float t = floorf(__fdiv_rn(__fsub_rn(xyz[e], o), s));
-    const bool ok = isfinite(t) && t >= -1073741824.0f && t < 1073741824.0f;
-    ijk[e] = ok ? (int32_t)t : 0;
-    if (!ok) atomicAdd(n_bad, 1);
-}
-
 extern "C" fx_status fx_build_index_grid_from_points(const float* d_xyz, int64_t n_rows, const int64_t* h_joffsets,
                                                      int32_t B, const float* h_origin, const float* h_voxel_size,
                                                      void* stream, fx_grid** out) {
@@ -1549,35 +1736,16 @@ extern "C" fx_status fx_build_index_grid_from_points(const float* d_xyz, int64_t
             return FX_EINVAL;
         }
     if (n_rows > (int64_t)INT32_MAX) { set_error("more than 2^31-1 input rows"); return FX_ERANGE; }
-    hipStream_t st = (hipStream_t)stream;
-    int32_t* d_ijk = nullptr;
-    // the counter of invalid points sits behind the coordinates, in the same allocation
-    const size_t ijk_bytes = (sizeof(int32_t) * 3 * (size_t)std::max<int64_t>(n_rows, 1) + 15) & ~size_t(15);
-    FX_TRY(dev_alloc((void**)&d_ijk, ijk_bytes + 16, st));
-    int32_t* d_bad = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(d_ijk) + ijk_bytes);
-    hipError_t e = hipMemsetAsync(d_bad, 0, sizeof(int32_t), st);
-    if (e == hipSuccess && n_rows > 0) {
-        ProfScope ps(kProfPointsToIjk, st);
-        const int64_t n3 = 3 * n_rows;
-        k_points_to_ijk<<<(unsigned)((n3 + 255) / 256), 256, 0, st>>>(d_xyz, n3, h_origin[0], h_origin[1], h_origin[2],
-                                                                    h_voxel_size[0], h_voxel_size[1], h_voxel_size[2],
-                                                                    d_ijk, d_bad);
-        e = hipGetLastError();
-    }
-    if (e != hipSuccess) { dev_free(d_ijk, st); set_error("point quantisation failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
+    RowSource rows{};
+    rows.xyz = d_xyz;
+    for (int a = 0; a < 3; ++a) { rows.o[a] = h_origin[a]; rows.s[a] = h_voxel_size[a]; }
     fx_grid* g = nullptr;
-    fx_status rc = fx_build_index_grid(d_ijk, n_rows, h_joffsets, B, stream, &g);    // synchronises the stream
-    int32_t bad = 0;
-    if (rc == FX_OK) {
-        e = hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) { rc = FX_EDEVICE; set_error("read-back failed: %s", hipGetErrorString(e)); }
+    FX_TRY(build_index_grid_checked(rows, n_rows, h_joffsets, B, stream, &g));
+    if (g->hdr.n_bad > 0) {
+        set_error("%d point coordinates are not finite or fall outside [-2^30, 2^30) voxels", g->hdr.n_bad);
+        fx_grid_destroy(g);
+        return FX_ERANGE;
     }
-    dev_free(d_ijk, st);
-    if (rc == FX_OK && bad > 0) {
-        set_error("%d point coordinates are not finite or fall outside [-2^30, 2^30) voxels", bad);
-        rc = FX_ERANGE;
-    }
-    if (rc != FX_OK) { if (g) fx_grid_destroy(g); return rc; }
     *out = g;
     return FX_OK;
 }
@@ -1586,10 +1754,10 @@ fx_status fx::grid_coarsen2_for_map(const fx_grid* g, int K, hipStream_t st, fx_
     // The coarse grid has at most as many nodes per level as the fine one, so one attempt with the fine grid's
     // counts as capacities always fits; its leaves come from the fine leaves, not from a row per voxel.
     fx_grid* o = nullptr;
-    const BatchRanges none{nullptr, 0, 0};
+    const BatchRanges none{};
     LeafSource from;
     from.kind = LeafSource::kCoarsen; from.grid = g; from.link_K = K;
-    FX_TRY(build_attempt(nullptr, g->hdr.n_leaf, none, g->B, g->hdr.n_upper, g->hdr.n_lower, g->hdr.n_leaf, true, st, &o, from));
+    FX_TRY(build_attempt(RowSource{}, g->hdr.n_leaf, none, g->B, g->hdr.n_upper, g->hdr.n_lower, g->hdr.n_leaf, true, st, &o, from));
     if (o->hdr.overflow) {
         const int ov = o->hdr.overflow;
         fx_grid_destroy(o);
@@ -1619,9 +1787,9 @@ extern "C" fx_status fx_grid_subdivide2(const fx_grid* g, void* stream, fx_grid*
     if (hipMemsetAsync(d_bad, 0, sizeof(int32_t), st) != hipSuccess) { dev_free(d_bad, st); set_error("fx_grid_subdivide2: fill failed"); return FX_EDEVICE; }
     LeafSource from;
     from.kind = LeafSource::kSubdivide; from.grid = g; from.d_bad = d_bad;
-    const BatchRanges none{nullptr, 0, 0};
+    const BatchRanges none{};
     fx_grid* o = nullptr;
-    fx_status rc = build_attempt(nullptr, g->hdr.n_leaf, none, g->B, (int)cap_upper, (int)cap_lower, (int)cap_leaf, true, st, &o, from);
+    fx_status rc = build_attempt(RowSource{}, g->hdr.n_leaf, none, g->B, (int)cap_upper, (int)cap_lower, (int)cap_leaf, true, st, &o, from);
     int32_t bad = 0;
     if (rc == FX_OK && hipMemcpy(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess) {
         rc = FX_EDEVICE; set_error("fx_grid_subdivide2: read-back failed");
@@ -1655,12 +1823,12 @@ extern "C" fx_status fx_grid_pad(const fx_grid* g, int32_t r, void* stream, fx_g
             cap_upper = std::min<int64_t>(27 * nu, 8 * nu + 8);
     fx_grid* o = nullptr;
     fx_status rc = FX_OK;
-    const BatchRanges none{nullptr, 0, 0};
+    const BatchRanges none{};
     LeafSource from;
     from.kind = LeafSource::kPad; from.grid = g; from.r = r; from.d_bad = d_bad;
     for (int attempt = 0; attempt < 6; ++attempt) {
         if (hipMemsetAsync(d_bad, 0, sizeof(int32_t), st) != hipSuccess) { rc = FX_EDEVICE; set_error("fx_grid_pad: fill failed"); break; }
-        rc = build_attempt(nullptr, nl, none, g->B, (int)cap_upper, (int)cap_lower, (int)cap_leaf, true, st, &o, from);
+        rc = build_attempt(RowSource{}, nl, none, g->B, (int)cap_upper, (int)cap_lower, (int)cap_leaf, true, st, &o, from);
         if (rc != FX_OK) break;
         const int ov = o->hdr.overflow;
         if (!ov) break;

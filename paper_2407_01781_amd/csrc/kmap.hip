@@ -130,17 +130,16 @@ __global__ void k_leaf_neighbors(TreeView tin, TreeView tout, int stride, int64_
 }
 
 // The table of the map that is expected next, launched by the grid build before the host knows the counts of the
-// grid it has just built (tout): they come from the device header (the view's own are not set) and the launch covers
-// the leaf capacity.  self: the map of the grid onto itself (tin is ignored).
+// grid it has just built (tout): they come from the device header (the view's own are not set).  self: the map of the grid onto itself (tin is ignored).
 template <int K>
 __global__ void k_leaf_links(TreeView tin, TreeView tout, int self, int stride, const GridHeader* __restrict__ hdr,
                              int32_t* __restrict__ nbr, int32_t* __restrict__ tile_first_leaf) {
     if (hdr->overflow) return;                 // a level did not fit: the tree is incomplete and the build is repeated
     tout.n_upper = hdr->n_upper; tout.n_lower = hdr->n_lower; tout.n_leaf = hdr->n_leaf;
     if (self) tin = tout;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)tout.n_leaf * 27) return;
-    leaf_neighbors_item<K, false>(tin, tout, stride, hdr->n_voxels, e, nbr, tile_first_leaf, 0, nullptr, nullptr);
+    const int64_t n = (int64_t)tout.n_leaf * 27;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+        leaf_neighbors_item<K, false>(tin, tout, stride, hdr->n_voxels, e, nbr, tile_first_leaf, 0, nullptr, nullptr);
 }
 
 // stage_leaf with the neighbour leaves read from the table
@@ -983,7 +982,7 @@ extern "C" fx_status fx_build_kernel_map_onto(fx_grid* g_in, fx_grid* g_out, int
 void fx::enqueue_leaf_links(fx_grid* g, hipStream_t st, const fx_grid* g_in, int K, int stride) {
     if (option(kOptLeafLinks) == 0 || g->d_leaf_links || (K != 2 && K != 3)) return;
     // Worth it while it hides behind the read-back (some 12 us; 10 us for the 38 k leaves of 1 M LiDAR rows, whose
-    // capacity is 127 k).  On large grids it would only delay whatever the caller does next (376 k leaves: 105 us of a
+    // capacity is 191 k).  On large grids it would only delay whatever the caller does next (376 k leaves: 105 us of a
     // point cloud's 0.8 ms) and hold 28 words per leaf of capacity for a map that may never come.
     constexpr int kMaxShadowLeaves = 1 << 18;
     if (g->cap_leaf > kMaxShadowLeaves) return;
@@ -993,7 +992,7 @@ void fx::enqueue_leaf_links(fx_grid* g, hipStream_t st, const fx_grid* g_in, int
     g->d_leaf_links = (int32_t*)p;
     g->d_tile_first_leaf = g->d_leaf_links + n_links;
     g->links_K = K; g->links_stride = stride;
-    const unsigned nb = (unsigned)((n_links + 255) / 256);
+    const unsigned nb = (unsigned)std::min<size_t>((n_links + 255) / 256, 4096);
     const TreeView tout = g->view(), tin = g_in ? g_in->view() : tout;
     if (K == 2) k_leaf_links<2><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->d_leaf_links, g->d_tile_first_leaf);
     else k_leaf_links<3><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->d_leaf_links, g->d_tile_first_leaf);

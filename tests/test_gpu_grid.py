@@ -166,3 +166,43 @@ def test_grids_around_the_origin_have_eight_upper_nodes_each(B):
     g, og = H.both_grids(ijk, jo)
     assert g.counts()[2] == 8 * B
     H.check_grid(g, og)
+
+
+@pytest.mark.parametrize("B", [1, 3, 8, 9, 16, 17])
+@pytest.mark.parametrize("far", [0, 1 << 19, -(1 << 19) - 1])
+def test_row_passes_packed_and_wide_rows(B, far):
+    # bucket path (more than 65536 rows) with ranges in the arguments (up to 8 grids) and on the device, rows as one
+    # packed word (coordinates in [-2^19, 2^19), up to 16 grids: the last coordinate is one short of the limit) and as
+    # two; the row count leaves a last group of fewer than four rows, and some rows belong to no grid
+    n = 70003
+    pts = np.random.default_rng(500 + B).integers(-80, 80, size=(n, 3)).astype(np.int32)
+    pts[11] = [(1 << 19) - 1, -(1 << 19), 0]
+    if far:
+        pts[17] = [3, far, -2]
+    cut = np.linspace(0, n, B + 1).astype(np.int64)
+    jo = np.stack([cut[:-1], cut[1:]], axis=1)
+    jo[:, 1] -= 2                                        # two rows behind every grid are nobody's
+    g, og = H.both_grids(pts, jo)
+    H.check_grid(g, og)
+
+
+@pytest.mark.parametrize("n,voxels_per_leaf", [(70000, 1), (200000, 1), (200000, 2)])
+def test_sparse_rows_in_the_bucket_pass_walk_the_bucket_in_rounds(n, voxels_per_leaf):
+    # one or two voxels per leaf: a bucket of ~2000 rows has more leaves than its table and takes them class by class
+    rng = np.random.default_rng(600 + n)
+    base = rng.integers(-3000, 3000, size=(n // voxels_per_leaf, 3)) * 8
+    pts = np.concatenate([base + np.array([q, 1, 2]) for q in range(voxels_per_leaf)]).astype(np.int32)
+    pts = pts[rng.permutation(pts.shape[0])]
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    H.check_grid(g, og)
+
+
+@pytest.mark.parametrize("n", [8 * 1024 * 512 - 1, 8 * 1024 * 512 + 3])
+def test_rows_per_workgroup_of_the_row_passes_at_their_limit(n):
+    # 4096 rows per workgroup below 4 M rows (on 256 compute units), 8192 from there on: same grid as from the distinct
+    # rows alone
+    few = G.gaussian_points(700, 30000, sigma=40.0)
+    pts = torch.from_numpy(few).cuda().repeat(n // few.shape[0] + 1, 1)[:n].contiguous()
+    g = B.build_index_grid(pts, np.array([[0, n]]))
+    og = O.OracleGrid(few, np.array([[0, few.shape[0]]]))
+    H.check_grid(g, og)
