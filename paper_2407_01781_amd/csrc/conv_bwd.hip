@@ -997,6 +997,10 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // scalar kernel, which is left with the other channel counts and fp32).
     bool mfma = dt != FX_F32 && km->n_tiles > 0 && C_in % 8 == 0 && C_out % 8 == 0 &&
                 ((reinterpret_cast<uintptr_t>(d_feat) | reinterpret_cast<uintptr_t>(d_gout)) & 15) == 0 && !force_scalar();
+    // up to 16 input channels: the kernel whose contraction rows are (offset, channel) pairs; the tile kernel would stage
+    // 32 channels per offset
+    const bool low = !force_scalar() && lowdepth_supported(dt, km->K3, C_in);
+    mfma = mfma && !low;
     // Per-leaf dispatch, as in the forward pass: on a grid that mixes locally dense leaves with sparse ones the pairs
     // of the dense leaves' outputs are summed by the leaf-window kernel (over the list of those leaves) and all
     // others by the tile kernel over the copy of the map that leaves those outputs out; both write partial sums of
@@ -1074,6 +1078,12 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
 #undef FX_WGRAD_SHAPE
 #undef FX_WGRAD_ONE
         if (e == hipSuccess) e = hipGetLastError();
+    } else if (low) {
+        FX_TRY(kmap_ensure_dense(const_cast<fx_kmap*>(km), st));
+        n_ranges = lowdepth_wgrad_ranges(km->n_out);
+        FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * n_ranges, st));
+        const fx_status rl = lowdepth_wgrad_partial(km->d_nbmap, km->n_out, km->K3, d_feat, d_gout, dt, C_in, C_out, part, n_ranges, st);
+        if (rl != FX_OK) { dev_free(part, st); return rl; }
     } else {
         fx_status rc = kmap_ensure_dense(const_cast<fx_kmap*>(km), st);
         if (rc != FX_OK) return rc;

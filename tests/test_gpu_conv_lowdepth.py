@@ -1,0 +1,72 @@
+"""GPU parity at up to 16 contracted channels of a 16-bit type: forward, input gradient and weight gradient against the oracle.
+
+Tolerances as in the other convolution tests: per-row relative L2 <= 2e-2 for 16-bit outputs (one rounding of fp32 sums of
+exact products is 2^-9), and per-offset relative Frobenius <= 2e-3 for the fp32 weight gradient."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_common as H
+import paper_2407_01781_amd as fx
+from oracle import cpu_oracle as O
+from workloads import generators as G
+
+pytestmark = pytest.mark.gpu
+
+
+def _cloud(n):
+    """n rows: a solid corner (every tap present) and scattered voxels (hardly any)."""
+    rng = np.random.default_rng(n)
+    solid = np.stack(np.meshgrid(*[np.arange(6)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    far = rng.integers(-40, 40, size=(n, 3))
+    return np.unique(np.concatenate([solid[: n // 2], far])[:n].astype(np.int32), axis=0)
+
+
+# row counts around the 32-row blocks and 64-voxel chunks; channel counts below, at and above the padded 4, 8 and 16 and
+# the 32- and 64-column slices (odd ones leave element-wise loads and stores)
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 3000])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 4, 32), ("bf16", 3, 32), ("bf16", 1, 20), ("f16", 8, 64), ("bf16", 5, 33),
+                                              ("f16", 12, 100), ("bf16", 16, 31), ("f16", 16, 64)])
+def test_low_depth_against_the_oracle(n, dtype, c_in, c_out):
+    pts = _cloud(n)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, wt = G.features_and_weights(21, og.num_voxels, c_in, c_out, 27, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(22).standard_normal((og.num_voxels, c_out)).astype(np.float32), dtype)
+    d_x, d_w, d_gy = (H.to_device_storage(a, dtype) for a in (feat, wt, gy))
+    y = H.nan_filled((og.num_voxels, c_out), H.TORCH_DT[dtype])
+    fx.sparse_conv_fwd(km, d_x, d_w, out=y)
+    H.conv_tolerance_check(y.float().cpu().numpy(), O.conv(og, og, 3, 1, feat, wt), dtype, 27, c_in)
+    y32 = fx.sparse_conv_fwd(km, d_x, d_w, out_dtype=torch.float32)
+    assert np.abs(y32.cpu().numpy() - O.conv(og, og, 3, 1, feat, wt)).max() <= 1e-4 * np.sqrt(27 * c_in)
+    # the other way round: c_in channels contracted by the input gradient of a c_out -> c_in layer
+    wt_b = np.ascontiguousarray(wt.transpose(0, 2, 1))
+    gx = fx.sparse_conv_bwd_data(km, d_x, H.to_device_storage(wt_b, dtype)).float().cpu().numpy()
+    H.conv_tolerance_check(gx, O.conv_bwd_data(og, og, 3, 1, feat, wt_b), dtype, 27, c_in)
+    gw = H.nan_filled((27, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    num = np.sqrt(((gw.cpu().numpy() - ref) ** 2).sum(axis=(1, 2)))
+    den = np.maximum(np.sqrt((ref ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))
+    assert (num / den).max() <= 2e-3
+    assert torch.equal(gw, fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32))
+
+
+@pytest.mark.parametrize("K,stride", [(1, 1), (5, 1), (2, 2), (3, 2)])
+@pytest.mark.parametrize("c_in,c_out", [(4, 32), (8, 40), (16, 64)])
+def test_low_depth_other_kernel_sizes(K, stride, c_in, c_out):
+    # 5x5x5 at more than four channels does not fit and stays on the scalar kernel
+    pts = _cloud(2000)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, K, stride)
+    ogo = O.output_grid(og, K, stride)
+    feat, wt = G.features_and_weights(23, og.num_voxels, c_in, c_out, K ** 3, "bf16")
+    gy = G.round_to_dtype(np.random.default_rng(24).standard_normal((ogo.num_voxels, c_out)).astype(np.float32), "bf16")
+    d_x, d_w, d_gy = (H.to_device_storage(a, "bf16") for a in (feat, wt, gy))
+    y = fx.sparse_conv_fwd(km, d_x, d_w).float().cpu().numpy()
+    H.conv_tolerance_check(y, O.conv(og, ogo, K, stride, feat, wt), "bf16", K ** 3, c_in)
+    gw = fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32).cpu().numpy()
+    ref = O.conv_bwd_weight(og, ogo, K, stride, feat, gy)
+    num = np.sqrt(((gw - ref) ** 2).sum(axis=(1, 2)))
+    den = np.maximum(np.sqrt((ref ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))
+    assert (num / den).max() <= 2e-3
