@@ -1288,7 +1288,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         return rc;
     }
     FX_TRY(kmap_ensure_dense(const_cast<fx_kmap*>(km), st));
-    if (!force_scalar && lowdepth_supported(in_dt, km->K3, C_in))
+    if (!force_scalar && lowdepth_supported(in_dt, km->K3, C_in, km->n_in))
         return lowdepth_conv_on_table(km->d_nbmap, km->n_out, km->K3, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt, st, mode);
     return conv_scalar_on_table(km->d_nbmap, km->n_out, km->K3, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt, st, mode);
 }

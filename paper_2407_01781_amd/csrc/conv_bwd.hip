@@ -999,7 +999,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
                 ((reinterpret_cast<uintptr_t>(d_feat) | reinterpret_cast<uintptr_t>(d_gout)) & 15) == 0 && !force_scalar();
     // up to 16 input channels: the kernel whose contraction rows are (offset, channel) pairs; the tile kernel would stage
     // 32 channels per offset
-    const bool low = !force_scalar() && lowdepth_supported(dt, km->K3, C_in);
+    const bool low = !force_scalar() && lowdepth_supported(dt, km->K3, C_in, km->n_in);
     mfma = mfma && !low;
     // Per-leaf dispatch, as in the forward pass: on a grid that mixes locally dense leaves with sparse ones the pairs
     // of the dense leaves' outputs are summed by the leaf-window kernel (over the list of those leaves) and all

@@ -198,7 +198,7 @@ fx_status conv_scalar_on_table(const int32_t* d_table, int64_t n_rows, int K3, c
 
 // The same sums at up to 16 contracted channels of a 16-bit type on the matrix units (conv_lowdepth.hip), and the weight
 // gradient at up to 16 input channels as partial sums part[n_ranges][K3][C_in][C_out], n_ranges = lowdepth_wgrad_ranges.
-bool lowdepth_supported(fx_dtype dt, int K3, int C_contract);
+bool lowdepth_supported(fx_dtype dt, int K3, int C_contract, int64_t n_source_rows);
 fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3, const void* d_feat, fx_dtype dt, const void* d_w,
                                  int32_t C_in, int32_t C_out, void* d_out, fx_dtype out_dt, hipStream_t st, int mode);
 int lowdepth_wgrad_ranges(int64_t n_rows);

@@ -44,10 +44,10 @@ __device__ __forceinline__ typename Words<N>::type load_channels(const uint16_t*
 // operand layout wants from it: two rows of four channels, one of eight, or half a row of sixteen.  The gathers of
 // seven multiplies are in flight together.  The weights are laid out in operand order in LDS once per (persistent)
 // workgroup; with two n-tiles (NT) the columns interleave, so a lane stores two adjacent channels.
-template <typename T, bool OUT_F32, int CP, int NT>
-__global__ void __launch_bounds__(kLdThreads)
+template <typename T, bool OUT_F32, int CP, int NT, bool WHOLE>
+__global__ void __launch_bounds__(kLdThreads, 4)
 k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const uint16_t* __restrict__ feat,
-                const uint16_t* __restrict__ w, int C_in, int C_out, void* __restrict__ out, int mode, int whole) {
+                const uint16_t* __restrict__ w, int C_in, int C_out, void* __restrict__ out, int mode) {
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int kTaps = 16 / CP;                                  // offsets per multiply
@@ -57,16 +57,22 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t* nb = reinterpret_cast<int32_t*>(lds_raw + (size_t)n_steps * NT * 1024) + wave * kGroup * K3;
     const int co0 = blockIdx.y * 32 * NT;
-    for (int e = threadIdx.x; e < n_steps * NT * 512; e += kLdThreads) {
-        const int el = e & 7, l = (e >> 3) & 63, nt = (e >> 9) % NT, s = (e >> 9) / NT;
-        const int k = 16 * s + 8 * (l >> 5) + el, kappa = k / CP, ci = k % CP;
-        const int co = co0 + (NT == 2 ? 2 * (l & 31) + nt : (l & 31));
-        uint16_t v = 0;
-        if (kappa < K3 && ci < C_in && co < C_out) {
-            const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
-            v = (mode & kWeightsTransposed) ? w[(kw * C_out + co) * C_in + ci] : w[(kw * C_in + ci) * C_out + co];
+    for (int e0 = threadIdx.x; e0 < n_steps * NT * 512; e0 += 7 * kLdThreads) {      // seven loads in flight
+        uint16_t v[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) {
+            const int e = e0 + u * kLdThreads, el = e & 7, l = (e >> 3) & 63, nt = (e >> 9) % NT, s = (e >> 9) / NT;
+            const int k = 16 * s + 8 * (l >> 5) + el, kappa = k / CP, ci = k % CP;
+            const int co = co0 + (NT == 2 ? 2 * (l & 31) + nt : (l & 31));
+            v[u] = 0;
+            if (kappa < K3 && ci < C_in && co < C_out) {
+                const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
+                v[u] = (mode & kWeightsTransposed) ? w[(kw * C_out + co) * C_in + ci] : w[(kw * C_in + ci) * C_out + co];
+            }
         }
-        wl[e] = v;
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (e0 + u * kLdThreads < n_steps * NT * 512) wl[e0 + u * kLdThreads] = v[u];
     }
     __syncthreads();
     const int n = lane & 31, h = lane >> 5;
@@ -91,13 +97,13 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
                 if (CP == 4) {
                     const int t0 = 4 * s + 2 * h;
                     const int r0 = t0 < K3 ? my[t0] : -1, r1 = t0 + 1 < K3 ? my[t0 + 1] : -1;
-                    const u32x2 lo = load_channels<4>(feat + (int64_t)r0 * C_in, r0 >= 0, C_in, whole);
-                    const u32x2 hi = load_channels<4>(feat + (int64_t)r1 * C_in, r1 >= 0, C_in, whole);
+                    const u32x2 lo = load_channels<4>(feat + (uint32_t)r0 * (uint32_t)C_in, r0 >= 0, C_in, WHOLE);
+                    const u32x2 hi = load_channels<4>(feat + (uint32_t)r1 * (uint32_t)C_in, r1 >= 0, C_in, WHOLE);
                     a[u] = u32x4{lo[0], lo[1], hi[0], hi[1]};
                 } else {       // one row of eight channels, or channels 8h .. 8h + 7 of a row of sixteen
                     const int t0 = CP == 8 ? 2 * s + h : s, c0 = CP == 8 ? 0 : 8 * h;
                     const int r0 = t0 < K3 ? my[t0] : -1;
-                    a[u] = load_channels<8>(feat + (int64_t)r0 * C_in + c0, r0 >= 0, C_in - c0, whole);
+                    a[u] = load_channels<8>(feat + ((uint32_t)r0 * (uint32_t)C_in + c0), r0 >= 0, C_in - c0, WHOLE);
                 }
             }
 #pragma unroll
@@ -256,8 +262,8 @@ inline size_t wgrad_lds(int K3, int CP, int NT) {
 
 // Up to 16 contracted channels of a 16-bit type, and operands that fit the LDS of a compute unit (all kernel sizes up to 3;
 // 5x5x5 at up to 4 channels).
-bool lowdepth_supported(fx_dtype dt, int K3, int C_contract) {
-    if (dt == FX_F32 || C_contract > 16) return false;
+bool lowdepth_supported(fx_dtype dt, int K3, int C_contract, int64_t n_source_rows) {
+    if (dt == FX_F32 || C_contract > 16 || n_source_rows * C_contract > 0xFFFFFFFFll) return false;     // 32-bit element offsets
     const int CP = padded_channels(C_contract);
     return conv_lds(K3, CP, 2) <= 160 * 1024 && wgrad_lds(K3, CP, 2) <= 160 * 1024 && (K3 * CP + 31) / 32 <= 4 * kLdWaves;
 }
@@ -269,20 +275,25 @@ fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3,
     const int NT = C_out > 32 ? 2 : 1;
     const size_t lds = conv_lds(K3, CP, NT);
     const int64_t n_blocks = (n_rows + kGroup - 1) / kGroup;
-    // persistent workgroups, as many as LDS lets a compute unit hold (up to 8), no more than there are blocks
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(8, (size_t)160 * 1024 / lds));
+    // Persistent workgroups, as many as a compute unit holds at once (four by registers, fewer by LDS), no more than
+    // there are blocks (7 a unit, in turn, took 42 us for 347 k voxels 4 -> 32)
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, (size_t)160 * 1024 / lds));
     const int n_y = (C_out + 32 * NT - 1) / (32 * NT);
     const int64_t want = std::max<int64_t>(1, (int64_t)compute_units() * per_cu / n_y);
     const dim3 grid((unsigned)std::min<int64_t>((n_blocks + kLdWaves - 1) / kLdWaves, want), (unsigned)n_y);
     ProfScope ps(kProfConvScalar, st);
     hipError_t e = hipSuccess;
-#define FX_LD_NT(T, F32, CPV, NTV)                                                                                       \
+#define FX_LD_WHOLE(T, F32, CPV, NTV, WH)                                                                                \
     do {                                                                                                                 \
-        if (lds > 64 * 1024) e = hipFuncSetAttribute((const void*)k_conv_lowdepth<T, F32, CPV, NTV>,                     \
+        if (lds > 64 * 1024) e = hipFuncSetAttribute((const void*)k_conv_lowdepth<T, F32, CPV, NTV, WH>,                 \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
         if (e == hipSuccess)                                                                                             \
-            k_conv_lowdepth<T, F32, CPV, NTV><<<grid, kLdThreads, lds, st>>>(d_table, n_rows, K3, (const uint16_t*)d_feat, \
-                (const uint16_t*)d_w, C_in, C_out, d_out, mode, whole ? 1 : 0);                                          \
+            k_conv_lowdepth<T, F32, CPV, NTV, WH><<<grid, kLdThreads, lds, st>>>(d_table, n_rows, K3,                    \
+                (const uint16_t*)d_feat, (const uint16_t*)d_w, C_in, C_out, d_out, mode);                                \
+    } while (0)
+#define FX_LD_NT(T, F32, CPV, NTV)                                                                                       \
+    do {                                                                                                                 \
+        if (whole) FX_LD_WHOLE(T, F32, CPV, NTV, true); else FX_LD_WHOLE(T, F32, CPV, NTV, false);                       \
     } while (0)
 #define FX_LD_CP(T, F32, CPV) do { if (NT == 2) FX_LD_NT(T, F32, CPV, 2); else FX_LD_NT(T, F32, CPV, 1); } while (0)
 #define FX_LD(T, F32) do { if (CP == 4) FX_LD_CP(T, F32, 4); else if (CP == 8) FX_LD_CP(T, F32, 8); else FX_LD_CP(T, F32, 16); } while (0)
@@ -291,6 +302,7 @@ fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3,
 #undef FX_LD
 #undef FX_LD_CP
 #undef FX_LD_NT
+#undef FX_LD_WHOLE
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) { set_error("low-depth convolution launch failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
     return FX_OK;
