@@ -246,6 +246,28 @@ k_voxels_to_leaves(const RowSource rows, int64_t n_rows, const BatchRanges joff,
 // when any of its 8 children is), 16 bits in each of four words of the coarse leaf's mask.  One thread per fine
 // leaf claims the coarse leaf in the table of the direct path (slots hold a representative fine leaf + 1) and ORs
 // its four words in -- tens of thousands of items instead of a row per fine voxel through the whole voxel pass.
+struct CoarsePiece { int li, lj, lk, first_word; uint64_t word[4]; };
+__device__ __forceinline__ CoarsePiece coarse_piece(const fx_leaf* __restrict__ lf) {
+    CoarsePiece c;
+    const int oi = lf->origin[0], oj = lf->origin[1], ok = lf->origin[2];
+    c.li = oi >> 4; c.lj = oj >> 4; c.lk = ok >> 4;                // coarse leaf coordinate: (origin >> 1) >> 3
+    c.first_word = (oi >> 1) & 7;                                  // 0 or 4 along each axis: the block inside the coarse leaf
+    const int bj = (oj >> 1) & 7, bk = (ok >> 1) & 7;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        uint64_t m = lf->mask[2 * a] | lf->mask[2 * a + 1];         // pairs along i
+        m = (m | (m >> 1)) & 0x5555555555555555ull;                 // pairs along k, kept at the even bits
+        m = (m | (m >> 1)) & 0x3333333333333333ull;                 // ... gathered into the low nibble of every byte
+        m = (m | (m >> 2)) & 0x0F0F0F0F0F0F0F0Full;
+        m = (m | (m >> 8)) & 0x00FF00FF00FF00FFull;                 // pairs along j: bytes 0, 2, 4, 6
+        uint64_t r = 0;
+#pragma unroll
+        for (int cj = 0; cj < 4; ++cj) r |= ((m >> (16 * cj)) & 0xFull) << ((bj + cj) * 8 + bk);
+        c.word[a] = r;
+    }
+    return c;
+}
+
 constexpr int kCoarseThreads = 512;
 __global__ void __launch_bounds__(kCoarseThreads)
 k_coarse_leaves(TreeView fine, int32_t* __restrict__ slots, uint32_t slot_mask, LeafList L, GridHeader* hdr) {
@@ -256,23 +278,9 @@ k_coarse_leaves(TreeView fine, int32_t* __restrict__ slots, uint32_t slot_mask, 
     bool claimed = false;
     if (has) {
         const fx_leaf* lf = fine.leaf + f;
-        const int oi = lf->origin[0], oj = lf->origin[1], ok = lf->origin[2];
+        const CoarsePiece c = coarse_piece(lf);
         b = lf->batch;
-        li = oi >> 4; lj = oj >> 4; lk = ok >> 4;                      // coarse leaf coordinate: (origin >> 1) >> 3
-        const int bi = (oi >> 1) & 7, bj = (oj >> 1) & 7, bk = (ok >> 1) & 7;   // 0 or 4: the block inside the coarse leaf
-        uint64_t word[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            uint64_t m = lf->mask[2 * a] | lf->mask[2 * a + 1];         // pairs along i
-            m = (m | (m >> 1)) & 0x5555555555555555ull;                 // pairs along k, kept at the even bits
-            m = (m | (m >> 1)) & 0x3333333333333333ull;                 // ... gathered into the low nibble of every byte
-            m = (m | (m >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-            m = (m | (m >> 8)) & 0x00FF00FF00FF00FFull;                 // pairs along j: bytes 0, 2, 4, 6
-            uint64_t r = 0;
-#pragma unroll
-            for (int cj = 0; cj < 4; ++cj) r |= ((m >> (16 * cj)) & 0xFull) << ((bj + cj) * 8 + bk);
-            word[a] = r;
-        }
+        li = c.li; lj = c.lj; lk = c.lk;
         h = leaf_hash(b, li, lj, lk) & slot_mask;
         bool found = false;
         for (uint32_t probe = 0; probe <= slot_mask; ++probe) {
@@ -293,7 +301,7 @@ k_coarse_leaves(TreeView fine, int32_t* __restrict__ slots, uint32_t slot_mask, 
         else {
 #pragma unroll
             for (int a = 0; a < 4; ++a)
-                if (word[a]) atomicOr((unsigned long long*)&L.mask[(size_t)h * 8 + bi + a], (unsigned long long)word[a]);
+                if (c.word[a]) atomicOr((unsigned long long*)&L.mask[(size_t)h * 8 + c.first_word + a], (unsigned long long)c.word[a]);
         }
     }
     // (with an update of the list's counter per wave, 590 of them for 38 k fine leaves, this launch took 14 us)
@@ -1254,6 +1262,220 @@ __global__ void k_publish(const GridHeader* __restrict__ hdr, const int64_t* __r
     if (t == 0) __hip_atomic_store(host_ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// ---------------------------------------------------------------------------------- small grids, one launch
+// The passes above are a chain of a dozen launches of 3-6 us each, most of it latency, whatever the size: 10 k rows took
+// 57 us, in this one launch 23.  Up to kSmallRows rows (or fine leaves, for a coarse grid) one workgroup does the whole build in LDS.  Its
+// leaves are collected in an LDS table of (leaf, 512-bit mask); then they are simply sorted -- the fields of a leaf's
+// coordinate in tree order (grid; root tile; upper offset; lower offset) are one integer -- and node numbers fall out as
+// scans of the places where a prefix of that integer changes.  Counts and ranges go straight to the host.  What it does
+// not hold -- more than kSmallSlots leaves, coordinates beyond 2^18, more than 16 grids, more root tiles than the
+// capacity -- sets overflow bit 8 and the build starts over with the passes.
+constexpr int kSmallThreads = 1024, kSmallSlots = 2048, kSmallRows = 16384;
+constexpr size_t kSmallLds = sizeof(uint64_t) * 9 * kSmallSlots;
+enum SmallSource { kSmallIjk = 0, kSmallPoints = 1, kSmallCoarse = 2 };
+
+template <int SOURCE>
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_grid(const RowSource rows, int n_rows, const BatchRanges joff, int B, TreeView fine, GridPtrs g, unsigned char* __restrict__ host,
+             int32_t* __restrict__ host_ticket, int32_t ticket) {
+    extern __shared__ __align__(16) unsigned char small_lds[];
+    unsigned long long* slot = reinterpret_cast<unsigned long long*>(small_lds);     // [kSmallSlots] leaf (0: empty), later the sorted keys
+    unsigned long long* mask = slot + kSmallSlots;                                   // [kSmallSlots][8]
+    __shared__ int overflow, n_bad;
+    __shared__ unsigned long long dense;
+    const int tid = threadIdx.x;
+    for (int e = tid; e < kSmallSlots * 9 / 2; e += kSmallThreads) reinterpret_cast<ulonglong2*>(small_lds)[e] = make_ulonglong2(0ull, 0ull);
+    if (tid == 0) { overflow = 0; n_bad = 0; dense = 0ull; }
+    __syncthreads();
+
+    // ---- leaves: leaf coordinates biased by 2^15 (16 bits each), grid, a set top bit
+    constexpr int half = 1 << 15;
+    auto claim = [&](int li, int lj, int lk, int b) -> int {
+        if (((uint32_t)(li + half) | (uint32_t)(lj + half) | (uint32_t)(lk + half)) >= 2u * half) { overflow = 256; return -1; }
+        const unsigned long long self = (1ull << 63) | ((unsigned long long)(uint32_t)b << 48) | ((unsigned long long)(uint32_t)(li + half) << 32) |
+                                        ((unsigned long long)(uint32_t)(lj + half) << 16) | (unsigned long long)(uint32_t)(lk + half);
+        uint32_t h = leaf_hash(b, li, lj, lk) & (kSmallSlots - 1);
+        for (int probe = 0; probe < kSmallSlots; ++probe) {
+            unsigned long long s = __hip_atomic_load(&slot[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (s == 0ull) s = atomicCAS(&slot[h], 0ull, self);
+            if (s == 0ull || s == self) return (int)h;
+            h = (h + 1) & (kSmallSlots - 1);
+        }
+        overflow = 256;
+        return -1;
+    };
+    if (SOURCE == kSmallCoarse) {
+        for (int f = tid; f < n_rows; f += kSmallThreads) {
+            const fx_leaf* lf = fine.leaf + f;
+            const CoarsePiece c = coarse_piece(lf);
+            const int h = claim(c.li, c.lj, c.lk, lf->batch);
+            if (h < 0) continue;
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                if (c.word[a]) atomicOr(&mask[h * 8 + c.first_word + a], (unsigned long long)c.word[a]);
+        }
+    } else {
+        int bad = 0;
+        constexpr int kGroups = kSmallRows / (4 * kSmallThreads);
+        int3 v[kGroups][4];
+        int n[kGroups];
+#pragma unroll
+        for (int c = 0; c < kGroups; ++c)        // all of the thread's rows are requested at once
+            n[c] = load_four_rows<SOURCE == kSmallPoints>(rows, n_rows, 4 * (c * kSmallThreads + tid), v[c], bad);
+#pragma unroll
+        for (int c = 0; c < kGroups; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b = q < n[c] ? find_batch(joff, B, 4 * (c * kSmallThreads + tid) + q) : -1;
+                if (b < 0) continue;
+                const int3 x = v[c][q];
+                const int h = claim(x.x >> 3, x.y >> 3, x.z >> 3, b);
+                if (h >= 0) atomicOr(&mask[h * 8 + (x.x & 7)], 1ull << (((x.y & 7) << 3) | (x.z & 7)));
+            }
+        if (SOURCE == kSmallPoints && bad) atomicAdd(&n_bad, bad);
+    }
+    __syncthreads();
+
+    // ---- keys: [grid 4][tile 3 x 7][upper offset 3 x 5][lower offset 3 x 4][slot 11], compacted, padded to a power of two
+    unsigned long long key[2];
+    uint32_t have = 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const unsigned long long s = slot[2 * tid + q];
+        key[q] = ~0ull;
+        if (s == 0ull) continue;
+        ++have;
+        const uint32_t a[3] = {(uint32_t)(s >> 32) & 0xFFFFu, (uint32_t)(s >> 16) & 0xFFFFu, (uint32_t)s & 0xFFFFu};
+        unsigned long long k = (s >> 48) & 15ull;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) k = (k << 7) | (a[d] >> 9);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) k = (k << 5) | ((a[d] >> 4) & 31u);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) k = (k << 4) | (a[d] & 15u);
+        key[q] = (k << 11) | (uint32_t)(2 * tid + q);
+    }
+    uint32_t n_leaf_u;
+    uint32_t at = block_exclusive_scan(have, &n_leaf_u);
+    const int n_leaf = (int)n_leaf_u;
+    int padded = 64;
+    while (padded < n_leaf) padded <<= 1;
+    for (int e = tid; e < padded; e += kSmallThreads) slot[e] = ~0ull;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (key[q] != ~0ull) slot[at++] = key[q];
+    __syncthreads();
+    for (int size = 2; size <= padded; size <<= 1)
+        for (int step = size >> 1; step > 0; step >>= 1) {
+            if (tid < padded / 2) {
+                const int i = 2 * tid - (tid & (step - 1)), j = i + step;
+                const unsigned long long x = slot[i], y = slot[j];
+                if ((x > y) == ((i & size) == 0)) { slot[i] = y; slot[j] = x; }
+            }
+            // a wave's 64 compare-exchanges of a step below 64 stay within the wave's own 128 elements
+            if (step > 64 || (step == 1 && size >= 128)) __syncthreads();
+            else { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); __builtin_amdgcn_wave_barrier(); }
+        }
+    __syncthreads();
+
+    // ---- node numbers: thread = two consecutive leaves
+    unsigned long long prev = tid ? slot[2 * tid - 1] : ~0ull;
+    uint32_t heads = 0, cnt[2] = {0, 0};
+    uint64_t pre[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int p = 2 * tid + q;
+        key[q] = p < padded ? slot[p] : ~0ull;
+        if (p >= n_leaf) continue;
+        const unsigned long long before = q ? key[0] : prev;
+        const bool first = p == 0;
+        heads += (first || (key[q] >> 23) != (before >> 23)) ? 1u : 0u;                 // a new lower node
+        heads += (first || (key[q] >> 38) != (before >> 38)) ? (1u << 16) : 0u;         // a new upper node
+        const unsigned long long* m = mask + (size_t)(key[q] & (kSmallSlots - 1)) * 8;
+        uint32_t acc = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            acc += (uint32_t)__popcll(m[w]);
+            if (w < 7) pre[q] |= (uint64_t)acc << (9 * w);
+        }
+        cnt[q] = acc;
+    }
+    {
+        uint32_t d = (cnt[0] >= (uint32_t)kDenseLeafVoxels ? cnt[0] : 0u) + (cnt[1] >= (uint32_t)kDenseLeafVoxels ? cnt[1] : 0u);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) d += (uint32_t)__shfl_xor((int)d, o);
+        if ((tid & 63) == 0 && d) atomicAdd(&dense, (unsigned long long)d);
+    }
+    uint32_t all_heads, n_vox;
+    uint32_t nodes = block_exclusive_scan(heads, &all_heads);
+    uint32_t offset = block_exclusive_scan(cnt[0] + cnt[1], &n_vox);
+    const int n_lower = (int)(all_heads & 0xFFFFu), n_upper = (int)(all_heads >> 16);
+    if (tid == 0 && (n_upper > g.cap_upper || n_lower > g.cap_lower || n_leaf > g.cap_leaf)) overflow = 256;
+    __syncthreads();
+    const bool fits = overflow == 0;
+    if (fits) {
+        for (int e = tid; e < n_upper * kUpperWords; e += kSmallThreads) g.upper_mask[e] = 0ull;
+        for (int e = tid; e < n_lower * kLowerWords; e += kSmallThreads) g.lower_mask[e] = 0ull;
+        for (int b = tid; b <= B; b += kSmallThreads) g.vox_base[b] = 0;
+        __builtin_amdgcn_s_waitcnt(0);         // the zeros have arrived before other waves update them
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int p = 2 * tid + q;
+            if (p >= n_leaf) continue;
+            const unsigned long long k = key[q], before = q ? key[0] : prev;
+            const bool first = p == 0;
+            const bool new_lower = first || (k >> 23) != (before >> 23), new_upper = first || (k >> 38) != (before >> 38);
+            nodes += (new_lower ? 1u : 0u) + (new_upper ? (1u << 16) : 0u);
+            const int l = (int)(nodes & 0xFFFFu) - 1, u = (int)(nodes >> 16) - 1;
+            const int loff = (int)(k >> 11) & 4095, uoff = (int)(k >> 23) & 32767;
+            const int b = (int)(k >> 59);
+            int o[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {      // field d of every level, most significant first
+                const int tile = (int)(k >> (38 + 7 * (2 - d))) & 127, uo = (uoff >> (5 * (2 - d))) & 31, lo = (loff >> (4 * (2 - d))) & 15;
+                o[d] = ((((tile << 9) | (uo << 4) | lo) - half) * 8);
+            }
+            if (new_upper) { g.root_key[u] = tile_key(o[0], o[1], o[2]); g.root_batch[u] = b; }
+            if (new_lower) {
+                atomicOr((unsigned long long*)(g.upper_mask + (size_t)u * kUpperWords + (uoff >> 6)), 1ull << (uoff & 63));
+                if (first || (k >> 29) != (before >> 29)) g.upper_prefix[(size_t)u * kUpperWords + (uoff >> 6)] = (uint32_t)l;
+            }
+            atomicOr((unsigned long long*)(g.lower_mask + (size_t)l * kLowerWords + (loff >> 6)), 1ull << (loff & 63));
+            if (first || (k >> 17) != (before >> 17)) g.lower_prefix[(size_t)l * kLowerWords + (loff >> 6)] = (uint32_t)p;
+            fx_leaf* lf = g.leaf + p;
+            const unsigned long long* m = mask + (size_t)(k & (kSmallSlots - 1)) * 8;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) lf->mask[w] = m[w];
+            lf->prefix = pre[q];
+            lf->offset = offset;
+            lf->origin[0] = o[0]; lf->origin[1] = o[1]; lf->origin[2] = o[2];
+            lf->batch = b;
+            // first voxel of this grid and of the empty ones before it; after the last leaf, of those behind
+            for (int e = first ? 0 : (int)(before >> 59) + 1; e <= b; ++e) g.vox_base[e] = offset;
+            if (p == n_leaf - 1)
+                for (int e = b + 1; e <= B; ++e) g.vox_base[e] = n_vox;
+            offset += cnt[q];
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) {
+        GridHeader hdr;
+        hdr.n_tiles_raw = n_upper; hdr.n_upper = n_upper; hdr.n_lower = n_lower; hdr.n_leaf = n_leaf;
+        hdr.overflow = overflow; hdr.n_leaf_raw = n_leaf; hdr.n_bad = n_bad; hdr.wide_rows = 0;
+        hdr.n_voxels = n_vox; hdr.n_voxels_dense = (int64_t)dense;
+        *g.hdr = hdr;
+        *reinterpret_cast<GridHeader*>(host) = hdr;
+    }
+    if (tid >= 64) return;                     // the first wave tells the host: B <= 16
+    if (fits && tid <= B) reinterpret_cast<int64_t*>(host + sizeof(GridHeader))[tid] = g.vox_base[tid];
+    __threadfence_system();
+    __builtin_amdgcn_wave_barrier();
+    if (tid == 0) __hip_atomic_store(host_ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------------------------- queries
 // A wave takes eight consecutive leaves, lane = (leaf, word of its mask): eight lanes' popcounts give every word its
 // place among the leaf's voxels, and the leaves' voxels are consecutive by construction (offset), so the wave's voxels
@@ -1358,6 +1580,41 @@ static fx_status scan_level(const fx_grid* g, LevelScan s, int cap_nodes, ScanSy
     FX_HIP_TRY(hipGetLastError());
     return FX_OK;
 }
+
+// The counts and ranges that the device writes into pinned host memory, and the ticket it writes last.
+struct ReadBack {
+    unsigned char* host = nullptr;
+    int32_t* host_ticket = nullptr;
+    int32_t ticket = 0;
+    fx_status prepare(int B) {
+        void* stage = nullptr;
+        const size_t ticket_off = align_up(sizeof(GridHeader) + sizeof(int64_t) * ((size_t)B + 1), 64);
+        FX_TRY(host_staging(&stage, ticket_off + 64));
+        static thread_local int32_t next_ticket = 0;
+        ticket = ++next_ticket == 0 ? ++next_ticket : next_ticket;   // never 0
+        host = (unsigned char*)stage;
+        host_ticket = reinterpret_cast<int32_t*>(host + ticket_off);
+        *(volatile int32_t*)host_ticket = 0;
+        return FX_OK;
+    }
+    hipError_t wait(hipStream_t st) const {
+        // poll the ticket for a while (a few hundred microseconds at most for the sizes where latency
+        // matters), then fall back to waiting for the stream, which also reports any device error
+        volatile int32_t* t = host_ticket;
+        bool seen = false;
+        for (int spin = 0; spin < 200000 && !seen; ++spin) {
+            seen = (*t == ticket);
+            if (!seen) __builtin_ia32_pause();
+        }
+        const hipError_t e = seen ? hipSuccess : hipStreamSynchronize(st);
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return e;
+    }
+    void take(fx_grid* g) const {
+        memcpy(&g->hdr, host, sizeof(GridHeader));
+        memcpy(g->h_vox_base, host + sizeof(GridHeader), sizeof(int64_t) * ((size_t)g->B + 1));
+    }
+};
 
 // One attempt with the given node capacities.  On FX_OK, (*out)->hdr.overflow tells whether a
 // capacity was too small (the counts found so far are valid up to the overflowing level).
@@ -1539,36 +1796,66 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
         FX_TRY_OR_FAIL(hipGetLastError());
     }
     // one read-back: counts + per-grid ranges (Sec. 3.3 step 10)
-    const size_t hdr_bytes = sizeof(GridHeader);
-    const size_t vb_bytes = sizeof(int64_t) * ((size_t)B + 1);
-    void* stage = nullptr;
-    const size_t ticket_off = align_up(hdr_bytes + vb_bytes, 64);
-    rc = host_staging(&stage, ticket_off + 64);
+    ReadBack rb;
+    rc = rb.prepare(B);
     if (rc != FX_OK) return fail(rc);
-    static thread_local int32_t next_ticket = 0;
-    const int32_t ticket = ++next_ticket == 0 ? ++next_ticket : next_ticket;   // never 0
-    volatile int32_t* h_ticket = reinterpret_cast<volatile int32_t*>((char*)stage + ticket_off);
-    *h_ticket = 0;
-    k_publish<<<1, 256, 0, st>>>(g->d_hdr, g->d_vox_base, B, (unsigned char*)stage, (int32_t*)h_ticket, ticket);
+    k_publish<<<1, 256, 0, st>>>(g->d_hdr, g->d_vox_base, B, rb.host, rb.host_ticket, rb.ticket);
     FX_TRY_OR_FAIL(hipGetLastError());
     // runs on the device while the host waits for the ticket and returns to its caller
     if (from.kind == LeafSource::kCoarsen && from.link_K) enqueue_leaf_links(g, st, from.grid, from.link_K, 2);
     else enqueue_leaf_links(g, st, nullptr, 3, 1);
-    {
-        // poll the ticket for a while (a few hundred microseconds at most for the sizes where latency
-        // matters), then fall back to waiting for the stream, which also reports any device error
-        bool seen = false;
-        for (int spin = 0; spin < 200000 && !seen; ++spin) {
-            seen = (*h_ticket == ticket);
-            if (!seen) __builtin_ia32_pause();
-        }
-        if (!seen) FX_TRY_OR_FAIL(hipStreamSynchronize(st));
-        std::atomic_thread_fence(std::memory_order_acquire);
-    }
-    memcpy(&g->hdr, stage, hdr_bytes);
-    memcpy(g->h_vox_base, (char*)stage + hdr_bytes, vb_bytes);
+    FX_TRY_OR_FAIL(rb.wait(st));
+    rb.take(g);
     dev_free(scratch, st);
 #undef FX_TRY_OR_FAIL
+    *out = g;
+    return FX_OK;
+}
+
+// The whole build in one launch (k_small_grid).  *out stays null when the grid is not one it holds: the caller goes on with
+// the passes.
+static fx_status build_small(const RowSource& rows, int64_t n_rows, const BatchRanges& joff, int32_t B, hipStream_t st, const LeafSource& from,
+                             fx_grid** out) {
+    *out = nullptr;
+    if (n_rows < 1 || n_rows > kSmallRows || B < 1 || B > 16 || (B > kInlineRanges && from.kind == LeafSource::kRows) ||
+        option(kOptGridDirect) == 1) return FX_OK;
+    fx_grid* g = new (std::nothrow) fx_grid();
+    if (!g) { set_error("host allocation failed"); return FX_ENOMEM; }
+    g->B = B; g->stream = st;
+    g->cap_leaf = g->cap_lower = (int)std::min<int64_t>(n_rows, kSmallSlots);
+    g->cap_upper = (int)std::min<int64_t>(n_rows, kRankInBlock);
+    layout(g);
+    fx_status rc = dev_alloc(&g->buf, g->buf_bytes, st);
+    if (rc != FX_OK) { delete g; return rc; }
+    layout(g);
+    g->h_vox_base = (int64_t*)calloc((size_t)B + 1, sizeof(int64_t));
+    ReadBack rb;
+    rc = rb.prepare(B);
+    if (rc != FX_OK) { fx_grid_destroy(g); return rc; }
+    hipError_t e = hipSuccess;
+#define FX_SMALL(SOURCE, TREE)                                                                                                      \
+    do {                                                                                                                            \
+        e = hipFuncSetAttribute((const void*)k_small_grid<SOURCE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLds);     \
+        if (e == hipSuccess)                                                                                                        \
+            k_small_grid<SOURCE><<<1, kSmallThreads, kSmallLds, st>>>(rows, (int)n_rows, joff, B, TREE, ptrs_of(g), rb.host,        \
+                                                                      rb.host_ticket, rb.ticket);                                   \
+    } while (0)
+    {
+        ProfScope ps(kProfVoxelsToLeaves, st);
+        if (from.kind == LeafSource::kCoarsen) FX_SMALL(kSmallCoarse, from.grid->view());
+        else if (rows.xyz) FX_SMALL(kSmallPoints, TreeView{});
+        else FX_SMALL(kSmallIjk, TreeView{});
+    }
+#undef FX_SMALL
+    if (e == hipSuccess) e = hipGetLastError();
+    if (e == hipSuccess) {
+        if (from.kind == LeafSource::kCoarsen && from.link_K) enqueue_leaf_links(g, st, from.grid, from.link_K, 2);
+        else enqueue_leaf_links(g, st, nullptr, 3, 1);
+        e = rb.wait(st);
+    }
+    if (e != hipSuccess) { fx_grid_destroy(g); set_error("grid build: %s", hipGetErrorString(e)); return FX_EDEVICE; }
+    rb.take(g);
+    if (g->hdr.overflow) { fx_grid_destroy(g); return FX_OK; }
     *out = g;
     return FX_OK;
 }
@@ -1583,6 +1870,8 @@ static fx_status build_with_ranges(const RowSource& rows, int64_t n_rows, const 
     int cap_lower = (int)std::min<int64_t>(some, 64 * (int64_t)std::max(B, 1) + 512 + n_rows / 256);
     int cap_leaf = (int)std::min<int64_t>(some, 65536 + n_rows / 8);
     bool direct = option(kOptGridDirect) == 1;
+    FX_TRY(build_small(rows, n_rows, d_joff, B, st, LeafSource(), out));
+    if (*out) return FX_OK;
     for (int attempt = 0; attempt < 9; ++attempt) {
         fx_grid* g = nullptr;
         FX_TRY(build_attempt(rows, n_rows, d_joff, B, cap_upper, cap_lower, cap_leaf, direct, st, &g));
@@ -1757,6 +2046,8 @@ fx_status fx::grid_coarsen2_for_map(const fx_grid* g, int K, hipStream_t st, fx_
     const BatchRanges none{};
     LeafSource from;
     from.kind = LeafSource::kCoarsen; from.grid = g; from.link_K = K;
+    FX_TRY(build_small(RowSource{}, g->hdr.n_leaf, none, g->B, st, from, &o));
+    if (o) { *out = o; return FX_OK; }
     FX_TRY(build_attempt(RowSource{}, g->hdr.n_leaf, none, g->B, g->hdr.n_upper, g->hdr.n_lower, g->hdr.n_leaf, true, st, &o, from));
     if (o->hdr.overflow) {
         const int ov = o->hdr.overflow;

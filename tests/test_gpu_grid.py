@@ -206,3 +206,41 @@ def test_rows_per_workgroup_of_the_row_passes_at_their_limit(n):
     g = B.build_index_grid(pts, np.array([[0, n]]))
     og = O.OracleGrid(few, np.array([[0, few.shape[0]]]))
     H.check_grid(g, og)
+
+
+@pytest.mark.parametrize("case", ["one", "rows", "rows+1", "slots", "slots+1", "tiles", "tiles+1", "edge", "beyond", "batch8", "batch9"])
+def test_small_grids_in_one_launch_and_at_its_limits(case):
+    # up to 16384 rows, 2048 leaves, 72 root tiles, coordinates in [-2^18, 2^18) and 8 grids in one launch; one more of
+    # any and the build takes the passes
+    rng = np.random.default_rng(800)
+    jo = None
+    if case == "one":
+        pts = np.array([[-1, 5, 9]], np.int32)
+    elif case.startswith("rows"):
+        pts = rng.integers(-40, 40, size=(16384 + (case == "rows+1"), 3)).astype(np.int32)
+    elif case.startswith("slots"):
+        n = 2048 + (case == "slots+1")
+        pts = np.stack([np.arange(n) % 13 - 6, np.arange(n) // 13 % 13, np.arange(n) // 169], axis=1).astype(np.int32) * 8
+    elif case.startswith("tiles"):
+        n = 72 + (case == "tiles+1")
+        pts = np.stack([np.arange(n) % 9 - 4, np.arange(n) // 9, -np.arange(n) % 3], axis=1).astype(np.int32) * 4096 + 7
+    elif case in ("edge", "beyond"):
+        m = 1 << 18
+        pts = np.concatenate([rng.integers(-20, 20, size=(500, 3)), [[m - 1, -m, 0], [-m, m - 1, m - 1 if case == "edge" else m]]]).astype(np.int32)
+    else:
+        pts = rng.integers(-30, 30, size=(5000, 3)).astype(np.int32)
+        b = int(case[5:])
+        cut = np.sort(np.concatenate([[0, 0], rng.integers(0, 5000, size=b - 2), [5000]]))     # the first grid is empty
+        jo = np.stack([cut[:-1], cut[1:]], axis=1).astype(np.int64)
+    pts = np.concatenate([pts, pts[: pts.shape[0] // 7]]) if case not in ("rows", "rows+1") and jo is None else pts
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]) if jo is None else jo)
+    H.check_grid(g, og)
+    gc, ogc = g.coarsen2(), og.coarsen2()
+    H.check_grid(gc, ogc)
+    d = torch.from_numpy(np.ascontiguousarray(pts)).cuda()
+    batch = torch.zeros(pts.shape[0], dtype=torch.int32, device="cuda")
+    if jo is not None:
+        for b in range(jo.shape[0]):
+            batch[jo[b, 0]:jo[b, 1]] = b
+    idx = g.ijk_to_index(d, batch).cpu().numpy()
+    assert np.array_equal(g.ijk()[0].cpu().numpy()[idx], pts)
