@@ -129,6 +129,12 @@ __device__ __forceinline__ int leaf_weight_index(int kappa, int c, int p, int n_
     return mirrored ? ((26 - kappa) * n_produce + p) * n_contract + c : (kappa * n_contract + c) * n_produce + p;
 }
 
+// Sixteen contracted channels (J = 4) fill 64 KB with the window alone: with the weights in LDS besides (27 KB), one
+// workgroup fits a compute unit.  In registers (108 for up to 16 produced channels) two do, and two waves per SIMD are
+// the register budget that goes with it: 16 -> 8 on a solid scene of 1 M voxels 279 -> 200 us.
+constexpr bool leaf_weights_in_registers(int J, int NT) { return 27 * J * NT <= (J == 4 ? 108 : 64); }
+constexpr int leaf_waves_per_simd(int J, int NT) { return J == 4 && NT == 1 ? 2 : 4; }
+
 // J = C_in / 4 MFMA k-steps per tap, NT row tiles of 16 produced channels (n_produce <= 16 NT of them exist,
 // a multiple of 4: the others multiply zero weights and are not stored), WREG: every lane keeps its share of
 // the weights (27 * J * NT values) in registers instead of LDS.
@@ -142,7 +148,7 @@ __device__ __forceinline__ int leaf_weight_index(int kappa, int c, int p, int n_
 // input channels J*q .. J*q + J-1 of its voxel's neighbour (k-step j contracts channels {J*q + j})
 // and, per row tile, the same channels of output channel 16*nt + v of the weights.
 template <int J, int NT, bool WREG, bool FULLP>     // FULLP: all 16 NT produced channels exist
-__global__ __launch_bounds__(kLeafThreads, 4) void k_conv_leaf(TreeView t, const float* __restrict__ feat,
+__global__ __launch_bounds__(kLeafThreads, leaf_waves_per_simd(J, NT)) void k_conv_leaf(TreeView t, const float* __restrict__ feat,
                                                             const float* __restrict__ w, float* __restrict__ out,
                                                             int64_t n_voxels, int mirrored, int n_produce_arg) {
     constexpr int C_in = 4 * J, C_out = 16 * NT;
@@ -1018,8 +1024,6 @@ fx_status leaf_wgrad16_partial(const fx_grid* g, const void* d_feat, const void*
 }
 
 namespace {
-
-constexpr bool leaf_weights_in_registers(int J, int NT) { return 27 * J * NT <= 64; }
 
 size_t leaf_lds_bytes(int J, int NT) {
     const int C_in = 4 * J, C_out = 16 * NT;
