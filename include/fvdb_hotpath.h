@@ -86,7 +86,8 @@ void fx_release_cached_memory(void);
  *   "leaf_dispatch"  3x3x3 stride-1 maps: 0 never / 1 always (when the shape allows) hand the call to the
  *                    leaf-window kernels, 2 always split it per leaf; automatic: by mean leaf occupancy and the
  *                    share of voxels in dense leaves (see fx_sparse_conv_fwd)
- *   "fp32_tiles"     1: FX_F32 takes the matrix-unit tile kernel at any grid size (automatic: from ~128 tiles on)
+ *   "fp32_tiles"     1: FX_F32 takes the matrix-unit tile kernel on every tiled map (automatic: only where tiles are many,
+ *                    rows shared and produced channels more than 16; otherwise one wave per 16 voxels)
  *   "conv_gather"    0 / 1: the LDS-staged / the gather kernel on every tiled map (automatic: by the kind of map)
  *   "gather_lds"     0: the gather kernels fetch their weights per step instead of keeping them in LDS; 1: the
  *                    forward gather kernel keeps one 64-channel output slice's weights in LDS (automatic: two

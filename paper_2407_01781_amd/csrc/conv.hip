@@ -1092,6 +1092,154 @@ __global__ void k_conv_scalar4(const int32_t* __restrict__ nbmap, int64_t n_out,
     }
 }
 
+// ---------------------------------------------------------------------------------- fp32, few tiles
+// fp32 over a tiled map whose tiles are too few to fill the chip with one workgroup each: one wave owns 16 voxels (half a
+// column block) x 16 NT produced channels, so that ten thousand voxels at 32 channels are 1200 independent waves.  The
+// voxels' input rows are resolved from the map's id blocks into LDS (four taps at a time, independent loads), taps that
+// no voxel of the 16 has are dropped, and the wave walks (tap, 16 channels): one 16-byte piece of a row per lane and the
+// weights straight from the caller's array, kF32Batch steps ahead of the multiplies.  v_mfma_f32_16x16x4_f32 multiplies
+// in true fp32; the produced channels are its rows, so a lane ends with four adjacent channels of one voxel.  Bound by the
+// latency of the gathers at small sizes, by the matrix units and weight reads from L2 beyond.  Measured against one
+// scalar thread per four outputs and the dense table that took (14 us at first use): sphere of 9.9 k voxels 32 -> 32
+// 53 -> 20 us, 64 -> 64 140 -> 44, 1.4 k voxels 40 -> 16, 48.8 k voxels 64 -> 64 492 -> 126 (151 before the loads of
+// a stage were made unconditional, so that all of them are in flight together).
+constexpr int kF32Voxels = 16;
+constexpr int kF32Batch = 4;
+
+template <int NT, bool TRANSPOSED>
+__global__ void __launch_bounds__(64)
+k_conv_gather_f32(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
+                  const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
+                  int block_stride, int K3, const float* __restrict__ feat, const float* __restrict__ w, int C_in, int C_out,
+                  int n_col, float* __restrict__ out, int flipped, int vec_store) {
+    __shared__ int32_t row_of[29][kF32Voxels];       // by rank of the tap among those the 16 voxels have (28: ranks they do not)
+    __shared__ int32_t tap_of[29];
+    const int lane = threadIdx.x, v = lane & 15, q = lane >> 4;
+    const int col = (int)(blockIdx.x % n_col);
+    const int64_t half = blockIdx.x / n_col;
+    const int hb = (int)(half & 1), g = (int)((half >> 1) % kGroupsPerTile);
+    const int64_t tile = (half >> 1) / kGroupsPerTile;
+    const TileHeader* H = tile_hdr + tile;
+    const int wv = tile_wave_of(g), gi = tile_slot_of(g), n = hb * kF32Voxels + v;
+    const uint32_t gm = (uint32_t)uni((int)H->group_mask[g]), wm = (uint32_t)uni((int)H->wave_mask[wv]);
+    const int n_valid = uni(H->n_out), flags = uni(H->flags), win_lo = uni(H->win_lo), win_n = uni(H->win_n);
+    const size_t blk0 = (size_t)tile * block_stride + (uint32_t)uni((int)H->wave_block0[wv]);
+    const int local = tile_perm[tile * kTileT + g * kGroup + n];
+    if (__ballot(local < n_valid) == 0) return;      // the last tile's empty column blocks
+
+    // lane (v, q) resolves the taps of rank q, q + 4, ... of the group's mask (each has an id block) for voxel v, all
+    // loads of a stage unconditional so that they are in flight together
+    int n_live = 0;
+    if (gm) {
+        const int32_t* rows = tile_rows + tile * (int64_t)row_stride;
+        uint32_t id[7], mine[7];
+        uint32_t m = gm;
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const uint32_t m1 = m & (m - 1), m2 = m1 & (m1 - 1), m3 = m2 & (m2 - 1);      // 0 stays 0
+            mine[j] = q == 0 ? m : q == 1 ? m1 : q == 2 ? m2 : m3;
+            m = m3 & (m3 - 1);
+            const int kappa = __ffs(mine[j] ? mine[j] : gm) - 1;
+            id[j] = tile_blocks[(blk0 + __popc(wm & ((1u << kappa) - 1u))) * kIdBlockElems + n * kGroupsPerWave + gi];
+        }
+        int32_t listed[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            if (flags & kTileLdsOffsets) id[j] = id[j] / kRowBytes == (uint32_t)kRowCap ? kNoRow : id[j] / kRowBytes;
+            if (!mine[j]) id[j] = kNoRow;
+            const bool far = id[j] != kNoRow && id[j] >= (uint32_t)win_n;
+            listed[j] = *(far ? rows + (id[j] - (uint32_t)win_n) : reinterpret_cast<const int32_t*>(H));
+        }
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const int32_t r = id[j] == kNoRow ? -1 : id[j] < (uint32_t)win_n ? win_lo + (int32_t)id[j] : listed[j];
+            const uint64_t b = __ballot(r >= 0);
+            int at = 28;                              // taps that none of the 16 voxels has go nowhere
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if ((b >> (16 * s)) & 0xffffu) { if (q == s) at = n_live; ++n_live; }
+            row_of[at][v] = r;
+            tap_of[at] = __ffs(mine[j]) - 1;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a wave's LDS accesses are processed in order
+    __builtin_amdgcn_wave_barrier();
+
+    const int nchunk = C_in >> 4, n_steps = n_live * nchunk;
+    int co[NT];                                       // the channel whose weights this lane reads (columns beyond the last: dropped)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) co[t] = min(16 * (col * NT + t) + v, C_out - 1);
+    f32x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    int c = 0, rank = 0;                              // the next step to fetch; past the last one the last tap is read again
+    auto fetch = [&](f32x4 (&x)[kF32Batch], f32x4 (&wt)[kF32Batch][NT], bool (&has)[kF32Batch]) {
+#pragma unroll
+        for (int u = 0; u < kF32Batch; ++u) {
+            const int32_t r = row_of[rank][v];
+            const int kappa = uni(tap_of[rank]), kw = flipped ? K3 - 1 - kappa : kappa;
+            const int ci = 16 * c + 4 * q;
+            has[u] = r >= 0;
+            x[u] = *reinterpret_cast<const f32x4*>(feat + (int64_t)max(r, 0) * C_in + ci);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (TRANSPOSED) {
+                    wt[u][t] = *reinterpret_cast<const f32x4*>(w + ((int64_t)kw * C_out + co[t]) * C_in + ci);
+                } else {
+                    const float* p = w + ((int64_t)kw * C_in + ci) * C_out + co[t];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) wt[u][t][j] = p[(int64_t)j * C_out];
+                }
+            }
+            ++c;
+            const bool wrap = c == nchunk;
+            c = wrap ? 0 : c;
+            rank = min(rank + (wrap ? 1 : 0), n_live - 1);
+        }
+    };
+    auto multiply = [&](const f32x4 (&x)[kF32Batch], const f32x4 (&wt)[kF32Batch][NT], const bool (&has)[kF32Batch], int done) {
+#pragma unroll
+        for (int u = 0; u < kF32Batch; ++u) {
+            if (done + u < n_steps) {                 // uniform
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float xv = has[u] ? x[u][j] : 0.f;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[u][t][j], xv, acc[t], 0, 0, 0);
+                }
+            }
+        }
+    };
+    if (n_steps > 0) {
+        f32x4 xa[kF32Batch], xb[kF32Batch], wa[kF32Batch][NT], wb[kF32Batch][NT];
+        bool ha[kF32Batch], hb2[kF32Batch];
+        fetch(xa, wa, ha);
+#pragma unroll 1
+        for (int s = 0; s < n_steps; s += 2 * kF32Batch) {
+            fetch(xb, wb, hb2);
+            __builtin_amdgcn_sched_barrier(0);        // a batch is requested before the one at hand is multiplied
+            multiply(xa, wa, ha, s);
+            fetch(xa, wa, ha);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(xb, wb, hb2, s + kF32Batch);
+        }
+    }
+    if (local >= n_valid) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int c0 = 16 * (col * NT + t) + 4 * q;
+        float* o = out + (tile * kTileT + local) * (int64_t)C_out + c0;
+        if (vec_store) {
+            if (c0 < C_out) *reinterpret_cast<f32x4*>(o) = acc[t];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c0 + j < C_out) o[j] = acc[t][j];
+        }
+    }
+}
+
 template <typename T, bool OUT_F32>
 static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* wp, int32_t* counters, int C_in, int C_out,
                               void* out, hipStream_t st) {
@@ -1170,6 +1318,25 @@ static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void*
                                                                  km->row_stride, km->d_tile_blocks, km->block_stride,
                                                                  n_items, (const uint16_t*)feat, (const uint16_t*)wp,
                                                                  C_in, C_out, out);
+    return hipGetLastError();
+}
+
+static hipError_t launch_gather_f32(const fx_kmap* km, const float* feat, const float* w, int C_in, int C_out, float* out,
+                                    int mode, hipStream_t st) {
+    const int64_t halves = km->n_tiles * (int64_t)kGroupsPerTile * 2;
+    // two n-tiles per wave share the gathered rows once there are four waves for every SIMD without them
+    const bool two = C_out > 16 && halves * ((C_out + 15) / 16) >= (int64_t)compute_units() * 16;
+    const int n_col = two ? (C_out + 31) / 32 : (C_out + 15) / 16;
+    const unsigned grid = (unsigned)(halves * n_col);
+    const int flipped = (mode & kWeightsFlipped) ? 1 : 0;
+    const int vec_store = C_out % 4 == 0 && ((uintptr_t)out & 15) == 0;
+#define FX_GATHER_F32(NT_, TR_)                                                                                          \
+    k_conv_gather_f32<NT_, TR_><<<grid, 64, 0, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride,    \
+                                                     km->d_tile_blocks, km->block_stride, km->K3, feat, w, C_in, C_out,   \
+                                                     n_col, out, flipped, vec_store)
+    if (mode & kWeightsTransposed) { if (two) FX_GATHER_F32(2, true); else FX_GATHER_F32(1, true); }
+    else { if (two) FX_GATHER_F32(2, false); else FX_GATHER_F32(1, false); }
+#undef FX_GATHER_F32
     return hipGetLastError();
 }
 
@@ -1274,9 +1441,22 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
     // The tile kernel takes input rows in 64-byte chunks (32 channels of a 16-bit type, 16 of fp32) and
     // pads the produced channels to 64 with zero weights; the gather kernel for strided maps needs whole
     // 64-channel slices of a 16-bit type.  Everything else is left to the scalar kernel.
-    // fp32 multiplies at 1/16 of the 16-bit rate on the matrix units, so a grid of few tiles (one
-    // workgroup each) is served faster by the scalar kernel spread over the whole chip
     const int64_t n_items = km->n_tiles * (int64_t)((C_out + kCoutSlice - 1) / kCoutSlice);
+    // fp32 by independent waves where the tile kernel fills the chip badly (few tiles), stages rows that are used about
+    // once, or pads most of its 64 channels.  Measured, waves / tiles in us: 96 items (48.8 k voxels of sheets, 64 -> 64)
+    // 126 / 194, 174 items equal; 2x2x2 strided on 195 k voxels 64 -> 64 70 / 121, 3x3x3 219 / 366, on 980 k voxels 64 -> 128
+    // 401 / 516; 16 -> 16 on 980 k voxels 174 / 228; 32 -> 32 on 195 k voxels (381 items) 137 / 201, but 425 / 395 on 980 k
+    // LiDAR voxels and 68 / 67 on the inverse map.  Pieces of 16 bytes need rows and weights aligned to them; the last
+    // condition keeps the launch below 2^32 threads.
+    const bool f32_waves = in_dt == FX_F32 && km->n_tiles > 0 && C_in % 16 == 0 && option(kOptFp32Tiles) != 1 && !force_scalar &&
+                           (n_items < compute_units() / 2 || !map_shares_rows(km) ||
+                            (!km->is_inverse && (C_out <= 16 || (C_out <= 32 && n_items < 2 * compute_units())))) &&
+                           (((uintptr_t)d_feat | (uintptr_t)d_w) & 15) == 0 && n_items < (1 << 19);
+    if (f32_waves) {
+        ProfScope ps(kProfConvGather, st);
+        FX_HIP_TRY(launch_gather_f32(km, (const float*)d_feat, (const float*)d_w, C_in, C_out, (float*)d_out, mode, st));
+        return FX_OK;
+    }
     const bool mfma = conv_tiles_shape_ok(km, in_dt, C_in, C_out) &&
                       (in_dt != FX_F32 || n_items >= compute_units() / 2 || option(kOptFp32Tiles) == 1) &&   // fp32_tiles = 1: at any size
                       !force_scalar;
