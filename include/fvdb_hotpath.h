@@ -248,8 +248,12 @@ void fx_kmap_destroy(fx_kmap* km);
  * Which kernel runs (all give the same sum within the stated tolerance):
  *   - the matrix units (v_mfma_f32_32x32x16 for FX_F16 / FX_BF16; v_mfma_f32_32x32x2_f32, true fp32 products, for
  *     FX_F32) when the map is tiled (K^3 <= 27), C_in * sizeof(element) is a multiple of 64 bytes (32 channels of
- *     a 16-bit type, 16 of fp32) and C_out is even (padded to 64 with zero weights); FX_F32 only from about 128
- *     tiles on (smaller grids are served faster by the scalar kernel spread over the chip);
+ *     a 16-bit type, 16 of fp32) and C_out is even (padded to 64 with zero weights);
+ *   - FX_F32 with C_in a multiple of 16 and 16-byte aligned feat and w, where those tiles are few (fewer than half the
+ *     compute units), rows are not shared (K = stride, strided maps) or C_out is small: one wave per 16 voxels on
+ *     v_mfma_f32_16x16x4_f32, true fp32 products as well; few tiles of any other fp32 shape: the scalar kernel;
+ *   - FX_F16 / FX_BF16 with C_in <= 16 on maps with a dense table: v_mfma_f32_32x32x16 with (offset, channel) as the
+ *     contracted dimension;
  *   - on a 3x3x3 stride-1 submanifold map whose grid is locally dense (mean leaf occupancy >= 0.40, or >= 0.08
  *     for FX_F32 with C_in not a multiple of 16) and whose shape fx_sparse_conv_leaf_fwd serves: the
  *     leaf-window kernels;
