@@ -39,6 +39,40 @@ __device__ __forceinline__ typename Words<N>::type load_channels(const uint16_t*
 }
 
 // ---------------------------------------------------------------------------------- forward
+// A sum runs over the offsets that a row has.  The multiplies give a missing neighbour a row of zeros, which adds nothing
+// unless a weight is infinite or NaN; a workgroup that stages such a weight takes this form, which leaves missing
+// neighbours out, for all of its rows (one thread per output element, in the order of the scalar kernel).
+template <typename T> __device__ __forceinline__ bool not_finite(uint16_t bits);
+template <> __device__ __forceinline__ bool not_finite<__bf16>(uint16_t bits) { return (bits & 0x7F80u) == 0x7F80u; }
+template <> __device__ __forceinline__ bool not_finite<_Float16>(uint16_t bits) { return (bits & 0x7C00u) == 0x7C00u; }
+
+template <typename T, bool OUT_F32>
+__device__ __forceinline__ void conv_existing_pairs(const int32_t* __restrict__ table, int64_t n_rows, int K3,
+                                                    const uint16_t* __restrict__ feat, const uint16_t* __restrict__ w, int C_in,
+                                                    int C_out, void* __restrict__ out, int mode, int co0, int cols) {
+    const int64_t n = n_rows * cols, stride = (int64_t)gridDim.x * kLdThreads;
+#pragma unroll 1
+    for (int64_t e = (int64_t)blockIdx.x * kLdThreads + threadIdx.x; e < n; e += stride) {
+        const int64_t row = e / cols;
+        const int co = co0 + (int)(e - row * cols);
+        float acc = 0.f;
+#pragma unroll 1
+        for (int kappa = 0; kappa < K3; ++kappa) {
+            const int32_t r = table[row * K3 + kappa];
+            if (r < 0) continue;
+            const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
+#pragma unroll 1
+            for (int ci = 0; ci < C_in; ++ci) {
+                const uint16_t wv = (mode & kWeightsTransposed) ? w[(kw * C_out + co) * C_in + ci] : w[(kw * C_in + ci) * C_out + co];
+                acc = fmaf(Elem<T>::to_float(feat[(int64_t)r * C_in + ci]), Elem<T>::to_float(wv), acc);
+            }
+        }
+        const int64_t at = row * C_out + co;
+        if (OUT_F32) reinterpret_cast<float*>(out)[at] = acc;
+        else reinterpret_cast<uint16_t*>(out)[at] = Elem<T>::from_float(acc);
+    }
+}
+
 // Wave = 32 consecutive rows of the table.  The rows' K3 entries are contiguous: read coalesced, kept in LDS (a stride of
 // 27 words hits all banks).  Per multiply, lane (n, h) gathers the eight (offset, channel) values of voxel n that the
 // operand layout wants from it: two rows of four channels, one of eight, or half a row of sixteen.  The gathers of
@@ -57,6 +91,7 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t* nb = reinterpret_cast<int32_t*>(lds_raw + (size_t)n_steps * NT * 1024) + wave * kGroup * K3;
     const int co0 = blockIdx.y * 32 * NT;
+    bool odd_weight = false;
     for (int e0 = threadIdx.x; e0 < n_steps * NT * 512; e0 += 7 * kLdThreads) {      // seven loads in flight
         uint16_t v[7];
 #pragma unroll
@@ -71,10 +106,15 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
             }
         }
 #pragma unroll
+        for (int u = 0; u < 7; ++u) odd_weight |= not_finite<T>(v[u]);
+#pragma unroll
         for (int u = 0; u < 7; ++u)
             if (e0 + u * kLdThreads < n_steps * NT * 512) wl[e0 + u * kLdThreads] = v[u];
     }
-    __syncthreads();
+    if (__syncthreads_or(odd_weight)) {
+        conv_existing_pairs<T, OUT_F32>(table, n_rows, K3, feat, w, C_in, C_out, out, mode, co0, min(C_out - co0, 32 * NT));
+        return;
+    }
     const int n = lane & 31, h = lane >> 5;
     const int64_t n_blocks = (n_rows + kGroup - 1) / kGroup, stride = (int64_t)gridDim.x * kLdWaves;
     for (int64_t blk = (int64_t)blockIdx.x * kLdWaves + wave; blk < n_blocks; blk += stride) {

@@ -70,3 +70,35 @@ def test_low_depth_other_kernel_sizes(K, stride, c_in, c_out):
     num = np.sqrt(((gw - ref) ** 2).sum(axis=(1, 2)))
     den = np.maximum(np.sqrt((ref ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))
     assert (num / den).max() <= 2e-3
+
+
+def _same_non_finite(y, ref):
+    """Infinities and NaN exactly where the reference has them; returns the elements that are finite in both."""
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(ref), ref, 0), np.where(np.isinf(y), y, 0))
+    return np.isfinite(ref)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 4, 32), ("bf16", 3, 40), ("bf16", 8, 100), ("f16", 16, 64)])
+@pytest.mark.parametrize("backward", [False, True])
+def test_non_finite_weights_reach_only_the_rows_with_that_tap(dtype, c_in, c_out, backward):
+    # a sum runs over existing neighbours: an infinite or NaN weight of one offset must not turn rows without a neighbour
+    # there into NaN (0 * inf).  One output column holds the infinity, another the NaN; the rest stay finite everywhere.
+    pts = _cloud(700)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, wt = G.features_and_weights(41, og.num_voxels, c_in, c_out, 27, dtype)
+    wt[3, 0, 5] = np.inf
+    wt[22, c_in - 1, c_out - 1] = np.nan
+    d_x = H.to_device_storage(feat, dtype)
+    if backward:
+        wt_b = np.ascontiguousarray(wt.transpose(0, 2, 1))
+        y = fx.sparse_conv_bwd_data(km, d_x, H.to_device_storage(wt_b, dtype), out_dtype=torch.float32)
+        ref = O.conv_bwd_data(og, og, 3, 1, feat, wt_b)
+    else:
+        y = fx.sparse_conv_fwd(km, d_x, H.to_device_storage(wt, dtype), out_dtype=torch.float32)
+        ref = O.conv(og, og, 3, 1, feat, wt)
+    y = y.cpu().numpy()
+    ok = _same_non_finite(y, ref)
+    assert 0 < (~ok).sum() < 2 * og.num_voxels
+    assert np.abs(y[ok] - ref[ok]).max() <= 1e-4 * np.sqrt(27 * c_in)
