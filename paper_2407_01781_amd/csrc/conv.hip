@@ -1225,6 +1225,35 @@ k_conv_gather_f32(const TileHeader* __restrict__ tile_hdr, const uint16_t* __res
             multiply(xb, wb, hb2, s + kF32Batch);
         }
     }
+    // A sum runs over the taps that a voxel has.  The multiplies give a missing one zeros, which add nothing unless a
+    // weight is infinite or NaN; that leaves a sum that is not finite, and a wave with such a sum makes its sums again
+    // from existing taps only.
+    bool again = false;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) again |= !isfinite(acc[t][j]);
+    if (__ballot(again)) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int s = 0; s < n_live; ++s) {
+            const int32_t r = row_of[s][v];
+            if (r < 0) continue;
+            const int kw = flipped ? K3 - 1 - tap_of[s] : tap_of[s];
+#pragma unroll 1
+            for (int ci = 0; ci < C_in; ++ci) {
+                const float x = feat[(int64_t)r * C_in + ci];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int oc = min(16 * (col * NT + t) + 4 * q + j, C_out - 1);
+                        acc[t][j] = fmaf(x, TRANSPOSED ? w[((int64_t)kw * C_out + oc) * C_in + ci] : w[((int64_t)kw * C_in + ci) * C_out + oc], acc[t][j]);
+                    }
+            }
+        }
+    }
     if (local >= n_valid) return;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {

@@ -60,3 +60,34 @@ def test_two_column_blocks_a_wave(c_in, c_out):
 @pytest.mark.parametrize("c_in,c_out", [(16, 32), (32, 16)])
 def test_unaligned_rows_take_the_scalar_kernel(c_in, c_out):
     _check(500, 3, 1, c_in, c_out, shift=1)
+
+
+@pytest.mark.parametrize("K,stride,n,c_in,c_out", [(3, 1, 700, 32, 32), (3, 1, 700, 16, 5), (3, 1, 20_000, 64, 64), (2, 2, 3000, 32, 64),
+                                                   (3, 2, 3000, 48, 40)])
+@pytest.mark.parametrize("backward", [False, True])
+def test_non_finite_weights_reach_only_the_rows_with_that_tap(K, stride, n, c_in, c_out, backward):
+    # 0 * inf is NaN: an infinite or NaN weight of one offset must not reach rows without a neighbour there.  One output
+    # column holds the infinity, another the NaN; the others stay finite everywhere.
+    pts = _cloud(n)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, K, stride)
+    ogo = O.output_grid(og, K, stride)
+    n_src, n_dst = (ogo, og) if backward else (og, ogo)
+    x, wt = G.features_and_weights(33, n_src.num_voxels, c_in, c_out, K ** 3, "f32")
+    wt[1, 0, 2] = np.inf
+    wt[K ** 3 - 2, c_in - 1, c_out - 1] = np.nan
+    if backward:
+        wt = np.ascontiguousarray(wt.transpose(0, 2, 1))
+        y = fx.sparse_conv_bwd_data(km, torch.from_numpy(x).cuda(), torch.from_numpy(wt).cuda())
+        ref = O.conv_bwd_data(og, ogo, K, stride, x, wt)
+    else:
+        y = fx.sparse_conv_fwd(km, torch.from_numpy(x).cuda(), torch.from_numpy(wt).cuda())
+        ref = O.conv(og, ogo, K, stride, x, wt)
+    y = y.cpu().numpy()
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    assert np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
+    ok = np.isfinite(ref)
+    assert 0 < (~ok).sum() < 2 * n_dst.num_voxels
+    # the row-wise bar of the finite case, over the columns that are finite everywhere
+    cols = ok.all(axis=0)
+    H.conv_tolerance_check(y[:, cols], ref[:, cols], "f32", K ** 3, c_in)
