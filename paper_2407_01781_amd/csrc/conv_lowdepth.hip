@@ -39,45 +39,15 @@ __device__ __forceinline__ typename Words<N>::type load_channels(const uint16_t*
 }
 
 // ---------------------------------------------------------------------------------- forward
-// A sum runs over the offsets that a row has.  The multiplies give a missing neighbour a row of zeros, which adds nothing
-// unless a weight is infinite or NaN; a workgroup that stages such a weight takes this form, which leaves missing
-// neighbours out, for all of its rows (one thread per output element, in the order of the scalar kernel).
-template <typename T> __device__ __forceinline__ bool not_finite(uint16_t bits);
-template <> __device__ __forceinline__ bool not_finite<__bf16>(uint16_t bits) { return (bits & 0x7F80u) == 0x7F80u; }
-template <> __device__ __forceinline__ bool not_finite<_Float16>(uint16_t bits) { return (bits & 0x7C00u) == 0x7C00u; }
-
-template <typename T, bool OUT_F32>
-__device__ __forceinline__ void conv_existing_pairs(const int32_t* __restrict__ table, int64_t n_rows, int K3,
-                                                    const uint16_t* __restrict__ feat, const uint16_t* __restrict__ w, int C_in,
-                                                    int C_out, void* __restrict__ out, int mode, int co0, int cols) {
-    const int64_t n = n_rows * cols, stride = (int64_t)gridDim.x * kLdThreads;
-#pragma unroll 1
-    for (int64_t e = (int64_t)blockIdx.x * kLdThreads + threadIdx.x; e < n; e += stride) {
-        const int64_t row = e / cols;
-        const int co = co0 + (int)(e - row * cols);
-        float acc = 0.f;
-#pragma unroll 1
-        for (int kappa = 0; kappa < K3; ++kappa) {
-            const int32_t r = table[row * K3 + kappa];
-            if (r < 0) continue;
-            const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
-#pragma unroll 1
-            for (int ci = 0; ci < C_in; ++ci) {
-                const uint16_t wv = (mode & kWeightsTransposed) ? w[(kw * C_out + co) * C_in + ci] : w[(kw * C_in + ci) * C_out + co];
-                acc = fmaf(Elem<T>::to_float(feat[(int64_t)r * C_in + ci]), Elem<T>::to_float(wv), acc);
-            }
-        }
-        const int64_t at = row * C_out + co;
-        if (OUT_F32) reinterpret_cast<float*>(out)[at] = acc;
-        else reinterpret_cast<uint16_t*>(out)[at] = Elem<T>::from_float(acc);
-    }
-}
-
 // Wave = 32 consecutive rows of the table.  The rows' K3 entries are contiguous: read coalesced, kept in LDS (a stride of
 // 27 words hits all banks).  Per multiply, lane (n, h) gathers the eight (offset, channel) values of voxel n that the
 // operand layout wants from it: two rows of four channels, one of eight, or half a row of sixteen.  The gathers of
 // seven multiplies are in flight together.  The weights are laid out in operand order in LDS once per (persistent)
 // workgroup; with two n-tiles (NT) the columns interleave, so a lane stores two adjacent channels.
+// A sum runs over the offsets that a row has.  The multiplies give a missing neighbour a row of zeros, which adds nothing
+// unless a weight is infinite or NaN; that leaves sums that are not finite, and a wave with such a sum makes the sums of
+// its 32 rows again from existing neighbours only.  (4 -> 32 on 347 k voxels takes 25.2 us; 28.1 with a look at the weights
+// as they are staged instead, whose loads then waited for each other.)
 template <typename T, bool OUT_F32, int CP, int NT, bool WHOLE>
 __global__ void __launch_bounds__(kLdThreads, 4)
 k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const uint16_t* __restrict__ feat,
@@ -91,7 +61,6 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t* nb = reinterpret_cast<int32_t*>(lds_raw + (size_t)n_steps * NT * 1024) + wave * kGroup * K3;
     const int co0 = blockIdx.y * 32 * NT;
-    bool odd_weight = false;
     for (int e0 = threadIdx.x; e0 < n_steps * NT * 512; e0 += 7 * kLdThreads) {      // seven loads in flight
         uint16_t v[7];
 #pragma unroll
@@ -106,15 +75,10 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
             }
         }
 #pragma unroll
-        for (int u = 0; u < 7; ++u) odd_weight |= not_finite<T>(v[u]);
-#pragma unroll
         for (int u = 0; u < 7; ++u)
             if (e0 + u * kLdThreads < n_steps * NT * 512) wl[e0 + u * kLdThreads] = v[u];
     }
-    if (__syncthreads_or(odd_weight)) {
-        conv_existing_pairs<T, OUT_F32>(table, n_rows, K3, feat, w, C_in, C_out, out, mode, co0, min(C_out - co0, 32 * NT));
-        return;
-    }
+    __syncthreads();
     const int n = lane & 31, h = lane >> 5;
     const int64_t n_blocks = (n_rows + kGroup - 1) / kGroup, stride = (int64_t)gridDim.x * kLdWaves;
     for (int64_t blk = (int64_t)blockIdx.x * kLdWaves + wave; blk < n_blocks; blk += stride) {
@@ -157,23 +121,70 @@ k_conv_lowdepth(const int32_t* __restrict__ table, int64_t n_rows, int K3, const
                 }
             }
         }
+        // All gathers have arrived (vmcnt 0): said here once, because the compiler cannot tell it across the skipped steps and
+        // waits for every store before the next where its registers are those of a gather (8 -> 64: 51 us in place of 44).
+        __builtin_amdgcn_s_waitcnt(0x0F70);
         // register v of lane (n, h): voxel 8 * (v / 4) + 4 * h + v % 4 of the block, channel(s) of column n
         const int co = co0 + (NT == 2 ? 2 * n : n);
+        float all = 0.f;                              // not finite if one of the sums is not
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * h + (v & 3);
-            if (r >= valid) continue;
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) all += acc[t][v];
+        auto store = [&](int r, const float (&sum)[NT]) {          // the lane's channel(s) of row r of the block
             const int64_t at = (row0 + r) * C_out + co;
             if (NT == 2 && co + 1 < C_out && (C_out & 1) == 0) {
-                if (OUT_F32) *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(out) + at) = f32x2{acc[0][v], acc[NT - 1][v]};
-                else *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + at) = Elem<T>::pack2(acc[0][v], acc[NT - 1][v]);
+                if (OUT_F32) *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(out) + at) = f32x2{sum[0], sum[NT - 1]};
+                else *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + at) = Elem<T>::pack2(sum[0], sum[NT - 1]);
             } else {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     if (co + t >= C_out) continue;
-                    if (OUT_F32) reinterpret_cast<float*>(out)[at + t] = acc[t][v];
-                    else reinterpret_cast<uint16_t*>(out)[at + t] = Elem<T>::from_float(acc[t][v]);
+                    if (OUT_F32) reinterpret_cast<float*>(out)[at + t] = sum[t];
+                    else reinterpret_cast<uint16_t*>(out)[at + t] = Elem<T>::from_float(sum[t]);
                 }
+            }
+        };
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+            if (r >= valid) continue;
+            float sum[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) sum[t] = acc[t][v];
+            store(r, sum);
+        }
+        if (__ballot(!isfinite(all))) {
+#pragma unroll 1
+            for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+                if (r >= valid) continue;
+                float sum[NT] = {};
+#pragma unroll 1
+                for (int kappa = 0; kappa < K3; ++kappa) {
+                    const int32_t src = nb[r * K3 + kappa];
+                    if (src < 0) continue;
+                    const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
+#pragma unroll 1
+                    for (int c0 = 0; c0 < C_in; c0 += 4) {           // four channels in flight
+                        float x[4], wv[4][NT];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int ci = min(c0 + u, C_in - 1);
+                            x[u] = Elem<T>::to_float(feat[(int64_t)src * C_in + ci]);
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) {
+                                const int oc = min(co + t, C_out - 1);       // columns that do not exist are not stored
+                                wv[u][t] = Elem<T>::to_float((mode & kWeightsTransposed) ? w[(kw * C_out + oc) * C_in + ci] : w[(kw * C_in + ci) * C_out + oc]);
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) sum[t] = c0 + u < C_in ? fmaf(x[u], wv[u][t], sum[t]) : sum[t];
+                    }
+                }
+                store(r, sum);
             }
         }
         __builtin_amdgcn_wave_barrier();              // the table entries are replaced for the next block
