@@ -102,3 +102,28 @@ def test_non_finite_weights_reach_only_the_rows_with_that_tap(dtype, c_in, c_out
     ok = _same_non_finite(y, ref)
     assert 0 < (~ok).sum() < 2 * og.num_voxels
     assert np.abs(y[ok] - ref[ok]).max() <= 1e-4 * np.sqrt(27 * c_in)
+
+
+@pytest.mark.parametrize("n", [200, 3000])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 4, 32), ("bf16", 3, 40), ("bf16", 8, 100), ("f16", 16, 31), ("bf16", 16, 64)])
+def test_non_finite_output_gradients_reach_only_the_offsets_their_voxels_have(n, dtype, c_in, c_out):
+    # 0 * inf is NaN: infinities and NaN in gout must not reach the weight gradient of offsets where their voxel has no
+    # neighbour.  A few columns hold one, one column is not finite anywhere, the others stay finite.
+    pts = _cloud(n)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, _ = G.features_and_weights(43, og.num_voxels, c_in, c_out, 27, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(44).standard_normal((og.num_voxels, c_out)).astype(np.float32), dtype)
+    gy[og.num_voxels // 2, 3] = np.inf
+    gy[0, 9] = -np.inf
+    gy[og.num_voxels - 1, c_out - 1] = np.nan
+    gy[:, 17] = np.inf
+    gw = H.nan_filled((27, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype), out_dtype=torch.float32, out=gw)
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    y = gw.cpu().numpy()
+    ok = _same_non_finite(y, ref)
+    assert ok[:, :, [3, 9, c_out - 1]].any() and not ok[:, :, [3, 9, c_out - 1]].all()
+    num = np.sqrt((np.subtract(y, ref, where=ok, out=np.zeros_like(ref)) ** 2).sum(axis=(1, 2)))
+    den = np.maximum(np.sqrt((np.where(ok, ref, 0) ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))
+    assert (num / den).max() <= 2e-3
