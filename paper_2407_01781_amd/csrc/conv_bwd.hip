@@ -691,6 +691,79 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 if (ci < ci_n && cb * 32 + n < co_n) dst[(int64_t)ci * C_out + cb * 32] = acc[j][cb][v];
             }
     }
+    if (!kMasked) return;
+
+    // A sum runs over the pairs that exist; the product gives a missing pair a row of zeros, which adds nothing unless
+    // the voxel's gout is infinite or NaN (and the identity product mixes such a value of feat into its whole row).  Either
+    // leaves sums that are not finite: the wave makes the sums of such an offset again, pair by pair.
+    uint32_t again = 0;
+#pragma unroll
+    for (int j = 0; j < kWgOffsetsPerWave; ++j) {
+        bool odd = false;
+#pragma unroll
+        for (int cb = 0; cb < kHalves; ++cb) {
+            float all = 0.f;                          // of the channels that exist (whole pieces of eight)
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                if (8 * p < ci_n) all += (acc[j][cb][4 * p] + acc[j][cb][4 * p + 1]) + (acc[j][cb][4 * p + 2] + acc[j][cb][4 * p + 3]);
+            odd |= cb * 32 + n < co_n && !isfinite(all);
+        }
+        if (__ballot(odd)) again |= 1u << j;
+    }
+#pragma unroll 1
+    for (; again; again &= again - 1) {
+        const int kappa = wave + kWgWaves * (__ffs(again) - 1);
+        if (kappa >= K3) continue;
+        float sum[kHalves][16];
+#pragma unroll
+        for (int cb = 0; cb < kHalves; ++cb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[cb][v] = 0.f;
+#pragma unroll 1
+        for (int64_t c = next_mine(t0); c < t1; c = next_mine(c + 1)) {
+            const int64_t tile = tile_of(c);
+            const TileHeader* H = tile_hdr + tile;
+            const int flags = uni(H->flags), win_lo = uni(H->win_lo), win_n = uni(H->win_n), n_valid = uni(H->n_out);
+#pragma unroll 1
+            for (int g = 0; g < kGroupsPerTile; ++g) {
+                if (MODE == kWgOthers && g != range) continue;
+                if (!(((uint32_t)uni((int)H->group_mask[g]) >> kappa) & 1u)) continue;
+                // lane n: the row of voxel n of the column block at this offset, and its output
+                const int fw = tile_wave_of(g);
+                const uint32_t wm = (uint32_t)uni((int)H->wave_mask[fw]);
+                const size_t b = (size_t)tile * block_stride + (uint32_t)uni((int)H->wave_block0[fw]) + __popc(wm & ((1u << kappa) - 1u));
+                uint32_t id = tile_blocks[b * kIdBlockElems + n * kGroupsPerWave + tile_slot_of(g)];
+                if (flags & kTileLdsOffsets) id = id / kRowBytes == (uint32_t)kRowCap ? kNoRow : id / kRowBytes;
+                const int local = tile_perm[tile * kTileT + g * kGroup + n];
+                int row = -1;
+                if (id != kNoRow && local < n_valid) row = id < (uint32_t)win_n ? win_lo + (int)id : tile_rows[tile * (int64_t)row_stride + (id - win_n)];
+#pragma unroll 1
+                for (uint32_t m = (uint32_t)__ballot(row >= 0); m; m &= m - 1) {
+                    const int voxel = __ffs(m) - 1;
+                    const uint16_t* x = feat + (int64_t)__shfl(row, voxel) * C_in + cib * kWgCi;
+                    const uint16_t* y = gout + (tile * kTileT + __shfl(local, voxel)) * (int64_t)C_out + cob * kWgCo + n;
+                    float yv[kHalves];
+#pragma unroll
+                    for (int cb = 0; cb < kHalves; ++cb) yv[cb] = cb * 32 + n < co_n ? Elem<T>::to_float(y[cb * 32]) : 0.f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int ci = 8 * (v >> 2) + 4 * h + (v & 3);
+                        const float xv = ci < ci_n ? Elem<T>::to_float(x[ci]) : 0.f;
+#pragma unroll
+                        for (int cb = 0; cb < kHalves; ++cb) sum[cb][v] = fmaf(xv, yv[cb], sum[cb][v]);
+                    }
+                }
+            }
+        }
+        float* dst = part + (((int64_t)range_out * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
+#pragma unroll
+        for (int cb = 0; cb < kHalves; ++cb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int ci = 8 * (v >> 2) + 4 * h + (v & 3);
+                if (ci < ci_n && cb * 32 + n < co_n) dst[(int64_t)ci * C_out + cb * 32] = sum[cb][v];
+            }
+    }
 }
 
 // gw[e] = part[0][e] + part[1][e] + ... in ascending order, rounded once to the output type.  One

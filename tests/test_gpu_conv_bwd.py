@@ -302,3 +302,32 @@ def test_weight_gradient_of_partial_channel_blocks(dims, dtype, c_in, c_out, fx_
     fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
     _wgrad_check(gw.cpu().numpy(), O.conv_bwd_weight(og, og, 3, 1, feat, gy), 2e-3)
     assert torch.equal(gw, fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32))
+
+
+@pytest.mark.parametrize("dims", [(40, 24, 8), (26, 26, 26)])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("f16", 32, 32), ("bf16", 24, 24), ("bf16", 40, 96), ("f16", 96, 40)])
+@pytest.mark.parametrize("where", ["gout", "feat"])
+def test_non_finite_values_in_partial_channel_blocks_stay_with_their_pairs(dims, dtype, c_in, c_out, where, fx_opt):
+    # a sum runs over existing pairs: an infinite or NaN value must not reach the weight gradient of offsets where its
+    # voxel has no neighbour (0 * inf), nor other channels of its row (the identity product of unstaged tiles).  The
+    # rest stays at the file's bar.
+    fx_opt("leaf_dispatch", "0")
+    rng = np.random.default_rng(190 + dims[0])
+    cloud = rng.integers(-60, 60, size=(6000, 3)).astype(np.int32)
+    ax = [np.arange(d, dtype=np.int32) + 200 for d in dims]
+    block = np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.concatenate([cloud, block])[rng.permutation(6000 + block.shape[0])]
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, _ = G.features_and_weights(17, og.num_voxels, c_in, c_out, 27, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(18).standard_normal((og.num_voxels, c_out)).astype(np.float32), dtype)
+    a = gy if where == "gout" else feat
+    n = og.num_voxels
+    a[n // 3, 1], a[0, 5], a[n - 1, a.shape[1] - 1] = np.inf, -np.inf, np.nan
+    y = fx.sparse_conv_bwd_weight(km, H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype), out_dtype=torch.float32).cpu().numpy()
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(ref), ref, 0), np.where(np.isinf(y), y, 0))
+    ok = np.isfinite(ref)
+    assert 0 < (~ok).sum() <= 3 * 27 * max(c_in, c_out)
+    _wgrad_check(np.where(ok, y, 0), np.where(ok, ref, 0), 2e-3)
