@@ -1269,8 +1269,16 @@ __global__ void k_publish(const GridHeader* __restrict__ hdr, const int64_t* __r
 // coordinate in tree order (grid; root tile; upper offset; lower offset) are one integer -- and node numbers fall out as
 // scans of the places where a prefix of that integer changes.  Counts and ranges go straight to the host.  What it does
 // not hold -- more than kSmallSlots leaves, coordinates beyond 2^18, more than 16 grids, more root tiles than the
-// capacity -- sets overflow bit 8 and the build starts over with the passes.
+// capacity -- sets overflow bit 8 and the build starts over with the passes.  A leaf that finds no slot within kSmallProbes
+// steps is the first sign of that, and every thread then stops: rows that walked a full table to its end, or the long
+// runs of linear probing near it, took milliseconds (16 k rows alone in their leaves 5 ms, 1728 leaves 240 us where the
+// passes take 110).  Steps grow by one each time: 1300 leaves need up to 16 of them, 1800 up to 64.  A row stops at 16,
+// because beyond 1300 leaves the passes are as fast, and an attempt given up then costs 10 us; a fine leaf, of which a
+// thread has a few only, at 64.  A coarse grid has no more leaves than the fine one; the leaves of surfaces join three or
+// more to one (LiDAR scenes 2.8 to 3.5, indoor scenes, sheets and spheres 3.7 to 5.8), leaves of one or two voxels may not.
 constexpr int kSmallThreads = 1024, kSmallSlots = 2048, kSmallRows = 16384;
+constexpr int kSmallProbes = 16, kSmallProbesCoarse = 64;
+constexpr int kSmallLeaves = 1700, kSmallFineLeaves = 6144, kFilledVoxels = 4;      // mean voxels of a leaf from which on neighbours are likely
 constexpr size_t kSmallLds = sizeof(uint64_t) * 9 * kSmallSlots;
 enum SmallSource { kSmallIjk = 0, kSmallPoints = 1, kSmallCoarse = 2 };
 
@@ -1290,22 +1298,25 @@ k_small_grid(const RowSource rows, int n_rows, const BatchRanges joff, int B, Tr
 
     // ---- leaves: leaf coordinates biased by 2^15 (16 bits each), grid, a set top bit
     constexpr int half = 1 << 15;
+    auto gave_up = [&]() { return __hip_atomic_load(&overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0; };
+    auto give_up = [&]() { __hip_atomic_store(&overflow, 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
     auto claim = [&](int li, int lj, int lk, int b) -> int {
-        if (((uint32_t)(li + half) | (uint32_t)(lj + half) | (uint32_t)(lk + half)) >= 2u * half) { overflow = 256; return -1; }
+        if (((uint32_t)(li + half) | (uint32_t)(lj + half) | (uint32_t)(lk + half)) >= 2u * half) { give_up(); return -1; }
         const unsigned long long self = (1ull << 63) | ((unsigned long long)(uint32_t)b << 48) | ((unsigned long long)(uint32_t)(li + half) << 32) |
                                         ((unsigned long long)(uint32_t)(lj + half) << 16) | (unsigned long long)(uint32_t)(lk + half);
         uint32_t h = leaf_hash(b, li, lj, lk) & (kSmallSlots - 1);
-        for (int probe = 0; probe < kSmallSlots; ++probe) {
+        for (int probe = 0; probe < (SOURCE == kSmallCoarse ? kSmallProbesCoarse : kSmallProbes); ++probe) {
             unsigned long long s = __hip_atomic_load(&slot[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (s == 0ull) s = atomicCAS(&slot[h], 0ull, self);
             if (s == 0ull || s == self) return (int)h;
-            h = (h + 1) & (kSmallSlots - 1);
+            if ((probe & 7) == 7 && gave_up()) return -1;
+            h = (h + probe + 1) & (kSmallSlots - 1);
         }
-        overflow = 256;
+        give_up();
         return -1;
     };
     if (SOURCE == kSmallCoarse) {
-        for (int f = tid; f < n_rows; f += kSmallThreads) {
+        for (int f = tid; f < n_rows && !gave_up(); f += kSmallThreads) {
             const fx_leaf* lf = fine.leaf + f;
             const CoarsePiece c = coarse_piece(lf);
             const int h = claim(c.li, c.lj, c.lk, lf->batch);
@@ -1323,7 +1334,8 @@ k_small_grid(const RowSource rows, int n_rows, const BatchRanges joff, int B, Tr
         for (int c = 0; c < kGroups; ++c)        // all of the thread's rows are requested at once
             n[c] = load_four_rows<SOURCE == kSmallPoints>(rows, n_rows, 4 * (c * kSmallThreads + tid), v[c], bad);
 #pragma unroll
-        for (int c = 0; c < kGroups; ++c)
+        for (int c = 0; c < kGroups; ++c) {
+            if (gave_up()) break;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int b = q < n[c] ? find_batch(joff, B, 4 * (c * kSmallThreads + tid) + q) : -1;
@@ -1332,9 +1344,21 @@ k_small_grid(const RowSource rows, int n_rows, const BatchRanges joff, int B, Tr
                 const int h = claim(x.x >> 3, x.y >> 3, x.z >> 3, b);
                 if (h >= 0) atomicOr(&mask[h * 8 + (x.x & 7)], 1ull << (((x.y & 7) << 3) | (x.z & 7)));
             }
+        }
         if (SOURCE == kSmallPoints && bad) atomicAdd(&n_bad, bad);
     }
     __syncthreads();
+    if (overflow) {                            // the same for all threads: nothing sets it between here and the next barrier
+        if (tid == 0) {
+            GridHeader hdr{};
+            hdr.overflow = overflow;
+            *g.hdr = hdr;
+            *reinterpret_cast<GridHeader*>(host) = hdr;
+            __threadfence_system();
+            __hip_atomic_store(host_ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        return;
+    }
 
     // ---- keys: [grid 4][tile 3 x 7][upper offset 3 x 5][lower offset 3 x 4][slot 11], compacted, padded to a power of two
     unsigned long long key[2];
@@ -1760,9 +1784,11 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
 #undef FX_ROW_PASS
         } else {
             const unsigned nb_rows = (unsigned)((n_rows + kDirectThreads - 1) / kDirectThreads);
+            // few fine leaves: more workgroups (15.8 k of them 10.1 us, 12.4 with 512 threads); many: fewer updates of the counter
+            const unsigned coarse_threads = n_rows <= 16384 ? kCoarseThreads / 2 : kCoarseThreads;
             ProfScope ps(kProfVoxelsToLeaves, st);
             if (from.kind == LeafSource::kCoarsen)
-                k_coarse_leaves<<<(unsigned)((n_rows + kCoarseThreads - 1) / kCoarseThreads), kCoarseThreads, 0, st>>>(from.grid->view(), d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
+                k_coarse_leaves<<<(unsigned)((n_rows + coarse_threads - 1) / coarse_threads), coarse_threads, 0, st>>>(from.grid->view(), d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr);
             else if (from.kind == LeafSource::kPad) {
                 k_pad_claim<<<(unsigned)((n_rows * 32 + kPadClaimThreads - 1) / kPadClaimThreads), kPadClaimThreads, 0, st>>>(
                     from.grid->view(), from.r, d_slots, (uint32_t)(n_slots - 1), L, g->d_hdr, from.d_bad);
@@ -1817,6 +1843,8 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
 static fx_status build_small(const RowSource& rows, int64_t n_rows, const BatchRanges& joff, int32_t B, hipStream_t st, const LeafSource& from,
                              fx_grid** out) {
     *out = nullptr;
+    if (from.kind == LeafSource::kCoarsen && n_rows > kSmallLeaves &&
+        (n_rows > kSmallFineLeaves || from.grid->hdr.n_voxels < kFilledVoxels * n_rows)) return FX_OK;
     if (n_rows < 1 || n_rows > kSmallRows || B < 1 || B > 16 || (B > kInlineRanges && from.kind == LeafSource::kRows) ||
         option(kOptGridDirect) == 1) return FX_OK;
     fx_grid* g = new (std::nothrow) fx_grid();

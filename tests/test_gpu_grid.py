@@ -1,5 +1,6 @@
 """GPU parity: index-grid build and queries, bit-exact against the oracle."""
 import itertools
+import time
 
 import numpy as np
 import pytest
@@ -210,8 +211,8 @@ def test_rows_per_workgroup_of_the_row_passes_at_their_limit(n):
 
 @pytest.mark.parametrize("case", ["one", "rows", "rows+1", "slots", "slots+1", "tiles", "tiles+1", "edge", "beyond", "batch8", "batch9"])
 def test_small_grids_in_one_launch_and_at_its_limits(case):
-    # up to 16384 rows, 2048 leaves, 72 root tiles, coordinates in [-2^18, 2^18) and 8 grids in one launch; one more of
-    # any and the build takes the passes
+    # up to 16384 rows, 72 root tiles, coordinates in [-2^18, 2^18) and 8 grids in one launch; one more of any and the
+    # build takes the passes, as it does where the table of 2048 leaves gets full (2048 and one more of them)
     rng = np.random.default_rng(800)
     jo = None
     if case == "one":
@@ -244,3 +245,44 @@ def test_small_grids_in_one_launch_and_at_its_limits(case):
             batch[jo[b, 0]:jo[b, 1]] = b
     idx = g.ijk_to_index(d, batch).cpu().numpy()
     assert np.array_equal(g.ijk()[0].cpu().numpy()[idx], pts)
+
+
+def _best_us(fn, repeat=15):
+    best = float("inf")
+    for _ in range(repeat):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        fn()
+        torch.cuda.synchronize()
+        best = min(best, 1e6 * (time.perf_counter() - t))
+    return best
+
+
+@pytest.mark.parametrize("case", ["6000 in 120^3", "16384 alone", "coarse"])
+def test_small_grids_that_do_not_fit_are_given_up_early(case, fx_opt):
+    # more leaves than the one-launch build's table: it must stop at the first sign of that and leave the grid to the
+    # passes.  Against the passes alone (some 100 us) the attempt adds a launch and a read-back; rows that walk the
+    # full table to its end add 15 to 50 times the passes.
+    rng = np.random.default_rng(900)
+    if case == "6000 in 120^3":
+        pts = rng.integers(-60, 60, size=(6000, 3)).astype(np.int32)
+    elif case == "16384 alone":
+        base = rng.permutation(40 ** 3)[:16384]
+        pts = (np.stack([base % 40, base // 40 % 40, base // 1600], axis=1).astype(np.int32) - 20) * 8 + 3
+    else:        # 6000 fine leaves, each the only one of its coarse leaf
+        base = rng.permutation(30 ** 3)[:6000]
+        pts = (np.stack([base % 30, base // 30 % 30, base // 900], axis=1).astype(np.int32) - 15) * 16 + 3
+    jo = np.array([[0, pts.shape[0]]])
+    g, og = H.both_grids(pts, jo)
+    H.check_grid(g, og)
+    d = torch.from_numpy(pts).cuda()
+    if case == "coarse":
+        H.check_grid(g.coarsen2(), og.coarsen2())
+        build = lambda: g.coarsen2()                                   # noqa: E731
+    else:
+        build = lambda: B.build_index_grid(d, jo)                      # noqa: E731
+    mine = _best_us(build)
+    fx_opt("grid_direct", "1")
+    passes = _best_us(build)
+    print(f"{case}: {mine:.0f} us, the passes alone {passes:.0f} us")
+    assert mine <= 2.0 * passes + 20.0
