@@ -762,8 +762,10 @@ k_bucket_scatter(const RowSource rows, int64_t n_rows, const BatchRanges joff, i
 // One workgroup per bucket: the bucket's distinct leaves and their masks, built in LDS.  The table's slots hold the
 // leaf itself when the rows are packed records (17 bits per leaf coordinate, so a probe is one LDS read), a
 // representative row + 1 otherwise.  A bucket with more leaves than slots (very sparse points) is walked in rounds, each
-// of which takes the leaves of one class by further bits of their hash: 4, then 16 of them.
-constexpr int kBucketThreads = 1024;
+// of which takes the leaves of one class by two further bits of their hash; a class that is still too large is cut once
+// more by two.  A row that finds no slot within kBucketProbes steps (one longer each time) says so: rows that walked a
+// full table to its end read 1024 slots one after the other, in every round that came to nothing.
+constexpr int kBucketThreads = 1024, kBucketProbes = 64;
 __global__ void __launch_bounds__(kBucketThreads)
 k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint32_t* __restrict__ bucket_start, LeafList L, GridHeader* hdr) {
     __shared__ unsigned long long slot[kBucketSlots];     // 0 = empty
@@ -779,8 +781,8 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
         const uint64_t c = records[n_rows + r];
         return make_int4((int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)c, (int)(uint32_t)(c >> 32));
     };
-    int classes = 1;
-    for (int round = 0; round < classes; ++round) {
+    uint32_t class_mask = 0, class_value = 0;             // this round's leaves: hash bits 24.. under the mask
+    while (true) {
         slot[tid] = 0ull;
         for (int e = tid; e < kBucketSlots * 4; e += kBucketThreads) reinterpret_cast<ulonglong2*>(mask)[e] = make_ulonglong2(0ull, 0ull);
         __syncthreads();
@@ -789,14 +791,14 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
             const int4 v = row_at(r);
             const int li = v.x >> 3, lj = v.y >> 3, lk = v.z >> 3;
             const uint32_t hash = leaf_hash(v.w, li, lj, lk);
-            if ((int)((hash >> 24) & (classes - 1)) != round) continue;
+            if (((hash >> 24) & class_mask) != class_value) continue;
             uint32_t h = (hash >> 12) & (kBucketSlots - 1);   // other bits than the bucket's
             // the leaf as a nonzero word: biased coordinates of 17 bits, grid, a set top bit
             const unsigned long long self = is_wide ? (unsigned long long)(r - begin) + 1ull
                 : (1ull << 63) | ((unsigned long long)(uint32_t)v.w << 51) | ((unsigned long long)(uint32_t)(li + (1 << 16)) << 34) |
                   ((unsigned long long)(uint32_t)(lj + (1 << 16)) << 17) | (unsigned long long)(uint32_t)(lk + (1 << 16));
             bool found = false;
-            for (int probe = 0; probe < kBucketSlots; ++probe) {
+            for (int probe = 0; probe < kBucketProbes; ++probe) {
                 unsigned long long s = __hip_atomic_load(&slot[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (s == 0ull) {
                     s = atomicCAS(&slot[h], 0ull, self);
@@ -808,17 +810,16 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
                     const int4 o = row_at(begin + (uint32_t)(s - 1ull));
                     if ((o.x >> 3) == li && (o.y >> 3) == lj && (o.z >> 3) == lk && o.w == v.w) { found = true; break; }
                 }
-                h = (h + 1) & (kBucketSlots - 1);
+                h = (h + probe + 1) & (kBucketSlots - 1);
             }
-            if (found) atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
-            else full = true;
+            if (!found) { full = true; break; }
+            atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
         }
         if (__syncthreads_or(full)) {
-            // nothing of the first round has been listed yet: start over with more classes.  A later round that still
-            // fills up (or a class of 16) leaves it to the path without buckets.
-            if (round > 0 || classes == 16) { if (tid == 0) atomicOr(&hdr->overflow, 64); return; }
-            classes = classes == 1 ? 4 : 16;
-            round = -1;
+            // nothing of this class has been listed: take its first quarter instead.  A sixteenth of a bucket that still
+            // fills the table is left to the path without buckets.
+            if (class_mask == 15) { if (tid == 0) atomicOr(&hdr->overflow, 64); return; }
+            class_mask = class_mask * 4 + 3;
             continue;
         }
         // append the leaves to the list (thread = table slot)
@@ -844,6 +845,15 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
                 *reinterpret_cast<ulonglong2*>(&L.mask[(size_t)pos * 8 + w]) = *reinterpret_cast<const ulonglong2*>(&mask[tid * 8 + w]);
         } else if (s != 0ull) {
             atomicOr(&hdr->overflow, 4);
+        }
+        // the next class: the next quarter of the same one, then the next one (class_value & 3), cut the same way
+        if (class_mask == 0) return;
+        if (class_mask == 3) {
+            if (++class_value == 4) return;
+        } else {
+            class_value += 4;
+            if (class_value == 19) return;            // the last quarter of class 3
+            if (class_value > 15) class_value = (class_value & 3) + 1;
         }
         __syncthreads();
     }

@@ -286,3 +286,21 @@ def test_small_grids_that_do_not_fit_are_given_up_early(case, fx_opt):
     passes = _best_us(build)
     print(f"{case}: {mine:.0f} us, the passes alone {passes:.0f} us")
     assert mine <= 2.0 * passes + 20.0
+
+
+@pytest.mark.parametrize("n", [70_001, 200_000, 500_000])
+def test_rows_alone_in_their_leaves_leave_a_full_bucket_early(n):
+    # one voxel per leaf, 1100 to 2000 of them in a bucket whose table holds 1024: the round over all of them and, at the
+    # largest, those over quarters come to nothing and must end at the first row without a slot.  Against the build of as
+    # many rows in 27 k leaves, a twentieth of them at the largest: 1.5 to 4.2 times its time; rows that walked full tables
+    # made it 10 to 14 times at the two larger sizes.
+    base = np.random.default_rng(910).permutation(128 ** 3)[:n]
+    alone = (np.stack([base % 128, base // 128 % 128, base // 16384], axis=1).astype(np.int32) - 64) * 8 + 5
+    near = np.random.default_rng(911).integers(-120, 120, size=(n, 3)).astype(np.int32)
+    jo = np.array([[0, n]])
+    g, og = H.both_grids(alone, jo)
+    H.check_grid(g, og)
+    d_alone, d_near = torch.from_numpy(alone).cuda(), torch.from_numpy(near).cuda()
+    t_alone, t_near = _best_us(lambda: B.build_index_grid(d_alone, jo)), _best_us(lambda: B.build_index_grid(d_near, jo))
+    print(f"{n} rows alone: {t_alone:.0f} us, near {t_near:.0f} us")
+    assert t_alone <= 7.0 * t_near
