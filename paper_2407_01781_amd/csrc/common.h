@@ -128,14 +128,14 @@ struct fx_grid {
     uint32_t* d_lower_prefix = nullptr;
     fx_leaf* d_leaf = nullptr;
     // Prepared by the grid build behind its last step, while the host waits for the counts (see enqueue_leaf_links):
-    // [27 * cap_leaf] the leaves of the input grid around every leaf (-1: none) -- the table a kernel map onto this
+    // [27 * links_max] the leaves of the input grid around every leaf (-1: none) -- the table a kernel map onto this
     // grid starts from: by default the 3x3x3 stride-1 map of the grid onto itself; for the coarse grid that a strided
     // map makes for itself, that map's (links_K, links_stride; its input grid is the one the map is being built from)
-    // -- then [cap_leaf + 2] the leaf that holds the first voxel of every run of 512 voxels.
-    // Valid for work on `stream` only.  Null when not prepared.
+    // -- then [links_max + 2] the leaf that holds the first voxel of every run of 512 voxels.
+    // Valid for work on `stream` only.  Null when not prepared (or for more leaves than links_max).
     int32_t* d_leaf_links = nullptr;
     int32_t* d_tile_first_leaf = nullptr;
-    int32_t links_K = 0, links_stride = 0;
+    int32_t links_K = 0, links_stride = 0, links_max = 0;
     fx::TreeView view() const {
         fx::TreeView v;
         v.root_key = d_root_key; v.root_batch = d_root_batch;

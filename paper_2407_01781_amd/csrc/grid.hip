@@ -1842,6 +1842,10 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     else enqueue_leaf_links(g, st, nullptr, 3, 1);
     FX_TRY_OR_FAIL(rb.wait(st));
     rb.take(g);
+    if (g->d_leaf_links && g->hdr.n_leaf > g->links_max) {
+        dev_free(g->d_leaf_links, st);
+        g->d_leaf_links = nullptr; g->d_tile_first_leaf = nullptr;
+    }
     dev_free(scratch, st);
 #undef FX_TRY_OR_FAIL
     *out = g;

@@ -132,9 +132,10 @@ __global__ void k_leaf_neighbors(TreeView tin, TreeView tout, int stride, int64_
 // The table of the map that is expected next, launched by the grid build before the host knows the counts of the
 // grid it has just built (tout): they come from the device header (the view's own are not set).  self: the map of the grid onto itself (tin is ignored).
 template <int K>
-__global__ void k_leaf_links(TreeView tin, TreeView tout, int self, int stride, const GridHeader* __restrict__ hdr,
+__global__ void k_leaf_links(TreeView tin, TreeView tout, int self, int stride, const GridHeader* __restrict__ hdr, int max_leaves,
                              int32_t* __restrict__ nbr, int32_t* __restrict__ tile_first_leaf) {
     if (hdr->overflow) return;                 // a level did not fit: the tree is incomplete and the build is repeated
+    if (hdr->n_leaf > max_leaves) return;      // not prepared (the host drops the table when it knows the count)
     tout.n_upper = hdr->n_upper; tout.n_lower = hdr->n_lower; tout.n_leaf = hdr->n_leaf;
     if (self) tin = tout;
     const int64_t n = (int64_t)tout.n_leaf * 27;
@@ -983,19 +984,23 @@ void fx::enqueue_leaf_links(fx_grid* g, hipStream_t st, const fx_grid* g_in, int
     if (option(kOptLeafLinks) == 0 || g->d_leaf_links || (K != 2 && K != 3)) return;
     // Worth it while it hides behind the read-back (some 12 us; 10 us for the 38 k leaves of 1 M LiDAR rows, whose
     // capacity is 191 k).  On large grids it would only delay whatever the caller does next (376 k leaves: 105 us of a
-    // point cloud's 0.8 ms) and hold 28 words per leaf of capacity for a map that may never come.
-    constexpr int kMaxShadowLeaves = 1 << 18;
-    if (g->cap_leaf > kMaxShadowLeaves) return;
+    // point cloud's 0.8 ms) and hold 28 words per leaf for a map that may never come.  Beyond a capacity of 256 k leaves
+    // (1.6 M rows) the table is therefore made for up to 64 k leaves, as a dense grid of that many rows has (8 M rows of a
+    // cloud: 12 k): points to grid and map, 1.6 M / 2 M / 4 M rows in some 10 k leaves 262 / 274 / 372 us without, 253 / 268 /
+    // 369 with it; 10 M rows in 377 k leaves, where the launch finds too many, as before.
+    constexpr int kAnyLeaves = 1 << 18, kShadowLeaves = 1 << 16;
+    g->links_max = g->cap_leaf <= kAnyLeaves ? g->cap_leaf : kShadowLeaves;
     void* p = nullptr;
-    const size_t n_links = 27 * (size_t)g->cap_leaf, n_first = (size_t)g->cap_leaf + 2;     // runs of 512 voxels <= leaves + 1
+    const size_t n_links = 27 * (size_t)g->links_max, n_first = (size_t)g->links_max + 2;     // runs of 512 voxels <= leaves + 1
     if (dev_alloc(&p, sizeof(int32_t) * (n_links + n_first), st) != FX_OK) return;
     g->d_leaf_links = (int32_t*)p;
     g->d_tile_first_leaf = g->d_leaf_links + n_links;
     g->links_K = K; g->links_stride = stride;
-    const unsigned nb = (unsigned)std::min<size_t>((n_links + 255) / 256, 4096);
+    // (where the launch may find nothing to do, fewer workgroups: a thousand of them cost some 0.3 us)
+    const unsigned nb = (unsigned)std::min<size_t>((n_links + 255) / 256, g->cap_leaf <= kAnyLeaves ? 4096 : 1024);
     const TreeView tout = g->view(), tin = g_in ? g_in->view() : tout;
-    if (K == 2) k_leaf_links<2><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->d_leaf_links, g->d_tile_first_leaf);
-    else k_leaf_links<3><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->d_leaf_links, g->d_tile_first_leaf);
+    if (K == 2) k_leaf_links<2><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->links_max, g->d_leaf_links, g->d_tile_first_leaf);
+    else k_leaf_links<3><<<nb, 256, 0, st>>>(tin, tout, g_in ? 0 : 1, stride, g->d_hdr, g->links_max, g->d_leaf_links, g->d_tile_first_leaf);
     if (hipGetLastError() != hipSuccess) { dev_free(p, st); g->d_leaf_links = nullptr; g->d_tile_first_leaf = nullptr; }
 }
 

@@ -304,3 +304,16 @@ def test_rows_alone_in_their_leaves_leave_a_full_bucket_early(n):
     t_alone, t_near = _best_us(lambda: B.build_index_grid(d_alone, jo)), _best_us(lambda: B.build_index_grid(d_near, jo))
     print(f"{n} rows alone: {t_alone:.0f} us, near {t_near:.0f} us")
     assert t_alone <= 7.0 * t_near
+
+
+@pytest.mark.parametrize("sigma,few", [(25.0, True), (70.0, False)])
+def test_kernel_map_of_a_grid_whose_prepared_table_is_limited(sigma, few, fx_opt):
+    # beyond 1.6 M rows the build prepares the map's table for up to 64 k leaves only: a grid below that uses it, one
+    # above makes its own; the map is that of a build that prepares nothing
+    pts = torch.from_numpy(G.gaussian_points(920, 1_700_000, sigma=sigma)).cuda()
+    jo = np.array([[0, pts.shape[0]]])
+    g = B.build_index_grid(pts, jo)
+    assert (g.counts()[0] <= 1 << 16) == few
+    mine = B.build_kernel_map(g, 3, 1).dense()
+    fx_opt("leaf_links", "0")
+    assert torch.equal(mine, B.build_kernel_map(B.build_index_grid(pts, jo), 3, 1).dense())
