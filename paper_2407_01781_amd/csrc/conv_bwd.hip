@@ -1153,7 +1153,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         if (e == hipSuccess) e = hipGetLastError();
     } else if (low) {
         FX_TRY(kmap_ensure_dense(const_cast<fx_kmap*>(km), st));
-        n_ranges = lowdepth_wgrad_ranges(km->n_out);
+        n_ranges = lowdepth_wgrad_ranges(km->n_out, km->K3, C_in, C_out);
         FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * n_ranges, st));
         const fx_status rl = lowdepth_wgrad_partial(km->d_nbmap, km->n_out, km->K3, d_feat, d_gout, dt, C_in, C_out, part, n_ranges, st);
         if (rl != FX_OK) { dev_free(part, st); return rl; }

@@ -201,7 +201,7 @@ fx_status conv_scalar_on_table(const int32_t* d_table, int64_t n_rows, int K3, c
 bool lowdepth_supported(fx_dtype dt, int K3, int C_contract, int64_t n_source_rows);
 fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3, const void* d_feat, fx_dtype dt, const void* d_w,
                                  int32_t C_in, int32_t C_out, void* d_out, fx_dtype out_dt, hipStream_t st, int mode);
-int lowdepth_wgrad_ranges(int64_t n_rows);
+int lowdepth_wgrad_ranges(int64_t n_rows, int K3, int C_in, int C_out);
 fx_status lowdepth_wgrad_partial(const int32_t* d_table, int64_t n_rows, int K3, const void* d_feat, const void* d_gout, fx_dtype dt,
                                  int32_t C_in, int32_t C_out, float* part, int n_ranges, hipStream_t st);
 

@@ -401,11 +401,17 @@ fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3,
     return FX_OK;
 }
 
-// Two workgroups per compute unit, at least four chunks of 64 voxels each: 512 partial sums of the small weight tensor
-// (14 KB at 4 -> 32 channels) are 7 MB for the reduction.
-int lowdepth_wgrad_ranges(int64_t n_rows) {
-    const int64_t chunks = (n_rows + kLdVoxels - 1) / kLdVoxels;
-    return (int)std::max<int64_t>(1, std::min<int64_t>((chunks + 3) / 4, 2 * compute_units()));
+// Two workgroups per compute unit (and column slice), at least four chunks of 64 voxels each, and at most 64 MB of partial
+// sums, which the reduction reads again: 512 of them are 7 MB at 4 -> 32 channels, but 226 MB at 16 -> 256.  On 347 k
+// voxels 16 -> 128 / 256 / 512 and 4 -> 512 took 195 / 431 / 874 and 215 us without the last, 169 / 325 / 636 and 195
+// with it; 32 MB make 16 -> 64 141 in place of 99.
+int lowdepth_wgrad_ranges(int64_t n_rows, int K3, int C_in, int C_out) {
+    const int64_t chunks = (n_rows + kLdVoxels - 1) / kLdVoxels, bytes = sizeof(float) * (int64_t)K3 * C_in * C_out;
+    const int64_t cu = compute_units(), n_y = C_out > 32 ? (C_out + 63) / 64 : 1;
+    const int64_t round = cu * (C_in <= 4 ? 4 : 1);          // workgroups side by side: four a unit fit at four channels, one at sixteen
+    int64_t most = std::min<int64_t>(2 * cu, ((int64_t)64 << 20) / bytes);
+    if (most < 2 * cu && most * n_y > round) most = most * n_y / round * round / n_y;        // whole rounds
+    return (int)std::max<int64_t>(1, std::min<int64_t>((chunks + 3) / 4, most));
 }
 
 fx_status lowdepth_wgrad_partial(const int32_t* d_table, int64_t n_rows, int K3, const void* d_feat, const void* d_gout, fx_dtype dt,

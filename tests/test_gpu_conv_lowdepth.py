@@ -127,3 +127,20 @@ def test_non_finite_output_gradients_reach_only_the_offsets_their_voxels_have(n,
     num = np.sqrt((np.subtract(y, ref, where=ok, out=np.zeros_like(ref)) ** 2).sum(axis=(1, 2)))
     den = np.maximum(np.sqrt((np.where(ok, ref, 0) ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))
     assert (num / den).max() <= 2e-3
+
+
+def test_weight_gradient_of_many_columns_over_fewer_ranges():
+    # 16 -> 256: the partial sums are limited to 64 MB, 128 ranges on 256 compute units, which 33 k rows reach
+    pts = np.unique(np.random.default_rng(45).integers(-24, 24, size=(60_000, 3)).astype(np.int32), axis=0)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    assert og.num_voxels > 33_000
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, _ = G.features_and_weights(46, og.num_voxels, 16, 256, 27, "bf16")
+    gy = G.round_to_dtype(np.random.default_rng(47).standard_normal((og.num_voxels, 256)).astype(np.float32), "bf16")
+    d_x, d_gy = H.to_device_storage(feat, "bf16"), H.to_device_storage(gy, "bf16")
+    gw = H.nan_filled((27, 16, 256), torch.float32)
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    num = np.sqrt(((gw.cpu().numpy() - ref) ** 2).sum(axis=(1, 2)))
+    assert (num / np.sqrt((ref ** 2).sum(axis=(1, 2)))).max() <= 2e-3
+    assert torch.equal(gw, fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32))
