@@ -194,6 +194,14 @@ __device__ __forceinline__ uint32_t leaf_hash(int b, int li, int lj, int lk) {
     return mix32(mix32(mix32(mix32(0x811C9DC5u, (uint32_t)b), (uint32_t)li), (uint32_t)lj), (uint32_t)lk);
 }
 
+// Points of a batch without grids: no pass reads them, but coordinates that no cell holds are refused there too.
+__global__ void k_count_bad_points(const RowSource rows, int64_t n_rows, GridHeader* hdr) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int bad = 0;
+    if (r < n_rows) load_row<true>(rows, r, bad);
+    if (bad) atomicAdd(&hdr->n_bad, bad);
+}
+
 // ---- direct path
 constexpr int kDirectThreads = 256;
 template <bool kPoints>
@@ -1829,6 +1837,10 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
         const int lb = std::max(1, (g->cap_leaf + kLeafChunk - 1) / kLeafChunk);
         { ProfScope ps(kProfScanLeaf, st);
           k_scan_leaves<<<lb, kScanThreads, 0, st>>>(g->d_leaf, d_leaf_count, g->d_hdr, scan_sync(2), g->d_vox_base, B); }
+        FX_TRY_OR_FAIL(hipGetLastError());
+    }
+    if (n_rows > 0 && B == 0 && rows.xyz) {
+        k_count_bad_points<<<(unsigned)((n_rows + 255) / 256), 256, 0, st>>>(rows, n_rows, g->d_hdr);
         FX_TRY_OR_FAIL(hipGetLastError());
     }
     // one read-back: counts + per-grid ranges (Sec. 3.3 step 10)

@@ -61,6 +61,12 @@ def test_empty_cloud_and_invalid_points():
     bad = torch.tensor([[0.0, 0.0, 0.0], [float("nan"), 1.0, 1.0], [1.0, 3e12, 0.0]], device="cuda")
     with pytest.raises(fx.FxError, match="not finite or fall outside"):
         fx.build_index_grid_from_points(bad, np.array([[0, 3]], np.int64))
+    # also where no grid owns them
+    with pytest.raises(fx.FxError, match="not finite or fall outside"):
+        fx.build_index_grid_from_points(bad, np.zeros((0, 2), np.int64))
+    with pytest.raises(fx.FxError, match="not finite or fall outside"):
+        fx.build_index_grid_from_points(bad, np.array([[0, 1]], np.int64))
+    assert fx.build_index_grid_from_points(bad[:1].contiguous(), np.zeros((0, 2), np.int64)).num_voxels == 0
     # the library still works afterwards
     ok = fx.build_index_grid_from_points(bad[:1].contiguous(), np.array([[0, 1]], np.int64))
     assert ok.num_voxels == 1
