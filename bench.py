@@ -484,14 +484,14 @@ def main():
     }
     paper_protocol["conv_cold_effective_TFLOPs"] = flops / (paper_protocol["conv_cold_ms"] * 1e-3) / 1e12
 
-    dom = next(k for k in ("k_conv_mfma", "k_conv_gather", "k_conv_leaf", "k_conv_scalar") if k in kern_ms)
+    dom = next(k for k in ("k_conv_mfma", "k_conv_gather", "k_conv_leaf", "k_conv_lowdepth", "k_conv_scalar") if k in kern_ms)
     dom_ms = kern_ms[dom]
     # Both roofs of the dominant kernel.  Algorithmic bytes of one launch: every input row and every output row once,
     # the weights once, and the kernel map in the form the kernel reads (the tiled map's bytes).  The binding roof is
     # min(matrix peak, intensity x HBM peak); `bound` names it and `frac_of_binding_roof` is measured against it.
     peak = MFMA_PEAK_TFLOPS[w.dtype] if dom != "k_conv_scalar" else FP32_VALU_PEAK_TFLOPS
     achieved = flops / (dom_ms * 1e-3) / 1e12
-    conv_bytes_with_map = conv_bytes + (tiled_bytes if dom in ("k_conv_mfma", "k_conv_gather") else (kmap_bytes if dom == "k_conv_scalar" else 0))
+    conv_bytes_with_map = conv_bytes + (tiled_bytes if dom in ("k_conv_mfma", "k_conv_gather") else (kmap_bytes if dom in ("k_conv_lowdepth", "k_conv_scalar") else 0))
     intensity = flops / conv_bytes_with_map
     hbm_roof_tflops = intensity * HBM_PEAK_GBS / 1e3
     binding = min(peak, hbm_roof_tflops)

@@ -56,8 +56,8 @@ int compute_units();
 enum ProfSlot {
     kProfBucketCount = 0, kProfBucketScan, kProfBucketScatter, kProfBucketLeaves, kProfVoxelsToLeaves, kProfFindTiles, kProfRankTiles, kProfInsertUpper, kProfScanUpper, kProfInsertLower, kProfScanLower,
     kProfInsertLeaf, kProfScanLeaf, kProfGridIjk, kProfNbmap, kProfLeafNeighbors, kProfBuildTiles,
-    kProfPackWeights, kProfConvMfma, kProfConvGather, kProfConvScalar, kProfMemset,
-    kProfDgradStrided, kProfWgrad, kProfWgradReduce, kProfPool, kProfUpsample, kProfConvLeaf, kProfPointsToIjk, kProfSlotCount
+    kProfPackWeights, kProfConvMfma, kProfConvGather, kProfConvLowdepth, kProfConvScalar, kProfMemset,
+    kProfDgradStrided, kProfWgrad, kProfWgradReduce, kProfPool, kProfUpsample, kProfConvLeaf, kProfSmallGrid, kProfSlotCount
 };
 bool prof_enabled();
 void prof_begin(int slot, hipStream_t s);
@@ -84,7 +84,7 @@ struct GridHeader {
     int32_t n_upper;
     int32_t n_lower;
     int32_t n_leaf;
-    int32_t overflow;     // bit0: upper capacity, bit1: lower, bit2: leaf, bit3: tile limit, bit4: voxel count, bit5: leaf table full, bit6: a bucket's LDS table full, bit7: a scan's bounded wait expired
+    int32_t overflow;     // bit0: upper capacity, bit1: lower, bit2: leaf, bit3: tile limit, bit4: voxel count, bit5: leaf table full, bit6: a bucket's LDS table full, bit7: a scan's bounded wait expired, bit8: not a grid that the one-launch build holds
     int32_t n_leaf_raw;   // distinct leaves found by the voxel pass (may exceed capacity)
     int32_t n_bad;        // points whose cell is not representable (grids built from points)
     int32_t wide_rows;    // some input row does not fit the build's packed 8-byte record

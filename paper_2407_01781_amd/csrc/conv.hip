@@ -1474,7 +1474,8 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
     // fp32 by independent waves where the tile kernel fills the chip badly (few tiles), stages rows that are used about
     // once, or pads most of its 64 channels.  Measured, waves / tiles in us: 96 items (48.8 k voxels of sheets, 64 -> 64)
     // 126 / 194, 174 items equal; 2x2x2 strided on 195 k voxels 64 -> 64 70 / 121, 3x3x3 219 / 366, on 980 k voxels 64 -> 128
-    // 401 / 516; 16 -> 16 on 980 k voxels 174 / 228; 32 -> 32 on 195 k voxels (381 items) 137 / 201, but 425 / 395 on 980 k
+    // 401 / 516; at depth on strided maps of 980 k voxels 2x2x2 128 -> 128 639 / 950, 256 -> 256 2327 / 3144, 3x3x3
+    // 128 -> 128 1203 / 1973, 256 -> 256 4677 / 6772; 16 -> 16 on 980 k voxels 174 / 228; 32 -> 32 on 195 k voxels (381 items) 137 / 201, but 425 / 395 on 980 k
     // LiDAR voxels and 68 / 67 on the inverse map.  Pieces of 16 bytes need rows and weights aligned to them; the last
     // condition keeps the launch below 2^32 threads.
     const bool f32_waves = in_dt == FX_F32 && km->n_tiles > 0 && C_in % 16 == 0 && option(kOptFp32Tiles) != 1 && !force_scalar &&

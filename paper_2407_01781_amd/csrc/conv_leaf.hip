@@ -131,7 +131,7 @@ __device__ __forceinline__ int leaf_weight_index(int kappa, int c, int p, int n_
 
 // Sixteen contracted channels (J = 4) fill 64 KB with the window alone: with the weights in LDS besides (27 KB), one
 // workgroup fits a compute unit.  In registers (108 for up to 16 produced channels) two do, and two waves per SIMD are
-// the register budget that goes with it: 16 -> 8 on a solid scene of 1 M voxels 279 -> 200 us.
+// the register budget that goes with it: 16 -> 8 on a solid scene of 1 M voxels 279 -> 205 us.
 constexpr bool leaf_weights_in_registers(int J, int NT) { return 27 * J * NT <= (J == 4 ? 108 : 64); }
 constexpr int leaf_waves_per_simd(int J, int NT) { return J == 4 && NT == 1 ? 2 : 4; }
 

@@ -353,12 +353,16 @@ inline size_t wgrad_lds(int K3, int CP, int NT) {
 
 }  // namespace
 
+// Tiles of 32 (offset, channel) rows that a wave of the weight gradient holds: 1, or for more rows one number per channel
+// padding (2x2x2 and 3x3x3 at 8 channels have 2 and 7 tiles for four waves, 3x3x3 at 16 and 5x5x5 at 4 have 14 and 16).
+constexpr int most_tiles_per_wave(int CP) { return CP == 8 ? 2 : 4; }
+
 // Up to 16 contracted channels of a 16-bit type, and operands that fit the LDS of a compute unit (all kernel sizes up to 3;
 // 5x5x5 at up to 4 channels).
 bool lowdepth_supported(fx_dtype dt, int K3, int C_contract, int64_t n_source_rows) {
     if (dt == FX_F32 || C_contract > 16 || n_source_rows * C_contract > 0xFFFFFFFFll) return false;     // 32-bit element offsets
     const int CP = padded_channels(C_contract);
-    return conv_lds(K3, CP, 2) <= 160 * 1024 && wgrad_lds(K3, CP, 2) <= 160 * 1024 && (K3 * CP + 31) / 32 <= 4 * kLdWaves;
+    return conv_lds(K3, CP, 2) <= 160 * 1024 && wgrad_lds(K3, CP, 2) <= 160 * 1024 && (K3 * CP + 31) / 32 <= most_tiles_per_wave(CP) * kLdWaves;
 }
 
 fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3, const void* d_feat, fx_dtype dt, const void* d_w,
@@ -374,7 +378,7 @@ fx_status lowdepth_conv_on_table(const int32_t* d_table, int64_t n_rows, int K3,
     const int n_y = (C_out + 32 * NT - 1) / (32 * NT);
     const int64_t want = std::max<int64_t>(1, (int64_t)compute_units() * per_cu / n_y);
     const dim3 grid((unsigned)std::min<int64_t>((n_blocks + kLdWaves - 1) / kLdWaves, want), (unsigned)n_y);
-    ProfScope ps(kProfConvScalar, st);
+    ProfScope ps(kProfConvLowdepth, st);
     hipError_t e = hipSuccess;
 #define FX_LD_WHOLE(T, F32, CPV, NTV, WH)                                                                                \
     do {                                                                                                                 \
@@ -421,7 +425,7 @@ fx_status lowdepth_wgrad_partial(const int32_t* d_table, int64_t n_rows, int K3,
     const bool gout_whole = C_out % 8 == 0 && (reinterpret_cast<uintptr_t>(d_gout) & 15) == 0;
     const int NT = C_out > 32 ? 2 : 1;
     const size_t lds = wgrad_lds(K3, CP, NT);
-    const int mt = ((K3 * CP + 31) / 32 + kLdWaves - 1) / kLdWaves;      // tiles per wave: 1, 2 or up to 4
+    const bool one_tile = (K3 * CP + 31) / 32 <= kLdWaves;               // per wave
     const dim3 grid((unsigned)n_ranges, (unsigned)((C_out + 32 * NT - 1) / (32 * NT)));
     ProfScope ps(kProfWgrad, st);
     hipError_t e = hipSuccess;
@@ -434,7 +438,7 @@ fx_status lowdepth_wgrad_partial(const int32_t* d_table, int64_t n_rows, int K3,
                 (const uint16_t*)d_gout, C_in, C_out, part, whole ? 1 : 0, gout_whole ? 1 : 0);                          \
     } while (0)
 #define FX_LD_NT(T, CPV, MTV) do { if (NT == 2) FX_LD_MT(T, CPV, MTV, 2); else FX_LD_MT(T, CPV, MTV, 1); } while (0)
-#define FX_LD_CP(T, CPV) do { if (mt == 1) FX_LD_NT(T, CPV, 1); else if (mt == 2) FX_LD_NT(T, CPV, 2); else FX_LD_NT(T, CPV, 4); } while (0)
+#define FX_LD_CP(T, CPV) do { if (one_tile) FX_LD_NT(T, CPV, 1); else FX_LD_NT(T, CPV, most_tiles_per_wave(CPV)); } while (0)
 #define FX_LD(T) do { if (CP == 4) FX_LD_CP(T, 4); else if (CP == 8) FX_LD_CP(T, 8); else FX_LD_CP(T, 16); } while (0)
     if (dt == FX_BF16) FX_LD(__bf16); else FX_LD(_Float16);
 #undef FX_LD

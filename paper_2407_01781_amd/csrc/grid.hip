@@ -1895,7 +1895,7 @@ static fx_status build_small(const RowSource& rows, int64_t n_rows, const BatchR
                                                                       rb.host_ticket, rb.ticket);                                   \
     } while (0)
     {
-        ProfScope ps(kProfVoxelsToLeaves, st);
+        ProfScope ps(kProfSmallGrid, st);
         if (from.kind == LeafSource::kCoarsen) FX_SMALL(kSmallCoarse, from.grid->view());
         else if (rows.xyz) FX_SMALL(kSmallPoints, TreeView{});
         else FX_SMALL(kSmallIjk, TreeView{});
