@@ -262,13 +262,17 @@ void fx_kmap_destroy(fx_kmap* km);
  *     the leaf-window kernel, all other outputs to the tile kernel over a second copy of the map, built on the
  *     first such call and kept with the map;
  *   - everything else: a scalar kernel (fp32 FMA in offset-then-channel order).
+ * Infinite and NaN weights: the tile, gather and leaf-window kernels multiply a missing neighbour as a row of zeros, so
+ * such a weight makes NaN of its column in every row they multiply it for; the wave-per-16-voxels kernel, the kernels at
+ * C_in <= 16 and the scalar kernel sum over existing neighbours only, and it reaches no row without that tap.
  */
 fx_status fx_sparse_conv_fwd(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, const void* d_w,
                              int32_t C_in, int32_t C_out, void* d_out, fx_dtype out_dt, void* stream);
 
 /* fx_sparse_conv_fwd for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same result bits; the memory
- * the kernels need beyond inputs and outputs (the packed weights and eight work-list counters) is a static
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments; always the tile and gather kernels, with the same
+ * result bits where fx_sparse_conv_fwd takes them too (it may take the leaf-window kernels or, for FX_F32, the
+ * wave-per-16-voxels kernel, whose sums agree within the tolerance); the memory the kernels need beyond inputs and outputs (the packed weights and eight work-list counters) is a static
  * device array of FX_NOALLOC_MAX_WEIGHT_BYTES + 256 bytes that each GPU the library runs on holds until the
  * process ends.  The call allocates and frees nothing, on the device or through any library.
  *   Serves the matrix-unit kernels only: a tiled map (K^3 <= 27), C_in * sizeof(element) a multiple of 64,
@@ -308,11 +312,14 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * map an input is shared by up to 8 outputs and the sum is gathered per input through the inverse map
  * (a tiled map of its own, built on the first such call and kept with km; no atomics, fixed order).
  * MFMA paths: FX_F16 / FX_BF16 with C_in % 64 == 0 and C_out % 64 == 0 (bwd_data: C_in % 64 == 0
- * and C_out % 32 == 0; bwd_weight: C_in % 8 == 0 and C_out % 8 == 0) on tiled maps; everything
- * else takes scalar kernels.  In the MFMA weight-gradient kernel a tile whose input rows do not all
- * fit the kernel's local memory has its operand transposed by a multiplication with the identity; on
- * such a tile a non-finite value in feat makes the whole 32-channel block of gw that it touches NaN
- * rather than only its own row.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
+ * and C_out % 32 == 0; bwd_weight: C_in % 8 == 0 and C_out % 8 == 0) on tiled maps; the kernels at up to 16
+ * contracted channels (bwd_data: C_out; bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as
+ * the forward pass; everything else takes scalar kernels.  Non-finite values: where C_in % 32 == 0 and
+ * C_out % 64 == 0 the MFMA weight-gradient kernels multiply a missing pair as zeros, so an infinite or NaN value of gout
+ * makes its column of gw NaN for every offset that one of the 32 voxels of its column block has, and a tile whose input rows do
+ * not all fit the kernel's local memory has its operand transposed by a multiplication with the identity, so that such a
+ * value in feat makes the whole 32-channel block of gw that it touches NaN rather than only its own row.  All other
+ * shapes sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
  * the leaf-window kernels: at those shapes a locally dense grid (mean leaf occupancy >= 0.40) is summed leaf by
  * leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a grid that mixes dense and sparse leaves is split per
  * leaf between that kernel and the tile kernel inside the call (option leaf_dispatch as for the forward pass).

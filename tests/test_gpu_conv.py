@@ -102,10 +102,20 @@ def test_pointwise_and_5x5x5_kernels(K, dtype, c_in, c_out):
         H.conv_tolerance_check(y.float().cpu().numpy(), closed, dtype, 1, c_in)
 
 
-@pytest.mark.parametrize("tiles", ["0", "1"])
+@pytest.mark.parametrize("tiles", ["0", "1", "scalar"])
 def test_fp32_scalar_and_tile_kernels_on_config1(tiles, fx_opt):
-    fx_opt("fp32_tiles", tiles)
-    y, ref, dt, k3, c_in = _run(G.workload("sphere64"))
+    # 0: one wave per 16 voxels, 1: the tile kernel, scalar: neither
+    if tiles == "scalar":
+        fx_opt("force_scalar", "1")
+    else:
+        fx_opt("fp32_tiles", tiles)
+    w = G.workload("sphere64")
+    fx.profile_enable(True)
+    fx.profile_reset()
+    y, ref, dt, k3, c_in = _run(w)
+    ran = fx.profile_read()
+    fx.profile_enable(False)
+    assert {"0": "k_conv_gather", "1": "k_conv_mfma", "scalar": "k_conv_scalar"}[tiles] in ran
     H.conv_tolerance_check(y, ref, dt, k3, c_in)
 
 
