@@ -114,6 +114,14 @@ constexpr int kBlockBufBytes = kMaxIdBlocks * kIdBlockElems * 2;
 __device__ __forceinline__ int lds_row_offset(int row, int p) { return (int)(lds_row_code((uint32_t)row) ^ (uint32_t)(p << 4)); }
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
+// Global input row behind a local row id of a tile (-1: none).
+__device__ __forceinline__ int32_t tile_row_of(uint32_t id, int flags, int win_lo, int win_n,
+                                               const int32_t* __restrict__ rows) {
+    if (flags & kTileLdsOffsets) id = (id / kRowBytes == (uint32_t)kRowCap) ? kNoRow : id / kRowBytes;
+    if (id == kNoRow) return -1;
+    return id < (uint32_t)win_n ? win_lo + (int32_t)id : rows[id - (uint32_t)win_n];
+}
+
 // How the packed operand fragments are read from the caller's W[K^3][C_in][C_out] (two flags):
 //   kWeightsForward        fragment (kappa, cin, cout) = W[kappa][cin][cout]
 //   kWeightsTransposed     fragment (kappa, a, b)      = W[kappa][b][a]            (roles of the channel
@@ -171,6 +179,14 @@ __device__ __forceinline__ u32x2 tr_read4(const unsigned char* p) {
     __builtin_memcpy(&w, &v, 8);
     return w;
 }
+
+// The weight gradient of a 16-bit type over the tiles of a map as partial sums (conv_wgrad.h): channel counts that are
+// multiples of 8, in blocks of kWgCi x kWgCo, 16-byte aligned feat and gout.
+constexpr int kWgCi = kCinChunk;            // 32: the row chunk staged in LDS
+constexpr int kWgCo = 64;
+template <typename T>
+hipError_t launch_wgrad_tiles(const fx_kmap* km, const void* d_feat, const void* d_gout, int C_in, int C_out, float* part, int n_ranges,
+                              bool split, int n_listed, hipStream_t st);
 
 // Weight gradient of the 3x3x3 submanifold convolution from the leaf window (fp32 at low depth; f16 / bf16 at
 // C_in % 32 == 0 and C_out % 64 == 0), and the ordered
