@@ -319,7 +319,7 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * makes its column of gw NaN for every offset that one of the 32 voxels of its column block has, and a tile whose input rows do
  * not all fit the kernel's local memory has its operand transposed by a multiplication with the identity, so that such a
  * value in feat makes the whole 32-channel block of gw that it touches NaN rather than only its own row.  All other
- * shapes sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
+ * shapes, and all on strided maps, sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
  * the leaf-window kernels: at those shapes a locally dense grid (mean leaf occupancy >= 0.40) is summed leaf by
  * leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a grid that mixes dense and sparse leaves is split per
  * leaf between that kernel and the tile kernel inside the call (option leaf_dispatch as for the forward pass).

@@ -679,7 +679,14 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     float* part = nullptr;
     hipError_t e = hipSuccess;
     int n_ranges = 1;
-    if (mfma) {
+    // Strided maps, whose tiles share no rows: a wave per offset that walks the map's blocks alone (k_wgrad_pairs, with the
+    // figures of both; the tile kernel was slower on every map and channel count tried).
+    if (mfma && km->stride == 2) {
+        n_ranges = wgrad_pairs_ranges(km, C_in, C_out);
+        FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * n_ranges, st));
+        ProfScope ps(kProfWgrad, st);
+        e = launch_wgrad_pairs(km, d_feat, d_gout, dt, C_in, C_out, part, n_ranges, st);
+    } else if (mfma) {
         const fx_kmap* km_all = km;
         km = kmt;
         const int n_cblk = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
@@ -687,7 +694,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         if (n_ranges > 8) n_ranges -= n_ranges % 8;   // see the block-to-XCD mapping in the kernel
         // Sparse submanifold maps with at most a few tiles that are not staged in LDS: the sixteen-wave launch for the
         // staged tiles and, if there are others, the launch that spreads those over one workgroup per column block
-        // (see WgradMode).  Strided maps, maps between two grids and dense grids: one launch that
+        // (see WgradMode).  Maps between two grids and dense grids: one launch that
         // takes every tile.  (With a per-leaf split the tiles walked are those of the map without the dense leaves.)
         const double occ = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         bool split = km->stride == 1 && km->gin == km->gout && !km->is_inverse && occ < 0.20;

@@ -68,8 +68,8 @@ static_assert(kGroupsPerWave == 4 && kTileWaves == 4, "id blocks of four column 
 // staged ones.  When the map has at most kMaxListedTiles such tiles (counted once per map), kWgStaged (16 waves)
 // takes the staged tiles of the ranges, and kWgOthers (8 waves, both forms) takes the listed tiles with one
 // workgroup per column block of a tile, so that no workgroup carries a whole one: workgroup s sums column block s
-// of every listed tile into partial sum n_ranges + s.  Other maps (strided, between two grids, dense grids, whose
-// tiles mostly list one row per pair) take one launch of kWgAll (8 waves, both forms, every tile of the range).
+// of every listed tile into partial sum n_ranges + s.  Other maps (between two grids, dense grids, whose
+// tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of kWgAll (8 waves, both forms, every tile of the range).
 // Either way a partial sum is made of the same terms in a fixed order.
 enum WgradMode { kWgAll = 0, kWgStaged = 1, kWgOthers = 2 };
 

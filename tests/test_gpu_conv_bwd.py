@@ -331,3 +331,33 @@ def test_non_finite_values_in_partial_channel_blocks_stay_with_their_pairs(dims,
     ok = np.isfinite(ref)
     assert 0 < (~ok).sum() <= 3 * 27 * max(c_in, c_out)
     _wgrad_check(np.where(ok, y, 0), np.where(ok, ref, 0), 2e-3)
+
+
+@pytest.mark.parametrize("kernel", [2, 3])
+@pytest.mark.parametrize("n_rows", [1, 33, 700, 20000])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 128), ("f16", 24, 40), ("bf16", 96, 72)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_weight_gradient_of_strided_maps(kernel, n_rows, dtype, c_in, c_out, odd):
+    # one wave per offset walks the blocks of a range: fewer blocks than ranges, ranges that start and end inside a
+    # tile, whole and partial channel blocks; every element written, the same bits twice.  odd: infinite and NaN values
+    # reach the sums of their own pairs only, the rest stays at the file's bar.
+    rng = np.random.default_rng(400 + n_rows)
+    side = max(2, int(round(3 * n_rows ** (1 / 3))))
+    pts = np.unique(rng.integers(-side, side, size=(n_rows, 3)).astype(np.int32), axis=0)
+    g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, kernel, 2)
+    ogc = og.coarsen2()
+    feat, _ = G.features_and_weights(19, og.num_voxels, c_in, c_out, kernel ** 3, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(20).standard_normal((ogc.num_voxels, c_out)).astype(np.float32), dtype)
+    if odd:
+        feat[og.num_voxels // 2, 1], gy[0, 5], gy[-1, c_out - 1] = np.inf, -np.inf, np.nan
+    d_x, d_gy = H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype)
+    gw = H.nan_filled((kernel ** 3, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
+    ref, y = O.conv_bwd_weight(og, ogc, kernel, 2, feat, gy), gw.cpu().numpy()
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(ref), ref, 0), np.where(np.isinf(y), y, 0))
+    ok = np.isfinite(ref)
+    assert ok.all() != odd
+    _wgrad_check(np.where(ok, y, 0), np.where(ok, ref, 0), 2e-3)
+    assert torch.equal(gw.view(torch.int32), fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32).view(torch.int32))
