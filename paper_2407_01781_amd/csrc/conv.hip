@@ -414,17 +414,37 @@ __device__ __forceinline__ void produce_meta(unsigned char* lds_blocks, uint16_t
                                          (lds_ptr_t)lds_perm, 16, 0, 0);
 }
 
-// Next unclaimed work item: first from the list of the workgroup's own XCD, then from the others'.
-// The first wg_per_xcd items of every list are taken statically by that XCD's workgroups.
+// Next unclaimed work item, taken by a whole wave: first from the list of the workgroup's own XCD, then from the others'.
+// The first wg_per_xcd items of every list are taken statically by that XCD's workgroups.  Updates of the counters, which
+// share a line, run one after the other at memory, 15-45 ns each: once its own list is empty a workgroup looks at all
+// counters with one load and claims only from a list that still has items, and it stops asking when none has (open_lists
+// holds what is left to ask: the own list, others).  With a claim tried on each of the eight lists the 2048 updates of the
+// last items were most of a call of few items: 32 -> 32, 220 k voxels, 432 items, 71 -> 44 us.
 __device__ __forceinline__ int64_t take_work(int32_t* __restrict__ counters, int xcd, int per_xcd, int wg_per_xcd,
-                                             int64_t n_work) {
-    for (int v = 0; v < 8; ++v) {
-        const int x = (xcd + v) & 7;
-        const int64_t begin = (int64_t)x * per_xcd;
-        const int64_t end = min(n_work, begin + per_xcd);
-        if (begin + wg_per_xcd >= end) continue;
-        const int64_t w = begin + wg_per_xcd + atomicAdd(&counters[x], 1);
-        if (w < end) return w;
+                                             int64_t n_work, int lane, int& open_lists) {
+    const int x = (xcd + lane) & 7;                            // lane v < 8: the v-th list in order of preference
+    const int64_t begin = (int64_t)x * per_xcd + wg_per_xcd;
+    const int64_t left = min(n_work, (int64_t)(x + 1) * per_xcd) - begin;
+    while (open_lists) {
+        uint32_t mask = 1u;
+        if (!(open_lists & 1)) {
+            bool some = false;
+            if (lane < 8 && left > 0) some = (int64_t)__hip_atomic_load(&counters[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < left;
+            mask = (uint32_t)__ballot(some) & 0xFFu;
+            if (!mask) open_lists = 0;
+        }
+        for (; mask; mask &= mask - 1) {
+            const int v = __ffs(mask) - 1;
+            int got = 0;
+            bool hit = false;
+            if (lane == v && left > 0) {
+                got = atomicAdd(&counters[x], 1);
+                hit = got < left;
+            }
+            if (__ballot(hit)) return (((int64_t)__builtin_amdgcn_readlane((int)(begin >> 32), v) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)begin, v)) + __builtin_amdgcn_readlane(got, v);
+        }
+        open_lists &= ~1;
     }
     return -1;
 }
@@ -575,13 +595,11 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
     if (wave >= kTileWaves) {
         // ---------------- producers
         const int pwave = wave - kTileWaves;
+        int open_lists = 3;
         if (pwave == 0) {   // items that start in phases 0 and 1
             announce(L.meta[0], first, nslice, tile_hdr, lane);
             if (nchunk == 1) {
-                int64_t w = 0;
-                if (lane == 0) w = take_work(counters, xcd, per_xcd, wg_per_xcd, n_work);
-                w = __shfl(w, 0);
-                announce(L.meta[1], w, nslice, tile_hdr, lane);
+                announce(L.meta[1], take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, open_lists), nslice, tile_hdr, lane);
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
@@ -603,6 +621,11 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             const Item cur = item_of(M, work, nslice);
             for (int c = 0; c < nchunk; ++c, ++phase) {
                 const int rb = (phase + 1) & 1;
+                // an item starts two phases from now: claimed before this phase's rows are requested, whose loads the
+                // claim and the header would otherwise wait for
+                if (pwave == 0 && (phase + 2) % nchunk == 0)
+                    announce(L.meta[((phase + 2) / nchunk) % kMetaSlots],
+                             take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, open_lists), nslice, tile_hdr, lane);
                 if (c != nchunk - 1) {
                     produce_rows_resolved(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
                 } else {
@@ -615,12 +638,6 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
                         resolve_rows(gr, nxt, pwave, lane, tile_rows, row_stride);
                         produce_rows_resolved(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
                     }
-                }
-                if (pwave == 0 && (phase + 2) % nchunk == 0) {   // an item starts two phases from now
-                    int64_t w = 0;
-                    if (lane == 0) w = take_work(counters, xcd, per_xcd, wg_per_xcd, n_work);
-                    w = __shfl(w, 0);
-                    announce(L.meta[((phase + 2) / nchunk) % kMetaSlots], w, nslice, tile_hdr, lane);
                 }
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();
