@@ -30,31 +30,47 @@ namespace fx {
 // and the 32 lanes of a half-wave store one whole output row.
 template <typename E>   // uint16_t or uint32_t: the bits of one element
 __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out,
-                               int32_t* __restrict__ counters, int mode) {
+                               int32_t* __restrict__ counters, int mode, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles) {
     if (blockIdx.x == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0;   // the convolution's work-list counters
+    if (tile_hdr && blockIdx.x == gridDim.x - 1) {
+        // a workgroup of its own lists the tiles whose rows are not all staged in LDS, in no particular order (their number,
+        // then the first kMaxLongTiles of them): the tile kernel starts with those
+        __shared__ int32_t found;
+        if (threadIdx.x == 0) found = 0;
+        __syncthreads();
+        for (int64_t t = threadIdx.x; t < n_tiles; t += blockDim.x)
+            if (!(tile_hdr[t].flags & kTileLdsOffsets)) {
+                const int at = atomicAdd(&found, 1);
+                if (at < kMaxLongTiles) counters[9 + at] = (int32_t)t;
+            }
+        __syncthreads();
+        if (threadIdx.x == 0) { counters[8] = found; counters[9 + kMaxLongTiles] = 0; }
+        return;
+    }
     constexpr int EPL = 16 / (int)sizeof(E);     // elements per lane fragment
     constexpr int kChunk = 4 * EPL;              // input channels per 64-byte row chunk
-    const int nchunk = C_in / kChunk, nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
-    const int64_t total = (int64_t)K3 * C_in * nslice * kCoutSlice;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        int64_t r = e;
-        const int el = (int)(r % EPL); r /= EPL;
-        const int lane = (int)(r & 63); r >>= 6;
-        const int ks = (int)(r & 1); r >>= 1;
-        const int nt = (int)(r & 1); r >>= 1;
-        const int s = (int)(r % nslice); r /= nslice;
-        const int c = (int)(r % nchunk); r /= nchunk;
-        const int kappa = (int)r;
+    typedef __attribute__((ext_vector_type(EPL))) E Frag;
+    const uint32_t nchunk = C_in / kChunk, nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
+    const uint32_t total = (uint32_t)K3 * nchunk * nslice * 256;         // fragments
+    const uint32_t stride = (gridDim.x - (tile_hdr ? 1 : 0)) * blockDim.x;
+    for (uint32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < total; f += stride) {
+        const uint32_t lane = f & 63, ks = (f >> 6) & 1, nt = (f >> 7) & 1;
+        uint32_t r = f >> 8;
+        const uint32_t sl = r % nslice; r /= nslice;
+        const uint32_t c = r % nchunk, kappa = r / nchunk;
         const int m = lane & 31, kq = lane >> 5;
-        const int cin = c * kChunk + ks * 2 * EPL + kq * EPL + el;
-        const int cout = s * kCoutSlice + 2 * m + nt;
-        E v = 0;
-        if (cout < C_out) {
-            const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
-            if (mode & kWeightsTransposed) v = w[(kw * C_out + cout) * C_in + cin];
-            else v = w[(kw * C_in + cin) * C_out + cout];
+        const int cin = c * kChunk + ks * 2 * EPL + kq * EPL, cout = sl * kCoutSlice + 2 * m + nt;
+        Frag v;
+        const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
+        const int64_t at = (mode & kWeightsTransposed) ? (kw * C_out + cout) * C_in + cin : (kw * C_in + cin) * C_out + cout;
+        const int64_t step = (mode & kWeightsTransposed) ? 1 : C_out;
+        if ((mode & kWeightsTransposed) && cout < C_out && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
+            v = *reinterpret_cast<const Frag*>(w + at);        // a fragment is contiguous; C_in is a multiple of EPL
+        } else {
+#pragma unroll
+            for (int el = 0; el < EPL; ++el) v[el] = cout < C_out ? w[at + el * step] : (E)0;
         }
-        wp[e] = v;
+        reinterpret_cast<Frag*>(wp)[f] = v;
     }
 }
 
@@ -63,14 +79,14 @@ size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes) {
 }
 
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
-                         int mode, hipStream_t st) {
-    const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / elem_bytes);
-    const unsigned nb = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
+                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles) {
+    const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / 16);
+    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 4096)) + (tile_hdr ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode);
+        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, tile_hdr, n_tiles);
     else
-        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode);
+        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, tile_hdr, n_tiles);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
@@ -421,16 +437,18 @@ __device__ __forceinline__ void produce_meta(unsigned char* lds_blocks, uint16_t
 // holds what is left to ask: the own list, others).  With a claim tried on each of the eight lists the 2048 updates of the
 // last items were most of a call of few items: 32 -> 32, 220 k voxels, 432 items, 71 -> 44 us.
 __device__ __forceinline__ int64_t take_work(int32_t* __restrict__ counters, int xcd, int per_xcd, int wg_per_xcd,
-                                             int64_t n_work, int lane, int& open_lists) {
-    const int x = (xcd + lane) & 7;                            // lane v < 8: the v-th list in order of preference
+                                             int64_t n_work, int lane, int n_orphans, int& open_lists) {
+    // lane v < 8: the v-th list in order of preference; lane 8: the static items of workgroups 0 .. n_orphans - 1, which
+    // start with something else
+    const int x = (xcd + lane) & 7, counter = lane < 8 ? x : 9 + kMaxLongTiles;
     const int64_t begin = (int64_t)x * per_xcd + wg_per_xcd;
-    const int64_t left = min(n_work, (int64_t)(x + 1) * per_xcd) - begin;
+    const int64_t left = lane < 8 ? min(n_work, (int64_t)(x + 1) * per_xcd) - begin : n_orphans;
     while (open_lists) {
         uint32_t mask = 1u;
         if (!(open_lists & 1)) {
             bool some = false;
-            if (lane < 8 && left > 0) some = (int64_t)__hip_atomic_load(&counters[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < left;
-            mask = (uint32_t)__ballot(some) & 0xFFu;
+            if (lane < 9 && left > 0) some = (int64_t)__hip_atomic_load(&counters[counter], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < left;
+            mask = (uint32_t)__ballot(some);
             if (!mask) open_lists = 0;
         }
         for (; mask; mask &= mask - 1) {
@@ -438,25 +456,32 @@ __device__ __forceinline__ int64_t take_work(int32_t* __restrict__ counters, int
             int got = 0;
             bool hit = false;
             if (lane == v && left > 0) {
-                got = atomicAdd(&counters[x], 1);
+                got = atomicAdd(&counters[counter], 1);
                 hit = got < left;
             }
-            if (__ballot(hit)) return (((int64_t)__builtin_amdgcn_readlane((int)(begin >> 32), v) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)begin, v)) + __builtin_amdgcn_readlane(got, v);
+            if (__ballot(hit)) {
+                const int64_t nth = __builtin_amdgcn_readlane(got, v);
+                return v < 8 ? (int64_t)((xcd + v) & 7) * per_xcd + wg_per_xcd + nth : (nth & 7) * per_xcd + (nth >> 3);
+            }
         }
         open_lists &= ~1;
     }
     return -1;
 }
 
-// One wave announces work item `work` (or the end of the list) in a slot of the ring.
-__device__ __forceinline__ void announce(MetaSlot& M, int64_t work, int nslice, const TileHeader* __restrict__ tile_hdr,
-                                         int lane) {
+// One wave announces work item `work` (or the end of the list) in a slot of the ring; returns the flags of its tile.
+__device__ __forceinline__ int announce(MetaSlot& M, int64_t work, int nslice, const TileHeader* __restrict__ tile_hdr,
+                                        int lane) {
+    int32_t v = 0;
     if (work >= 0) {
         const int32_t* src = reinterpret_cast<const int32_t*>(tile_hdr + work / nslice);
-        if (lane < (int)(sizeof(TileHeader) / 4)) reinterpret_cast<int32_t*>(&M.hdr)[lane] = src[lane];
+        if (lane < (int)(sizeof(TileHeader) / 4)) {
+            v = src[lane];
+            reinterpret_cast<int32_t*>(&M.hdr)[lane] = v;
+        }
     }
     if (lane == 0) M.work = work;
+    return __builtin_amdgcn_readlane(v, offsetof(TileHeader, flags) / 4);
 }
 
 // offset (in 16-byte fragments, wave-uniform) of the first weight fragment for (slice, chunk, offset)
@@ -596,17 +621,38 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         // ---------------- producers
         const int pwave = wave - kTileWaves;
         int open_lists = 3;
-        if (pwave == 0) {   // items that start in phases 0 and 1
-            announce(L.meta[0], first, nslice, tile_hdr, lane);
-            if (nchunk == 1) {
-                announce(L.meta[1], take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, open_lists), nslice, tile_hdr, lane);
+        int64_t start = first;
+        int n_orphans = 0;
+        bool skip_long = false;
+        if (pwave == 0 && per_xcd > wg_per_xcd && 7 * (int64_t)per_xcd + wg_per_xcd / 2 < n_work) {
+            // Items of long tiles (rows gathered from global memory: two to four times a staged item) would end the launch
+            // alone if they were claimed last.  When all of them are listed the first workgroups start with one each, claims
+            // pass them over, and the static items of those workgroups are claimed like the others (at most the lower half
+            // of every XCD's workgroups, all of which have a static item: see the condition above).  With one item a
+            // workgroup there is nothing to reorder.  bf16 on 195 k voxels of sheets (four long tiles of 381), 128 -> 128
+            // 165 -> 149 us, 256 -> 256 515 -> 457; 221 k LiDAR voxels (five of 432) 64 -> 64 61 -> 50, 256 -> 256 407 -> 372.
+            const int n_long = uni(counters[8]);
+            if (n_long > 0 && n_long <= kMaxLongTiles && n_long * nslice <= (int)gridDim.x / 2) {
+                skip_long = true;
+                n_orphans = n_long * nslice;
+                if ((int)blockIdx.x < n_orphans) start = (int64_t)counters[9 + blockIdx.x % n_long] * nslice + blockIdx.x / n_long;
             }
+        }
+        auto announce_next = [&](MetaSlot& M) {
+            int64_t w;
+            do w = take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, n_orphans, open_lists);
+            while (!(announce(M, w, nslice, tile_hdr, lane) & kTileLdsOffsets) && w >= 0 && skip_long);
+        };
+        if (pwave == 0) {   // items that start in phases 0 and 1
+            const int flags = announce(L.meta[0], start, nslice, tile_hdr, lane);
+            if (skip_long && start == first && (int)blockIdx.x >= n_orphans && !(flags & kTileLdsOffsets)) announce_next(L.meta[0]);
+            if (nchunk == 1) announce_next(L.meta[1]);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         int32_t gr[kSlabsPerProducer];
-        {
-            const Item cur = item_of(L.meta[0], first, nslice);
+        if (slot_work(L.meta[0]) >= 0) {       // a workgroup whose static item is another's start may find nothing left
+            const Item cur = item_of(L.meta[0], slot_work(L.meta[0]), nslice);
             produce_meta(L.blocks[0], L.perm[0], cur, pwave, lane, tile_perm, tile_blocks, block_stride);
             resolve_rows(gr, cur, pwave, lane, tile_rows, row_stride);
             produce_rows_resolved(L.rows[0], gr, pwave, lane, feat, pitch, 0);
@@ -623,9 +669,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
                 const int rb = (phase + 1) & 1;
                 // an item starts two phases from now: claimed before this phase's rows are requested, whose loads the
                 // claim and the header would otherwise wait for
-                if (pwave == 0 && (phase + 2) % nchunk == 0)
-                    announce(L.meta[((phase + 2) / nchunk) % kMetaSlots],
-                             take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, open_lists), nslice, tile_hdr, lane);
+                if (pwave == 0 && (phase + 2) % nchunk == 0) announce_next(L.meta[((phase + 2) / nchunk) % kMetaSlots]);
                 if (c != nchunk - 1) {
                     produce_rows_resolved(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
                 } else {
@@ -654,8 +698,9 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             const int w_kappa_stride = nchunk * nslice * 4 * 64;
             const uint32_t m0 = (uint32_t)uni((int)L.meta[0].hdr.wave_mask[wave]);
             const uint32_t m1 = m0 & (m0 - 1);
-            wa_at = w_frag(nslice, w_kappa_stride, (int)(first % nslice), 0, first_offset(m0));
-            wb_at = m1 ? w_frag(nslice, w_kappa_stride, (int)(first % nslice), 0, first_offset(m1)) : wa_at;
+            const int slice0 = (int)(max(slot_work(L.meta[0]), (int64_t)0) % nslice);
+            wa_at = w_frag(nslice, w_kappa_stride, slice0, 0, first_offset(m0));
+            wb_at = m1 ? w_frag(nslice, w_kappa_stride, slice0, 0, first_offset(m1)) : wa_at;
             const vec8* w0 = reinterpret_cast<const vec8*>(wp) + lane;
 #pragma unroll
             for (int f = 0; f < 4; ++f) { wa[f] = (w0 + wa_at)[f * 64]; wb[f] = (w0 + wb_at)[f * 64]; }
@@ -1395,9 +1440,9 @@ FX_DEV_TIMING_EXPORT(fx_debug_conv_timing)
 
 
 // Device memory the matrix-unit kernels need beyond inputs and outputs: the packed weights and, behind them, the
-// eight work-list counters of the persistent kernel.
+// work-list counters of the persistent kernel with its list of long tiles.
 static size_t conv_scratch_bytes(int K3, int C_in, int C_out, int esize) {
-    return packed_weight_bytes(K3, C_in, C_out, esize) + 8 * sizeof(int32_t);    // the packed part is a multiple of 64 bytes
+    return packed_weight_bytes(K3, C_in, C_out, esize) + kConvWorkInts * sizeof(int32_t);    // the packed part is a multiple of 64 bytes
 }
 
 // The tiled map's convolution on the matrix units with that memory supplied by the caller (`scratch`, at least
@@ -1414,7 +1459,7 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     // others: the LDS-staged kernel
     const int fg = option(kOptConvGather);          // 0 / 1: the LDS-staged / the gather kernel on every map
     const bool gather = (fg >= 0 ? fg == 1 : !map_shares_rows(km)) && in_dt != FX_F32 && C_out % kCoutSlice == 0;
-    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st);
+    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, gather ? nullptr : km->d_tile_hdr, km->n_tiles);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gather) {
         ProfScope ps(kProfConvGather, st);
@@ -1575,7 +1620,7 @@ extern "C" fx_status fx_sparse_conv_fwd(const fx_kmap* km, const void* d_feat, f
 // The array's name stands for the symbol in host code; its device address is looked up once per device and only
 // that address is ever handed to kernels.
 namespace {
-constexpr size_t kNoAllocScratchBytes = FX_NOALLOC_MAX_WEIGHT_BYTES + 256;
+constexpr size_t kNoAllocScratchBytes = FX_NOALLOC_MAX_WEIGHT_BYTES + 224 + kConvWorkInts * sizeof(int32_t);
 __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices];

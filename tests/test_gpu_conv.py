@@ -385,3 +385,26 @@ def test_tiles_of_512_one_voxel_leaves(K, stride):
         gy = G.round_to_dtype(np.random.default_rng(4244).standard_normal((ogo.num_voxels, 64)).astype(np.float32), "bf16")
         gx = fx.sparse_conv_bwd_data(km, H.to_device_storage(gy, "bf16"), H.to_device_storage(wt, "bf16"))
         H.conv_tolerance_check(gx.float().cpu().numpy(), O.conv_bwd_data(og, ogo, K, stride, gy, wt), "bf16", 27, 64)
+
+
+@pytest.mark.parametrize("corner", [-2000, 1000])
+@pytest.mark.parametrize("dims,c_in,c_out", [((40, 24, 8), 32, 512), ((40, 24, 8), 96, 320), ((26, 26, 26), 32, 512)])
+def test_long_tiles_among_more_items_than_workgroups(corner, dims, c_in, c_out, fx_opt):
+    # a cloud with one solid block, in the first or in the last tiles: a few tiles whose rows are not all staged start
+    # first, their workgroups' own items are claimed by others, claims pass the long ones over (40 x 24 x 8, with one and
+    # with several phases an item); more of them than are listed leave the order alone (26^3).  Every row is written once.
+    fx_opt("leaf_dispatch", "0")
+    rng = np.random.default_rng(500 + dims[0])
+    cloud = rng.integers(-300, 300, size=(40000, 3)).astype(np.int32)
+    ax = [np.arange(d, dtype=np.int32) + corner for d in dims]
+    block = np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.concatenate([cloud, block])[rng.permutation(40000 + block.shape[0])]
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, wt = G.features_and_weights(21, og.num_voxels, c_in, c_out, 27, "bf16")
+    y = H.nan_filled((og.num_voxels, c_out), torch.bfloat16)
+    fx.sparse_conv_fwd(km, H.to_device_storage(feat, "bf16"), H.to_device_storage(wt, "bf16"), out=y)
+    y = y.float().cpu().numpy()
+    assert np.isfinite(y).all()
+    for s in list(range(0, og.num_voxels - 300, 6000)) + [og.num_voxels - 300]:
+        H.conv_tolerance_check(y[s:s + 300], O.conv(og, og, 3, 1, feat, wt, s, s + 300)[s:s + 300], "bf16", 27, c_in)
