@@ -682,10 +682,10 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // Strided maps, whose tiles share no rows: a wave per offset that walks the map's blocks alone (k_wgrad_pairs, with the
     // figures of both; the tile kernel was slower on every map and channel count tried).
     if (mfma && km->stride == 2) {
-        n_ranges = wgrad_pairs_ranges(km, C_in, C_out);
+        n_ranges = wgrad_pairs_ranges(km, C_in, C_out, 0);
         FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * n_ranges, st));
         ProfScope ps(kProfWgrad, st);
-        e = launch_wgrad_pairs(km, d_feat, d_gout, dt, C_in, C_out, part, n_ranges, st);
+        e = launch_wgrad_pairs(km, d_feat, d_gout, dt, C_in, C_out, part, n_ranges, 0, st);
     } else if (mfma) {
         const fx_kmap* km_all = km;
         km = kmt;
@@ -693,8 +693,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         n_ranges = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles, compute_units() / n_cblk));
         if (n_ranges > 8) n_ranges -= n_ranges % 8;   // see the block-to-XCD mapping in the kernel
         // Sparse submanifold maps with at most a few tiles that are not staged in LDS: the sixteen-wave launch for the
-        // staged tiles and, if there are others, the launch that spreads those over one workgroup per column block
-        // (see WgradMode).  Maps between two grids and dense grids: one launch that
+        // staged tiles and, if there are others, k_wgrad_pairs over the list of those (see WgradMode).  Maps between two grids and dense grids: one launch that
         // takes every tile.  (With a per-leaf split the tiles walked are those of the map without the dense leaves.)
         const double occ = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         bool split = km->stride == 1 && km->gin == km->gout && !km->is_inverse && occ < 0.20;
@@ -703,7 +702,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
             split = km->h_n_unstaged <= kMaxListedTiles;
         }
         const int n_listed = split ? km->h_n_unstaged : 0;
-        const int list_ranges = n_listed > 0 ? kGroupsPerTile : 0;       // one partial sum per column block of the listed tiles
+        const int list_ranges = n_listed > 0 ? wgrad_pairs_ranges(km, C_in, C_out, n_listed) : 0;
         FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * (n_ranges + list_ranges + leaf_ranges), st));
         if (leaf_ranges) {
             const fx_status rl = leaf_wgrad16_partial(km_all->gin, d_feat, d_gout, dt, C_in, C_out, km->d_dense_leaves, km->d_n_dense,
@@ -711,8 +710,10 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
             if (rl != FX_OK) { dev_free(part, st); return rl; }
         }
         ProfScope ps(kProfWgrad, st);
-        e = dt == FX_BF16 ? launch_wgrad_tiles<__bf16>(km, d_feat, d_gout, C_in, C_out, part, n_ranges, split, n_listed, st)
-                          : launch_wgrad_tiles<_Float16>(km, d_feat, d_gout, C_in, C_out, part, n_ranges, split, n_listed, st);
+        e = dt == FX_BF16 ? launch_wgrad_tiles<__bf16>(km, d_feat, d_gout, C_in, C_out, part, n_ranges, split, st)
+                          : launch_wgrad_tiles<_Float16>(km, d_feat, d_gout, C_in, C_out, part, n_ranges, split, st);
+        if (e == hipSuccess && n_listed > 0)
+            e = launch_wgrad_pairs(km, d_feat, d_gout, dt, C_in, C_out, part + (size_t)total * n_ranges, list_ranges, n_listed, st);
         n_ranges += list_ranges;      // what the reduction adds up
     } else if (low) {
         FX_TRY(kmap_ensure_dense(const_cast<fx_kmap*>(km), st));

@@ -189,12 +189,13 @@ constexpr int kWgCi = kCinChunk;            // 32: the row chunk staged in LDS
 constexpr int kWgCo = 64;
 template <typename T>
 hipError_t launch_wgrad_tiles(const fx_kmap* km, const void* d_feat, const void* d_gout, int C_in, int C_out, float* part, int n_ranges,
-                              bool split, int n_listed, hipStream_t st);
+                              bool staged_only, hipStream_t st);
 
-// The same for the strided maps (conv_wgrad_pairs.hip), partial sums part[n_ranges][K3][C_in][C_out].
-int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out);
+// The same for the strided maps and (n_listed > 0) for the first n_listed tiles of km->d_unstaged_list
+// (conv_wgrad_pairs.hip), partial sums part[n_ranges][K3][C_in][C_out].
+int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out, int n_listed);
 hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, float* part,
-                              int n_ranges, hipStream_t st);
+                              int n_ranges, int n_listed, hipStream_t st);
 
 // Weight gradient of the 3x3x3 submanifold convolution from the leaf window (fp32 at low depth; f16 / bf16 at
 // C_in % 32 == 0 and C_out % 64 == 0), and the ordered

@@ -66,12 +66,11 @@ static_assert(kGroupsPerWave == 4 && kTileWaves == 4, "id blocks of four column 
 // LDS latencies -- and took 150 us where the eight-wave kernel with both forms took 204 (1 M-voxel LiDAR grid,
 // 64 -> 64); 30 us of those 204 were one workgroup's single tile of the other kind, which costs as much as four
 // staged ones.  When the map has at most kMaxListedTiles such tiles (counted once per map), kWgStaged (16 waves)
-// takes the staged tiles of the ranges, and kWgOthers (8 waves, both forms) takes the listed tiles with one
-// workgroup per column block of a tile, so that no workgroup carries a whole one: workgroup s sums column block s
-// of every listed tile into partial sum n_ranges + s.  Other maps (between two grids, dense grids, whose
-// tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of kWgAll (8 waves, both forms, every tile of the range).
-// Either way a partial sum is made of the same terms in a fixed order.
-enum WgradMode { kWgAll = 0, kWgStaged = 1, kWgOthers = 2 };
+// takes the staged tiles of the ranges, and k_wgrad_pairs the listed ones, a wave per offset.  Other maps (between two
+// grids, dense grids, whose tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of
+// kWgAll (8 waves, both forms, every tile of the range).  Either way a partial sum is made of the same terms in a
+// fixed order.
+enum WgradMode { kWgAll = 0, kWgStaged = 1 };
 
 //
 // SHAPE: kWgFull when both channel counts are whole blocks (no masks: with them the sixteen-wave kernel spills 16
@@ -84,8 +83,7 @@ __global__ void __launch_bounds__(64 * W, 1)
 k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
              const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
              int block_stride, int64_t n_tiles, int n_ranges, const uint16_t* __restrict__ feat,
-             const uint16_t* __restrict__ gout, int C_in, int C_out, int K3, float* __restrict__ part,
-             const int32_t* __restrict__ tile_list, int n_listed) {
+             const uint16_t* __restrict__ gout, int C_in, int C_out, int K3, float* __restrict__ part) {
     constexpr int kWgWaves = W;
     constexpr int kGoutSlabsPerWave = kGoutSlabs / kWgWaves;
     constexpr int kWgOffsetsPerWave = (kMaxK3Tiled + kWgWaves - 1) / kWgWaves;
@@ -101,15 +99,15 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     // Workgroup b runs on XCD b % 8.  The channel blocks of one tile range read the same gout tiles and
     // id blocks: with the number of ranges a multiple of 8 they get block indices 8 apart, so they share
     // an XCD and its L2 and run side by side.
-    int blk = blockIdx.x % n_cblk, range = blockIdx.x / n_cblk;      // kWgOthers: range = the column block it sums
-    if (MODE != kWgOthers && n_ranges % 8 == 0) {
+    int blk = blockIdx.x % n_cblk, range = blockIdx.x / n_cblk;
+    if (n_ranges % 8 == 0) {
         blk = (blockIdx.x >> 3) % n_cblk;
         range = (int)(blockIdx.x / (8 * n_cblk)) * 8 + (blockIdx.x & 7);
     }
     const int cib = blk % n_cib, cob = blk / n_cib;
     // channels from the block's first to the row's end
     const int ci_n = kMasked ? C_in - cib * kWgCi : kWgCi, co_n = kMasked ? C_out - cob * kWgCo : kWgCo;
-    const int64_t t0 = MODE == kWgOthers ? 0 : n_tiles * range / n_ranges, t1 = MODE == kWgOthers ? n_listed : n_tiles * (range + 1) / n_ranges;
+    const int64_t t0 = n_tiles * range / n_ranges, t1 = n_tiles * (range + 1) / n_ranges;
 
     if (tid < kRowBytes / 16) reinterpret_cast<u32x4*>(L.rows + kRowCap * kRowBytes)[tid] = u32x4{0, 0, 0, 0};
 
@@ -157,24 +155,22 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
 #pragma unroll
         for (int j = 0; j < kGoutSlabsPerWave; ++j) nx_local[j] = tile_perm[t * kTileT + 8 * (wave + kWgWaves * j) + (lane >> 3)];
     };
-    // the tiles that this workgroup takes, in order: positions t0 .. t1 of its range (kWgStaged: the staged ones
-    // among them) or of the list
-    auto tile_of = [&](int64_t c) -> int64_t { return MODE == kWgOthers ? (int64_t)uni(tile_list[c]) : c; };
+    // the tiles that this workgroup takes, in order: those of its range (kWgStaged: the staged ones among them)
     auto next_mine = [&](int64_t c) {
         if (MODE == kWgStaged)
             while (c < t1 && !(uni(tile_hdr[c].flags) & kTileLdsOffsets)) ++c;
         return c;
     };
     int64_t cur = next_mine(t0);
-    if (cur < t1) resolve(tile_of(cur));
+    if (cur < t1) resolve(cur);
     while (cur < t1) {
         const int64_t cur_next = next_mine(cur + 1);
-        const int64_t tile = tile_of(cur);
+        const int64_t tile = cur;
         const TileHeader* H = tile_hdr + tile;
         const int flags = uni(H->flags), win_lo = uni(H->win_lo), win_n = uni(H->win_n), n_list = uni(H->n_list);
         const int n_blocks = uni(H->n_blocks), n_valid = uni(H->n_out);
         const int n_staged = (flags & kTileDirect) ? 0 : min(win_n + n_list, kRowCap);
-        const bool general = MODE == kWgStaged ? false : MODE == kWgOthers ? true : !(flags & kTileLdsOffsets);
+        const bool general = MODE == kWgStaged ? false : !(flags & kTileLdsOffsets);
         const int32_t* my_rows = tile_rows + tile * (int64_t)row_stride;
         uint32_t wmask[kTileWaves], gmask[kGroupsPerTile];
         int block0[kTileWaves];
@@ -207,7 +203,6 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
 #pragma unroll
             for (int j = 0; j < kGoutSlabsPerWave; ++j) {
                 const int slab = wave + kWgWaves * j, slot = 8 * slab + (lane >> 3);
-                if (MODE == kWgOthers && slab / (kGroup / 8) != range) continue;   // only the slots of this workgroup's column block
                 const int gpiece = (lane & 7) ^ (((slot >> 1) & 1) << 2);        // the piece stored at position lane & 7
                 if (local[j] < n_valid) {
                     const uint16_t* src = gout + (tile * kTileT + local[j]) * (int64_t)C_out + cob * kWgCo + gpiece * 8;
@@ -223,7 +218,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 const int off = s * 1024 + lane * 16;
                 if (off < bytes) __builtin_amdgcn_global_load_lds(bsrc + off, (lds_ptr_t)(L.blocks + s * 1024), 16, 0, 0);
             }
-            if (cur_next < t1) resolve(tile_of(cur_next));
+            if (cur_next < t1) resolve(cur_next);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -235,7 +230,6 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
             if (kappa >= K3) continue;
 #pragma unroll
             for (int fw = 0; fw < kTileWaves; ++fw) {
-                if (MODE == kWgOthers && fw != tile_wave_of(range)) continue;     // the column block this workgroup sums
                 const uint32_t wm = wmask[fw];
                 if (!((wm >> kappa) & 1u)) continue;
                 const int b = block0[fw] + __popc(wm & ((1u << kappa) - 1u));
@@ -257,7 +251,6 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                     if (general && (gi & 1) == 0) {
 #pragma unroll
                         for (int gj = gi; gj < gi + 2; ++gj) {
-                            if (MODE == kWgOthers && tile_group_of(fw, gj) != range) continue;
                             if (!((gmask[tile_group_of(fw, gj)] >> kappa) & 1u)) continue;
                             const uint32_t id = (ids[gj >> 1] >> (16 * (gj & 1))) & 0xFFFFu;
                             const bool staged = id < (uint32_t)n_staged;
@@ -276,7 +269,6 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                         }
                     }
                     const int g = tile_group_of(fw, gi);
-                    if (MODE == kWgOthers && g != range) continue;
                     if (!((gmask[g] >> kappa) & 1u)) continue;
                     vec8 fT[2];
                     if (!general) {
@@ -322,12 +314,11 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     }
 
     // ---- partial sums of this range: lane (co = n, h), register 4b + r  ->  ci = 8b + 4h + r
-    const int range_out = MODE == kWgOthers ? n_ranges + range : range;
 #pragma unroll
     for (int j = 0; j < kWgOffsetsPerWave; ++j) {
         const int kappa = wave + kWgWaves * j;
         if (kappa >= K3) continue;
-        float* dst = part + (((int64_t)range_out * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
+        float* dst = part + (((int64_t)range * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
 #pragma unroll
         for (int cb = 0; cb < kHalves; ++cb)
 #pragma unroll
@@ -366,12 +357,11 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
             for (int v = 0; v < 16; ++v) sum[cb][v] = 0.f;
 #pragma unroll 1
         for (int64_t c = next_mine(t0); c < t1; c = next_mine(c + 1)) {
-            const int64_t tile = tile_of(c);
+            const int64_t tile = c;
             const TileHeader* H = tile_hdr + tile;
             const int flags = uni(H->flags), win_lo = uni(H->win_lo), win_n = uni(H->win_n), n_valid = uni(H->n_out);
 #pragma unroll 1
             for (int g = 0; g < kGroupsPerTile; ++g) {
-                if (MODE == kWgOthers && g != range) continue;
                 if (!(((uint32_t)uni((int)H->group_mask[g]) >> kappa) & 1u)) continue;
                 // lane n: the row of voxel n of the column block at this offset, and its output
                 const int fw = tile_wave_of(g);
@@ -398,7 +388,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 }
             }
         }
-        float* dst = part + (((int64_t)range_out * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
+        float* dst = part + (((int64_t)range * K3 + kappa) * C_in + cib * kWgCi) * C_out + cob * kWgCo + n;
 #pragma unroll
         for (int cb = 0; cb < kHalves; ++cb)
 #pragma unroll
@@ -409,33 +399,29 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     }
 }
 
-// The partial sums part[n_ranges (+ kGroupsPerTile)][K3][C_in][C_out] of the map's tiles; split: the sixteen-wave launch and,
-// for n_listed tiles, the launch that spreads them over column blocks (see WgradMode).
+// The partial sums part[n_ranges][K3][C_in][C_out] of the map's tiles; staged_only: the sixteen-wave launch, which leaves
+// out tiles that are not staged (see WgradMode).
 template <typename T>
 hipError_t launch_wgrad_tiles(const fx_kmap* km, const void* d_feat, const void* d_gout, int C_in, int C_out, float* part, int n_ranges,
-                              bool split, int n_listed, hipStream_t st) {
+                              bool staged_only, hipStream_t st) {
     const int n_cblk = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
     const size_t lds = sizeof(WgradLds);
     hipError_t e = hipSuccess;
-#define FX_WGRAD_ONE(W, MODE, SHAPE, NWG)                                                                              \
+#define FX_WGRAD_ONE(W, MODE, SHAPE)                                                                                   \
     do {                                                                                                               \
-        if (e == hipSuccess)                                                                                           \
-            e = hipFuncSetAttribute((const void*)k_wgrad_mfma<T, W, MODE, SHAPE>,                                      \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                             \
+        e = hipFuncSetAttribute((const void*)k_wgrad_mfma<T, W, MODE, SHAPE>,                                          \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                 \
         if (e == hipSuccess) {                                                                                         \
-            k_wgrad_mfma<T, W, MODE, SHAPE><<<(unsigned)(n_cblk * (NWG)), 64 * W, lds, st>>>(                          \
+            k_wgrad_mfma<T, W, MODE, SHAPE><<<(unsigned)(n_cblk * n_ranges), 64 * W, lds, st>>>(                       \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride, \
-                km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, km->K3, part,    \
-                km->d_unstaged_list, n_listed);                                                                        \
+                km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, km->K3, part);   \
             e = hipGetLastError();                                                                                     \
         }                                                                                                              \
     } while (0)
 #define FX_WGRAD_SHAPE(SHAPE)                                                                                          \
     do {                                                                                                               \
-        if (split) {                                                                                                   \
-            FX_WGRAD_ONE(16, kWgStaged, SHAPE, n_ranges);                                                              \
-            if (n_listed > 0) FX_WGRAD_ONE(8, kWgOthers, SHAPE, kGroupsPerTile);                                       \
-        } else FX_WGRAD_ONE(8, kWgAll, SHAPE, n_ranges);                                                               \
+        if (staged_only) FX_WGRAD_ONE(16, kWgStaged, SHAPE);                                                           \
+        else FX_WGRAD_ONE(8, kWgAll, SHAPE);                                                                           \
     } while (0)
     if (C_in % kWgCi == 0 && C_out % kWgCo == 0) FX_WGRAD_SHAPE(kWgFull);
     else if (C_out <= 32) FX_WGRAD_SHAPE(kWgNarrow);

@@ -20,6 +20,11 @@ namespace fx {
 // over existing pairs only, whatever the values are.  Eight waves with two blocks in flight each are 3 us faster on
 // maps of a few thousand outputs and as fast at K = 2, but 17 % slower at K = 3.
 //
+// LISTED: the same over a list of tiles of a submanifold map, those whose rows the tile kernel cannot stage (tile_list,
+// n_tiles entries; such a tile may have a window).  Against a workgroup per column block of such a tile
+// in the tile kernel's other form, the whole call, bf16: 221 k LiDAR voxels with five such tiles 64 -> 64 79 -> 69 us,
+// 256 -> 256 536 -> 498; 195 k voxels of sheets with four 256 -> 256 581 -> 546; 980 k LiDAR voxels with three 181 -> 178.
+//
 // A workgroup takes eight consecutive offsets of a range; the jobs of one range (channel blocks and, at K = 3, four
 // octets of offsets) are placed on one XCD (workgroup b runs on XCD b % 8) so that they share its L2.
 // 987 k-voxel LiDAR grid, bf16, reduction included, k_wgrad_mfma -> here: (2,2) map 64 -> 64 89 -> 58 us, 64 -> 128
@@ -33,12 +38,13 @@ constexpr int kPairsLdsBytes = kGroup * kPairsRowBytes;        // one side's row
 constexpr int kPairsLdsTotal = kPairsWaves * 2 * kPairsLdsBytes;
 static_assert(kPairsLdsTotal <= 160 * 1024 && 4 * kPairsLdsBytes == kPairsBlk * kPairsBlk * 4, "LDS budget; two waves' rows hold one wave's sums");
 
-template <typename T>
+template <typename T, bool LISTED>
 __global__ void __launch_bounds__(64 * kPairsWaves)
 k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
               const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
               int block_stride, int64_t n_tiles, int n_ranges, const uint16_t* __restrict__ feat,
-              const uint16_t* __restrict__ gout, int C_in, int C_out, int K3, float* __restrict__ part) {
+              const uint16_t* __restrict__ gout, int C_in, int C_out, int K3, float* __restrict__ part,
+              const int32_t* __restrict__ tile_list) {
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
@@ -60,7 +66,9 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
 
     // ---- the column blocks of the range that have the offset, in order
     typedef const __attribute__((address_space(4))) TileHeader ConstHeader;
-    struct Block { int tile, g; uint32_t id_block; bool valid; };
+    struct Block { int tile, g; uint32_t id_block; int win_lo, win_n; bool valid; };
+    typedef const __attribute__((address_space(4))) int32_t ConstInt;
+    auto tile_of = [&](int i) __attribute__((always_inline)) { return LISTED ? (int)((ConstInt*)tile_list)[i] : i; };
     int it_tile = (int)(g_lo / kGroupsPerTile) - 1;
     const int last_tile = (int)((g_hi + kGroupsPerTile - 1) / kGroupsPerTile) - 1;
     uint32_t present = 0;                                      // column blocks of it_tile still to take
@@ -68,19 +76,20 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
         while (present == 0 && it_tile < last_tile) {
             ++it_tile;
             // scalar loads: they do not queue behind the rows in flight
-            ConstHeader* H = (ConstHeader*)(tile_hdr + it_tile);
+            ConstHeader* H = (ConstHeader*)(tile_hdr + tile_of(it_tile));
 #pragma unroll
             for (int g = 0; g < kGroupsPerTile; ++g) present |= ((H->group_mask[g] >> kappa) & 1u) << g;
             const int64_t first = (int64_t)it_tile * kGroupsPerTile;
             if (first < g_lo) present &= ~0u << (int)(g_lo - first);
             if (first + kGroupsPerTile > g_hi) present &= (1u << (int)(g_hi - first)) - 1u;
         }
-        Block b = {0, 0, 0u, present != 0};
+        Block b = {0, 0, 0u, 0, 0, present != 0};
         if (b.valid) {
-            b.tile = it_tile;
+            b.tile = tile_of(it_tile);
             b.g = __ffs(present) - 1;
             present &= present - 1;
-            ConstHeader* H = (ConstHeader*)(tile_hdr + it_tile);
+            ConstHeader* H = (ConstHeader*)(tile_hdr + b.tile);
+            if (LISTED) { b.win_lo = H->win_lo; b.win_n = H->win_n; }
             const int w = tile_wave_of(b.g);
             b.id_block = H->wave_block0[w] + __popc(H->wave_mask[w] & ((1u << kappa) - 1u));
         }
@@ -96,7 +105,7 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     };
     uint32_t id, loc;                   // local row id and output (inside the tile) of voxel n of the block whose ids are in flight
     Block blk;
-    int32_t row, locr;                  // row number and output of the block before it
+    int32_t row, window_row, locr;      // row number (LISTED: that of the window where it is not -1) and output of the block before it
     uint32_t has;                       // and its voxels that have the offset
     int32_t out0;                       // first output row of its tile
     u32x4 X[4], Y[4];                   // rows of the block before that one
@@ -111,7 +120,9 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     auto load_row = [&]() __attribute__((always_inline)) {
         const bool mine = blk.valid && id != kNoRow;
         has = (uint32_t)__ballot(mine);                        // lanes 32 .. 63 repeat lanes 0 .. 31
-        row = tile_rows[(int64_t)blk.tile * row_stride + (mine ? id : 0u)];
+        const bool in_window = LISTED && id < (uint32_t)blk.win_n;
+        row = tile_rows[(int64_t)blk.tile * row_stride + (mine && !in_window ? id - (uint32_t)blk.win_n : 0u)];
+        if (LISTED) window_row = mine && in_window ? blk.win_lo + (int32_t)id : -1;
         locr = (int32_t)loc;
         out0 = blk.tile * kTileT;
     };
@@ -126,8 +137,9 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
         const uint32_t m = has;
         hasd = m;
         const int some = m ? __ffs(m) - 1 : 0;                 // a voxel that has the offset
-        const int32_t r0 = m ? __builtin_amdgcn_readlane(row, some) : 0, l0 = m ? __builtin_amdgcn_readlane(locr, some) : 0;
         const int lane = (int)lane_now();
+        if (LISTED && window_row >= 0) row = window_row;
+        const int32_t r0 = m ? __builtin_amdgcn_readlane(row, some) : 0, l0 = m ? __builtin_amdgcn_readlane(locr, some) : 0;
         const bool mine = (m >> (lane & 31)) & 1u;
         const int32_t r = mine ? row : r0, l = (mine ? locr : l0) + out0;
 #pragma unroll
@@ -232,26 +244,34 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
             }
 }
 
-int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out) {
-    const int n_jobs = (km->K3 + kPairsOffsets - 1) / kPairsOffsets * ((C_in + kPairsBlk - 1) / kPairsBlk) * ((C_out + kPairsBlk - 1) / kPairsBlk);
-    // one workgroup per compute unit; on small maps no range shorter than four column blocks
-    int n = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles * (kGroupsPerTile / 4), compute_units() / n_jobs));
+static int pairs_jobs(const fx_kmap* km, int C_in, int C_out) {
+    return (km->K3 + kPairsOffsets - 1) / kPairsOffsets * ((C_in + kPairsBlk - 1) / kPairsBlk) * ((C_out + kPairsBlk - 1) / kPairsBlk);
+}
+
+int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out, int n_listed) {
+    // one workgroup per compute unit; no range shorter than four column blocks, or, of a list, whose blocks are few and
+    // whose latency is what counts, than two and at most sixteen ranges
+    const int most = compute_units() / pairs_jobs(km, C_in, C_out);
+    if (n_listed) return std::max(1, std::min(most, std::min(16, n_listed * (kGroupsPerTile / 2))));
+    const int n = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles * (kGroupsPerTile / 4), most));
     return n > 8 ? n - n % 8 : n;        // see the block-to-XCD mapping in the kernel
 }
 
 hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, float* part,
-                              int n_ranges, hipStream_t st) {
-    const int n_jobs = (km->K3 + kPairsOffsets - 1) / kPairsOffsets * ((C_in + kPairsBlk - 1) / kPairsBlk) * ((C_out + kPairsBlk - 1) / kPairsBlk);
-#define FX_PAIRS(T)                                                                                                    \
+                              int n_ranges, int n_listed, hipStream_t st) {
+    const unsigned grid = (unsigned)(pairs_jobs(km, C_in, C_out) * n_ranges);
+    hipError_t e = hipSuccess;
+#define FX_PAIRS(T, LISTED)                                                                                            \
     do {                                                                                                               \
-        e = hipFuncSetAttribute((const void*)k_wgrad_pairs<T>, hipFuncAttributeMaxDynamicSharedMemorySize, kPairsLdsTotal); \
+        e = hipFuncSetAttribute((const void*)k_wgrad_pairs<T, LISTED>, hipFuncAttributeMaxDynamicSharedMemorySize, kPairsLdsTotal); \
         if (e == hipSuccess)                                                                                           \
-            k_wgrad_pairs<T><<<(unsigned)(n_jobs * n_ranges), 64 * kPairsWaves, kPairsLdsTotal, st>>>(                 \
+            k_wgrad_pairs<T, LISTED><<<grid, 64 * kPairsWaves, kPairsLdsTotal, st>>>(                                  \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride, \
-                km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, km->K3, part);   \
+                LISTED ? n_listed : km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, \
+                km->K3, part, km->d_unstaged_list);                                                                    \
     } while (0)
-    hipError_t e;
-    if (dt == FX_BF16) FX_PAIRS(__bf16); else FX_PAIRS(_Float16);
+    if (dt == FX_BF16) { if (n_listed) FX_PAIRS(__bf16, true); else FX_PAIRS(__bf16, false); }
+    else { if (n_listed) FX_PAIRS(_Float16, true); else FX_PAIRS(_Float16, false); }
 #undef FX_PAIRS
     return e == hipSuccess ? hipGetLastError() : e;
 }
