@@ -27,10 +27,11 @@ namespace fx {
 // the eight input channels 16 * kstep + 8 * kq .. + 7 of column n.  Column n of n-tile t is output
 // channel 2n + t of the slice, so that lane n of an accumulator row (32x32 accumulator layout: lane
 // half h, register v -> voxel row 8*(v/4) + 4*h + v%4) holds two adjacent channels, one per n-tile,
-// and the 32 lanes of a half-wave store one whole output row.
+// and the 32 lanes of a half-wave store one whole output row.  With one n-tile (n_nt = 1) a slice is 32
+// channels and column n is channel n of it.
 template <typename E>   // uint16_t or uint32_t: the bits of one element
 __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out,
-                               int32_t* __restrict__ counters, int mode, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles) {
+                               int32_t* __restrict__ counters, int mode, int n_nt, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles) {
     if (blockIdx.x == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0;   // the convolution's work-list counters
     if (tile_hdr && blockIdx.x == gridDim.x - 1) {
         // a workgroup of its own lists the tiles whose rows are not all staged in LDS, in no particular order (their number,
@@ -50,16 +51,19 @@ __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int 
     constexpr int EPL = 16 / (int)sizeof(E);     // elements per lane fragment
     constexpr int kChunk = 4 * EPL;              // input channels per 64-byte row chunk
     typedef __attribute__((ext_vector_type(EPL))) E Frag;
-    const uint32_t nchunk = C_in / kChunk, nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
-    const uint32_t total = (uint32_t)K3 * nchunk * nslice * 256;         // fragments
+    const uint32_t cols = 32 * n_nt;                                     // channels of a slice
+    const uint32_t nchunk = C_in / kChunk, nslice = (C_out + cols - 1) / cols;
+    const uint32_t total = (uint32_t)K3 * nchunk * nslice * n_nt * 128;  // fragments
     const uint32_t stride = (gridDim.x - (tile_hdr ? 1 : 0)) * blockDim.x;
     for (uint32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < total; f += stride) {
-        const uint32_t lane = f & 63, ks = (f >> 6) & 1, nt = (f >> 7) & 1;
-        uint32_t r = f >> 8;
+        const uint32_t lane = f & 63, ks = (f >> 6) & 1;
+        uint32_t r = f >> 7;
+        const uint32_t nt = n_nt == 2 ? r & 1 : 0;
+        if (n_nt == 2) r >>= 1;
         const uint32_t sl = r % nslice; r /= nslice;
         const uint32_t c = r % nchunk, kappa = r / nchunk;
         const int m = lane & 31, kq = lane >> 5;
-        const int cin = c * kChunk + ks * 2 * EPL + kq * EPL, cout = sl * kCoutSlice + 2 * m + nt;
+        const int cin = c * kChunk + ks * 2 * EPL + kq * EPL, cout = sl * cols + n_nt * m + nt;
         Frag v;
         const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
         const int64_t at = (mode & kWeightsTransposed) ? (kw * C_out + cout) * C_in + cin : (kw * C_in + cin) * C_out + cout;
@@ -79,14 +83,14 @@ size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes) {
 }
 
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
-                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles) {
+                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles, int n_nt) {
     const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / 16);
     const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 4096)) + (tile_hdr ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, tile_hdr, n_tiles);
+        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles);
     else
-        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, tile_hdr, n_tiles);
+        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
@@ -95,8 +99,8 @@ void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out,
 // (slot -> local output number).  Each store instruction covers two whole output rows.
 typedef __attribute__((address_space(1))) unsigned char global_byte;
 
-template <typename T, bool OUT_F32, bool FULL>
-__device__ __forceinline__ void store_block_rows_impl(const f32x16 (&acc)[2], const uint16_t* perm_g, global_byte* tile_out,
+template <typename T, bool OUT_F32, bool FULL, int NT>
+__device__ __forceinline__ void store_block_rows_impl(const f32x16 (&acc)[NT], const uint16_t* perm_g, global_byte* tile_out,
                                                       uint32_t row_bytes, uint32_t lane_off, int n_valid, bool lane_ok, int h) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
@@ -107,11 +111,14 @@ __device__ __forceinline__ void store_block_rows_impl(const f32x16 (&acc)[2], co
             if (!FULL && ((int)local >= n_valid || !lane_ok)) continue;
             global_byte* dst = tile_out + (uint32_t)(__umul24(local, row_bytes) + lane_off);   // 32-bit offset from a wave-uniform base
             const int v = 4 * b + r;
-            if (OUT_F32) {
+            if (NT == 1) {
+                if (OUT_F32) *reinterpret_cast<__attribute__((address_space(1))) float*>(dst) = acc[0][v];
+                else *reinterpret_cast<__attribute__((address_space(1))) uint16_t*>(dst) = (uint16_t)Elem<T>::pack2(acc[0][v], 0.f);
+            } else if (OUT_F32) {
                 typedef __attribute__((ext_vector_type(2))) float f32x2;
-                *reinterpret_cast<__attribute__((address_space(1))) f32x2*>(dst) = f32x2{acc[0][v], acc[1][v]};
+                *reinterpret_cast<__attribute__((address_space(1))) f32x2*>(dst) = f32x2{acc[0][v], acc[NT - 1][v]};
             } else {
-                *reinterpret_cast<__attribute__((address_space(1))) uint32_t*>(dst) = Elem<T>::pack2(acc[0][v], acc[1][v]);
+                *reinterpret_cast<__attribute__((address_space(1))) uint32_t*>(dst) = Elem<T>::pack2(acc[0][v], acc[NT - 1][v]);
             }
         }
     }
@@ -181,19 +188,19 @@ k_conv_scalar4_ldsw(const int32_t* __restrict__ nbmap, int64_t n_out, int K3, co
     }
 }
 
-template <typename T, bool OUT_F32>
-__device__ __forceinline__ void store_block_rows(const f32x16 (&acc)[2], const uint16_t* perm_g, unsigned char* tile_out,
+template <typename T, bool OUT_F32, int NT>
+__device__ __forceinline__ void store_block_rows(const f32x16 (&acc)[NT], const uint16_t* perm_g, unsigned char* tile_out,
                                                  int C_out, int cols, int n_valid, int n, int h, bool all_rows) {
     const uint32_t esize = OUT_F32 ? 4u : 2u;
-    const uint32_t row_bytes = (uint32_t)C_out * esize, lane_off = 2u * (uint32_t)n * esize;
+    const uint32_t row_bytes = (uint32_t)C_out * esize, lane_off = (uint32_t)NT * (uint32_t)n * esize;
     // keep the base in scalar registers: the stores then take it as their scalar address operand
     const uint64_t bits = reinterpret_cast<uint64_t>(tile_out);
     const uint32_t lo = (uint32_t)uni((int)(uint32_t)bits), hi = (uint32_t)uni((int)(uint32_t)(bits >> 32));
     global_byte* base = (global_byte*)(((uint64_t)hi << 32) | lo);
-    if (all_rows && n_valid == kTileT && cols == kCoutSlice)      // otherwise: rows beyond the tile's end or left to another kernel (0xFFFF)
-        store_block_rows_impl<T, OUT_F32, true>(acc, perm_g, base, row_bytes, lane_off, n_valid, true, h);
+    if (all_rows && n_valid == kTileT && cols == 32 * NT)      // otherwise: rows beyond the tile's end or left to another kernel (0xFFFF)
+        store_block_rows_impl<T, OUT_F32, true, NT>(acc, perm_g, base, row_bytes, lane_off, n_valid, true, h);
     else
-        store_block_rows_impl<T, OUT_F32, false>(acc, perm_g, base, row_bytes, lane_off, n_valid, 2 * n < cols, h);
+        store_block_rows_impl<T, OUT_F32, false, NT>(acc, perm_g, base, row_bytes, lane_off, n_valid, NT * n < cols, h);
 }
 
 
@@ -263,13 +270,13 @@ __device__ __forceinline__ uint32_t id_word(const V& v, int e) { return v[e]; }
 // wa_at / wb_at record what the two sets hold, so that a call normally starts with both in
 // flight (and fetches them itself if a call in between was skipped).  GENERAL adds the fallback
 // for rows that are not staged in LDS.
-template <typename T, bool GENERAL>
+template <typename T, bool GENERAL, int NT>
 __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, const unsigned char* lds_blocks,
-                                             f32x16 (&acc)[kGroupsPerWave][2],
+                                             f32x16 (&acc)[kGroupsPerWave][NT],
                                              const uint32_t (&gmask)[kGroupsPerWave], uint32_t wave_mask,
                                              int wave_block0, const typename Elem<T>::vec8* __restrict__ wbase0,
-                                             uint32_t lane_off, int w_base, int w_kappa_stride, typename Elem<T>::vec8 (&wa)[4],
-                                             typename Elem<T>::vec8 (&wb)[4], int& wa_at, int& wb_at, int w_after0,
+                                             uint32_t lane_off, int w_base, int w_kappa_stride, typename Elem<T>::vec8 (&wa)[2 * NT],
+                                             typename Elem<T>::vec8 (&wb)[2 * NT], int& wa_at, int& wb_at, int w_after0,
                                              int w_after1, int n, int h, int n_staged, int win_lo, int win_n,
                                              const int32_t* __restrict__ my_rows, const unsigned char* __restrict__ feat,
                                              int64_t pitch, int c) {
@@ -292,10 +299,10 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
         const int past = (w_after1 & last) | (w_after0 & ~last);
         return ((w_base + k * w_kappa_stride) & in) | (past & ~in);
     };
-    auto fetch_w = [&](vec8 (&w)[4], int off) {   // [mtile*2 + kstep]; uniform base + 32-bit lane offset
+    auto fetch_w = [&](vec8 (&w)[2 * NT], int off) {   // [mtile*2 + kstep]; uniform base + 32-bit lane offset
         const unsigned char* ws = reinterpret_cast<const unsigned char*>(wbase0 + off);
 #pragma unroll
-        for (int f = 0; f < 4; ++f) w[f] = *reinterpret_cast<const vec8*>(ws + lane_off + f * 1024);
+        for (int f = 0; f < 2 * NT; ++f) w[f] = *reinterpret_cast<const vec8*>(ws + lane_off + f * 1024);
     };
     const uint32_t hsel = (uint32_t)h << 4;
     // B fragments (16 channels x 32 voxels, two k-steps) of column block gi for offset kappa
@@ -327,7 +334,7 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
             bf[1] = *reinterpret_cast<const vec8*>(lds_rows + (a0 ^ 32u));
         }
     };
-    vec8 wc[4];
+    vec8 wc[2 * NT];
     vec8 bf[NG][2];   // one set: a group's fragments for the next offset are fetched right after its multiplies
     int q0 = pop_kappa(), q1 = pop_kappa(), q2 = pop_kappa(), it = 0;   // offsets of steps it, it+1, it+2
     if (wa_at != w_offset(0, q0)) fetch_w(wa, w_offset(0, q0));          // only after a call was skipped
@@ -346,7 +353,7 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
     }
     // one step: fetch the weights of step it+2 and the ids of step it+2, then, group by group,
     // multiply the current offset and fetch the group's fragments for the next one
-    auto step = [&](const vec8 (&wcur)[4], vec8 (&wload)[4]) {
+    auto step = [&](const vec8 (&wcur)[2 * NT], vec8 (&wload)[2 * NT]) {
         fetch_w(wload, w_offset(it + 2, q2));
         const IdVec ids_next = idn;
         idn = idp[min(it + 2, n_off - 1) * kGroup];
@@ -356,7 +363,7 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks)      // k-step outermost: consecutive MFMAs never share an accumulator
 #pragma unroll
-                    for (int mt = 0; mt < 2; ++mt) acc[gi][mt] = Elem<T>::mma(bf[gi][ks], wcur[mt * 2 + ks], acc[gi][mt]);
+                    for (int mt = 0; mt < NT; ++mt) acc[gi][mt] = Elem<T>::mma(bf[gi][ks], wcur[mt * 2 + ks], acc[gi][mt]);
             }
             fetch_b(bf[gi], ids_next, gi, q1);
         }
@@ -486,8 +493,9 @@ __device__ __forceinline__ int announce(MetaSlot& M, int64_t work, int nslice, c
 
 // offset (in 16-byte fragments, wave-uniform) of the first weight fragment for (slice, chunk, offset)
 // (the packed weights of one call stay far below 2^31 fragments)
+template <int NT = 2>
 __device__ __forceinline__ int w_frag(int nslice, int w_kappa_stride, int slice, int c, int kappa) {
-    return ((c * nslice + slice) * 4) * 64 + kappa * w_kappa_stride;
+    return ((c * nslice + slice) * 2 * NT) * 64 + kappa * w_kappa_stride;
 }
 
 __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs(mask) - 1 : 0; }
@@ -500,13 +508,13 @@ __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs
 // across items: the last steps of an item already fetch the first weights of the next one (MN
 // is its slot), ahead of the write-back stores -- loads and stores retire in order, and weights
 // requested after the stores would have to wait for them.
-template <typename T, bool OUT_F32, bool GENERAL>
+template <typename T, bool OUT_F32, bool GENERAL, int NT>
 __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, const MetaSlot& MN, const Item& I, int phase,
                                              int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                              const int32_t* __restrict__ tile_rows, int row_stride,
                                              const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
-                                             int64_t pitch, int C_out, void* __restrict__ out, typename Elem<T>::vec8 (&wa)[4],
-                                             typename Elem<T>::vec8 (&wb)[4], int& wa_at, int& wb_at,
+                                             int64_t pitch, int C_out, void* __restrict__ out, typename Elem<T>::vec8 (&wa)[2 * NT],
+                                             typename Elem<T>::vec8 (&wb)[2 * NT], int& wa_at, int& wb_at,
                                              unsigned long long (&tm)[4]) {
     typedef typename Elem<T>::vec8 vec8;
     constexpr int NG = kGroupsPerWave;
@@ -517,13 +525,13 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
     const uint32_t wave_mask = (uint32_t)uni((int)M.hdr.wave_mask[wave]);
     const int wave_block0 = uni((int)M.hdr.wave_block0[wave]);
     const int32_t* my_rows = tile_rows + I.tile * (int64_t)row_stride;
-    const int w_kappa_stride = nchunk * nslice * 4 * 64;
+    const int w_kappa_stride = nchunk * nslice * 2 * NT * 64;
 
-    f32x16 acc[NG][2];
+    f32x16 acc[NG][NT];
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi)
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[gi][mt][v] = 0.f;
 
@@ -539,15 +547,15 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
                 nsl = nwork >= 0 ? (int)(nwork % nslice) : I.slice;
                 nmask = nwork >= 0 ? (uint32_t)uni((int)MN.hdr.wave_mask[wave]) : 0u;
             }
-            w_after0 = w_frag(nslice, w_kappa_stride, nsl, nc, first_offset(nmask));
+            w_after0 = w_frag<NT>(nslice, w_kappa_stride, nsl, nc, first_offset(nmask));
             const uint32_t more = nmask & (nmask - 1);
-            w_after1 = more ? w_frag(nslice, w_kappa_stride, nsl, nc, first_offset(more)) : w_after0;
+            w_after1 = more ? w_frag<NT>(nslice, w_kappa_stride, nsl, nc, first_offset(more)) : w_after0;
         }
         if (wave_mask) {
             FX_CYCLES_BEGIN();
-            offsets_loop<T, GENERAL>(L.rows[(phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
+            offsets_loop<T, GENERAL, NT>(L.rows[(phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
                                      reinterpret_cast<const vec8*>(wp), (uint32_t)lane * 16u,
-                                     w_frag(nslice, w_kappa_stride, I.slice, c, 0), w_kappa_stride, wa, wb, wa_at, wb_at,
+                                     w_frag<NT>(nslice, w_kappa_stride, I.slice, c, 0), w_kappa_stride, wa, wb, wa_at, wb_at,
                                      w_after0, w_after1, n, h, I.n_staged, I.win_lo, I.win_n, my_rows, feat, pitch, c);
             FX_CYCLES_ADD(tm[0]);
         }
@@ -555,17 +563,17 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
     }
     FX_CYCLES_BEGIN();
     unsigned char* tile_out = reinterpret_cast<unsigned char*>(out) +
-                              ((I.tile * kTileT) * C_out + (int64_t)I.slice * kCoutSlice) * (OUT_F32 ? 4 : 2);
+                              ((I.tile * kTileT) * C_out + (int64_t)I.slice * (32 * NT)) * (OUT_F32 ? 4 : 2);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi)
-        store_block_rows<T, OUT_F32>(acc[gi], L.perm[pb] + tile_group_of(wave, gi) * kGroup, tile_out, C_out,
-                                     min(kCoutSlice, C_out - I.slice * kCoutSlice), I.n_valid, n, h, I.all_rows);
+        store_block_rows<T, OUT_F32, NT>(acc[gi], L.perm[pb] + tile_group_of(wave, gi) * kGroup, tile_out, C_out,
+                                     min(32 * NT, C_out - I.slice * (32 * NT)), I.n_valid, n, h, I.all_rows);
     FX_CYCLES_ADD(tm[2]);
 }
 
 // Items whose rows are not all staged in LDS take this path: a real call, so that its registers
 // are allocated apart from the main loop's.
-template <typename T, bool OUT_F32>
+template <typename T, bool OUT_F32, int NT>
 __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                                   const int32_t* __restrict__ tile_rows, int row_stride,
                                                   const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
@@ -575,27 +583,27 @@ __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, i
     ConvLds& L = *reinterpret_cast<ConvLds*>(lds_raw);
     const MetaSlot& M = L.meta[slot];
     const Item I = item_of(M, slot_work(M), nslice);
-    vec8 wa[4], wb[4];
+    vec8 wa[2 * NT], wb[2 * NT];
     int wa_at = -1, wb_at = -1;
     unsigned long long tm[4] = {0, 0, 0, 0};
-    consume_item<T, OUT_F32, true>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane, tile_rows,
+    consume_item<T, OUT_F32, true, NT>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane, tile_rows,
                                    row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, tm);
 }
 
 // Persistent workgroups, one per compute unit.  Work items (tile of 512 consecutive outputs x
-// slice of 64 output channels) are cut into eight contiguous lists, one per XCD, so that
+// slice of 32 NT output channels) are cut into eight contiguous lists, one per XCD, so that
 // neighbouring tiles, which share halo rows, meet in the same L2; a workgroup starts with a fixed
 // item of its XCD's list and then claims items through per-list counters (its own list first),
 // which evens out tiles of different cost.  Time advances in phases of one 32-channel chunk.
 // Waves 0-3 are consumers: wave w owns 4 of the tile's 16 column blocks (128 outputs, 4 x 2
-// accumulator tiles of 32x32) and multiplies out of one half of LDS.  Waves 4-7 are producers:
+// accumulator tiles of 32x32, 4 x 1 for NT = 1) and multiplies out of one half of LDS.  Waves 4-7 are producers:
 // meanwhile they copy the rows of the next phase (and, at a tile change, its id blocks) from
 // global memory straight into the other half, and the first of them announces the item that
 // starts two phases later (claim + tile header) in a ring of three slots.  One barrier per phase
 // hands everything over; both roles walk the same ring and execute the same barriers.
 // Producers and consumers are separate waves because a wave's loads complete in order: the
 // consumer's short weight fetches must not queue behind the long HBM reads.
-template <typename T, bool OUT_F32>
+template <typename T, bool OUT_F32, int NT>
 __global__ void __launch_bounds__(kConvThreads, 1)
 k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
             const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
@@ -607,7 +615,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
     ConvLds& L = *reinterpret_cast<ConvLds*>(lds_raw);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t pitch = (int64_t)C_in * Elem<T>::kBytes;                      // bytes per feature row
-    const int nchunk = (int)(pitch / kRowBytes), nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
+    const int nchunk = (int)(pitch / kRowBytes), nslice = (C_out + 32 * NT - 1) / (32 * NT);
 
     // workgroup b runs on XCD b % 8 (round-robin dispatch)
     const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3, wg_per_xcd = gridDim.x >> 3;
@@ -692,18 +700,18 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         unsigned long long tm[4] = {0, 0, 0, 0};
         const unsigned long long t_start = FX_CYCLES_NOW();
         __syncthreads();
-        vec8 wa[4], wb[4];
+        vec8 wa[2 * NT], wb[2 * NT];
         int wa_at, wb_at;
         {   // weights of the first two offsets of the first item
-            const int w_kappa_stride = nchunk * nslice * 4 * 64;
+            const int w_kappa_stride = nchunk * nslice * 2 * NT * 64;
             const uint32_t m0 = (uint32_t)uni((int)L.meta[0].hdr.wave_mask[wave]);
             const uint32_t m1 = m0 & (m0 - 1);
             const int slice0 = (int)(max(slot_work(L.meta[0]), (int64_t)0) % nslice);
-            wa_at = w_frag(nslice, w_kappa_stride, slice0, 0, first_offset(m0));
-            wb_at = m1 ? w_frag(nslice, w_kappa_stride, slice0, 0, first_offset(m1)) : wa_at;
+            wa_at = w_frag<NT>(nslice, w_kappa_stride, slice0, 0, first_offset(m0));
+            wb_at = m1 ? w_frag<NT>(nslice, w_kappa_stride, slice0, 0, first_offset(m1)) : wa_at;
             const vec8* w0 = reinterpret_cast<const vec8*>(wp) + lane;
 #pragma unroll
-            for (int f = 0; f < 4; ++f) { wa[f] = (w0 + wa_at)[f * 64]; wb[f] = (w0 + wb_at)[f * 64]; }
+            for (int f = 0; f < 2 * NT; ++f) { wa[f] = (w0 + wa_at)[f * 64]; wb[f] = (w0 + wb_at)[f * 64]; }
         }
         __syncthreads();
         int phase = 0, n_items = 0;
@@ -714,13 +722,13 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
             if (cur.general) {
-                consume_item_general<T, OUT_F32>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows, row_stride,
+                consume_item_general<T, OUT_F32, NT>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows, row_stride,
                                                  feat, wp, pitch, C_out, out);
                 wa_at = wb_at = -1;       // nothing is handed over a call
 #pragma unroll
-                for (int f = 0; f < 4; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
+                for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
             } else {
-                consume_item<T, OUT_F32, false>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
+                consume_item<T, OUT_F32, false, NT>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
                                                 wave, lane, tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at,
                                                 wb_at, tm);
             }
@@ -1331,20 +1339,20 @@ k_conv_gather_f32(const TileHeader* __restrict__ tile_hdr, const uint16_t* __res
     }
 }
 
-template <typename T, bool OUT_F32>
+template <typename T, bool OUT_F32, int NT>
 static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* wp, int32_t* counters, int C_in, int C_out,
                               void* out, hipStream_t st) {
     const size_t lds = sizeof(ConvLds);
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma<T, OUT_F32>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma<T, OUT_F32, NT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int n_cu = compute_units();
-    const int64_t n_work = km->n_tiles * (int64_t)((C_out + kCoutSlice - 1) / kCoutSlice);
+    const int64_t n_work = km->n_tiles * (int64_t)((C_out + 32 * NT - 1) / (32 * NT));
     const int per_xcd = (int)((n_work + 7) / 8);
     // one workgroup per compute unit, a multiple of 8 (one share per XCD), no more than the work needs
     int grid = std::max(8, (n_cu / 8) * 8);
     grid = (int)std::min<int64_t>(grid, (int64_t)8 * per_xcd);
-    k_conv_mfma<T, OUT_F32><<<grid, kConvThreads, lds, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
+    k_conv_mfma<T, OUT_F32, NT><<<grid, kConvThreads, lds, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
                                                              km->row_stride, km->d_tile_blocks, km->block_stride, n_work,
                                                              per_xcd, counters, (const unsigned char*)feat,
                                                              (const unsigned char*)wp, C_in, C_out, out);
@@ -1459,7 +1467,14 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     // others: the LDS-staged kernel
     const int fg = option(kOptConvGather);          // 0 / 1: the LDS-staged / the gather kernel on every map
     const bool gather = (fg >= 0 ? fg == 1 : !map_shares_rows(km)) && in_dt != FX_F32 && C_out % kCoutSlice == 0;
-    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, gather ? nullptr : km->d_tile_hdr, km->n_tiles);
+    // A work item of the tile kernel is a tile and 64 output channels, or 32 (half the multiplies, the same reads of features) where
+    // that leaves no padding (up to 32 channels) or where items of 64 keep at most half of the compute units busy:
+    // f16 32 -> 32 on 980 k voxels 97 -> 75 us, 317 k 45 -> 37; bf16 256 -> 256 on 13 k voxels (27 tiles, 108 items of 64)
+    // 84 -> 62, 54 k voxels 64 -> 64 (106 items) 41 -> 36.  Above half of the compute units narrow items need a second round.
+    const bool narrow = !gather && in_dt != FX_F32 &&
+                        (C_out <= 32 || km->n_tiles * (int64_t)((C_out + kCoutSlice - 1) / kCoutSlice) <= compute_units() / 2);
+    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, gather ? nullptr : km->d_tile_hdr, km->n_tiles,
+                        narrow ? 1 : 2);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gather) {
         ProfScope ps(kProfConvGather, st);
@@ -1471,14 +1486,13 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
                         : launch_gather<_Float16, false>(km, d_feat, wp, C_in, C_out, d_out, st);
     } else if (e == hipSuccess) {
         ProfScope ps(kProfConvMfma, st);
-        if (in_dt == FX_F32)
-            e = launch_mfma<float, true>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
-        else if (in_dt == FX_BF16)
-            e = out_f32 ? launch_mfma<__bf16, true>(km, d_feat, wp, counters, C_in, C_out, d_out, st)
-                        : launch_mfma<__bf16, false>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
-        else
-            e = out_f32 ? launch_mfma<_Float16, true>(km, d_feat, wp, counters, C_in, C_out, d_out, st)
-                        : launch_mfma<_Float16, false>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
+#define FX_MFMA(T, F32)                                                                                               \
+    (narrow ? launch_mfma<T, F32, 1>(km, d_feat, wp, counters, C_in, C_out, d_out, st)                                \
+            : launch_mfma<T, F32, 2>(km, d_feat, wp, counters, C_in, C_out, d_out, st))
+        if (in_dt == FX_F32) e = launch_mfma<float, true, 2>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
+        else if (in_dt == FX_BF16) e = out_f32 ? FX_MFMA(__bf16, true) : FX_MFMA(__bf16, false);
+        else e = out_f32 ? FX_MFMA(_Float16, true) : FX_MFMA(_Float16, false);
+#undef FX_MFMA
     }
     if (e != hipSuccess) { set_error("convolution launch failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
     return FX_OK;

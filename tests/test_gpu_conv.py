@@ -408,3 +408,17 @@ def test_long_tiles_among_more_items_than_workgroups(corner, dims, c_in, c_out, 
     assert np.isfinite(y).all()
     for s in list(range(0, og.num_voxels - 300, 6000)) + [og.num_voxels - 300]:
         H.conv_tolerance_check(y[s:s + 300], O.conv(og, og, 3, 1, feat, wt, s, s + 300)[s:s + 300], "bf16", 27, c_in)
+
+
+@pytest.mark.parametrize("dtype,out_f32", [("f16", False), ("bf16", True)])
+@pytest.mark.parametrize("c_in,c_out", [(32, 2), (32, 32), (96, 34), (64, 40), (32, 96), (64, 160)])
+def test_slices_of_32_output_channels(dtype, out_f32, c_in, c_out):
+    # few tiles, or up to 32 channels: work items of 32 channels, whole, partial and past the last whole slice of 64
+    w = G.workload("sheets_small")
+    ijk, jo = w.jagged_ijk(dup_fraction=0.0)
+    g, og = H.both_grids(ijk, jo)
+    km = fx.build_kernel_map(g, 3, 1)
+    feat, wt = G.features_and_weights(23, og.num_voxels, c_in, c_out, 27, dtype)
+    y = H.nan_filled((og.num_voxels, c_out), torch.float32 if out_f32 else H.TORCH_DT[dtype])
+    fx.sparse_conv_fwd(km, H.to_device_storage(feat, dtype), H.to_device_storage(wt, dtype), out_dtype=y.dtype, out=y)
+    H.conv_tolerance_check(y.float().cpu().numpy(), O.conv(og, og, 3, 1, feat, wt), dtype, 27, c_in)
