@@ -248,7 +248,9 @@ void fx_kmap_destroy(fx_kmap* km);
  * Which kernel runs (all give the same sum within the stated tolerance):
  *   - the matrix units (v_mfma_f32_32x32x16 for FX_F16 / FX_BF16; v_mfma_f32_32x32x2_f32, true fp32 products, for
  *     FX_F32) when the map is tiled (K^3 <= 27), C_in * sizeof(element) is a multiple of 64 bytes (32 channels of
- *     a 16-bit type, 16 of fp32) and C_out is even (padded to 64 with zero weights);
+ *     a 16-bit type, 16 of fp32) and C_out is even (padded to 32 or 64 with zero weights); for FX_F16 / FX_BF16 also any
+ *     C_in > 16 that is a multiple of 8 with 16-byte aligned feat and 4-byte aligned out (padded with zeros inside; not
+ *     in fx_sparse_conv_fwd_noalloc);
  *   - FX_F32 with C_in a multiple of 16 and 16-byte aligned feat and w, where those tiles are few (fewer than half the
  *     compute units), rows are not shared (K = stride, strided maps) or C_out is small: one wave per 16 voxels on
  *     v_mfma_f32_16x16x4_f32, true fp32 products as well; few tiles of any other fp32 shape: the scalar kernel;
@@ -264,7 +266,8 @@ void fx_kmap_destroy(fx_kmap* km);
  *   - everything else: a scalar kernel (fp32 FMA in offset-then-channel order).
  * Infinite and NaN weights: the tile, gather and leaf-window kernels multiply a missing neighbour as a row of zeros, so
  * such a weight makes NaN of its column in every row they multiply it for; the wave-per-16-voxels kernel, the kernels at
- * C_in <= 16 and the scalar kernel sum over existing neighbours only, and it reaches no row without that tap.
+ * C_in <= 16, the tile and gather kernels at C_in that is not a multiple of 32 (sums that are not finite are made again pair
+ * by pair) and the scalar kernel sum over existing neighbours only, and it reaches no row without that tap.
  */
 fx_status fx_sparse_conv_fwd(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, const void* d_w,
                              int32_t C_in, int32_t C_out, void* d_out, fx_dtype out_dt, void* stream);
@@ -311,8 +314,9 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * K = stride map every input has exactly one pair and its row is written once; on the 3x3x3 stride-2
  * map an input is shared by up to 8 outputs and the sum is gathered per input through the inverse map
  * (a tiled map of its own, built on the first such call and kept with km; no atomics, fixed order).
- * MFMA paths: FX_F16 / FX_BF16 with C_in % 64 == 0 and C_out % 64 == 0 (bwd_data: C_in % 64 == 0
- * and C_out % 32 == 0; bwd_weight: C_in % 8 == 0 and C_out % 8 == 0) on tiled maps; the kernels at up to 16
+ * MFMA paths: FX_F16 / FX_BF16 on tiled maps (bwd_data: as the forward pass with the channel counts exchanged, on a
+ * K = stride map from 16 x 16 channels on with C_out % 8 == 0, C_in even and the same alignments; bwd_weight: C_in % 8 == 0 and
+ * C_out % 8 == 0); the kernels at up to 16
  * contracted channels (bwd_data: C_out; bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as
  * the forward pass; everything else takes scalar kernels.  Non-finite values: where C_in % 32 == 0 and
  * C_out % 64 == 0 the MFMA weight-gradient kernels multiply a missing pair as zeros, so an infinite or NaN value of gout
@@ -342,8 +346,8 @@ fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_feat, const
  *        supported maps: K = stride (one pair per input, every row of d_out is written), stride 1
  *        (symmetric map: the forward kernels over the mirrored offsets) and 3x3x3 stride 2 (gathered per
  *        input through the inverse map, built on first use).  Types, accumulation and
- *        rounding as fx_sparse_conv_fwd; MFMA path for K = stride: FX_F16 / FX_BF16, C_in % 32 == 0,
- *        C_out % 64 == 0.
+ *        rounding as fx_sparse_conv_fwd; MFMA path for K = stride: FX_F16 / FX_BF16, C_in % 32 == 0 and
+ *        C_out % 64 == 0, or C_in % 8 == 0, C_out even, C_in * C_out >= 256, feat 16-byte and out 4-byte aligned.
  *   fx_pool2       km must be a (2,2) map.  out[o,c] = max (FX_POOL_MAX) or mean (FX_POOL_AVG) over the
  *                  ACTIVE children i = map(o,kappa) of feat[i,c]; the mean is the fp32 sum in offset
  *                  order divided by the number of active children (not by 8), rounded once to dt.

@@ -31,19 +31,28 @@ namespace fx {
 // channels and column n is channel n of it.
 template <typename E>   // uint16_t or uint32_t: the bits of one element
 __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out,
-                               int32_t* __restrict__ counters, int mode, int n_nt, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles) {
+                               int32_t* __restrict__ counters, int mode, int n_nt, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles, PairArgs again) {
     if (blockIdx.x == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0;   // the convolution's work-list counters
+    if (again.hdr && blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<PairArgs*>(counters + kPairArgsAt) = again;
     if (tile_hdr && blockIdx.x == gridDim.x - 1) {
         // a workgroup of its own lists the tiles whose rows are not all staged in LDS, in no particular order (their number,
         // then the first kMaxLongTiles of them): the tile kernel starts with those
         __shared__ int32_t found;
         if (threadIdx.x == 0) found = 0;
         __syncthreads();
-        for (int64_t t = threadIdx.x; t < n_tiles; t += blockDim.x)
-            if (!(tile_hdr[t].flags & kTileLdsOffsets)) {
-                const int at = atomicAdd(&found, 1);
-                if (at < kMaxLongTiles) counters[9 + at] = (int32_t)t;
+        for (int64_t t0 = threadIdx.x; t0 < n_tiles; t0 += 8 * blockDim.x) {       // eight headers in flight
+            int32_t flags[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) flags[u] = tile_hdr[min(t0 + u * (int)blockDim.x, n_tiles - 1)].flags;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t t = t0 + u * (int)blockDim.x;
+                if (t < n_tiles && !(flags[u] & kTileLdsOffsets)) {
+                    const int at = atomicAdd(&found, 1);
+                    if (at < kMaxLongTiles) counters[9 + at] = (int32_t)t;
+                }
             }
+        }
         __syncthreads();
         if (threadIdx.x == 0) { counters[8] = found; counters[9 + kMaxLongTiles] = 0; }
         return;
@@ -52,7 +61,7 @@ __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int 
     constexpr int kChunk = 4 * EPL;              // input channels per 64-byte row chunk
     typedef __attribute__((ext_vector_type(EPL))) E Frag;
     const uint32_t cols = 32 * n_nt;                                     // channels of a slice
-    const uint32_t nchunk = C_in / kChunk, nslice = (C_out + cols - 1) / cols;
+    const uint32_t nchunk = (C_in + kChunk - 1) / kChunk, nslice = (C_out + cols - 1) / cols;
     const uint32_t total = (uint32_t)K3 * nchunk * nslice * n_nt * 128;  // fragments
     const uint32_t stride = (gridDim.x - (tile_hdr ? 1 : 0)) * blockDim.x;
     for (uint32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < total; f += stride) {
@@ -68,29 +77,31 @@ __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int 
         const int64_t kw = (mode & kWeightsFlipped) ? K3 - 1 - kappa : kappa;
         const int64_t at = (mode & kWeightsTransposed) ? (kw * C_out + cout) * C_in + cin : (kw * C_in + cin) * C_out + cout;
         const int64_t step = (mode & kWeightsTransposed) ? 1 : C_out;
-        if ((mode & kWeightsTransposed) && cout < C_out && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
-            v = *reinterpret_cast<const Frag*>(w + at);        // a fragment is contiguous; C_in is a multiple of EPL
+        const bool in = cout < C_out && cin < C_in;             // C_in is a multiple of EPL
+        if ((mode & kWeightsTransposed) && in && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
+            v = *reinterpret_cast<const Frag*>(w + at);        // a fragment is contiguous
         } else {
 #pragma unroll
-            for (int el = 0; el < EPL; ++el) v[el] = cout < C_out ? w[at + el * step] : (E)0;
+            for (int el = 0; el < EPL; ++el) v[el] = in ? w[at + el * step] : (E)0;
         }
         reinterpret_cast<Frag*>(wp)[f] = v;
     }
 }
 
 size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes) {
-    return (size_t)elem_bytes * K3 * C_in * ((C_out + kCoutSlice - 1) / kCoutSlice) * kCoutSlice;
+    const int chunk = kRowBytes / elem_bytes;
+    return (size_t)elem_bytes * K3 * ((C_in + chunk - 1) / chunk * chunk) * ((C_out + kCoutSlice - 1) / kCoutSlice) * kCoutSlice;
 }
 
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
-                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles, int n_nt) {
+                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles, int n_nt, const PairArgs& again) {
     const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / 16);
     const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 4096)) + (tile_hdr ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles);
+        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
     else
-        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles);
+        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
@@ -204,6 +215,39 @@ __device__ __forceinline__ void store_block_rows(const f32x16 (&acc)[NT], const 
 }
 
 
+// The products give a missing neighbour a row of zeros, which adds nothing unless a weight is infinite or NaN.  Shapes that a
+// scalar kernel served before the matrix units did (C_in not a multiple of 32) keep its sums over existing pairs: a block whose
+// sums are not all finite is summed again here, a lane per channel, in offset-then-channel order, and stored over.
+template <typename T, bool OUT_F32>
+__device__ __noinline__ void sum_pairs_again(const PairArgs* args, const uint16_t* __restrict__ feat, int C_in, int C_out, int64_t tile, int g,
+                                             int co0, int cols, void* __restrict__ out) {
+    const PairArgs P = *args;
+    const int lane = threadIdx.x & 63, co = co0 + lane;
+    const bool mine = lane < cols && co < C_out;
+    const TileHeader* H = P.hdr + tile;
+    const uint32_t gm = H->group_mask[g], wm = H->wave_mask[tile_wave_of(g)];
+    const size_t b0 = (size_t)tile * P.block_stride + H->wave_block0[tile_wave_of(g)];
+    for (int v = 0; v < kGroup; ++v) {
+        const int local = P.perm[tile * kTileT + g * kGroup + v];
+        if (local >= H->n_out) continue;
+        float sum = 0.f;
+        for (uint32_t m = gm; m; m &= m - 1) {
+            const int kappa = __ffs(m) - 1;
+            const uint32_t id = P.blocks[(b0 + __popc(wm & ((1u << kappa) - 1u))) * kIdBlockElems + v * kGroupsPerWave + tile_slot_of(g)];
+            const int32_t row = tile_row_of(id, H->flags, H->win_lo, H->win_n, P.rows + tile * (int64_t)P.row_stride);
+            if (row < 0 || !mine) continue;
+            const int64_t kw = (P.mode & kWeightsFlipped) ? P.K3 - 1 - kappa : kappa;
+            for (int ci = 0; ci < C_in; ++ci)
+                sum = fmaf(Elem<T>::to_float(feat[(int64_t)row * C_in + ci]),
+                           Elem<T>::to_float((P.mode & kWeightsTransposed) ? P.w[(kw * C_out + co) * C_in + ci] : P.w[(kw * C_in + ci) * C_out + co]), sum);
+        }
+        const int64_t at = (tile * kTileT + local) * C_out + co;
+        if (!mine) continue;
+        if (OUT_F32) reinterpret_cast<float*>(out)[at] = sum;
+        else reinterpret_cast<uint16_t*>(out)[at] = Elem<T>::from_float(sum);
+    }
+}
+
 // ---------------------------------------------------------------------------------- MFMA kernel
 constexpr int kMetaSlots = 3;
 
@@ -270,7 +314,7 @@ __device__ __forceinline__ uint32_t id_word(const V& v, int e) { return v[e]; }
 // wa_at / wb_at record what the two sets hold, so that a call normally starts with both in
 // flight (and fetches them itself if a call in between was skipped).  GENERAL adds the fallback
 // for rows that are not staged in LDS.
-template <typename T, bool GENERAL, int NT>
+template <typename T, bool GENERAL, int NT, bool PARTIAL>
 __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, const unsigned char* lds_blocks,
                                              f32x16 (&acc)[kGroupsPerWave][NT],
                                              const uint32_t (&gmask)[kGroupsPerWave], uint32_t wave_mask,
@@ -323,9 +367,10 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
             if (__any(from_global)) {
                 if (from_global) {
                     const int64_t gr = id < (uint32_t)win_n ? (int64_t)win_lo + id : (int64_t)my_rows[id - win_n];
-                    const unsigned char* src = feat + gr * pitch + c * kRowBytes + h * 16;
-                    bf[0] = *reinterpret_cast<const vec8*>(src);
-                    bf[1] = *reinterpret_cast<const vec8*>(src + 32);
+                    const int at = c * kRowBytes + h * 16;       // a row that ends inside its last chunk: zeros beyond
+                    const unsigned char* src = feat + gr * pitch + at;
+                    if (!PARTIAL || at < pitch) bf[0] = *reinterpret_cast<const vec8*>(src);
+                    if (!PARTIAL || at + 32 < pitch) bf[1] = *reinterpret_cast<const vec8*>(src + 32);
                 }
             }
         } else {   // id = lds_row_code(row): 16-byte piece p of the row sits at id ^ (p << 4); pieces h and h + 2
@@ -379,23 +424,7 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
 
 // Producer side: one wave copies 1 KB slabs (16 rows of 64 bytes, or 4 id blocks) from global
 // memory straight into LDS; lane l of a slab load writes the 16 bytes at slab + 16*l.
-__device__ __forceinline__ void produce_rows(unsigned char* lds_rows, const Item& I, int pwave, int lane,
-                                             const int32_t* __restrict__ tile_rows, int row_stride,
-                                             const unsigned char* __restrict__ feat, int64_t pitch, int c) {
-    const int32_t* my_rows = tile_rows + I.tile * (int64_t)row_stride;
-    const int n_slabs = (I.n_staged + 15) >> 4;
-    const int piece = (lane & 3) ^ ((lane >> 4) & 3);   // stored position lane&3 holds piece (lane&3) ^ ((row >> 2) & 3)
-    for (int s = pwave; s < n_slabs; s += kProducerWaves) {
-        const int r = 16 * s + (lane >> 2);
-        if (r < I.n_staged) {
-            const int64_t gr = r < I.win_n ? (int64_t)I.win_lo + r : (int64_t)my_rows[r - I.win_n];
-            const unsigned char* src = feat + gr * pitch + c * kRowBytes + piece * 16;
-            __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(lds_rows + s * 1024), 16, 0, 0);
-        }
-    }
-}
-
-// The same with the global row of every slab a lane serves kept in registers: the rows of a tile
+// The global row of every slab a lane serves is kept in registers: the rows of a tile
 // are the same for all its chunks, so only the first chunk pays the dependent load of the halo list.
 constexpr int kSlabsPerProducer = ((kRowCap + 15) / 16 + kProducerWaves - 1) / kProducerWaves;
 
@@ -410,16 +439,23 @@ __device__ __forceinline__ void resolve_rows(int32_t (&gr)[kSlabsPerProducer], c
     }
 }
 
+template <bool PARTIAL>
 __device__ __forceinline__ void produce_rows_resolved(unsigned char* lds_rows, const int32_t (&gr)[kSlabsPerProducer],
                                                       int pwave, int lane, const unsigned char* __restrict__ feat,
                                                       int64_t pitch, int c) {
-    const int piece = (lane & 3) ^ ((lane >> 4) & 3);
+    const int piece = (lane & 3) ^ ((lane >> 4) & 3);       // stored position lane&3 holds piece (lane&3) ^ ((row >> 2) & 3)
+    const bool in = !PARTIAL || c * kRowBytes + piece * 16 < pitch;      // a row that ends inside its last chunk: zeros beyond
 #pragma unroll
     for (int j = 0; j < kSlabsPerProducer; ++j) {
-        if (gr[j] >= 0) {
+        if (gr[j] >= 0 && in) {
             const unsigned char* src = feat + (int64_t)gr[j] * pitch + c * kRowBytes + piece * 16;
             __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(lds_rows + (pwave + kProducerWaves * j) * 1024), 16, 0, 0);
         }
+    }
+    if (!in) {
+#pragma unroll
+        for (int j = 0; j < kSlabsPerProducer; ++j)
+            if (gr[j] >= 0) *reinterpret_cast<u32x4*>(lds_rows + (pwave + kProducerWaves * j) * 1024 + lane * 16) = u32x4{0, 0, 0, 0};
     }
 }
 
@@ -508,14 +544,14 @@ __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs
 // across items: the last steps of an item already fetch the first weights of the next one (MN
 // is its slot), ahead of the write-back stores -- loads and stores retire in order, and weights
 // requested after the stores would have to wait for them.
-template <typename T, bool OUT_F32, bool GENERAL, int NT>
+template <typename T, bool OUT_F32, bool GENERAL, int NT, bool PARTIAL>
 __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, const MetaSlot& MN, const Item& I, int phase,
                                              int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                              const int32_t* __restrict__ tile_rows, int row_stride,
                                              const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
                                              int64_t pitch, int C_out, void* __restrict__ out, typename Elem<T>::vec8 (&wa)[2 * NT],
                                              typename Elem<T>::vec8 (&wb)[2 * NT], int& wa_at, int& wb_at,
-                                             unsigned long long (&tm)[4]) {
+                                             const PairArgs* again, unsigned long long (&tm)[4]) {
     typedef typename Elem<T>::vec8 vec8;
     constexpr int NG = kGroupsPerWave;
     const int n = lane & 31, h = lane >> 5;
@@ -553,7 +589,7 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
         }
         if (wave_mask) {
             FX_CYCLES_BEGIN();
-            offsets_loop<T, GENERAL, NT>(L.rows[(phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
+            offsets_loop<T, GENERAL, NT, PARTIAL>(L.rows[(phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
                                      reinterpret_cast<const vec8*>(wp), (uint32_t)lane * 16u,
                                      w_frag<NT>(nslice, w_kappa_stride, I.slice, c, 0), w_kappa_stride, wa, wb, wa_at, wb_at,
                                      w_after0, w_after1, n, h, I.n_staged, I.win_lo, I.win_n, my_rows, feat, pitch, c);
@@ -562,22 +598,41 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
         { FX_CYCLES_BEGIN(); __syncthreads(); FX_CYCLES_ADD(tm[1]); }
     }
     FX_CYCLES_BEGIN();
+    bool odd = false;
+    if (PARTIAL) {
+        float all = 0.f;                              // not finite if one of the sums is not
+#pragma unroll
+        for (int gi = 0; gi < NG; ++gi)
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) all += acc[gi][mt][v];
+        odd = __ballot(!isfinite(all)) != 0;
+    }
     unsigned char* tile_out = reinterpret_cast<unsigned char*>(out) +
                               ((I.tile * kTileT) * C_out + (int64_t)I.slice * (32 * NT)) * (OUT_F32 ? 4 : 2);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi)
         store_block_rows<T, OUT_F32, NT>(acc[gi], L.perm[pb] + tile_group_of(wave, gi) * kGroup, tile_out, C_out,
                                      min(32 * NT, C_out - I.slice * (32 * NT)), I.n_valid, n, h, I.all_rows);
+    if constexpr (PARTIAL) {
+        if (odd) {
+            __builtin_amdgcn_s_waitcnt(0);            // the rows are stored over
+            for (int gi = 0; gi < NG; ++gi)
+                sum_pairs_again<T, OUT_F32>(again, reinterpret_cast<const uint16_t*>(feat), (int)(pitch / 2), C_out, I.tile, tile_group_of(wave, gi),
+                                            I.slice * 32 * NT, 32 * NT, out);
+        }
+    }
     FX_CYCLES_ADD(tm[2]);
 }
 
 // Items whose rows are not all staged in LDS take this path: a real call, so that its registers
 // are allocated apart from the main loop's.
-template <typename T, bool OUT_F32, int NT>
+template <typename T, bool OUT_F32, int NT, bool PARTIAL>
 __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                                   const int32_t* __restrict__ tile_rows, int row_stride,
                                                   const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
-                                                  int64_t pitch, int C_out, void* __restrict__ out) {
+                                                  int64_t pitch, int C_out, void* __restrict__ out, const PairArgs* again) {
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     ConvLds& L = *reinterpret_cast<ConvLds*>(lds_raw);
@@ -586,8 +641,8 @@ __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, i
     vec8 wa[2 * NT], wb[2 * NT];
     int wa_at = -1, wb_at = -1;
     unsigned long long tm[4] = {0, 0, 0, 0};
-    consume_item<T, OUT_F32, true, NT>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane, tile_rows,
-                                   row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, tm);
+    consume_item<T, OUT_F32, true, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane, tile_rows,
+                                   row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
 }
 
 // Persistent workgroups, one per compute unit.  Work items (tile of 512 consecutive outputs x
@@ -603,7 +658,9 @@ __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, i
 // hands everything over; both roles walk the same ring and execute the same barriers.
 // Producers and consumers are separate waves because a wave's loads complete in order: the
 // consumer's short weight fetches must not queue behind the long HBM reads.
-template <typename T, bool OUT_F32, int NT>
+// PARTIAL: rows that end inside their last 64-byte chunk (C_in not a multiple of 32; 16-bit types): zeros beyond, and sums that
+// are not finite are made again pair by pair.  (In the one kernel the tests cost 3 % at 64 -> 64 on 980 k voxels.)
+template <typename T, bool OUT_F32, int NT, bool PARTIAL>
 __global__ void __launch_bounds__(kConvThreads, 1)
 k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
             const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
@@ -615,7 +672,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
     ConvLds& L = *reinterpret_cast<ConvLds*>(lds_raw);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t pitch = (int64_t)C_in * Elem<T>::kBytes;                      // bytes per feature row
-    const int nchunk = (int)(pitch / kRowBytes), nslice = (C_out + 32 * NT - 1) / (32 * NT);
+    const int nchunk = (int)((pitch + kRowBytes - 1) / kRowBytes), nslice = (C_out + 32 * NT - 1) / (32 * NT);
 
     // workgroup b runs on XCD b % 8 (round-robin dispatch)
     const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3, wg_per_xcd = gridDim.x >> 3;
@@ -663,7 +720,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             const Item cur = item_of(L.meta[0], slot_work(L.meta[0]), nslice);
             produce_meta(L.blocks[0], L.perm[0], cur, pwave, lane, tile_perm, tile_blocks, block_stride);
             resolve_rows(gr, cur, pwave, lane, tile_rows, row_stride);
-            produce_rows_resolved(L.rows[0], gr, pwave, lane, feat, pitch, 0);
+            produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, 0);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -679,7 +736,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
                 // claim and the header would otherwise wait for
                 if (pwave == 0 && (phase + 2) % nchunk == 0) announce_next(L.meta[((phase + 2) / nchunk) % kMetaSlots]);
                 if (c != nchunk - 1) {
-                    produce_rows_resolved(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
+                    produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
                 } else {
                     const MetaSlot& MN = L.meta[(item_no + 1) % kMetaSlots];
                     const int64_t nwork = slot_work(MN);
@@ -688,7 +745,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
                         const int nb = (item_no + 1) & 1;
                         produce_meta(L.blocks[nb], L.perm[(item_no + 1) % 3], nxt, pwave, lane, tile_perm, tile_blocks, block_stride);
                         resolve_rows(gr, nxt, pwave, lane, tile_rows, row_stride);
-                        produce_rows_resolved(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
+                        produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
                     }
                 }
                 __builtin_amdgcn_s_waitcnt(0);
@@ -697,6 +754,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         }
     } else {
         // ---------------- consumers
+        const PairArgs* again = reinterpret_cast<const PairArgs*>(counters + kPairArgsAt);
         unsigned long long tm[4] = {0, 0, 0, 0};
         const unsigned long long t_start = FX_CYCLES_NOW();
         __syncthreads();
@@ -722,15 +780,15 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
             if (cur.general) {
-                consume_item_general<T, OUT_F32, NT>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows, row_stride,
-                                                 feat, wp, pitch, C_out, out);
+                consume_item_general<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows, row_stride,
+                                                 feat, wp, pitch, C_out, out, again);
                 wa_at = wb_at = -1;       // nothing is handed over a call
 #pragma unroll
                 for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
             } else {
-                consume_item<T, OUT_F32, false, NT>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
+                consume_item<T, OUT_F32, false, NT, PARTIAL>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
                                                 wave, lane, tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at,
-                                                wb_at, tm);
+                                                wb_at, again, tm);
             }
             ++n_items;
         }
@@ -758,14 +816,14 @@ __global__ void __launch_bounds__(64 * kGatherWaves)
 k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
               const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
               int block_stride, int64_t n_items, const uint16_t* __restrict__ feat, const uint16_t* __restrict__ wp,
-              int C_in, int C_out, void* __restrict__ out) {
+              int C_in, int C_out, void* __restrict__ out, const PairArgs* again) {
     typedef typename Elem<T>::vec8 vec8;
     __shared__ int32_t row_of[kGatherWaves][kMaxK3Tiled][kGroup];
     __shared__ __align__(16) int32_t out_of[kGatherWaves][kGroup];      // the block's output rows within the tile (-1: none)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t item = (int64_t)blockIdx.x * kGatherWaves + wave;
     if (item >= n_items) return;
-    const int nchunk = C_in / kCinChunk, nslice = C_out / kCoutSlice;
+    const int nchunk = (C_in + kCinChunk - 1) / kCinChunk, nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
     const int slice = (int)(item % nslice);
     const int64_t tg = item / nslice;
     const int g = (int)(tg % kGroupsPerTile);
@@ -820,9 +878,10 @@ k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
         const int32_t r = row_of[wave][rank][n];
         b[0] = zero; b[1] = zero;
         if (r >= 0) {
-            const uint16_t* src = feat + (int64_t)r * C_in + c * kCinChunk + h * 8;
-            b[0] = *reinterpret_cast<const vec8*>(src);
-            b[1] = *reinterpret_cast<const vec8*>(src + 16);
+            // a row that ends inside its last chunk: its last piece once more, for weights that are zero
+            const uint16_t* src = feat + (int64_t)r * C_in;
+            b[0] = *reinterpret_cast<const vec8*>(src + min(c * kCinChunk + h * 8, C_in - 8));
+            b[1] = *reinterpret_cast<const vec8*>(src + min(c * kCinChunk + h * 8 + 16, C_in - 8));
         }
         const vec8* ws = wl + w_frag(nslice, w_kappa_stride, slice, c, kappa);
 #pragma unroll
@@ -854,12 +913,21 @@ k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
         const i32x4 o4 = *reinterpret_cast<const i32x4*>(&out_of[wave][8 * q + 4 * h]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (o4[j] < 0) continue;
+            if (o4[j] < 0 || slice * kCoutSlice + 2 * n >= C_out) continue;
             const int64_t at = (tile * kTileT + o4[j]) * C_out + (int64_t)slice * kCoutSlice + 2 * n;
             if (OUT_F32)
                 *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(out) + at) = f32x2{acc[0][4 * q + j], acc[1][4 * q + j]};
             else
                 *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + at) = Elem<T>::pack2(acc[0][4 * q + j], acc[1][4 * q + j]);
+        }
+    }
+    if (again) {
+        float all = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) all += acc[0][v] + acc[1][v];
+        if (__ballot(!isfinite(all))) {
+            __builtin_amdgcn_s_waitcnt(0);
+            sum_pairs_again<T, OUT_F32>(again, feat, C_in, C_out, tile, g, slice * kCoutSlice, kCoutSlice, out);
         }
     }
 }
@@ -896,11 +964,11 @@ __global__ void __launch_bounds__(64 * W, 1)
 k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
                    const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
                    int block_stride, int64_t n_blocks_total, int K3, const uint16_t* __restrict__ feat,
-                   const uint16_t* __restrict__ wp, int C_in, int C_out, void* __restrict__ out) {
+                   const uint16_t* __restrict__ wp, int C_in, int C_out, void* __restrict__ out, const PairArgs* again) {
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
-    const int nchunk = C_in / kCinChunk, nslice = C_out / kCoutSlice, nset = nslice / NS;
+    const int nchunk = (C_in + kCinChunk - 1) / kCinChunk, nslice = (C_out + kCoutSlice - 1) / kCoutSlice, nset = nslice / NS;
     const int npair = nchunk / CP;                                       // steps per offset (the launch checks CP | nchunk)
     const int slice = (blockIdx.x % nset) * NS;                          // first slice of this workgroup's set
     const int wg = blockIdx.x / nset, n_wg = gridDim.x / nset;           // the launch makes gridDim a multiple of nset
@@ -1011,9 +1079,14 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
 #pragma unroll
             for (int j = 0; j < 2 * CP; ++j) b[j] = zero;
             if (r >= 0) {
-                const uint16_t* src = feat + (int64_t)r * C_in + f_c * (CP * kCinChunk) + h * 8;
+                // CP = 1: a row that ends inside its last chunk gives its last piece once more, for weights that are zero (the
+                // launch takes CP = 2 for rows of whole pairs of chunks only)
+                const uint16_t* src = feat + (int64_t)r * C_in;
 #pragma unroll
-                for (int j = 0; j < 2 * CP; ++j) b[j] = *reinterpret_cast<const vec8*>(src + 16 * j);
+                for (int j = 0; j < 2 * CP; ++j) {
+                    const int at = f_c * (CP * kCinChunk) + h * 8 + 16 * j;
+                    b[j] = *reinterpret_cast<const vec8*>(src + (CP == 1 ? min(at, C_in - 8) : at));
+                }
             }
             return (kappa * nchunk + f_c * CP) * NS * 4096 + lane * 16;
         };
@@ -1064,6 +1137,7 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
                 const int64_t at = (row0 + o4[j]) * C_out + (int64_t)slice * kCoutSlice + 2 * n;
 #pragma unroll
                 for (int sn = 0; sn < NS; ++sn) {
+                    if ((slice + sn) * kCoutSlice + 2 * n >= C_out) continue;
                     if (OUT_F32)
                         *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(out) + at + sn * kCoutSlice) =
                             f32x2{acc[2 * sn][4 * q + j], acc[2 * sn + 1][4 * q + j]};
@@ -1071,6 +1145,19 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
                         *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + at + sn * kCoutSlice) =
                             Elem<T>::pack2(acc[2 * sn][4 * q + j], acc[2 * sn + 1][4 * q + j]);
                 }
+            }
+        }
+        if (again) {
+            float all = 0.f;
+#pragma unroll
+            for (int t = 0; t < 2 * NS; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) all += acc[t][v];
+            if (__ballot(!isfinite(all))) {
+                __builtin_amdgcn_s_waitcnt(0);
+                for (int sn = 0; sn < NS; ++sn)
+                    sum_pairs_again<T, OUT_F32>(again, feat, C_in, C_out, tg / kGroupsPerTile, (int)(tg % kGroupsPerTile),
+                                                (slice + sn) * kCoutSlice, kCoutSlice, out);
             }
         }
         __builtin_amdgcn_wave_barrier();     // the table is rewritten for the next block
@@ -1339,11 +1426,11 @@ k_conv_gather_f32(const TileHeader* __restrict__ tile_hdr, const uint16_t* __res
     }
 }
 
-template <typename T, bool OUT_F32, int NT>
+template <typename T, bool OUT_F32, int NT, bool PARTIAL>
 static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* wp, int32_t* counters, int C_in, int C_out,
                               void* out, hipStream_t st) {
     const size_t lds = sizeof(ConvLds);
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma<T, OUT_F32, NT>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma<T, OUT_F32, NT, PARTIAL>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int n_cu = compute_units();
@@ -1352,7 +1439,7 @@ static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* w
     // one workgroup per compute unit, a multiple of 8 (one share per XCD), no more than the work needs
     int grid = std::max(8, (n_cu / 8) * 8);
     grid = (int)std::min<int64_t>(grid, (int64_t)8 * per_xcd);
-    k_conv_mfma<T, OUT_F32, NT><<<grid, kConvThreads, lds, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
+    k_conv_mfma<T, OUT_F32, NT, PARTIAL><<<grid, kConvThreads, lds, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
                                                              km->row_stride, km->d_tile_blocks, km->block_stride, n_work,
                                                              per_xcd, counters, (const unsigned char*)feat,
                                                              (const unsigned char*)wp, C_in, C_out, out);
@@ -1365,13 +1452,13 @@ static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* w
 // dynamic LDS bytes.  Maps with more than eight offsets take twelve waves (their tables are larger).
 struct GatherLdsPlan { int ns, cp, waves; size_t lds; };
 static GatherLdsPlan gather_lds_plan(const fx_kmap* km, int C_in, int C_out) {
-    const int nslice = C_out / kCoutSlice, nchunk = C_in / kCinChunk;
+    const int nslice = (C_out + kCoutSlice - 1) / kCoutSlice, nchunk = (C_in + kCinChunk - 1) / kCinChunk;
     const size_t w_slice = (size_t)km->K3 * nchunk * 4096;                   // packed weights of one output slice
     auto tables = [&](int waves) { return (size_t)waves * (km->K3 + 1) * kGroup * sizeof(int32_t); };
     GatherLdsPlan p = {0, 1, 0, 0};
     if (option(kOptGatherLds) == 0 || km->K3 > 27) return p;
     if (km->K3 <= 8 && nslice % 2 == 0 && 2 * w_slice + tables(kGatherPairWaves) <= 160 * 1024 && option(kOptGatherLds) != 1) {
-        p.ns = 2; p.cp = nchunk % 2 == 0 ? 2 : 1; p.waves = kGatherPairWaves;
+        p.ns = 2; p.cp = C_in % (2 * kCinChunk) == 0 ? 2 : 1; p.waves = kGatherPairWaves;
     } else if (km->K3 <= 8 && w_slice + tables(kGatherLdsWaves) <= 160 * 1024) {
         p.ns = 1; p.waves = kGatherLdsWaves;
     } else if (km->K3 > 8 && w_slice + tables(kGatherPairWaves) <= 160 * 1024) {
@@ -1383,11 +1470,11 @@ static GatherLdsPlan gather_lds_plan(const fx_kmap* km, int C_in, int C_out) {
 
 template <typename T, bool OUT_F32>
 static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void* wp, int C_in, int C_out, void* out,
-                                hipStream_t st) {
+                                const PairArgs* again, hipStream_t st) {
     const GatherLdsPlan plan = gather_lds_plan(km, C_in, C_out);
     if (plan.ns) {
         const int ns = plan.ns, cp = plan.cp, waves = plan.waves;
-        const int nslice = C_out / kCoutSlice;
+        const int nslice = (C_out + kCoutSlice - 1) / kCoutSlice;
         const bool few = km->K3 <= 8;            // ranks per lane half: 4, else 14
         const int64_t n_blocks_total = km->n_tiles * (int64_t)kGroupsPerTile;
         // one workgroup per compute unit, a multiple of the number of slice sets, no more than there is work for
@@ -1401,7 +1488,7 @@ static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void*
             if (e != hipSuccess) return e;                                                                               \
             k_conv_gather_ldsw<T, OUT_F32, NS_, CP_, W_, D_, R_><<<(unsigned)grid, 64 * W_, plan.lds, st>>>(             \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride,   \
-                n_blocks_total, km->K3, (const uint16_t*)feat, (const uint16_t*)wp, C_in, C_out, out);                   \
+                n_blocks_total, km->K3, (const uint16_t*)feat, (const uint16_t*)wp, C_in, C_out, out, again);            \
             return hipGetLastError();                                                                                    \
         }
         // measured at config 4 (64 -> 128) before the staged look-ahead: 58 us for (2, 2, 12 waves, 3 sets), 58-59
@@ -1411,12 +1498,12 @@ static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void*
 #undef FX_GATHER_LDSW
         return hipErrorInvalidValue;
     }
-    const int64_t n_items = km->n_tiles * (int64_t)kGroupsPerTile * (C_out / kCoutSlice);
+    const int64_t n_items = km->n_tiles * (int64_t)kGroupsPerTile * ((C_out + kCoutSlice - 1) / kCoutSlice);
     const unsigned grid = (unsigned)((n_items + kGatherWaves - 1) / kGatherWaves);
     k_conv_gather<T, OUT_F32><<<grid, 64 * kGatherWaves, 0, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
                                                                  km->row_stride, km->d_tile_blocks, km->block_stride,
                                                                  n_items, (const uint16_t*)feat, (const uint16_t*)wp,
-                                                                 C_in, C_out, out);
+                                                                 C_in, C_out, out, again);
     return hipGetLastError();
 }
 
@@ -1466,33 +1553,41 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     // maps whose tiles list one row per pair (strided; stride 1 back from a larger grid): the gather kernel;
     // others: the LDS-staged kernel
     const int fg = option(kOptConvGather);          // 0 / 1: the LDS-staged / the gather kernel on every map
-    const bool gather = (fg >= 0 ? fg == 1 : !map_shares_rows(km)) && in_dt != FX_F32 && C_out % kCoutSlice == 0;
+    const bool gather = (fg >= 0 ? fg == 1 : !map_shares_rows(km)) && in_dt != FX_F32;
     // A work item of the tile kernel is a tile and 64 output channels, or 32 (half the multiplies, the same reads of features) where
     // that leaves no padding (up to 32 channels) or where items of 64 keep at most half of the compute units busy:
     // f16 32 -> 32 on 980 k voxels 97 -> 75 us, 317 k 45 -> 37; bf16 256 -> 256 on 13 k voxels (27 tiles, 108 items of 64)
     // 84 -> 62, 54 k voxels 64 -> 64 (106 items) 41 -> 36.  Above half of the compute units narrow items need a second round.
     const bool narrow = !gather && in_dt != FX_F32 &&
                         (C_out <= 32 || km->n_tiles * (int64_t)((C_out + kCoutSlice - 1) / kCoutSlice) <= compute_units() / 2);
+    // rows that end inside a 64-byte chunk: shapes whose sums run over existing pairs only (see sum_pairs_again)
+    const bool partial = in_dt != FX_F32 && C_in % kCinChunk != 0;
+    PairArgs pairs = {};
+    if (partial)
+        pairs = {km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->d_tile_blocks, (const uint16_t*)d_w, km->row_stride, km->block_stride, mode, km->K3};
+    const PairArgs* again = partial ? reinterpret_cast<const PairArgs*>(counters + kPairArgsAt) : nullptr;
     launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, gather ? nullptr : km->d_tile_hdr, km->n_tiles,
-                        narrow ? 1 : 2);
+                        narrow ? 1 : 2, pairs);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gather) {
         ProfScope ps(kProfConvGather, st);
         if (in_dt == FX_BF16)
-            e = out_f32 ? launch_gather<__bf16, true>(km, d_feat, wp, C_in, C_out, d_out, st)
-                        : launch_gather<__bf16, false>(km, d_feat, wp, C_in, C_out, d_out, st);
+            e = out_f32 ? launch_gather<__bf16, true>(km, d_feat, wp, C_in, C_out, d_out, again, st)
+                        : launch_gather<__bf16, false>(km, d_feat, wp, C_in, C_out, d_out, again, st);
         else
-            e = out_f32 ? launch_gather<_Float16, true>(km, d_feat, wp, C_in, C_out, d_out, st)
-                        : launch_gather<_Float16, false>(km, d_feat, wp, C_in, C_out, d_out, st);
+            e = out_f32 ? launch_gather<_Float16, true>(km, d_feat, wp, C_in, C_out, d_out, again, st)
+                        : launch_gather<_Float16, false>(km, d_feat, wp, C_in, C_out, d_out, again, st);
     } else if (e == hipSuccess) {
         ProfScope ps(kProfConvMfma, st);
-#define FX_MFMA(T, F32)                                                                                               \
-    (narrow ? launch_mfma<T, F32, 1>(km, d_feat, wp, counters, C_in, C_out, d_out, st)                                \
-            : launch_mfma<T, F32, 2>(km, d_feat, wp, counters, C_in, C_out, d_out, st))
-        if (in_dt == FX_F32) e = launch_mfma<float, true, 2>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
+#define FX_MFMA_NT(T, F32, NT)                                                                                        \
+    (partial ? launch_mfma<T, F32, NT, true>(km, d_feat, wp, counters, C_in, C_out, d_out, st)                        \
+             : launch_mfma<T, F32, NT, false>(km, d_feat, wp, counters, C_in, C_out, d_out, st))
+#define FX_MFMA(T, F32) (narrow ? FX_MFMA_NT(T, F32, 1) : FX_MFMA_NT(T, F32, 2))
+        if (in_dt == FX_F32) e = launch_mfma<float, true, 2, false>(km, d_feat, wp, counters, C_in, C_out, d_out, st);
         else if (in_dt == FX_BF16) e = out_f32 ? FX_MFMA(__bf16, true) : FX_MFMA(__bf16, false);
         else e = out_f32 ? FX_MFMA(_Float16, true) : FX_MFMA(_Float16, false);
 #undef FX_MFMA
+#undef FX_MFMA_NT
     }
     if (e != hipSuccess) { set_error("convolution launch failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
     return FX_OK;
@@ -1563,7 +1658,13 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         FX_HIP_TRY(launch_gather_f32(km, (const float*)d_feat, (const float*)d_w, C_in, C_out, (float*)d_out, mode, st));
         return FX_OK;
     }
-    const bool mfma = conv_tiles_shape_ok(km, in_dt, C_in, C_out) &&
+    // A 16-bit type's rows of more than 16 channels need not be whole chunks: whole 16-byte pieces do, at addresses that are
+    // multiples of them (up to 16 channels: the low-depth kernels below).  Against the
+    // scalar kernel, 221 k LiDAR voxels, bf16, forward / input gradient in us: 48 -> 48 778 / 2209 -> 52 / 52, 24 -> 40
+    // 353 / 632 -> 46 / 43, (2,2) map 48 -> 48 108 -> 20, (3,2) map 48 -> 48 279 / 904 -> 42 / 38.
+    const bool pieces = in_dt != FX_F32 && km->n_tiles > 0 && C_in > 16 && C_in % 8 == 0 && C_out % 2 == 0 &&
+                        ((uintptr_t)d_feat & 15) == 0 && ((uintptr_t)d_out & 3) == 0;
+    const bool mfma = (conv_tiles_shape_ok(km, in_dt, C_in, C_out) || pieces) &&
                       (in_dt != FX_F32 || n_items >= compute_units() / 2 || option(kOptFp32Tiles) == 1) &&   // fp32_tiles = 1: at any size
                       !force_scalar;
     if (mfma) {

@@ -40,7 +40,7 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t item = (int64_t)blockIdx.x * kDgradWaves + wave;
     if (item >= n_items) return;
-    const int nchunk = C_contract / kCinChunk, nslice = C_produce / kCoutSlice;
+    const int nchunk = (C_contract + kCinChunk - 1) / kCinChunk, nslice = (C_produce + kCoutSlice - 1) / kCoutSlice;
     const int slice = (int)(item % nslice);
     const int64_t tg = item / nslice;
     const int g = (int)(tg % kGroupsPerTile);
@@ -86,10 +86,9 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
             for (int v = 0; v < 16; ++v) acc[mt][v] = 0.f;
         for (int c = 0; c < nchunk; ++c) {
             vec8 b[2] = {zero, zero}, wf[4];
-            if (valid) {
-                b[0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
-                b[1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
-            }
+            const int at = c * kCinChunk + h * 8;             // a row that ends inside its last chunk: zeros beyond
+            if (valid && at < C_contract) b[0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
+            if (valid && at + 16 < C_contract) b[1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
             const vec8* ws = wl + ((c * nslice + slice) * 4) * 64 + kappa * w_kappa_stride;
 #pragma unroll
             for (int f = 0; f < 4; ++f) wf[f] = ws[f * 64];
@@ -107,7 +106,7 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int32_t r = r4[j];
-                if (r < 0) continue;
+                if (r < 0 || col >= C_produce) continue;
                 if (OUT_F32)
                     *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(gin) + (int64_t)r * C_produce + col) =
                         f32x2{acc[0][4 * q + j], acc[1][4 * q + j]};
@@ -130,7 +129,8 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
 // blocks ahead: the header and permutation entry of block i + 2 are requested while block i
 // multiplies, the ids and the gout fragments of block i + 1 are requested before block i's offset
 // loop (into a second fragment set) and turned into the row table after it.  R = offset ranks a lane
-// half resolves (ceil(K^3 / 2)).
+// half resolves (ceil(K^3 / 2)).  WHOLE: whole chunks contracted and whole slices produced (the tests for what lies beyond
+// cost 5 % at 128 -> 64 on 980 k voxels).
 //
 // Operand roles: A = gout rows (32 voxels x 16 contracted channels), B = packed weights in the
 // interleaved layout (column n of n-tile t = produced channel 2n + t), so the produced rows lie along
@@ -140,7 +140,7 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
 constexpr int kDgradLdsWaves = 12;
 constexpr int kDgradMaxChunks = 4;
 
-template <typename T, bool OUT_F32, int W, int R>
+template <typename T, bool OUT_F32, int W, int R, bool WHOLE>
 __global__ void __launch_bounds__(64 * W, 1)
 k_dgrad_strided_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
                      const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
@@ -149,7 +149,7 @@ k_dgrad_strided_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
-    const int nchunk = C_contract / kCinChunk, nslice = C_produce / kCoutSlice;
+    const int nchunk = (C_contract + kCinChunk - 1) / kCinChunk, nslice = (C_produce + kCoutSlice - 1) / kCoutSlice;
     const int slice = blockIdx.x % nslice;
     const int wg = blockIdx.x / nslice, n_wg = gridDim.x / nslice;
     unsigned char* wlds = lds_raw;                                       // [kappa][chunk][4 fragments][64 lanes][16 bytes]
@@ -207,9 +207,14 @@ k_dgrad_strided_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __
 #pragma unroll
         for (int c = 0; c < kDgradMaxChunks; ++c) {
             b[c][0] = zero; b[c][1] = zero;
-            if (valid && c < nchunk) {
-                b[c][0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
-                b[c][1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
+            if (WHOLE || c < C_contract / kCinChunk) {
+                if (valid && c < nchunk) {
+                    b[c][0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
+                    b[c][1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
+                }
+            } else if (c < nchunk) {                          // the row ends inside this chunk: zeros beyond
+                if (valid && c * kCinChunk + h * 8 < C_contract) b[c][0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
+                if (valid && c * kCinChunk + h * 8 + 16 < C_contract) b[c][1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
             }
         }
     };
@@ -283,7 +288,7 @@ k_dgrad_strided_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int32_t r = r4[j];
-                    if (r < 0) continue;
+                    if (r < 0 || (!WHOLE && col >= C_produce)) continue;
                     if (OUT_F32)
                         *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(gin) + (int64_t)r * C_produce + col) =
                             f32x2{acc[0][4 * q + j], acc[1][4 * q + j]};
@@ -475,14 +480,21 @@ static hipError_t launch_reduce(const float* part, int n_ranges, int64_t total, 
 fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt, const void* d_w, int32_t C_contract,
                                int32_t C_produce, void* d_dst, fx_dtype out_dt, hipStream_t st, int mode) {
     const bool out_f32 = out_dt == FX_F32;
-    const bool mfma = dt != FX_F32 && km->n_tiles > 0 && C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0 &&
+    // Whole chunks and slices, or rows of whole 16-byte pieces at addresses that are multiples of them and an even number of
+    // produced channels, padded with zeros: every stored row is one pair's product, so padding reaches no result.  Against the
+    // scalar kernels, (2,2) map of 221 k LiDAR voxels, bf16, input gradient / transposed convolution in us: 64 -> 32 844 / 193
+    // -> 20 / 21, 128 -> 96 8890 / 1071 -> 38 / 38, 48 -> 48 969 / 300 -> 21 / 21, 40 -> 24 255 / 127 -> 19 / 20.  (Below 16 x 16
+    // channels the scalar kernels' work is small and they need no packing launch.)
+    const bool pieces = C_contract % 8 == 0 && C_produce % 2 == 0 && C_contract * C_produce >= 256 &&
+                        ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0;
+    const bool mfma = dt != FX_F32 && km->n_tiles > 0 && ((C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0) || pieces) &&
                       option(kOptForceScalar) != 1;
     if (mfma) {
         void* wp = nullptr;
         const size_t wbytes = packed_weight_bytes(km->K3, C_contract, C_produce, 2);
         FX_TRY(dev_alloc(&wp, wbytes + 8 * sizeof(int32_t), st));
         int32_t* counters = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(wp) + wbytes);
-        const int nslice = C_produce / kCoutSlice, nchunk = C_contract / kCinChunk;
+        const int nslice = (C_produce + kCoutSlice - 1) / kCoutSlice, nchunk = (C_contract + kCinChunk - 1) / kCinChunk;
         const size_t lds = (size_t)km->K3 * nchunk * 4096 + (size_t)kDgradLdsWaves * km->K3 * kGroup * sizeof(int32_t);
         const bool lds_weights = lds <= 160 * 1024 && nchunk <= kDgradMaxChunks && km->K3 <= 27 && option(kOptGatherLds) != 0;
         launch_pack_weights(d_w, wp, km->K3, C_contract, C_produce, 2, counters, mode, st);
@@ -492,24 +504,27 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
             int64_t grid = std::max(nslice, compute_units() / nslice * nslice);
             grid = std::min<int64_t>(grid, (n_blocks_total + kDgradLdsWaves - 1) / kDgradLdsWaves * nslice);
             ProfScope ps(kProfDgradStrided, st);
-#define FX_DGRAD_R(T, F32, R)                                                                                         \
+#define FX_DGRAD_W(T, F32, R, WHOLE)                                                                                  \
     do {                                                                                                              \
-        e = hipFuncSetAttribute((const void*)k_dgrad_strided_ldsw<T, F32, kDgradLdsWaves, R>,                         \
+        e = hipFuncSetAttribute((const void*)k_dgrad_strided_ldsw<T, F32, kDgradLdsWaves, R, WHOLE>,                  \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                                \
         if (e == hipSuccess)                                                                                          \
-            k_dgrad_strided_ldsw<T, F32, kDgradLdsWaves, R><<<(unsigned)grid, 64 * kDgradLdsWaves, lds, st>>>(         \
+            k_dgrad_strided_ldsw<T, F32, kDgradLdsWaves, R, WHOLE><<<(unsigned)grid, 64 * kDgradLdsWaves, lds, st>>>(         \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride, \
                 n_blocks_total, km->K3, (const uint16_t*)d_src, (const uint16_t*)wp, C_contract, C_produce, d_dst);    \
     } while (0)
+#define FX_DGRAD_R(T, F32, R)                                                                                         \
+    do { if (C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0) FX_DGRAD_W(T, F32, R, true); else FX_DGRAD_W(T, F32, R, false); } while (0)
 #define FX_DGRAD(T, F32)                                                                                              \
     do { if (km->K3 <= 8) FX_DGRAD_R(T, F32, 4); else FX_DGRAD_R(T, F32, 14); } while (0)
             if (dt == FX_BF16) { if (out_f32) FX_DGRAD(__bf16, true); else FX_DGRAD(__bf16, false); }
             else { if (out_f32) FX_DGRAD(_Float16, true); else FX_DGRAD(_Float16, false); }
 #undef FX_DGRAD
 #undef FX_DGRAD_R
+#undef FX_DGRAD_W
             if (e == hipSuccess) e = hipGetLastError();
         } else if (e == hipSuccess) {
-            const int64_t n_items = km->n_tiles * (int64_t)kGroupsPerTile * (C_produce / kCoutSlice);
+            const int64_t n_items = km->n_tiles * (int64_t)kGroupsPerTile * nslice;
             const unsigned grid = (unsigned)((n_items + kDgradWaves - 1) / kDgradWaves);
             ProfScope ps(kProfDgradStrided, st);
 #define FX_DGRAD(T, F32)                                                                                             \

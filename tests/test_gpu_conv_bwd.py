@@ -361,3 +361,62 @@ def test_weight_gradient_of_strided_maps(kernel, n_rows, dtype, c_in, c_out, odd
     assert ok.all() != odd
     _wgrad_check(np.where(ok, y, 0), np.where(ok, ref, 0), 2e-3)
     assert torch.equal(gw.view(torch.int32), fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32).view(torch.int32))
+
+
+@pytest.mark.parametrize("kernel,stride", [(3, 1), (2, 2), (3, 2)])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 48, 48), ("f16", 24, 40), ("bf16", 96, 34), ("f16", 32, 32), ("bf16", 40, 160)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_channel_counts_that_are_not_whole_chunks_and_slices(kernel, stride, dtype, c_in, c_out, shift):
+    # forward, input gradient and transposed convolution where a row ends inside its last 64-byte chunk and the produced
+    # channels inside their last slice; shift: the same from addresses that are not multiples of 16 bytes.  The cloud has
+    # staged and unstaged tiles (a solid block).  Every element is written.
+    rng = np.random.default_rng(610)
+    ax = [np.arange(d, dtype=np.int32) + 100 for d in (40, 24, 8)]
+    block = np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.unique(np.concatenate([rng.integers(-30, 30, size=(6000, 3)).astype(np.int32), block]), axis=0)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, kernel, stride)
+    ogo = O.output_grid(og, kernel, stride)
+    feat, wt = G.features_and_weights(25, og.num_voxels, c_in, c_out, kernel ** 3, dtype)
+    wt_t = np.ascontiguousarray(wt.transpose(0, 2, 1))
+    gy = G.round_to_dtype(np.random.default_rng(26).standard_normal((ogo.num_voxels, c_out)).astype(np.float32), dtype)
+
+    def dev(a):
+        flat = torch.empty(a.size + shift, dtype=H.TORCH_DT[dtype], device="cuda")
+        v = flat[shift:].view(a.shape)
+        v.copy_(torch.from_numpy(a))
+        return v
+
+    def out(n, c):
+        return torch.full((n * c + shift,), float("nan"), dtype=H.TORCH_DT[dtype], device="cuda")[shift:].view(n, c)
+
+    y = fx.sparse_conv_fwd(km, dev(feat), dev(wt), out=out(ogo.num_voxels, c_out))
+    H.conv_tolerance_check(y.float().cpu().numpy(), O.conv(og, ogo, kernel, stride, feat, wt), dtype, kernel ** 3, c_in)
+    gx = fx.sparse_conv_bwd_data(km, dev(gy), dev(wt), out=out(og.num_voxels, c_in))
+    H.conv_tolerance_check(gx.float().cpu().numpy(), O.conv_bwd_data(og, ogo, kernel, stride, gy, wt), dtype, kernel ** 3, c_out)
+    up = fx.sparse_conv_transpose_fwd(km, dev(gy), dev(wt_t))
+    H.conv_tolerance_check(up.float().cpu().numpy(), O.conv_transpose(og, ogo, kernel, stride, gy, wt_t), dtype, kernel ** 3, c_out)
+
+
+@pytest.mark.parametrize("kernel,stride", [(3, 1), (2, 2), (3, 2)])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 48, 48), ("f16", 24, 200)])
+def test_non_finite_weights_of_partial_chunks_stay_with_their_pairs(kernel, stride, dtype, c_in, c_out):
+    # infinite and NaN weights, and such a feature value, reach only rows that have the tap (the gradient of one tap of all
+    # taps is checked through the input gradient as well); the rest stays at the file's bar
+    rng = np.random.default_rng(611)
+    ax = [np.arange(d, dtype=np.int32) + 100 for d in (40, 24, 8)]
+    block = np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.unique(np.concatenate([rng.integers(-30, 30, size=(6000, 3)).astype(np.int32), block]), axis=0)
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, kernel, stride)
+    ogo = O.output_grid(og, kernel, stride)
+    feat, wt = G.features_and_weights(27, og.num_voxels, c_in, c_out, kernel ** 3, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(28).standard_normal((ogo.num_voxels, c_out)).astype(np.float32), dtype)
+    wt[1, 3, 5], wt[kernel ** 3 - 2, c_in - 1, c_out - 1], feat[7, 2] = np.inf, np.nan, -np.inf
+    y = fx.sparse_conv_fwd(km, H.to_device_storage(feat, dtype), H.to_device_storage(wt, dtype), out_dtype=torch.float32).cpu().numpy()
+    gx = fx.sparse_conv_bwd_data(km, H.to_device_storage(gy, dtype), H.to_device_storage(wt, dtype), out_dtype=torch.float32).cpu().numpy()
+    for a, ref, c in ((y, O.conv(og, ogo, kernel, stride, feat, wt), c_in), (gx, O.conv_bwd_data(og, ogo, kernel, stride, gy, wt), c_out)):
+        ok = np.isfinite(ref)
+        assert np.array_equal(np.isnan(a), np.isnan(ref)) and np.array_equal(np.where(np.isinf(ref), ref, 0), np.where(np.isinf(a), a, 0))
+        assert 0 < (~ok).sum() < ok.size // 2
+        H.conv_tolerance_check(np.where(ok, a, 0), np.where(ok, ref, 0), dtype, kernel ** 3, c)
