@@ -1039,16 +1039,18 @@ __global__ void k_place_leaves(LeafList L, GridPtrs g, uint32_t* __restrict__ le
 // first upper nodes' masks and sends each touched word to memory once, and only if memory does not show its bits
 // already (a stale read only costs a redundant atomic); leaves of further upper nodes look before they update memory
 // directly.  A scene around the origin of its coordinates has eight upper nodes, a batch eight per grid: with copies of
-// four nodes and no look, 376 k leaves of a point cloud around the origin took 390 us here, now 19.
+// four nodes and no look, 376 k leaves of a point cloud around the origin took 390 us here, now 19.  There are as many
+// copies as nodes are possible (n_copies, 4 KB each), up to what a compute unit's LDS holds beside the tile table; with
+// copies of twelve at most, 190 k leaves of two clouds around the origin took 113 us, now 13.
 constexpr int kInsertUpperThreads = 1024;
-constexpr int kAggUpper = 12;
+constexpr int kAggUpper = 38;
 // With at most kRankInBlock root tiles possible (the capacity of the upper level says so) the launch that ranks the
 // tiles is dropped: every workgroup ranks them itself into LDS (a handful of comparisons) and looks its leaves up
 // there; the first workgroup also writes the root table and the count for the launches that follow.
 constexpr int kRankInBlock = 72;
 __global__ void __launch_bounds__(kInsertUpperThreads) k_insert_upper(LeafList L, GridPtrs g,
-                                                                       const int32_t* __restrict__ rep_leaves, int rank_here) {
-    __shared__ unsigned long long bits[kAggUpper * kUpperWords];
+                                                                       const int32_t* __restrict__ rep_leaves, int rank_here, int n_copies) {
+    extern __shared__ __align__(16) unsigned long long bits[];
     __shared__ uint64_t tile_keys[kRankInBlock], ranked_key[kRankInBlock];
     __shared__ int32_t tile_batch[kRankInBlock], ranked_batch[kRankInBlock];
     if (g.hdr->overflow) return;
@@ -1087,7 +1089,7 @@ __global__ void __launch_bounds__(kInsertUpperThreads) k_insert_upper(LeafList L
     } else {
         n_upper = g.hdr->n_upper;
     }
-    const int n_agg_words = (n_upper < kAggUpper ? n_upper : kAggUpper) * kUpperWords;
+    const int n_agg_words = (n_upper < n_copies ? n_upper : n_copies) * kUpperWords;
     for (int e = threadIdx.x; e < n_agg_words; e += kInsertUpperThreads) bits[e] = 0ull;
     __syncthreads();
     const int64_t idx = (int64_t)blockIdx.x * kInsertUpperThreads + threadIdx.x;
@@ -1702,11 +1704,13 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     const size_t n_masks = partition ? (size_t)g->cap_leaf
                          : no_table ? 8 * (size_t)n_rows : n_slots + (from.kind == LeafSource::kPad ? (size_t)n_rows : 0);
     if (n_masks > 0x7FFFFFFFull) { fx_grid_destroy(g); set_error("grid build: too many leaves"); return FX_ERANGE; }
-    // Buckets of 1500 to 3000 rows: fewer, fuller buckets give the scatter pass longer runs per bucket and the
+    // Buckets of 1500 to 3000 rows from 800 k rows on: fewer, fuller buckets give the scatter pass longer runs per bucket and the
     // leaf pass fewer workgroups that each clear a 64 KB table (1 M rows: 98 us with ~1000 rows per bucket, 90 with
     // ~2000, 91 with ~4000, 107 with ~8000, which leaves half the compute units without a bucket; four grids of
     // 1.07 M rows: 140 / 123 / 117 / 111 us for ~500 / 1000 / 2000 / 4000).
-    int n_buckets = 64;
+    // At least one bucket per compute unit: with 128 of 1770 rows half the chip had none, and the buckets of sparse points
+    // overflowed their tables (226 k points in 190 k leaves: 60 -> 21 us for the leaf pass).
+    int n_buckets = 256;
     while (n_buckets < kMaxBuckets && (int64_t)n_buckets * kRowsPerBucket < n_rows) n_buckets <<= 1;
     // Rows per workgroup of the two row passes: 4096, or 8192 once that still makes two workgroups per compute unit
     // (longer runs per bucket, half the histogram).
@@ -1824,8 +1828,11 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
         const bool rank_in_block = g->cap_upper <= kRankInBlock;
         if (!rank_in_block) { ProfScope ps(kProfRankTiles, st); k_rank_tiles<<<kMaxTiles / 256, 256, 0, st>>>(L, d_rep, q); }
         { ProfScope ps(kProfInsertUpper, st);
-          k_insert_upper<<<nb_leaf_1024, kInsertUpperThreads, 0, st>>>(
-              L, q, d_rep, rank_in_block ? 1 : 0); }
+          const int n_copies = std::min(g->cap_upper, kAggUpper);
+          const size_t lds = sizeof(uint64_t) * kUpperWords * (size_t)n_copies;
+          if (lds > 64 * 1024) FX_TRY_OR_FAIL(hipFuncSetAttribute((const void*)k_insert_upper, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+          k_insert_upper<<<nb_leaf_1024, kInsertUpperThreads, lds, st>>>(
+              L, q, d_rep, rank_in_block ? 1 : 0, n_copies); }
         LevelScan su{g->d_upper_mask, g->d_upper_prefix, &g->d_hdr->n_upper, kUpperWords, &g->d_hdr->n_lower,
                      g->cap_lower, 2};
         { ProfScope ps(kProfScanUpper, st); if (scan_level(g, su, g->cap_upper, scan_sync(0), st) != FX_OK) return fail(FX_EDEVICE); }

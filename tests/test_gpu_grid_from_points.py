@@ -70,3 +70,11 @@ def test_empty_cloud_and_invalid_points():
     # the library still works afterwards
     ok = fx.build_index_grid_from_points(bad[:1].contiguous(), np.array([[0, 1]], np.int64))
     assert ok.num_voxels == 1
+
+
+@pytest.mark.parametrize("grids,per_grid", [(4, 30000), (5, 20000), (8, 12000)])
+def test_batches_of_clouds_around_the_origin(grids, per_grid):
+    # eight upper nodes a grid: 32, 40 and 64 of them, on either side of the 38 whose child bits are collected in LDS;
+    # 97 to 120 k rows, one to a few in a leaf, in as many buckets as compute units
+    clouds = [G.gaussian_point_cloud(70 + b, per_grid, 1.0) for b in range(grids)]
+    _check(clouds, (0.0, 0.0, 0.0), (0.011, 0.011, 0.011))
