@@ -96,12 +96,14 @@ size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes) {
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
                          int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles, int n_nt, const PairArgs& again) {
     const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / 16);
-    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + 255) / 256, 4096)) + (tile_hdr ? 1 : 0);
+    // small weights in workgroups of one wave, so that every compute unit has one
+    const unsigned bs = tile_hdr || total > 65536 ? 256u : 64u;
+    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + bs - 1) / bs, 4096)) + (tile_hdr ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, 256, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
+        k_pack_weights<uint16_t><<<nb, bs, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
     else
-        k_pack_weights<uint32_t><<<nb, 256, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
+        k_pack_weights<uint32_t><<<nb, bs, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
@@ -527,6 +529,20 @@ __device__ __forceinline__ int announce(MetaSlot& M, int64_t work, int nslice, c
     return __builtin_amdgcn_readlane(v, offsetof(TileHeader, flags) / 4);
 }
 
+// Whether the tile kernel starts with the long tiles: with one item a workgroup there is nothing to reorder, with more than
+// seven the claims even a long one out and the list costs the packing launch a microsecond.  The last condition: the lower
+// half of the last XCD's workgroups has static items.
+__host__ __device__ inline bool long_tiles_first(int64_t n_work, int grid) {
+    const int64_t per_xcd = (n_work + 7) / 8;
+    const int wg_per_xcd = grid >> 3;
+    return per_xcd > wg_per_xcd && per_xcd <= 7 * wg_per_xcd && 7 * per_xcd + wg_per_xcd / 2 < n_work;
+}
+
+// workgroups of the tile kernel: one per compute unit, a multiple of 8 (one share per XCD), no more than the work needs
+static int mfma_grid(int64_t n_work) {
+    return (int)std::min<int64_t>(std::max(8, (compute_units() / 8) * 8), 8 * ((n_work + 7) / 8));
+}
+
 // offset (in 16-byte fragments, wave-uniform) of the first weight fragment for (slice, chunk, offset)
 // (the packed weights of one call stay far below 2^31 fragments)
 template <int NT = 2>
@@ -689,18 +705,22 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         int64_t start = first;
         int n_orphans = 0;
         bool skip_long = false;
-        if (pwave == 0 && per_xcd > wg_per_xcd && 7 * (int64_t)per_xcd + wg_per_xcd / 2 < n_work) {
+        int flags = 0;
+        if (pwave == 0) {
+            const int n_long = long_tiles_first(n_work, gridDim.x) ? uni(counters[8]) : 0;              // in flight beside the first header
+            flags = announce(L.meta[0], first, nslice, tile_hdr, lane);
             // Items of long tiles (rows gathered from global memory: two to four times a staged item) would end the launch
             // alone if they were claimed last.  When all of them are listed the first workgroups start with one each, claims
             // pass them over, and the static items of those workgroups are claimed like the others (at most the lower half
-            // of every XCD's workgroups, all of which have a static item: see the condition above).  With one item a
-            // workgroup there is nothing to reorder.  bf16 on 195 k voxels of sheets (four long tiles of 381), 128 -> 128
+            // of every XCD's workgroups, all of which have a static item: see long_tiles_first).  bf16 on 195 k voxels of sheets (four long tiles of 381), 128 -> 128
             // 165 -> 149 us, 256 -> 256 515 -> 457; 221 k LiDAR voxels (five of 432) 64 -> 64 61 -> 50, 256 -> 256 407 -> 372.
-            const int n_long = uni(counters[8]);
             if (n_long > 0 && n_long <= kMaxLongTiles && n_long * nslice <= (int)gridDim.x / 2) {
                 skip_long = true;
                 n_orphans = n_long * nslice;
-                if ((int)blockIdx.x < n_orphans) start = (int64_t)counters[9 + blockIdx.x % n_long] * nslice + blockIdx.x / n_long;
+                if ((int)blockIdx.x < n_orphans) {
+                    start = (int64_t)counters[9 + blockIdx.x % n_long] * nslice + blockIdx.x / n_long;
+                    flags = announce(L.meta[0], start, nslice, tile_hdr, lane);
+                }
             }
         }
         auto announce_claimed = [&](MetaSlot& M, int64_t w) {
@@ -711,7 +731,6 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             announce_claimed(M, take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, n_orphans, open_lists));
         };
         if (pwave == 0) {   // items that start in phases 0 and 1
-            const int flags = announce(L.meta[0], start, nslice, tile_hdr, lane);
             if (skip_long && start == first && (int)blockIdx.x >= n_orphans && !(flags & kTileLdsOffsets)) announce_next(L.meta[0]);
             if (nchunk == 1) announce_next(L.meta[1]);
         }
@@ -734,16 +753,15 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             const Item cur = item_of(M, work, nslice);
             for (int c = 0; c < nchunk; ++c, ++phase) {
                 const int rb = (phase + 1) & 1;
-                // Two chains of dependent loads side by side: the next item's row numbers and the claim of the item that starts
-                // two phases from now, then the rows and that item's header.  (One after the other they were longer than a
+                if (c != nchunk - 1) produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
+                // At one chunk an item two chains of dependent loads side by side: the next item's row numbers and the claim of
+                // the item that starts two phases from now, then the rows and that item's header.  (One after the other they were longer than a
                 // phase's multiplies at one chunk an item: f16 32 -> 32 on 221 k voxels 36.0 -> 34.7 us, on 980 k 72 -> 71.)
                 const int64_t nwork = c == nchunk - 1 ? slot_work(L.meta[(item_no + 1) % kMetaSlots]) : -1;
                 if (nwork >= 0) resolve_rows(gr, item_of(L.meta[(item_no + 1) % kMetaSlots], nwork, nslice), pwave, lane, tile_rows, row_stride);
                 const bool claims = pwave == 0 && (phase + 2) % nchunk == 0;
                 const int64_t claimed = claims ? take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, n_orphans, open_lists) : -1;
-                if (c != nchunk - 1) {
-                    produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
-                } else if (nwork >= 0) {
+                if (nwork >= 0) {
                     const Item nxt = item_of(L.meta[(item_no + 1) % kMetaSlots], nwork, nslice);
                     produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
                     produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], nxt, pwave, lane, tile_perm, tile_blocks, block_stride);
@@ -1434,12 +1452,8 @@ static hipError_t launch_mfma(const fx_kmap* km, const void* feat, const void* w
     hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma<T, OUT_F32, NT, PARTIAL>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const int n_cu = compute_units();
     const int64_t n_work = km->n_tiles * (int64_t)((C_out + 32 * NT - 1) / (32 * NT));
-    const int per_xcd = (int)((n_work + 7) / 8);
-    // one workgroup per compute unit, a multiple of 8 (one share per XCD), no more than the work needs
-    int grid = std::max(8, (n_cu / 8) * 8);
-    grid = (int)std::min<int64_t>(grid, (int64_t)8 * per_xcd);
+    const int per_xcd = (int)((n_work + 7) / 8), grid = mfma_grid(n_work);
     k_conv_mfma<T, OUT_F32, NT, PARTIAL><<<grid, kConvThreads, lds, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
                                                              km->row_stride, km->d_tile_blocks, km->block_stride, n_work,
                                                              per_xcd, counters, (const unsigned char*)feat,
@@ -1567,7 +1581,9 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     if (partial)
         pairs = {km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->d_tile_blocks, (const uint16_t*)d_w, km->row_stride, km->block_stride, mode, km->K3};
     const PairArgs* again = partial ? reinterpret_cast<const PairArgs*>(counters + kPairArgsAt) : nullptr;
-    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, gather ? nullptr : km->d_tile_hdr, km->n_tiles,
+    const int64_t n_work = km->n_tiles * (int64_t)(narrow ? (C_out + 31) / 32 : (C_out + 63) / 64);
+    const bool list = !gather && long_tiles_first(n_work, mfma_grid(n_work));
+    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, list ? km->d_tile_hdr : nullptr, km->n_tiles,
                         narrow ? 1 : 2, pairs);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gather) {
