@@ -217,37 +217,114 @@ __device__ __forceinline__ void store_block_rows(const f32x16 (&acc)[NT], const 
 }
 
 
-// The products give a missing neighbour a row of zeros, which adds nothing unless a weight is infinite or NaN.  Shapes that a
-// scalar kernel served before the matrix units did (C_in not a multiple of 32) keep its sums over existing pairs: a block whose
-// sums are not all finite is summed again here, a lane per channel, in offset-then-channel order, and stored over.
-template <typename T, bool OUT_F32>
-__device__ __noinline__ void sum_pairs_again(const PairArgs* args, const uint16_t* __restrict__ feat, int C_in, int C_out, int64_t tile, int g,
-                                             int co0, int cols, void* __restrict__ out) {
-    const PairArgs P = *args;
-    const int lane = threadIdx.x & 63, co = co0 + lane;
-    const bool mine = lane < cols && co < C_out;
+// offset (in 16-byte fragments, wave-uniform) of the first weight fragment for (slice, chunk, offset)
+// (the packed weights of one call stay far below 2^31 fragments)
+template <int NT = 2>
+__device__ __forceinline__ int w_frag(int nslice, int w_kappa_stride, int slice, int c, int kappa) {
+    return ((c * nslice + slice) * 2 * NT) * 64 + kappa * w_kappa_stride;
+}
+
+// The products give a missing neighbour a row of zeros, which adds nothing unless a weight is infinite or NaN, and the gather
+// kernels multiply what stands for a row's missing end by weights of zero, which adds nothing unless a feature is.  Shapes
+// that a scalar kernel served before the matrix units did (C_in not a multiple of 32) keep its sums over existing pairs: a
+// column block whose sums are not all finite is summed again here, offset by offset, and only rows that have the offset take
+// its product.  One wave alone: the ids of the offset after next, the row numbers of the next one and the operands of the
+// next step are in flight while one is multiplied.  A batch that is NaN throughout (an overflow step under loss scaling), 268 k
+// LiDAR voxels, bf16, forward, in us, on finite values / here / in the scalar kernel: 3x3x3 48 -> 48 74 / 448 / 922, 24 -> 40 56 /
+// 366 / 419; (2,2) map 48 -> 48 21 / 50 / 127; (3,2) map 48 -> 48 43 / 86 / 308.  (A lane per channel walking voxels, offsets and
+// channels one after the other took 25 700, 12 200, 2 130 and 4 670.)
+template <typename T, bool OUT_F32, int NT, int MT>      // MT n-tiles, from mt0 on, of the NT of a slice of 32 NT channels
+__device__ __forceinline__ void sum_pairs_again(const PairArgs& P, const uint16_t* __restrict__ feat, const void* __restrict__ wp, int C_in, int C_out,
+                                                int64_t tile, int g, int slice, int mt0, void* __restrict__ out) {
+    typedef typename Elem<T>::vec8 vec8;
+    const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+    const int nchunk = (C_in + kCinChunk - 1) / kCinChunk, nslice = (C_out + 32 * NT - 1) / (32 * NT);
+    const int w_kappa_stride = nchunk * nslice * 2 * NT * 64;
     const TileHeader* H = P.hdr + tile;
-    const uint32_t gm = H->group_mask[g], wm = H->wave_mask[tile_wave_of(g)];
-    const size_t b0 = (size_t)tile * P.block_stride + H->wave_block0[tile_wave_of(g)];
-    for (int v = 0; v < kGroup; ++v) {
-        const int local = P.perm[tile * kTileT + g * kGroup + v];
-        if (local >= H->n_out) continue;
-        float sum = 0.f;
-        for (uint32_t m = gm; m; m &= m - 1) {
-            const int kappa = __ffs(m) - 1;
-            const uint32_t id = P.blocks[(b0 + __popc(wm & ((1u << kappa) - 1u))) * kIdBlockElems + v * kGroupsPerWave + tile_slot_of(g)];
-            const int32_t row = tile_row_of(id, H->flags, H->win_lo, H->win_n, P.rows + tile * (int64_t)P.row_stride);
-            if (row < 0 || !mine) continue;
-            const int64_t kw = (P.mode & kWeightsFlipped) ? P.K3 - 1 - kappa : kappa;
-            for (int ci = 0; ci < C_in; ++ci)
-                sum = fmaf(Elem<T>::to_float(feat[(int64_t)row * C_in + ci]),
-                           Elem<T>::to_float((P.mode & kWeightsTransposed) ? P.w[(kw * C_out + co) * C_in + ci] : P.w[(kw * C_in + ci) * C_out + co]), sum);
+    const uint32_t wm = H->wave_mask[tile_wave_of(g)];
+    const uint16_t* ids = P.blocks + ((size_t)tile * P.block_stride + H->wave_block0[tile_wave_of(g)]) * kIdBlockElems + n * kGroupsPerWave + tile_slot_of(g);
+    const int flags = H->flags, win_lo = H->win_lo, win_n = H->win_n;
+    const int32_t* rows = P.rows + tile * (int64_t)P.row_stride;
+    uint32_t rest = (uint32_t)uni((int)H->group_mask[g]);
+    auto pop = [&]() { const int k = __ffs(rest) - 1; rest &= rest - 1; return k; };     // -1: no offset left
+    auto load_id = [&](int k) -> uint32_t { return k < 0 ? kNoRow : (uint32_t)ids[(size_t)__popc(wm & ((1u << k) - 1u)) * kIdBlockElems]; };
+    auto row_behind = [&](uint32_t id) -> int32_t { return tile_row_of(id, flags, win_lo, win_n, rows); };
+    auto fetch = [&](int k, int32_t row, int c, vec8 (&b)[2], vec8 (&w)[2 * MT]) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b[ks][e] = 0;
+            const int at = c * kCinChunk + ks * 16 + h * 8;                      // a row that ends inside its last chunk: zeros beyond
+            if (row >= 0 && at < C_in) b[ks] = *reinterpret_cast<const vec8*>(feat + (int64_t)row * C_in + at);
         }
-        const int64_t at = (tile * kTileT + local) * C_out + co;
-        if (!mine) continue;
-        if (OUT_F32) reinterpret_cast<float*>(out)[at] = sum;
-        else reinterpret_cast<uint16_t*>(out)[at] = Elem<T>::from_float(sum);
+        const vec8* ws = reinterpret_cast<const vec8*>(wp) + lane + (w_frag<NT>(nslice, w_kappa_stride, slice, c, max(k, 0)) + mt0 * 128);
+#pragma unroll
+        for (int f = 0; f < 2 * MT; ++f) w[f] = ws[f * 64];
+    };
+    f32x16 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[mt][v] = 0.f;
+    int k0 = pop(), k1 = pop(), k2 = pop();
+    const uint32_t id0 = load_id(k0), id1 = load_id(k1);
+    uint32_t id2 = load_id(k2);
+    int32_t r0 = k0 < 0 ? -1 : row_behind(id0), r1 = k1 < 0 ? -1 : row_behind(id1);
+    vec8 b[2], w[2 * MT], bn[2], wn[2 * MT];
+    fetch(k0, r0, 0, b, w);
+#pragma unroll 1
+    while (k0 >= 0) {
+        const int k3 = pop();
+        const uint32_t id3 = load_id(k3);
+        const int32_t r2 = k2 < 0 ? -1 : row_behind(id2);
+        const uint32_t has = (uint32_t)__ballot(r0 >= 0) >> (4 * h);            // lanes 32 .. 63 repeat lanes 0 .. 31
+        f32x16 sum[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[mt][v] = 0.f;
+#pragma unroll 1
+        for (int c = 0; c < nchunk; ++c) {
+            const bool last = c == nchunk - 1;
+            fetch(last ? k1 : k0, last ? r1 : r0, last ? 0 : c + 1, bn, wn);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) sum[mt] = Elem<T>::mma(b[ks], w[mt * 2 + ks], sum[mt]);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) b[ks] = bn[ks];
+#pragma unroll
+            for (int f = 0; f < 2 * MT; ++f) w[f] = wn[f];
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)                                         // accumulator row 8 * (v / 4) + 4 * h + v % 4
+                acc[mt][v] = (has >> (8 * (v >> 2) + (v & 3))) & 1u ? acc[mt][v] + sum[mt][v] : acc[mt][v];
+        k0 = k1; k1 = k2; k2 = k3;
+        r0 = r1; r1 = r2; id2 = id3;
     }
+    const int col = slice * (32 * NT) + NT * n + mt0;
+    if (col >= C_out) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int local = P.perm[tile * kTileT + g * kGroup + 8 * (v >> 2) + 4 * h + (v & 3)];
+        if (local >= H->n_out) continue;                                        // past the tile's end, or another kernel's
+        const int64_t at = (tile * kTileT + local) * C_out + col;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            if (OUT_F32) reinterpret_cast<float*>(out)[at + mt] = acc[mt][v];
+            else reinterpret_cast<uint16_t*>(out)[at + mt] = Elem<T>::from_float(acc[mt][v]);
+        }
+    }
+}
+
+// a real call for the tile kernel, so that its registers are allocated apart from the main loop's; one n-tile, because a call
+// that takes more registers makes the compiler spill more around it (48 -> 48 4 % slower on finite values)
+template <typename T, bool OUT_F32, int NT>
+__device__ __noinline__ void sum_pairs_again_call(const PairArgs* args, const uint16_t* feat, const void* wp, int C_in, int C_out, int64_t tile,
+                                                  int g, int slice, int mt, void* out) {
+    sum_pairs_again<T, OUT_F32, NT, 1>(*args, feat, wp, C_in, C_out, tile, g, slice, mt, out);
 }
 
 // ---------------------------------------------------------------------------------- MFMA kernel
@@ -543,13 +620,6 @@ static int mfma_grid(int64_t n_work) {
     return (int)std::min<int64_t>(std::max(8, (compute_units() / 8) * 8), 8 * ((n_work + 7) / 8));
 }
 
-// offset (in 16-byte fragments, wave-uniform) of the first weight fragment for (slice, chunk, offset)
-// (the packed weights of one call stay far below 2^31 fragments)
-template <int NT = 2>
-__device__ __forceinline__ int w_frag(int nslice, int w_kappa_stride, int slice, int c, int kappa) {
-    return ((c * nslice + slice) * 2 * NT) * 64 + kappa * w_kappa_stride;
-}
-
 __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs(mask) - 1 : 0; }
 
 // Consumer side of one work item: multiply all chunks (one barrier after each, matching the
@@ -614,16 +684,17 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
         { FX_CYCLES_BEGIN(); __syncthreads(); FX_CYCLES_ADD(tm[1]); }
     }
     FX_CYCLES_BEGIN();
-    bool odd = false;
+    uint32_t odd = 0;                                 // column blocks with a sum that is not finite
     if (PARTIAL) {
-        float all = 0.f;                              // not finite if one of the sums is not
 #pragma unroll
-        for (int gi = 0; gi < NG; ++gi)
+        for (int gi = 0; gi < NG; ++gi) {
+            float all = 0.f;
 #pragma unroll
             for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) all += acc[gi][mt][v];
-        odd = __ballot(!isfinite(all)) != 0;
+            if (__ballot(!isfinite(all))) odd |= 1u << gi;
+        }
     }
     unsigned char* tile_out = reinterpret_cast<unsigned char*>(out) +
                               ((I.tile * kTileT) * C_out + (int64_t)I.slice * (32 * NT)) * (OUT_F32 ? 4 : 2);
@@ -634,9 +705,13 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
     if constexpr (PARTIAL) {
         if (odd) {
             __builtin_amdgcn_s_waitcnt(0);            // the rows are stored over
-            for (int gi = 0; gi < NG; ++gi)
-                sum_pairs_again<T, OUT_F32>(again, reinterpret_cast<const uint16_t*>(feat), (int)(pitch / 2), C_out, I.tile, tile_group_of(wave, gi),
-                                            I.slice * 32 * NT, 32 * NT, out);
+            for (; odd; odd &= odd - 1)
+                for (int mt = 0; mt < NT; ++mt)
+                    sum_pairs_again_call<T, OUT_F32, NT>(again, reinterpret_cast<const uint16_t*>(feat), wp, (int)(pitch / 2), C_out, I.tile,
+                                                         tile_group_of(wave, __ffs(odd) - 1), I.slice, mt, out);
+            wa_at = wb_at = -1;                       // nothing is handed over a call
+#pragma unroll
+            for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
         }
     }
     FX_CYCLES_ADD(tm[2]);
@@ -835,7 +910,7 @@ __global__ void __launch_bounds__(64 * kGatherWaves)
 k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
               const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
               int block_stride, int64_t n_items, const uint16_t* __restrict__ feat, const uint16_t* __restrict__ wp,
-              int C_in, int C_out, void* __restrict__ out, const PairArgs* again) {
+              int C_in, int C_out, void* __restrict__ out, bool partial) {
     typedef typename Elem<T>::vec8 vec8;
     __shared__ int32_t row_of[kGatherWaves][kMaxK3Tiled][kGroup];
     __shared__ __align__(16) int32_t out_of[kGatherWaves][kGroup];      // the block's output rows within the tile (-1: none)
@@ -940,13 +1015,13 @@ k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
                 *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + at) = Elem<T>::pack2(acc[0][4 * q + j], acc[1][4 * q + j]);
         }
     }
-    if (again) {
-        float all = 0.f;
+    if (partial) {
+        float all = 0.f;                     // not finite if one of the sums is not
 #pragma unroll
         for (int v = 0; v < 16; ++v) all += acc[0][v] + acc[1][v];
         if (__ballot(!isfinite(all))) {
-            __builtin_amdgcn_s_waitcnt(0);
-            sum_pairs_again<T, OUT_F32>(again, feat, C_in, C_out, tile, g, slice * kCoutSlice, kCoutSlice, out);
+            __builtin_amdgcn_s_waitcnt(0);   // the rows are stored over
+            sum_pairs_again<T, OUT_F32, 2, 2>({tile_hdr, tile_perm, tile_rows, tile_blocks, row_stride, block_stride}, feat, wp, C_in, C_out, tile, g, slice, 0, out);
         }
     }
 }
@@ -974,16 +1049,16 @@ k_conv_gather(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
 //   row table after it.
 // Workgroup b serves slice set b % (nslice / NS).  NS = output slices per workgroup, CP = 32-channel
 // chunks per step, W = waves per workgroup, D = fragment sets in flight, R = offset ranks a lane half
-// resolves (ceil(K^3 / 2)).
+// resolves (ceil(K^3 / 2)); PARTIAL: C_in is not a multiple of 32 (CP = 1; see sum_pairs_again).
 constexpr int kGatherLdsWaves = 16;
 constexpr int kGatherPairWaves = 12;
 
-template <typename T, bool OUT_F32, int NS, int CP, int W, int D, int R>
+template <typename T, bool OUT_F32, int NS, int CP, int W, int D, int R, bool PARTIAL>
 __global__ void __launch_bounds__(64 * W, 1)
 k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
                    const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
                    int block_stride, int64_t n_blocks_total, int K3, const uint16_t* __restrict__ feat,
-                   const uint16_t* __restrict__ wp, int C_in, int C_out, void* __restrict__ out, const PairArgs* again) {
+                   const uint16_t* __restrict__ wp, int C_in, int C_out, void* __restrict__ out) {
     typedef typename Elem<T>::vec8 vec8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
@@ -1073,6 +1148,8 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();                       // the weights are in LDS
 
+    unsigned long long odd = 0;            // PARTIAL: the wave's blocks with a sum that is not finite (bit 63: any from the 64th on)
+    int nth = 0;
 #pragma unroll 1
     for (int64_t tg = tg0; tg < n_blocks_total; tg += tg_stride) {
         const Hdr h2 = load_hdr(tg + 2 * tg_stride);
@@ -1098,13 +1175,12 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
 #pragma unroll
             for (int j = 0; j < 2 * CP; ++j) b[j] = zero;
             if (r >= 0) {
-                // CP = 1: a row that ends inside its last chunk gives its last piece once more, for weights that are zero (the
-                // launch takes CP = 2 for rows of whole pairs of chunks only)
+                // PARTIAL: a row that ends inside its last chunk gives its last piece once more, for weights that are zero
                 const uint16_t* src = feat + (int64_t)r * C_in;
 #pragma unroll
                 for (int j = 0; j < 2 * CP; ++j) {
                     const int at = f_c * (CP * kCinChunk) + h * 8 + 16 * j;
-                    b[j] = *reinterpret_cast<const vec8*>(src + (CP == 1 ? min(at, C_in - 8) : at));
+                    b[j] = *reinterpret_cast<const vec8*>(src + (PARTIAL ? min(at, C_in - 8) : at));
                 }
             }
             return (kappa * nchunk + f_c * CP) * NS * 4096 + lane * 16;
@@ -1166,22 +1242,30 @@ k_conv_gather_ldsw(const TileHeader* __restrict__ tile_hdr, const uint16_t* __re
                 }
             }
         }
-        if (again) {
-            float all = 0.f;
+        if (PARTIAL) {
+            float all = 0.f;                     // not finite if one of the sums is not
 #pragma unroll
             for (int t = 0; t < 2 * NS; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) all += acc[t][v];
-            if (__ballot(!isfinite(all))) {
-                __builtin_amdgcn_s_waitcnt(0);
-                for (int sn = 0; sn < NS; ++sn)
-                    sum_pairs_again<T, OUT_F32>(again, feat, C_in, C_out, tg / kGroupsPerTile, (int)(tg % kGroupsPerTile),
-                                                (slice + sn) * kCoutSlice, kCoutSlice, out);
-            }
+            if (__ballot(!isfinite(all))) odd |= 1ull << min(nth, 63);
+            ++nth;
         }
         __builtin_amdgcn_wave_barrier();     // the table is rewritten for the next block
         if (more) finish_table(tg + tg_stride, h1, idv, p1);
         h0 = h1; h1 = h2; p0 = p1; p1 = p2;
+    }
+    if constexpr (PARTIAL) {                     // after the loop, whose registers would be spilled around it
+        if (odd) __builtin_amdgcn_s_waitcnt(0);  // the rows are stored over
+        nth = 0;
+#pragma unroll 1
+        for (int64_t tg = tg0; odd && tg < n_blocks_total; tg += tg_stride, ++nth) {
+            if (!((odd >> min(nth, 63)) & 1)) continue;
+#pragma unroll 1
+            for (int sn = 0; sn < NS; ++sn)
+                sum_pairs_again<T, OUT_F32, 2, 2>({tile_hdr, tile_perm, tile_rows, tile_blocks, row_stride, block_stride}, feat, wp, C_in, C_out,
+                                               tg / kGroupsPerTile, (int)(tg % kGroupsPerTile), slice + sn, 0, out);
+        }
     }
 }
 
@@ -1485,7 +1569,8 @@ static GatherLdsPlan gather_lds_plan(const fx_kmap* km, int C_in, int C_out) {
 
 template <typename T, bool OUT_F32>
 static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void* wp, int C_in, int C_out, void* out,
-                                const PairArgs* again, hipStream_t st) {
+                                hipStream_t st) {
+    const bool partial = C_in % kCinChunk != 0;      // see sum_pairs_again
     const GatherLdsPlan plan = gather_lds_plan(km, C_in, C_out);
     if (plan.ns) {
         const int ns = plan.ns, cp = plan.cp, waves = plan.waves;
@@ -1496,20 +1581,22 @@ static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void*
         const int nset = nslice / ns;
         int64_t grid = std::max(nset, compute_units() / nset * nset);
         grid = std::min<int64_t>(grid, (n_blocks_total + waves - 1) / waves * nset);
-#define FX_GATHER_LDSW(NS_, CP_, W_, D_, R_)                                                                             \
-        if (ns == NS_ && cp == CP_ && waves == W_ && few == (R_ == 4)) {                                                 \
-            hipError_t e = hipFuncSetAttribute((const void*)k_conv_gather_ldsw<T, OUT_F32, NS_, CP_, W_, D_, R_>,        \
+#define FX_GATHER_LDSW(NS_, CP_, W_, D_, R_, PARTIAL_)                                                                   \
+        if (ns == NS_ && cp == CP_ && waves == W_ && few == (R_ == 4) && partial == PARTIAL_) {                          \
+            hipError_t e = hipFuncSetAttribute((const void*)k_conv_gather_ldsw<T, OUT_F32, NS_, CP_, W_, D_, R_, PARTIAL_>, \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds);              \
             if (e != hipSuccess) return e;                                                                               \
-            k_conv_gather_ldsw<T, OUT_F32, NS_, CP_, W_, D_, R_><<<(unsigned)grid, 64 * W_, plan.lds, st>>>(             \
+            k_conv_gather_ldsw<T, OUT_F32, NS_, CP_, W_, D_, R_, PARTIAL_><<<(unsigned)grid, 64 * W_, plan.lds, st>>>(   \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride,   \
-                n_blocks_total, km->K3, (const uint16_t*)feat, (const uint16_t*)wp, C_in, C_out, out, again);            \
+                n_blocks_total, km->K3, (const uint16_t*)feat, (const uint16_t*)wp, C_in, C_out, out);                   \
             return hipGetLastError();                                                                                    \
         }
         // measured at config 4 (64 -> 128) before the staged look-ahead: 58 us for (2, 2, 12 waves, 3 sets), 58-59
         // for 8 waves with 2 to 4 sets, 63-64 for one chunk per step, 79-81 for one slice per workgroup
-        FX_GATHER_LDSW(1, 1, kGatherLdsWaves, 4, 4) FX_GATHER_LDSW(1, 1, kGatherPairWaves, 2, 14)
-        FX_GATHER_LDSW(2, 1, kGatherPairWaves, 4, 4) FX_GATHER_LDSW(2, 2, kGatherPairWaves, 3, 4)
+        FX_GATHER_LDSW(1, 1, kGatherLdsWaves, 4, 4, false) FX_GATHER_LDSW(1, 1, kGatherPairWaves, 2, 14, false)
+        FX_GATHER_LDSW(2, 1, kGatherPairWaves, 4, 4, false) FX_GATHER_LDSW(2, 2, kGatherPairWaves, 3, 4, false)
+        FX_GATHER_LDSW(1, 1, kGatherLdsWaves, 4, 4, true) FX_GATHER_LDSW(1, 1, kGatherPairWaves, 2, 14, true)
+        FX_GATHER_LDSW(2, 1, kGatherPairWaves, 4, 4, true)
 #undef FX_GATHER_LDSW
         return hipErrorInvalidValue;
     }
@@ -1518,7 +1605,7 @@ static hipError_t launch_gather(const fx_kmap* km, const void* feat, const void*
     k_conv_gather<T, OUT_F32><<<grid, 64 * kGatherWaves, 0, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,
                                                                  km->row_stride, km->d_tile_blocks, km->block_stride,
                                                                  n_items, (const uint16_t*)feat, (const uint16_t*)wp,
-                                                                 C_in, C_out, out, again);
+                                                                 C_in, C_out, out, partial);
     return hipGetLastError();
 }
 
@@ -1578,9 +1665,7 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     // rows that end inside a 64-byte chunk: shapes whose sums run over existing pairs only (see sum_pairs_again)
     const bool partial = in_dt != FX_F32 && C_in % kCinChunk != 0;
     PairArgs pairs = {};
-    if (partial)
-        pairs = {km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->d_tile_blocks, (const uint16_t*)d_w, km->row_stride, km->block_stride, mode, km->K3};
-    const PairArgs* again = partial ? reinterpret_cast<const PairArgs*>(counters + kPairArgsAt) : nullptr;
+    if (partial && !gather) pairs = {km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->d_tile_blocks, km->row_stride, km->block_stride};
     const int64_t n_work = km->n_tiles * (int64_t)(narrow ? (C_out + 31) / 32 : (C_out + 63) / 64);
     const bool list = !gather && long_tiles_first(n_work, mfma_grid(n_work));
     launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, list ? km->d_tile_hdr : nullptr, km->n_tiles,
@@ -1589,11 +1674,11 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     if (e == hipSuccess && gather) {
         ProfScope ps(kProfConvGather, st);
         if (in_dt == FX_BF16)
-            e = out_f32 ? launch_gather<__bf16, true>(km, d_feat, wp, C_in, C_out, d_out, again, st)
-                        : launch_gather<__bf16, false>(km, d_feat, wp, C_in, C_out, d_out, again, st);
+            e = out_f32 ? launch_gather<__bf16, true>(km, d_feat, wp, C_in, C_out, d_out, st)
+                        : launch_gather<__bf16, false>(km, d_feat, wp, C_in, C_out, d_out, st);
         else
-            e = out_f32 ? launch_gather<_Float16, true>(km, d_feat, wp, C_in, C_out, d_out, again, st)
-                        : launch_gather<_Float16, false>(km, d_feat, wp, C_in, C_out, d_out, again, st);
+            e = out_f32 ? launch_gather<_Float16, true>(km, d_feat, wp, C_in, C_out, d_out, st)
+                        : launch_gather<_Float16, false>(km, d_feat, wp, C_in, C_out, d_out, st);
     } else if (e == hipSuccess) {
         ProfScope ps(kProfConvMfma, st);
 #define FX_MFMA_NT(T, F32, NT)                                                                                        \

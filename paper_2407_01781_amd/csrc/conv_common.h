@@ -142,11 +142,11 @@ enum WeightMode { kWeightsForward = 0, kWeightsTransposed = 1, kWeightsFlipped =
 // elem_bytes 2 or 4; a row of the packed array covers 64 bytes of input channels (32 or 16 of them)
 // and the produced channels are padded with zeros to a multiple of 64.  Returns the bytes packed.
 size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes);
-// What the matrix-unit kernels need to sum a column block again pair by pair (sum_pairs_again): the packing launch leaves it
-// behind the counters, so that the kernels carry one pointer.
+// What the tile kernel needs to sum a column block again pair by pair (sum_pairs_again): the packing launch leaves it
+// behind the counters, so that the kernel carries one pointer.
 struct PairArgs {
-    const TileHeader* hdr; const uint16_t* perm; const int32_t* rows; const uint16_t* blocks; const uint16_t* w;
-    int32_t row_stride, block_stride, mode, K3;
+    const TileHeader* hdr; const uint16_t* perm; const int32_t* rows; const uint16_t* blocks;
+    int32_t row_stride, block_stride;
 };
 constexpr int kMaxLongTiles = 32, kConvWorkInts = 64, kPairArgsAt = 44;
 static_assert(9 + kMaxLongTiles + 1 <= kPairArgsAt && kPairArgsAt * 4 + sizeof(PairArgs) <= kConvWorkInts * 4 && kPairArgsAt % 2 == 0,

@@ -420,3 +420,38 @@ def test_non_finite_weights_of_partial_chunks_stay_with_their_pairs(kernel, stri
         assert np.array_equal(np.isnan(a), np.isnan(ref)) and np.array_equal(np.where(np.isinf(ref), ref, 0), np.where(np.isinf(a), a, 0))
         assert 0 < (~ok).sum() < ok.size // 2
         H.conv_tolerance_check(np.where(ok, a, 0), np.where(ok, ref, 0), dtype, kernel ** 3, c)
+
+
+@pytest.mark.parametrize("kernel,stride,c_in,c_out", [(3, 1, 48, 48), (3, 1, 24, 40), (2, 2, 48, 48), (2, 2, 72, 160), (3, 2, 48, 48)])
+@pytest.mark.parametrize("where", ["values", "weights"])
+def test_non_finite_throughout_partial_chunks(kernel, stride, c_in, c_out, where):
+    # an overflow step: every sum is NaN and every block is made again pair by pair.  Forward and input gradient give NaN in
+    # every row that has a pair and zero in the others, and take a small multiple of the time on finite values (4 to 7
+    # times on sparse maps; with one lane per channel it was 150 times and more).
+    rng = np.random.default_rng(612)
+    pts = np.unique(rng.integers(-60, 60, size=(60000, 3)).astype(np.int32), axis=0)
+    g = fx.build_index_grid(torch.from_numpy(pts).cuda(), np.array([[0, pts.shape[0]]]))
+    km = fx.build_kernel_map(g, kernel, stride)
+    bad = torch.full((1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    w = torch.randn(kernel ** 3, c_in, c_out, device="cuda").bfloat16()
+    x, gy = torch.randn(g.num_voxels, c_in, device="cuda").bfloat16(), torch.randn(km.n_out, c_out, device="cuda").bfloat16()
+    x2, gy2, w2 = (x, gy, bad.expand_as(w).contiguous()) if where == "weights" else (bad.expand_as(x).contiguous(), bad.expand_as(gy).contiguous(), w)
+    table = km.dense()
+    has_out, has_in = (table >= 0).any(1), torch.zeros(g.num_voxels, dtype=torch.bool, device="cuda")
+    has_in[table[table >= 0].long()] = True
+    for run, has in ((lambda a, b, ww: fx.sparse_conv_fwd(km, a, ww), has_out), (lambda a, b, ww: fx.sparse_conv_bwd_data(km, b, ww), has_in)):
+        y = run(x2, gy2, w2)
+        assert torch.isnan(y[has]).all() and (y[~has] == 0).all()
+
+        def fastest(*args):
+            run(*args)
+            times = []
+            for _ in range(5):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                run(*args)
+                e[1].record()
+                torch.cuda.synchronize()
+                times.append(e[0].elapsed_time(e[1]))
+            return min(times)
+        assert fastest(x2, gy2, w2) < 30 * fastest(x, gy, w)
