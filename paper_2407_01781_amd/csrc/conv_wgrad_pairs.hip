@@ -200,14 +200,22 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     load_ids();
     load_row(); load_ids();
     spread_rows(); load_row(); load_ids(); load_rows();
+    // What one lane writes to LDS others read, and no barrier stands between: a wave's LDS accesses are processed in order, and
+    // the compiler is told to keep that order.
+    auto wave_lds_sync = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+    };
     // block j goes to LDS; rows of j + 1, row numbers of j + 2 and ids of j + 3 are requested; block j is multiplied
     while (hasd) {                       // every block of the list has the offset for some voxel
         to_lds();
+        wave_lds_sync();
         spread_rows();
         load_row();
         load_ids();
         load_rows();
         multiply();
+        wave_lds_sync();                 // read before the next block takes its place
     }
 
     // ---- the two waves of an offset meet: the second half of the range's blocks is added to the first
