@@ -250,7 +250,8 @@ void fx_kmap_destroy(fx_kmap* km);
  *     FX_F32) when the map is tiled (K^3 <= 27), C_in * sizeof(element) is a multiple of 64 bytes (32 channels of
  *     a 16-bit type, 16 of fp32) and C_out is even (padded to 32 or 64 with zero weights); for FX_F16 / FX_BF16 also any
  *     C_in > 16 that is a multiple of 8 with 16-byte aligned feat and 4-byte aligned out (padded with zeros inside; not
- *     in fx_sparse_conv_fwd_noalloc);
+ *     in fx_sparse_conv_fwd_noalloc; not for few products on 1x1x1 and, at C_in = 24, K = stride maps, which the scalar
+ *     kernel sums faster);
  *   - FX_F32 with C_in a multiple of 16 and 16-byte aligned feat and w, where those tiles are few (fewer than half the
  *     compute units), rows are not shared (K = stride, strided maps) or C_out is small: one wave per 16 voxels on
  *     v_mfma_f32_16x16x4_f32, true fp32 products as well; few tiles of any other fp32 shape: the scalar kernel;
@@ -315,9 +316,9 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * map an input is shared by up to 8 outputs and the sum is gathered per input through the inverse map
  * (a tiled map of its own, built on the first such call and kept with km; no atomics, fixed order).
  * MFMA paths: FX_F16 / FX_BF16 on tiled maps (bwd_data: as the forward pass with the channel counts exchanged, on a
- * K = stride map from 16 x 16 channels on with C_out % 8 == 0, C_in even and the same alignments; bwd_weight: C_in % 8 == 0 and
- * C_out % 8 == 0); the kernels at up to 16
- * contracted channels (bwd_data: C_out; bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as
+ * K = stride map with whole chunks and slices (C_out % 32 == 0, C_in % 64 == 0), or from 16 x 16 channels and 8 million
+ * multiplications (20 million where the weights do not fit LDS) on with C_out % 8 == 0, C_in even and the same alignments;
+ * bwd_weight: C_in % 8 == 0 and C_out % 8 == 0); the kernels at up to 16 contracted channels (bwd_data: C_out; bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as
  * the forward pass; everything else takes scalar kernels.  Non-finite values: where C_in % 32 == 0 and
  * C_out % 64 == 0 the MFMA weight-gradient kernels multiply a missing pair as zeros, so an infinite or NaN value of gout
  * makes its column of gw NaN for every offset that one of the 32 voxels of its column block has, and a tile whose input rows do
@@ -347,7 +348,8 @@ fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_feat, const
  *        (symmetric map: the forward kernels over the mirrored offsets) and 3x3x3 stride 2 (gathered per
  *        input through the inverse map, built on first use).  Types, accumulation and
  *        rounding as fx_sparse_conv_fwd; MFMA path for K = stride: FX_F16 / FX_BF16, C_in % 32 == 0 and
- *        C_out % 64 == 0, or C_in % 8 == 0, C_out even, C_in * C_out >= 256, feat 16-byte and out 4-byte aligned.
+ *        C_out % 64 == 0, or, from 20 million multiplications on, C_in % 8 == 0, C_out even, C_in * C_out >= 256, feat
+ *        16-byte and out 4-byte aligned.
  *   fx_pool2       km must be a (2,2) map.  out[o,c] = max (FX_POOL_MAX) or mean (FX_POOL_AVG) over the
  *                  ACTIVE children i = map(o,kappa) of feat[i,c]; the mean is the fp32 sum in offset
  *                  order divided by the number of active children (not by 8), rounded once to dt.

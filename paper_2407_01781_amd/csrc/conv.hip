@@ -1701,6 +1701,18 @@ static bool conv_tiles_shape_ok(const fx_kmap* km, fx_dtype in_dt, int C_in, int
     return km->n_tiles > 0 && ((int64_t)C_in * esize) % kRowBytes == 0 && C_out % 2 == 0;
 }
 
+// Partial chunks for which the scalar kernel is the faster one: few offsets make its chains short, and it needs no packing
+// launch.  bf16, scalar / matrix units in us.  K = 1, whose tiles are one multiply each: 24 -> 24 94 k voxels 11 / 15, 268 k
+// 15 / 31, 980 k 40 / 50; 24 -> 32 500 k 30 / 34, 980 k 51 / 47; 40 -> 24 500 k 34 / 42, 980 k 59 / 60; but 120 -> 8 268 k
+// 66 / 46, 24 -> 64 94 k 19 / 15; 48 -> 48 31 k 13 / 15, 96 k 21 / 15; 40 -> 40 160 k 22 / 23, 500 k 51 / 44; 200 -> 24 12 k
+// 16 / 18, 31 k 21 / 18; 24 -> 200 3.9 k 12 / 15, 12 k 25 / 15.  (2,2) map, forward, up to 24 channels in (a chain of 192
+// products): 24 -> 24 3.9 k voxels 13 / 15, 67 k 15 / 15, 95 k 18 / 15; 24 -> 8 317 k 14 / 15.
+static bool scalar_pays(const fx_kmap* km, int C_in, int C_out) {
+    const int64_t products = km->n_in * C_in * C_out, M = 1000 * 1000;         // per offset
+    if (km->K3 == 1) return products <= (C_in * C_out <= 1200 && C_in <= 72 ? 600 : C_out <= 48 ? 90 : 30) * M;
+    return km->K == km->stride && km->K3 * C_in <= 192 && products <= (C_out <= 8 ? 64 : 36) * M;
+}
+
 fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, const void* d_w, int32_t C_in,
                          int32_t C_out, void* d_out, fx_dtype out_dt, hipStream_t st, int mode) {
     const bool out_f32 = (out_dt == FX_F32);
@@ -1765,7 +1777,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
     // scalar kernel, 221 k LiDAR voxels, bf16, forward / input gradient in us: 48 -> 48 778 / 2209 -> 52 / 52, 24 -> 40
     // 353 / 632 -> 46 / 43, (2,2) map 48 -> 48 108 -> 20, (3,2) map 48 -> 48 279 / 904 -> 42 / 38.
     const bool pieces = in_dt != FX_F32 && km->n_tiles > 0 && C_in > 16 && C_in % 8 == 0 && C_out % 2 == 0 &&
-                        ((uintptr_t)d_feat & 15) == 0 && ((uintptr_t)d_out & 3) == 0;
+                        ((uintptr_t)d_feat & 15) == 0 && ((uintptr_t)d_out & 3) == 0 && !scalar_pays(km, C_in, C_out);
     const bool mfma = (conv_tiles_shape_ok(km, in_dt, C_in, C_out) || pieces) &&
                       (in_dt != FX_F32 || n_items >= compute_units() / 2 || option(kOptFp32Tiles) == 1) &&   // fp32_tiles = 1: at any size
                       !force_scalar;

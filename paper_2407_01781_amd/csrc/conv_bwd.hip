@@ -483,10 +483,18 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
     // Whole chunks and slices, or rows of whole 16-byte pieces at addresses that are multiples of them and an even number of
     // produced channels, padded with zeros: every stored row is one pair's product, so padding reaches no result.  Against the
     // scalar kernels, (2,2) map of 221 k LiDAR voxels, bf16, input gradient / transposed convolution in us: 64 -> 32 844 / 193
-    // -> 20 / 21, 128 -> 96 8890 / 1071 -> 38 / 38, 48 -> 48 969 / 300 -> 21 / 21, 40 -> 24 255 / 127 -> 19 / 20.  (Below 16 x 16
-    // channels the scalar kernels' work is small and they need no packing launch.)
+    // -> 20 / 21, 128 -> 96 8890 / 1071 -> 38 / 38, 48 -> 48 969 / 300 -> 21 / 21, 40 -> 24 255 / 127 -> 19 / 20.
+    // Below 16 x 16 channels, and of few products at any, the scalar kernels, which need no packing launch, are the faster ones.  Scalar / matrix units in us, input
+    // gradient (whose weights the scalar kernel reads across the lanes): 24 -> 24 3.9 k voxels 11 / 15, 12 k 14 / 16; 40 -> 24
+    // 12 k 18 / 16; transposed: 24 -> 24 12 k 11 / 16, 31 k 13 / 16; 24 -> 32 31 k 16 / 16; and where the weights do not fit
+    // LDS either way: contracting 200 channels 1.4 k voxels 21 / 42, 3.9 k 38 / 41 and 24 / 42.
+    const int nslice = (C_produce + kCoutSlice - 1) / kCoutSlice, nchunk = (C_contract + kCinChunk - 1) / kCinChunk;
+    const size_t lds = (size_t)km->K3 * nchunk * 4096 + (size_t)kDgradLdsWaves * km->K3 * kGroup * sizeof(int32_t);
+    const bool lds_weights = lds <= 160 * 1024 && nchunk <= kDgradMaxChunks && km->K3 <= 27 && option(kOptGatherLds) != 0;
+    const int64_t products = km->n_in * C_contract * C_produce;
     const bool pieces = C_contract % 8 == 0 && C_produce % 2 == 0 && C_contract * C_produce >= 256 &&
-                        ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0;
+                        ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0 &&
+                        products > ((mode & kWeightsTransposed) && lds_weights ? 8 : 20) * 1000 * 1000;
     const bool mfma = dt != FX_F32 && km->n_tiles > 0 && ((C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0) || pieces) &&
                       option(kOptForceScalar) != 1;
     if (mfma) {
@@ -494,9 +502,6 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
         const size_t wbytes = packed_weight_bytes(km->K3, C_contract, C_produce, 2);
         FX_TRY(dev_alloc(&wp, wbytes + 8 * sizeof(int32_t), st));
         int32_t* counters = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(wp) + wbytes);
-        const int nslice = (C_produce + kCoutSlice - 1) / kCoutSlice, nchunk = (C_contract + kCinChunk - 1) / kCinChunk;
-        const size_t lds = (size_t)km->K3 * nchunk * 4096 + (size_t)kDgradLdsWaves * km->K3 * kGroup * sizeof(int32_t);
-        const bool lds_weights = lds <= 160 * 1024 && nchunk <= kDgradMaxChunks && km->K3 <= 27 && option(kOptGatherLds) != 0;
         launch_pack_weights(d_w, wp, km->K3, C_contract, C_produce, 2, counters, mode, st);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess && lds_weights) {

@@ -90,3 +90,30 @@ def test_full_size_mixed_grid_every_row():
     y = out.float().cpu().numpy()
     assert np.isfinite(y).all()
     H.conv_tolerance_check(y, O.conv(og, og, 3, 1, feat, wt, threads=H.ORACLE_THREADS), "bf16", 27, 64)
+
+
+@pytest.mark.parametrize("op,kernel,stride,c_in,c_out,line", [
+    ("fwd", 1, 1, 24, 200, 6250), ("bwd_data", 1, 1, 200, 24, 6250), ("fwd", 2, 2, 24, 200, 7500), ("bwd_data", 2, 2, 40, 40, 5000),
+    ("bwd_data", 2, 2, 24, 200, 4166), ("transposed", 2, 2, 40, 40, 12500)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_partial_chunks_of_few_products_take_the_scalar_kernel(op, kernel, stride, c_in, c_out, line, past):
+    # one offset a voxel, or one pair an input: up to a number of products the scalar kernel, which packs no weights, is the
+    # faster one; both sides of the line against the oracle
+    rng = np.random.default_rng(71)
+    pts = np.unique(rng.integers(-20, 20, size=(3 * line, 3)).astype(np.int32), axis=0)
+    pts = pts[rng.permutation(pts.shape[0])[:line + past]]
+    g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
+    assert og.num_voxels == line + past
+    km, ogo = fx.build_kernel_map(g, kernel, stride), O.output_grid(og, kernel, stride)
+    feat, wt = G.features_and_weights(72, og.num_voxels, c_in, c_out, kernel ** 3, "bf16")
+    gy = G.round_to_dtype(np.random.default_rng(73).standard_normal((ogo.num_voxels, c_out)).astype(np.float32), "bf16")
+    wt_t = np.ascontiguousarray(wt.transpose(0, 2, 1))
+    dev = lambda a: H.to_device_storage(a, "bf16")
+    run, ref, contracted = {
+        "fwd": (lambda: fx.sparse_conv_fwd(km, dev(feat), dev(wt)), lambda: O.conv(og, ogo, kernel, stride, feat, wt), c_in),
+        "bwd_data": (lambda: fx.sparse_conv_bwd_data(km, dev(gy), dev(wt)), lambda: O.conv_bwd_data(og, ogo, kernel, stride, gy, wt), c_out),
+        "transposed": (lambda: fx.sparse_conv_transpose_fwd(km, dev(gy), dev(wt_t)), lambda: O.conv_transpose(og, ogo, kernel, stride, gy, wt_t), c_out),
+    }[op]
+    y, slots = _kernels_of(run)
+    assert ("k_pack_weights" in slots) == bool(past)
+    H.conv_tolerance_check(y.float().cpu().numpy(), ref(), "bf16", kernel ** 3, contracted)
