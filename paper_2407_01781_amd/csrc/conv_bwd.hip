@@ -405,6 +405,39 @@ __global__ void k_wgrad_reduce(const float* __restrict__ part, int n_ranges, int
     }
 }
 
+// The same for many ranges of a small tensor: eight waves of a workgroup take an eighth of the ranges each, for the same 64 x 4
+// elements, and meet in LDS in that order.  With one thread for all ranges of an element the chip had half a wave per
+// compute unit, each a chain of 24 loads.  (2,2) map of 95 k LiDAR voxels, bf16, the whole call: 24 -> 8 20.9 -> 15.6 us,
+// 64 -> 64 25.8 -> 21.9; with two launches, of 980 k voxels, 55 -> 50.  `total` is a multiple of 4.
+constexpr int kReduceWaves = 8;
+template <int OUT_DT>
+__global__ void __launch_bounds__(64 * kReduceWaves) k_wgrad_reduce_waves(const float* __restrict__ part, int n_ranges, int64_t total, void* __restrict__ gw) {
+    __shared__ f32x4 sums[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t q = (int64_t)blockIdx.x * 64 + lane;
+    const bool in = 4 * q < total;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int r = n_ranges * wave / kReduceWaves;
+    const int end = in ? n_ranges * (wave + 1) / kReduceWaves : r;
+    for (; r < end; r += 8) {                 // eight loads in flight, added in ascending order
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(part + (int64_t)min(r + u, end - 1) * total + 4 * q);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (r + u < end) s += v[u];
+    }
+    sums[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || !in) return;
+    for (int w = 1; w < kReduceWaves; ++w) s += sums[w][lane];
+    if (OUT_DT == FX_F32) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(gw) + 4 * q) = s;
+    else {
+        typedef typename std::conditional<OUT_DT == FX_F16, _Float16, __bf16>::type T;
+        *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(gw) + 4 * q) = u32x2{Elem<T>::pack2(s[0], s[1]), Elem<T>::pack2(s[2], s[3])};
+    }
+}
+
 // Scalar weight gradient: one thread per element of gw and per range of outputs, fp32 FMA in
 // output order; the ranges are added by k_wgrad_reduce.
 template <int DT>
@@ -700,7 +733,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     hipError_t e = hipSuccess;
     int n_ranges = 1;
     // Strided maps, whose tiles share no rows: a wave per offset that walks the map's blocks alone (k_wgrad_pairs, with the
-    // figures of both; the tile kernel was slower on every map and channel count tried).
+    // figures of both: the tile kernel is faster by 3 to 7 us at a few sizes only).
     if (mfma && km->stride == 2) {
         n_ranges = wgrad_pairs_ranges(km, C_in, C_out, 0);
         FX_TRY(dev_alloc((void**)&part, sizeof(float) * (size_t)total * n_ranges, st));
@@ -757,7 +790,16 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         e = hipGetLastError();
     }
     fx_status rc_red = FX_OK;
-    if (e == hipSuccess) rc_red = wgrad_reduce_ranges(part, n_ranges + (mfma ? leaf_ranges : 0), total, d_gw, out_dt, st);
+    // the strided maps' ranges are many and short; below 24 of them one thread's chain is as fast, and tensors of more than
+    // 128 k elements fill the chip with one thread each
+    if (e == hipSuccess && mfma && km->stride == 2 && n_ranges >= 24 && total <= 128 * 1024) {
+        ProfScope ps(kProfWgradReduce, st);
+        const unsigned nb = (unsigned)((total / 4 + 63) / 64);
+        if (out_dt == FX_F32) k_wgrad_reduce_waves<FX_F32><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
+        else if (out_dt == FX_F16) k_wgrad_reduce_waves<FX_F16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
+        else k_wgrad_reduce_waves<FX_BF16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
+        e = hipGetLastError();
+    } else if (e == hipSuccess) rc_red = wgrad_reduce_ranges(part, n_ranges + (mfma ? leaf_ranges : 0), total, d_gw, out_dt, st);
     dev_free(part, st);
     if (e != hipSuccess) { set_error("weight-gradient launch failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
     return rc_red;

@@ -1,4 +1,5 @@
-// Weight gradient of strided maps on the matrix units: kernel and launch.
+// Weight gradient on the matrix units where a tile's rows are not staged: strided maps, which share none, and listed tiles
+// of submanifold maps.  Kernel and launch.
 #include "conv_common.h"
 
 namespace fx {
@@ -20,29 +21,32 @@ namespace fx {
 // over existing pairs only, whatever the values are.  Eight waves with two blocks in flight each are 3 us faster on
 // maps of a few thousand outputs and as fast at K = 2, but 17 % slower at K = 3.
 //
-// LISTED: the same over a list of tiles of a submanifold map, those whose rows the tile kernel cannot stage (tile_list,
-// n_tiles entries; such a tile may have a window).  Against a workgroup per column block of such a tile
+// LISTED: the same over a list of tiles of a submanifold map, those whose rows the tile kernel cannot stage (tile_list;
+// such a tile may have a window).  Against a workgroup per column block of such a tile
 // in the tile kernel's other form, the whole call, bf16: 221 k LiDAR voxels with five such tiles 64 -> 64 79 -> 69 us,
 // 256 -> 256 536 -> 498; 195 k voxels of sheets with four 256 -> 256 581 -> 546; 980 k LiDAR voxels with three 181 -> 178.
 //
 // A workgroup takes eight consecutive offsets of a range; the jobs of one range (channel blocks and, at K = 3, four
 // octets of offsets) are placed on one XCD (workgroup b runs on XCD b % 8) so that they share its L2.
-// 987 k-voxel LiDAR grid, bf16, reduction included, k_wgrad_mfma -> here: (2,2) map 64 -> 64 89 -> 58 us, 64 -> 128
-// 152 -> 89, 128 -> 256 728 -> 276; (3,2) map 32 -> 64 116 -> 106, 64 -> 128 348 -> 200; (2,2) map of 4.7 k outputs,
-// 64 -> 128, 25 -> 22.
+// bf16, reduction included, k_wgrad_mfma -> here, in us: 980 k LiDAR voxels, (2,2) map 64 -> 64 89 -> 50, 64 -> 128 150 -> 85,
+// 128 -> 256 728 -> 276; (3,2) map 64 -> 64 165 -> 104, 64 -> 128 329 -> 197, 24 -> 8 95 -> 102, which is the chain of a block
+// whatever the channels are; 95 k LiDAR voxels (24 k outputs), (2,2) map 64 -> 64 21.5 -> 22, 24 -> 8 18 -> 16; 31 k (7.8 k outputs)
+// 64 -> 64 18 -> 18, 64 -> 128 19 -> 22, (3,2) map 36 -> 24; 4.7 k outputs of sheets, (2,2) map 64 -> 128 25 -> 19.
+// Small maps are a launch, the chain and the end: with the sums of both halves stored by one of them, a division of 64-bit
+// block numbers and a few spilled registers a map of 62 outputs took 12.8 us here instead of 8.8.
 constexpr int kPairsOffsets = 8;                               // offsets of a workgroup
 constexpr int kPairsWaves = 2 * kPairsOffsets;               // two halves of a range
 constexpr int kPairsBlk = 64;                                  // channels of a block, both sides
 constexpr int kPairsRowBytes = kPairsBlk * 2;
 constexpr int kPairsLdsBytes = kGroup * kPairsRowBytes;        // one side's rows of a column block
 constexpr int kPairsLdsTotal = kPairsWaves * 2 * kPairsLdsBytes;
-static_assert(kPairsLdsTotal <= 160 * 1024 && 4 * kPairsLdsBytes == kPairsBlk * kPairsBlk * 4, "LDS budget; two waves' rows hold one wave's sums");
+static_assert(kPairsLdsTotal <= 160 * 1024 && 4 * kPairsLdsBytes == kPairsBlk * kPairsBlk * 4, "LDS budget; a wave's rows hold half of its sums");
 
 template <typename T, bool LISTED>
 __global__ void __launch_bounds__(64 * kPairsWaves)
 k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
               const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
-              int block_stride, int64_t n_tiles, int n_ranges, const uint16_t* __restrict__ feat,
+              int block_stride, int64_t per_half, int extra, int n_ranges, const uint16_t* __restrict__ feat,
               const uint16_t* __restrict__ gout, int C_in, int C_out, int K3, float* __restrict__ part,
               const int32_t* __restrict__ tile_list) {
     typedef typename Elem<T>::vec8 vec8;
@@ -59,9 +63,10 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     const int oct = wave % kPairsOffsets, half = wave / kPairsOffsets;
     const int kappa = uni(job % n_kg * kPairsOffsets + oct);
     const int ci0 = job / n_kg % n_cib * kPairsBlk, co0 = job / n_kg / n_cib * kPairsBlk;
-    const int64_t n_groups = n_tiles * kGroupsPerTile;
-    const int64_t g_lo = n_groups * (2 * range + half) / (2 * n_ranges);
-    const int64_t g_hi = kappa < K3 ? n_groups * (2 * range + half + 1) / (2 * n_ranges) : g_lo;
+    // the wave's share of the column blocks: per_half, and one more for the first `extra` halves
+    const int nth = 2 * range + half;
+    const int64_t g_lo = nth * per_half + min(nth, extra);
+    const int64_t g_hi = kappa < K3 ? g_lo + per_half + (nth < extra) : g_lo;
     unsigned char* lx = lds_raw + (oct * 2 + half) * 2 * kPairsLdsBytes;
 
     // ---- the column blocks of the range that have the offset, in order
@@ -97,7 +102,8 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     };
 
     // ---- the stages of a column block
-    // the lane number made anew where it is needed: the registers of four waves per SIMD are all taken
+    // the lane number made anew where it is needed: the registers of four waves per SIMD are all taken, and one spilled to
+    // memory is loaded in order with the rows in flight
     auto lane_now = [&]() __attribute__((always_inline)) -> uint32_t {
         uint32_t l;
         asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
@@ -159,7 +165,7 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
     // voxel v's row: 16-byte piece p at position p ^ 4 * ((v >> 1) & 1), which spreads a transposing read over all banks
     unsigned char* st = lx + p8 * kPairsRowBytes + ((piece ^ (((p8 >> 1) & 1) << 2)) << 4);
     auto to_lds = [&]() __attribute__((always_inline)) {
-        const uint32_t mine = hasd >> p8;
+        const uint32_t mine = hasd >> (lane_now() >> 3);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool on = (mine >> (8 * i)) & 1u;
@@ -218,38 +224,29 @@ k_wgrad_pairs(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restric
         wave_lds_sync();                 // read before the next block takes its place
     }
 
-    // ---- the two waves of an offset meet: the second half of the range's blocks is added to the first
+    // ---- the two waves of an offset meet: each keeps the sums of 32 input channels and hands the others over
+    const int ln = (int)lane_now();
+    f32x4* mine = reinterpret_cast<f32x4*>(lx) + ln;
+    const f32x4* theirs = reinterpret_cast<const f32x4*>(lds_raw + (oct * 2 + 1 - half) * 2 * kPairsLdsBytes) + ln;
+    auto quad = [&](int a, int c, int b) { return f32x4{acc[a][c][4 * b], acc[a][c][4 * b + 1], acc[a][c][4 * b + 2], acc[a][c][4 * b + 3]}; };
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) mine[(c * 4 + b) * 64] = half ? quad(0, c, b) : quad(1, c, b);
     __syncthreads();
-    f32x4* sum = reinterpret_cast<f32x4*>(lds_raw + oct * 4 * kPairsLdsBytes) + lane;
-    if (half == 1) {
+    if (kappa >= K3) return;
+    // lane (co = n, h), register v -> ci = 8 * (v / 4) + 4 * h + v % 4: a half-wave stores 128 bytes of one row at a time
+    const int ci = ci0 + 32 * half + 4 * (ln >> 5), co = co0 + (ln & 31);
+    float* dst = part + (((int64_t)range * K3 + kappa) * C_in + ci) * (int64_t)C_out + co;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+        for (int b = 0; b < 4; ++b) {
+            const f32x4 sum = (half ? quad(1, c, b) : quad(0, c, b)) + theirs[(c * 4 + b) * 64];
+            if (ci + 8 * b < C_in && co + 32 * c < C_out)       // C_in is a multiple of 8
 #pragma unroll
-                for (int v = 0; v < 16; v += 4)
-                    sum[((a * 2 + c) * 4 + v / 4) * 64] = f32x4{acc[a][c][v], acc[a][c][v + 1], acc[a][c][v + 2], acc[a][c][v + 3]};
-    }
-    __syncthreads();
-    if (half == 1 || kappa >= K3) return;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][c][v] += sum[((a * 2 + c) * 4 + v / 4) * 64][v % 4];
-
-    // ---- partial sums of this range: lane (co = n, h), register v -> ci = 8 * (v / 4) + 4 * h + v % 4
-    float* dst = part + ((int64_t)range * K3 + kappa) * C_in * (int64_t)C_out;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int ci = ci0 + 32 * a + 8 * (v >> 2) + 4 * h + (v & 3), co = co0 + 32 * c + (lane & 31);
-                if (ci < C_in && co < C_out) dst[(int64_t)ci * C_out + co] = acc[a][c][v];
-            }
+                for (int e = 0; e < 4; ++e) dst[(8 * b + e) * (int64_t)C_out + 32 * c] = sum[e];
+        }
 }
 
 static int pairs_jobs(const fx_kmap* km, int C_in, int C_out) {
@@ -257,17 +254,19 @@ static int pairs_jobs(const fx_kmap* km, int C_in, int C_out) {
 }
 
 int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out, int n_listed) {
-    // one workgroup per compute unit; no range shorter than four column blocks, or, of a list, whose blocks are few and
-    // whose latency is what counts, than two and at most sixteen ranges
+    // one workgroup per compute unit; no range shorter than four column blocks (with two or three more partial sums than
+    // that saves, 7.8 k outputs 64 -> 128 26 and 23 us for 22; with eight 21, but 1.2 k outputs 64 -> 64 19 for 15), or, of a
+    // list, whose blocks are few and whose latency is what counts, than two and at most sixteen ranges
     const int most = compute_units() / pairs_jobs(km, C_in, C_out);
     if (n_listed) return std::max(1, std::min(most, std::min(16, n_listed * (kGroupsPerTile / 2))));
-    const int n = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles * (kGroupsPerTile / 4), most));
+    const int n = (int)std::max<int64_t>(1, std::min<int64_t>((km->n_out + 4 * kGroup - 1) / (4 * kGroup), most));
     return n > 8 ? n - n % 8 : n;        // see the block-to-XCD mapping in the kernel
 }
 
 hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, float* part,
                               int n_ranges, int n_listed, hipStream_t st) {
     const unsigned grid = (unsigned)(pairs_jobs(km, C_in, C_out) * n_ranges);
+    const int64_t n_groups = (n_listed ? n_listed : km->n_tiles) * (int64_t)kGroupsPerTile, n_halves = 2 * (int64_t)n_ranges;
     hipError_t e = hipSuccess;
 #define FX_PAIRS(T, LISTED)                                                                                            \
     do {                                                                                                               \
@@ -275,7 +274,7 @@ hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void*
         if (e == hipSuccess)                                                                                           \
             k_wgrad_pairs<T, LISTED><<<grid, 64 * kPairsWaves, kPairsLdsTotal, st>>>(                                  \
                 km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->row_stride, km->d_tile_blocks, km->block_stride, \
-                LISTED ? n_listed : km->n_tiles, n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, \
+                n_groups / n_halves, (int)(n_groups % n_halves), n_ranges, (const uint16_t*)d_feat, (const uint16_t*)d_gout, C_in, C_out, \
                 km->K3, part, km->d_unstaged_list);                                                                    \
     } while (0)
     if (dt == FX_BF16) { if (n_listed) FX_PAIRS(__bf16, true); else FX_PAIRS(__bf16, false); }

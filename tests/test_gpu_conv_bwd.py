@@ -455,3 +455,24 @@ def test_non_finite_throughout_partial_chunks(kernel, stride, c_in, c_out, where
                 times.append(e[0].elapsed_time(e[1]))
             return min(times)
         assert fastest(x2, gy2, w2) < 30 * fastest(x, gy, w)
+
+
+@pytest.mark.parametrize("n_out", [100, 3000, 5200, 9300, 33000])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 24, 40), ("f16", 64, 64), ("bf16", 24, 8), ("f16", 128, 160)])
+def test_weight_gradient_of_strided_maps_many_ranges(n_out, dtype, c_in, c_out):
+    # 16 to 256 ranges of column blocks (an eighth of them is 2 to 32, more and fewer than the eight loads of a step), the sums
+    # of few and of many elements; the 16-bit result is the fp32 one rounded once
+    rng = np.random.default_rng(660 + n_out)
+    side = int(round(1.3 * n_out ** (1 / 3))) + 2
+    pts = np.unique(rng.integers(-side, side, size=(n_out, 3)).astype(np.int32), axis=0) * 2
+    g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
+    km, ogc = fx.build_kernel_map(g, 2, 2), og.coarsen2()
+    feat, _ = G.features_and_weights(31, og.num_voxels, c_in, c_out, 8, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(32).standard_normal((ogc.num_voxels, c_out)).astype(np.float32), dtype)
+    d_x, d_gy = H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype)
+    gw = H.nan_filled((8, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32, out=gw)
+    _wgrad_check(gw.cpu().numpy(), O.conv_bwd_weight(og, ogc, 2, 2, feat, gy), 2e-3)
+    low = H.nan_filled((8, c_in, c_out), H.TORCH_DT[dtype])
+    fx.sparse_conv_bwd_weight(km, d_x, d_gy, out=low)
+    assert torch.equal(low.view(torch.int16), gw.to(H.TORCH_DT[dtype]).view(torch.int16))
