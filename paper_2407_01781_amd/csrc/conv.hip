@@ -21,6 +21,18 @@
 
 namespace fx {
 
+// Whether the tile kernel starts with the items of long tiles, whose rows are gathered from global memory (k_conv_mfma): there
+// are more items than workgroups, and the lower half of the last XCD's workgroups has static items (those of the workgroups
+// that start with long tiles are claimed like the others).  However many items a workgroup takes, a long one claimed last ends
+// the launch alone; where none is claimed late, starting with them costs a percent.  bf16, in the order of the list -> long
+// tiles first, us: 269 k LiDAR voxels 256 -> 256 (8.2 items a workgroup) 516 -> 446; 988 k with a solid block among the last
+// tiles 64 -> 64 (7.5) 152 -> 126, 128 -> 128 (15) 422 -> 384, 96 -> 192 (23) 480 -> 449; the block among the first 125 -> 127,
+// 378 -> 386, 442 -> 448; no block 123.5 -> 124.5, 374 -> 376, 437 -> 437; 1.18 M voxels of indoor scenes 148 -> 147.
+__host__ __device__ inline bool long_tiles_first(int64_t n_work, int wgs) {
+    const int64_t per_xcd = (n_work + 7) / 8;
+    return per_xcd > (wgs >> 3) && 7 * per_xcd + (wgs >> 3) / 2 < n_work;
+}
+
 // ---------------------------------------------------------------------------------- weight packing
 // Wp[kappa][cin chunk][cout slice][ntile 0..1][kstep 0..1][lane 0..63][8]: the 16-byte B-operand
 // fragment of each lane for one (offset, 32 input channels, 64 output channels): lane (n, kq) holds
@@ -31,26 +43,28 @@ namespace fx {
 // channels and column n is channel n of it.
 template <typename E>   // uint16_t or uint32_t: the bits of one element
 __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out,
-                               int32_t* __restrict__ counters, int mode, int n_nt, const TileHeader* __restrict__ tile_hdr, int64_t n_tiles, PairArgs again) {
+                               int32_t* __restrict__ counters, int mode, int n_nt, const uint8_t* __restrict__ tile_long, int64_t n_tiles, PairArgs again) {
     if (blockIdx.x == 0 && threadIdx.x < 8) counters[threadIdx.x] = 0;   // the convolution's work-list counters
     if (again.hdr && blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<PairArgs*>(counters + kPairArgsAt) = again;
-    if (tile_hdr && blockIdx.x == gridDim.x - 1) {
-        // a workgroup of its own lists the tiles whose rows are not all staged in LDS, in no particular order (their number,
-        // then the first kMaxLongTiles of them): the tile kernel starts with those
+    if (tile_long && blockIdx.x == gridDim.x - 1) {
+        // a workgroup of its own lists the long tiles, in no particular order (their number, then the first kMaxLongTiles of
+        // them): the tile kernel starts with those
         __shared__ int32_t found;
         if (threadIdx.x == 0) found = 0;
         __syncthreads();
-        for (int64_t t0 = threadIdx.x; t0 < n_tiles; t0 += 8 * blockDim.x) {       // eight headers in flight
-            int32_t flags[8];
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(tile_long);                // four tiles each; the last one's rest is zero
+        const int64_t n_words = (n_tiles + 3) / 4;
+        for (int64_t w0 = threadIdx.x; w0 < n_words; w0 += 4 * blockDim.x) {       // four words in flight
+            uint32_t is_long[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) flags[u] = tile_hdr[min(t0 + u * (int)blockDim.x, n_tiles - 1)].flags;
+            for (int u = 0; u < 4; ++u) is_long[u] = words[min(w0 + u * (int)blockDim.x, n_words - 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t t = t0 + u * (int)blockDim.x;
-                if (t < n_tiles && !(flags[u] & kTileLdsOffsets)) {
-                    const int at = atomicAdd(&found, 1);
-                    if (at < kMaxLongTiles) counters[9 + at] = (int32_t)t;
-                }
+            for (int u = 0; u < 4; ++u) {
+                const int64_t w = w0 + u * (int)blockDim.x;
+                uint32_t m = w < n_words ? is_long[u] : 0u;                        // a byte is 0 or 1
+                if (!m) continue;
+                int at = atomicAdd(&found, __popc(m));
+                for (; m && at < kMaxLongTiles; m &= m - 1) counters[9 + at++] = (int32_t)(4 * w) + (__ffs(m) - 1) / 8;
             }
         }
         __syncthreads();
@@ -63,7 +77,7 @@ __global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int 
     const uint32_t cols = 32 * n_nt;                                     // channels of a slice
     const uint32_t nchunk = (C_in + kChunk - 1) / kChunk, nslice = (C_out + cols - 1) / cols;
     const uint32_t total = (uint32_t)K3 * nchunk * nslice * n_nt * 128;  // fragments
-    const uint32_t stride = (gridDim.x - (tile_hdr ? 1 : 0)) * blockDim.x;
+    const uint32_t stride = (gridDim.x - (tile_long ? 1 : 0)) * blockDim.x;
     for (uint32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < total; f += stride) {
         const uint32_t lane = f & 63, ks = (f >> 6) & 1;
         uint32_t r = f >> 7;
@@ -94,16 +108,16 @@ size_t packed_weight_bytes(int K3, int C_in, int C_out, int elem_bytes) {
 }
 
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
-                         int mode, hipStream_t st, const TileHeader* tile_hdr, int64_t n_tiles, int n_nt, const PairArgs& again) {
+                         int mode, hipStream_t st, const uint8_t* tile_long, int64_t n_tiles, int n_nt, const PairArgs& again) {
     const int64_t total = (int64_t)(packed_weight_bytes(K3, C_in, C_out, elem_bytes) / 16);
     // small weights in workgroups of one wave, so that every compute unit has one
-    const unsigned bs = tile_hdr || total > 65536 ? 256u : 64u;
-    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + bs - 1) / bs, 4096)) + (tile_hdr ? 1 : 0);
+    const unsigned bs = tile_long || total > 65536 ? 256u : 64u;
+    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + bs - 1) / bs, 4096)) + (tile_long ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, bs, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
+        k_pack_weights<uint16_t><<<nb, bs, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_long, n_tiles, again);
     else
-        k_pack_weights<uint32_t><<<nb, bs, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_hdr, n_tiles, again);
+        k_pack_weights<uint32_t><<<nb, bs, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_long, n_tiles, again);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
@@ -604,15 +618,6 @@ __device__ __forceinline__ int announce(MetaSlot& M, int64_t work, int nslice, c
     }
     if (lane == 0) M.work = work;
     return __builtin_amdgcn_readlane(v, offsetof(TileHeader, flags) / 4);
-}
-
-// Whether the tile kernel starts with the long tiles: with one item a workgroup there is nothing to reorder, with more than
-// seven the claims even a long one out and the list costs the packing launch a microsecond.  The last condition: the lower
-// half of the last XCD's workgroups has static items.
-__host__ __device__ inline bool long_tiles_first(int64_t n_work, int grid) {
-    const int64_t per_xcd = (n_work + 7) / 8;
-    const int wg_per_xcd = grid >> 3;
-    return per_xcd > wg_per_xcd && per_xcd <= 7 * wg_per_xcd && 7 * per_xcd + wg_per_xcd / 2 < n_work;
 }
 
 // workgroups of the tile kernel: one per compute unit, a multiple of 8 (one share per XCD), no more than the work needs
@@ -1668,7 +1673,7 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     if (partial && !gather) pairs = {km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows, km->d_tile_blocks, km->row_stride, km->block_stride};
     const int64_t n_work = km->n_tiles * (int64_t)(narrow ? (C_out + 31) / 32 : (C_out + 63) / 64);
     const bool list = !gather && long_tiles_first(n_work, mfma_grid(n_work));
-    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, list ? km->d_tile_hdr : nullptr, km->n_tiles,
+    launch_pack_weights(d_w, wp, km->K3, C_in, C_out, esize, counters, mode, st, list ? km->d_tile_long : nullptr, km->n_tiles,
                         narrow ? 1 : 2, pairs);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gather) {

@@ -135,8 +135,9 @@ enum WeightMode { kWeightsForward = 0, kWeightsTransposed = 1, kWeightsFlipped =
 // the 32 lanes of a half-wave store one whole row slice.
 
 // Packs the weights (C_in = contracted channels, C_out = produced channels, in the sense of the
-// mode) and zeroes the eight work-list counters behind them.  With tile_hdr it also lists the tiles whose rows are not all
-// staged in LDS: their number goes to counters[8], the first kMaxLongTiles of them behind it (kConvWorkInts in all).
+// mode) and zeroes the eight work-list counters behind them.  With tile_long it also lists the long tiles (whose rows
+// are not all staged in LDS): their number goes to counters[8], the first kMaxLongTiles of them behind it (kConvWorkInts in
+// all).
 // n_nt = 1: slices of 32 produced channels, column m of the one n-tile = channel m.  `again` goes to counters[kPairArgsAt]
 // if it is set.  Contracted channels are padded with zeros to whole 64-byte chunks.
 // elem_bytes 2 or 4; a row of the packed array covers 64 bytes of input channels (32 or 16 of them)
@@ -152,7 +153,7 @@ constexpr int kMaxLongTiles = 32, kConvWorkInts = 64, kPairArgsAt = 44;
 static_assert(9 + kMaxLongTiles + 1 <= kPairArgsAt && kPairArgsAt * 4 + sizeof(PairArgs) <= kConvWorkInts * 4 && kPairArgsAt % 2 == 0,
               "counters, count, list, one more counter, pair arguments");
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
-                         int mode, hipStream_t st, const TileHeader* tile_hdr = nullptr, int64_t n_tiles = 0, int n_nt = 2,
+                         int mode, hipStream_t st, const uint8_t* tile_long = nullptr, int64_t n_tiles = 0, int n_nt = 2,
                          const PairArgs& again = PairArgs{});
 
 // The forward multiply-accumulate over a map with the weights read in the given mode: d_out[o,:]

@@ -98,6 +98,7 @@ struct fx_kmap {
     // tiled form
     int64_t n_tiles = 0;
     fx::TileHeader* d_tile_hdr = nullptr;   // [n_tiles]
+    uint8_t* d_tile_long = nullptr;         // [n_tiles, rounded up to 4 with zeros] 1: the tile's rows are not all staged (no kTileLdsOffsets)
     uint16_t* d_tile_perm = nullptr;        // [n_tiles][kTileT] output slot -> local output (0..T-1)
     int32_t* d_tile_rows = nullptr;         // [n_tiles][row_stride] global input rows (halo / direct)
     uint16_t* d_tile_blocks = nullptr;      // [n_tiles][block_stride][16][8] local row ids (id blocks)

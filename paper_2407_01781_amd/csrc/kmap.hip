@@ -433,7 +433,7 @@ template <int K, bool SUBM, bool INV = false, bool DEDUP = SUBM>
 __global__ void __launch_bounds__(kPackThreads, 8)
 k_build_tiles(TreeView tin, TreeView tout, int stride, const int32_t* __restrict__ leaf_nbr,
               const int32_t* __restrict__ tile_first_leaf, int64_t n_out, TileHeader* __restrict__ tile_hdr,
-              uint16_t* __restrict__ tile_perm, int32_t* __restrict__ tile_rows, int row_stride,
+              uint8_t* __restrict__ tile_long, uint16_t* __restrict__ tile_perm, int32_t* __restrict__ tile_rows, int row_stride,
               uint16_t* __restrict__ tile_blocks, int block_stride, int dense_min) {
     constexpr int K3 = K * K * K;
     static_assert(K3 <= kMaxK3Tiled, "tiled path supports up to 27 offsets");
@@ -766,6 +766,9 @@ k_build_tiles(TreeView tin, TreeView tout, int stride, const int32_t* __restrict
         H->n_blocks = run; H->n_out = n_valid;
         H->flags = (direct ? kTileDirect : (lds_codes ? kTileLdsOffsets : 0)) | (L.any_left_out ? kTilePartial : 0);
         H->n_pair_blocks = L.n_pair_blocks; H->pad = 0;
+        tile_long[tile] = !lds_codes;
+        if (tile + 1 == (int64_t)gridDim.x)          // the rest of the last four
+            for (int64_t t = tile + 1; t & 3; ++t) tile_long[t] = 0;
     }
 
     // ---- id blocks.  Entry [voxel column][wave slot] of block (convolution wave, offset) belongs to this thread
@@ -1019,12 +1022,13 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
     km->row_stride = kTileT * km->K3;
     km->block_stride = kTileWaves * km->K3;
 
-    // one allocation: stats | tile headers | perm | rows | blocks
+    // one allocation: stats | tile headers | long tiles | perm | rows | blocks
     const size_t nt = (size_t)std::max<int64_t>(km->n_tiles, 1);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t o_st = take(sizeof(int64_t) * (size_t)(4 + km->K3));
     const size_t o_th = take(sizeof(TileHeader) * nt);
+    const size_t o_tl = take((nt + 3) / 4 * 4);
     const size_t o_tp = take(sizeof(uint16_t) * kTileT * nt);
     const size_t o_tr = take(tiled ? sizeof(int32_t) * (size_t)km->row_stride * nt : 0);
     const size_t o_tb = take(tiled ? sizeof(uint16_t) * kIdBlockElems * (size_t)km->block_stride * nt : 0);
@@ -1041,6 +1045,7 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
     char* p = (char*)km->d_alloc;
     km->d_stats = (int64_t*)(p + o_st);
     km->d_tile_hdr = (TileHeader*)(p + o_th);
+    km->d_tile_long = (uint8_t*)(p + o_tl);
     km->d_tile_perm = (uint16_t*)(p + o_tp);
     km->d_tile_rows = (int32_t*)(p + o_tr);
     km->d_tile_blocks = (uint16_t*)(p + o_tb);
@@ -1073,7 +1078,7 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
         if (e == hipSuccess)                                                                                   \
             k_build_tiles<KV, SUBMV><<<ntl, kPackThreads, lds, st>>>(tin, tout, stride, d_leaf_nbr, d_tile_first, \
                                                                      km->n_out,                                \
-                                                                     km->d_tile_hdr, km->d_tile_perm,          \
+                                                                     km->d_tile_hdr, km->d_tile_long, km->d_tile_perm, \
                                                                      km->d_tile_rows, km->row_stride,          \
                                                                      km->d_tile_blocks, km->block_stride,      \
                                                                      dense_min);                               \
