@@ -318,12 +318,14 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * MFMA paths: FX_F16 / FX_BF16 on tiled maps (bwd_data: as the forward pass with the channel counts exchanged, on a
  * K = stride map with whole chunks and slices (C_out % 32 == 0, C_in % 64 == 0), or from 16 x 16 channels and 8 million
  * multiplications (20 million where the weights do not fit LDS) on with C_out % 8 == 0, C_in even and the same alignments;
- * bwd_weight: C_in % 8 == 0 and C_out % 8 == 0); the kernels at up to 16 contracted channels (bwd_data: C_out; bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as
- * the forward pass; everything else takes scalar kernels.  Non-finite values: where C_in % 32 == 0 and
- * C_out % 64 == 0 the MFMA weight-gradient kernels multiply a missing pair as zeros, so an infinite or NaN value of gout
- * makes its column of gw NaN for every offset that one of the 32 voxels of its column block has, and a tile whose input rows do
- * not all fit the kernel's local memory has its operand transposed by a multiplication with the identity, so that such a
- * value in feat makes the whole 32-channel block of gw that it touches NaN rather than only its own row.  All other
+ * bwd_weight: C_in % 8 == 0 and C_out % 8 == 0); the kernels at up to 16 contracted channels (bwd_data: C_out;
+ * bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as the forward pass; everything else takes
+ * scalar kernels.  Non-finite values: where C_in % 32 == 0 and C_out % 64 == 0 the tile kernel of the weight gradient
+ * multiplies a missing pair as zeros, so an infinite or NaN value of gout makes its column of gw NaN for every offset that one
+ * of the 32 voxels of its column block has, and a tile whose input rows do not all fit the kernel's local memory has its
+ * operand transposed by a multiplication with the identity (on dense grids, between two grids, and on sparse maps with more than
+ * 16 such tiles; 16 or fewer are summed over existing pairs), so that such a value in feat makes the whole 32-channel block of
+ * gw that it touches NaN rather than only its own row.  All other
  * shapes, and all on strided maps, sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
  * the leaf-window kernels: at those shapes a locally dense grid (mean leaf occupancy >= 0.40) is summed leaf by
  * leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a grid that mixes dense and sparse leaves is split per

@@ -344,7 +344,7 @@ __device__ __noinline__ void sum_pairs_again_call(const PairArgs* args, const ui
 // ---------------------------------------------------------------------------------- MFMA kernel
 constexpr int kMetaSlots = 3;
 
-// A work item (tile x 64-channel output slice) as the workgroup sees it: its number in the work
+// A work item (tile x slice of 32 NT output channels) as the workgroup sees it: its number in the work
 // list (-1: the list is exhausted) and a copy of the tile header.
 struct MetaSlot {
     int64_t work;
@@ -628,8 +628,8 @@ static int mfma_grid(int64_t n_work) {
 __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs(mask) - 1 : 0; }
 
 // Consumer side of one work item: multiply all chunks (one barrier after each, matching the
-// producers' barriers), then write the tile's outputs back (lane (n, h) holds channels
-// slice*64 + 32h .. +31 of output slot g*32 + n).  `phase` counts chunks since kernel start and
+// producers' barriers), then write the tile's outputs back (register v of lane (n, h) holds channels
+// slice * 32 NT + NT n .. + NT - 1 of output slot 32 g + 8 (v / 4) + 4 h + v % 4).  `phase` counts chunks since kernel start and
 // selects the LDS half; `mb` selects the half that holds this tile's id blocks.
 // The weight pipeline (wa, wb and their tags) runs across chunks and, in the LDS-only variant,
 // across items: the last steps of an item already fetch the first weights of the next one (MN
@@ -1657,8 +1657,10 @@ static fx_status conv_tiles_with_scratch(const fx_kmap* km, const void* d_feat, 
     void* wp = scratch;
     const size_t wbytes = packed_weight_bytes(km->K3, C_in, C_out, esize);
     int32_t* counters = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(wp) + wbytes);
-    // maps whose tiles list one row per pair (strided; stride 1 back from a larger grid): the gather kernel;
-    // others: the LDS-staged kernel
+    // maps whose tiles list one row per pair (strided; stride 1 back from a larger grid): the gather kernel, also where it
+    // pads the last slice; others: the LDS-staged kernel.  bf16, the LDS-staged kernel / the gather kernel, us: 980 k LiDAR
+    // voxels, (2,2) map 32 -> 32 92 / 31, 64 -> 96 186 / 48, (3,2) map 32 -> 32 145 / 55, 64 -> 96 360 / 168; the input gradient
+    // of the map onto the padded grid 32 <- 64 1650 / 816, 96 <- 64 2610 / 1426; 3.9 k voxels, (2,2) map 32 -> 32 25 / 16
     const int fg = option(kOptConvGather);          // 0 / 1: the LDS-staged / the gather kernel on every map
     const bool gather = (fg >= 0 ? fg == 1 : !map_shares_rows(km)) && in_dt != FX_F32;
     // A work item of the tile kernel is a tile and 64 output channels, or 32 (half the multiplies, the same reads of features) where
@@ -1757,9 +1759,9 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
                               st, mode);
     }
     const int esize = in_dt == FX_F32 ? 4 : 2;
-    // The tile kernel takes input rows in 64-byte chunks (32 channels of a 16-bit type, 16 of fp32) and
-    // pads the produced channels to 64 with zero weights; the gather kernel for strided maps needs whole
-    // 64-channel slices of a 16-bit type.  Everything else is left to the scalar kernel.
+    // The matrix-unit kernels take input rows in 64-byte chunks (32 channels of a 16-bit type, 16 of fp32; of a 16-bit type
+    // also whole 16-byte pieces, see `pieces` below) and pad an even number of produced channels to whole slices with zero
+    // weights: of 64, or 32 in the tile kernel.  Everything else is left to the low-depth and scalar kernels.
     const int64_t n_items = km->n_tiles * (int64_t)((C_out + kCoutSlice - 1) / kCoutSlice);
     // fp32 by independent waves where the tile kernel fills the chip badly (few tiles), stages rows that are used about
     // once, or pads most of its 64 channels.  Measured, waves / tiles in us: 96 items (48.8 k voxels of sheets, 64 -> 64)

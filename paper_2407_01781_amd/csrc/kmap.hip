@@ -97,15 +97,14 @@ __device__ __forceinline__ int lookup_entry(const NbLeafLds& lds, int oi, int oj
 template <int K, bool INV>
 __device__ __forceinline__ void leaf_neighbors_item(const TreeView& tin, const TreeView& tout, int stride, int64_t n_out,
                                                     int64_t e, int32_t* __restrict__ nbr, int32_t* __restrict__ tile_first_leaf,
-                                                    int dense_min, int32_t* __restrict__ dense_leaves, int32_t* __restrict__ n_dense) {
+                                                    int dense_min, uint8_t* __restrict__ leaf_dense) {
     constexpr int D0 = delta_min(K);
     const int f = (int)(e / 27), slot = (int)(e - (int64_t)f * 27);
     const fx_leaf* lf = tout.leaf + f;
     if (slot == 0) {
         const int64_t begin = lf->offset, end = f + 1 < tout.n_leaf ? tout.leaf[f + 1].offset : n_out;
         for (int64_t t = (begin + kTileT - 1) / kTileT; t * kTileT < end; ++t) tile_first_leaf[t] = f;
-        // per-leaf dispatch: the locally dense leaves are listed for the leaf-window kernel
-        if (dense_min > 0 && (int)(end - begin) >= dense_min) dense_leaves[atomicAdd(n_dense, 1)] = f;
+        if (dense_min > 0) leaf_dense[f] = (int)(end - begin) >= dense_min;      // per-leaf dispatch: see k_list_dense_leaves
     }
     const int oi = lf->origin[0], oj = lf->origin[1], ok = lf->origin[2];
     const int bi = INV ? ((oi - 1) >> 1) >> 3 : (stride * oi + D0) >> 3, bj = INV ? ((oj - 1) >> 1) >> 3 : (stride * oj + D0) >> 3,
@@ -122,11 +121,42 @@ __device__ __forceinline__ void leaf_neighbors_item(const TreeView& tin, const T
 
 template <int K, bool INV = false>
 __global__ void k_leaf_neighbors(TreeView tin, TreeView tout, int stride, int64_t n_out, int32_t* __restrict__ nbr,
-                                 int32_t* __restrict__ tile_first_leaf, int dense_min, int32_t* __restrict__ dense_leaves,
-                                 int32_t* __restrict__ n_dense) {
+                                 int32_t* __restrict__ tile_first_leaf, int dense_min, uint8_t* __restrict__ leaf_dense) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (int64_t)tout.n_leaf * 27) return;
-    leaf_neighbors_item<K, INV>(tin, tout, stride, n_out, e, nbr, tile_first_leaf, dense_min, dense_leaves, n_dense);
+    leaf_neighbors_item<K, INV>(tin, tout, stride, n_out, e, nbr, tile_first_leaf, dense_min, leaf_dense);
+}
+
+// One workgroup: the locally dense leaves, listed for the leaf-window kernel in ascending order, so that the sums it splits
+// over the list are the same for every map of a grid.  32 leaves a thread and step; bytes past n_leaf are not looked at.
+__global__ void __launch_bounds__(1024) k_list_dense_leaves(const uint8_t* __restrict__ leaf_dense, int n_leaf, int32_t* __restrict__ list,
+                                                            int32_t* __restrict__ n_dense) {
+    __shared__ uint32_t wave_count[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t base = 0;
+    for (int f0 = 0; f0 < n_leaf; f0 += 32 * 1024) {
+        const int f = f0 + 32 * tid;
+        uint32_t m = 0;                                    // bit u: leaf f + u is dense
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t four = f + 4 * u < n_leaf ? reinterpret_cast<const uint32_t*>(leaf_dense)[f / 4 + u] : 0u;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) m |= f + 4 * u + b < n_leaf ? ((four >> (8 * b)) & 1u) << (4 * u + b) : 0u;
+        }
+        uint32_t upto = (uint32_t)__popc(m);               // of this and the lanes before
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t before = (uint32_t)__shfl_up((int)upto, d);
+            if (lane >= d) upto += before;
+        }
+        if (lane == 63) wave_count[wave] = upto;
+        __syncthreads();
+        uint32_t at = base + upto - (uint32_t)__popc(m);
+        for (int w = 0; w < 16; ++w) { const uint32_t c = wave_count[w]; base += c; if (w < wave) at += c; }
+        for (; m; m &= m - 1) list[at++] = f + __ffs(m) - 1;
+        __syncthreads();
+    }
+    if (tid == 0) *n_dense = (int32_t)base;
 }
 
 // The table of the map that is expected next, launched by the grid build before the host knows the counts of the
@@ -140,7 +170,7 @@ __global__ void k_leaf_links(TreeView tin, TreeView tout, int self, int stride, 
     if (self) tin = tout;
     const int64_t n = (int64_t)tout.n_leaf * 27;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        leaf_neighbors_item<K, false>(tin, tout, stride, hdr->n_voxels, e, nbr, tile_first_leaf, 0, nullptr, nullptr);
+        leaf_neighbors_item<K, false>(tin, tout, stride, hdr->n_voxels, e, nbr, tile_first_leaf, 0, nullptr);
 }
 
 // stage_leaf with the neighbour leaves read from the table
@@ -1040,6 +1070,7 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
     const size_t o_ln = take(tiled && !links ? sizeof(int32_t) * 27 * (size_t)std::max(gout->hdr.n_leaf, 1) : 0);
     const size_t o_tf = take(tiled && !links ? sizeof(int32_t) * (nt + 1) : 0);
     const size_t o_dl = take(dense_min > 0 ? sizeof(int32_t) * ((size_t)std::max(gout->hdr.n_leaf, 1) + 1) : 0);
+    const size_t o_df = take(dense_min > 0 ? ((size_t)std::max(gout->hdr.n_leaf, 1) + 3) / 4 * 4 : 0);
     fx_status rc = dev_alloc(&km->d_alloc, off, st);
     if (rc != FX_OK) { fx_kmap_destroy(km); return rc; }
     char* p = (char*)km->d_alloc;
@@ -1053,10 +1084,10 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
     int32_t* d_tile_first = links ? gout->d_tile_first_leaf : (int32_t*)(p + o_tf);
     int32_t* d_n_dense = dense_min > 0 ? (int32_t*)(p + o_dl) : nullptr;        // the count, then the list
     int32_t* d_dense = dense_min > 0 ? d_n_dense + 1 : nullptr;
+    uint8_t* d_leaf_dense = (uint8_t*)(p + o_df);
     km->d_n_dense = d_n_dense; km->d_dense_leaves = d_dense;
 
     hipError_t e = hipSuccess;
-    if (d_n_dense) { k_fill_i32<<<1, 64, 0, st>>>(d_n_dense, 1, 0); e = hipGetLastError(); }
     if (e == hipSuccess && km->n_tiles > 0) {
         const size_t lds = sizeof(PackLds);
         const unsigned ntl = (unsigned)km->n_tiles;
@@ -1065,10 +1096,11 @@ fx_status fx::build_map(fx_grid* g_in, fx_grid* gout, int K, int stride, bool in
             ProfScope ps(kProfLeafNeighbors, st);
             const int64_t ne = (int64_t)gout->hdr.n_leaf * 27;
             const unsigned nbk = (unsigned)((ne + 255) / 256);
-            if (K == 1) k_leaf_neighbors<1><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_dense, d_n_dense);
-            else if (K == 2) k_leaf_neighbors<2><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_dense, d_n_dense);
-            else if (inverse) k_leaf_neighbors<3, true><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_dense, d_n_dense);
-            else k_leaf_neighbors<3><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_dense, d_n_dense);
+            if (K == 1) k_leaf_neighbors<1><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_leaf_dense);
+            else if (K == 2) k_leaf_neighbors<2><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_leaf_dense);
+            else if (inverse) k_leaf_neighbors<3, true><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_leaf_dense);
+            else k_leaf_neighbors<3><<<nbk, 256, 0, st>>>(tin, tout, stride, km->n_out, d_leaf_nbr, d_tile_first, dense_min, d_leaf_dense);
+            if (dense_min > 0) k_list_dense_leaves<<<1, 1024, 0, st>>>(d_leaf_dense, gout->hdr.n_leaf, d_dense, d_n_dense);
         }
         ProfScope ps(kProfBuildTiles, st);
 #define FX_TILES(KV, SUBMV...)                                                                                 \

@@ -117,3 +117,32 @@ def test_partial_chunks_of_few_products_take_the_scalar_kernel(op, kernel, strid
     y, slots = _kernels_of(run)
     assert ("k_pack_weights" in slots) == bool(past)
     H.conv_tolerance_check(y.float().cpu().numpy(), ref(), "bf16", kernel ** 3, contracted)
+
+
+@pytest.mark.parametrize("corner", [-4000, 3000])
+def test_list_of_dense_leaves_is_the_same_for_every_map(corner):
+    # 48 k leaves of one voxel and 512 full ones at either end of the leaf order (the list is made in steps of 32 k leaves):
+    # forward and weight gradient against the scalar kernel, and the same bits from every map of the grid
+    rng = np.random.default_rng(81)
+    cells = np.unique(rng.integers(-150, 150, size=(48500, 3)), axis=0) * 16 + 5
+    a = [np.arange(n, dtype=np.int64) + corner for n in (64, 64, 64)]
+    pts = np.concatenate([cells, np.stack(np.meshgrid(*a, indexing="ij"), axis=-1).reshape(-1, 3)]).astype(np.int32)
+    g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
+    cnt = np.diff(np.append(g.leaf_table()["offset"], g.num_voxels))
+    assert cnt.size > 32768 and (cnt >= 205).sum() >= 512
+    feat, wt = G.features_and_weights(82, og.num_voxels, 64, 64, 27, "bf16")
+    gy = G.round_to_dtype(np.random.default_rng(83).standard_normal((og.num_voxels, 64)).astype(np.float32), "bf16")
+    d_x, d_w, d_gy = (H.to_device_storage(v, "bf16") for v in (feat, wt, gy))
+    first = None
+    for _ in range(6):
+        km = fx.build_kernel_map(g, 3, 1)
+        gw, slots = _kernels_of(lambda: fx.sparse_conv_bwd_weight(km, d_x, d_gy, out_dtype=torch.float32))
+        first = gw if first is None else first
+        assert torch.equal(gw.view(torch.int32), first.view(torch.int32))
+    y, slots = _kernels_of(lambda: fx.sparse_conv_fwd(km, d_x, d_w))
+    assert "k_conv_leaf" in slots and "k_conv_mfma" in slots
+    for s in (0, og.num_voxels // 2, og.num_voxels - 400):
+        H.conv_tolerance_check(y[s:s + 400].float().cpu().numpy(), O.conv(og, og, 3, 1, feat, wt, s, s + 400)[s:s + 400], "bf16", 27, 64)
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    num = np.sqrt(((first.cpu().numpy().astype(np.float64) - ref) ** 2).sum(axis=(1, 2)))
+    assert (num / np.maximum(np.sqrt((ref ** 2).sum(axis=(1, 2))), 1e-3 * 64)).max() <= 2e-3
