@@ -26,10 +26,10 @@ namespace fx {
 // the B operand is W[kappa]^T in the packed fragment order (interleaved channels).  After the chunks
 // of one offset the accumulators hold gin rows of the 32 inputs map(o, kappa), the rows along the
 // registers and the channels across the lanes: a half-wave stores one row's 64-channel slice in one
-// piece, and the accumulators start again from zero.
+// piece, and the accumulators start again from zero.  WHOLE: whole chunks contracted and whole slices produced.
 constexpr int kDgradWaves = 4;
 
-template <typename T, bool OUT_F32>
+template <typename T, bool OUT_F32, bool WHOLE>
 __global__ void __launch_bounds__(64 * kDgradWaves)
 k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict__ tile_perm,
                 const int32_t* __restrict__ tile_rows, int row_stride, const uint16_t* __restrict__ tile_blocks,
@@ -86,9 +86,16 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
             for (int v = 0; v < 16; ++v) acc[mt][v] = 0.f;
         for (int c = 0; c < nchunk; ++c) {
             vec8 b[2] = {zero, zero}, wf[4];
-            const int at = c * kCinChunk + h * 8;             // a row that ends inside its last chunk: zeros beyond
-            if (valid && at < C_contract) b[0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
-            if (valid && at + 16 < C_contract) b[1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
+            if (WHOLE) {
+                if (valid) {
+                    b[0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
+                    b[1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
+                }
+            } else {
+                const int at = c * kCinChunk + h * 8;         // a row that ends inside its last chunk: zeros beyond
+                if (valid && at < C_contract) b[0] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk);
+                if (valid && at + 16 < C_contract) b[1] = *reinterpret_cast<const vec8*>(grow + c * kCinChunk + 16);
+            }
             const vec8* ws = wl + ((c * nslice + slice) * 4) * 64 + kappa * w_kappa_stride;
 #pragma unroll
             for (int f = 0; f < 4; ++f) wf[f] = ws[f * 64];
@@ -106,7 +113,7 @@ k_dgrad_strided(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restr
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int32_t r = r4[j];
-                if (r < 0 || col >= C_produce) continue;
+                if (r < 0 || (!WHOLE && col >= C_produce)) continue;
                 if (OUT_F32)
                     *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(gin) + (int64_t)r * C_produce + col) =
                         f32x2{acc[0][4 * q + j], acc[1][4 * q + j]};
@@ -528,8 +535,8 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
     const bool pieces = C_contract % 8 == 0 && C_produce % 2 == 0 && C_contract * C_produce >= 256 &&
                         ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0 &&
                         products > ((mode & kWeightsTransposed) && lds_weights ? 8 : 20) * 1000 * 1000;
-    const bool mfma = dt != FX_F32 && km->n_tiles > 0 && ((C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0) || pieces) &&
-                      option(kOptForceScalar) != 1;
+    const bool whole = C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0;
+    const bool mfma = dt != FX_F32 && km->n_tiles > 0 && (whole || pieces) && option(kOptForceScalar) != 1;
     if (mfma) {
         void* wp = nullptr;
         const size_t wbytes = packed_weight_bytes(km->K3, C_contract, C_produce, 2);
@@ -552,7 +559,7 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
                 n_blocks_total, km->K3, (const uint16_t*)d_src, (const uint16_t*)wp, C_contract, C_produce, d_dst);    \
     } while (0)
 #define FX_DGRAD_R(T, F32, R)                                                                                         \
-    do { if (C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0) FX_DGRAD_W(T, F32, R, true); else FX_DGRAD_W(T, F32, R, false); } while (0)
+    do { if (whole) FX_DGRAD_W(T, F32, R, true); else FX_DGRAD_W(T, F32, R, false); } while (0)
 #define FX_DGRAD(T, F32)                                                                                              \
     do { if (km->K3 <= 8) FX_DGRAD_R(T, F32, 4); else FX_DGRAD_R(T, F32, 14); } while (0)
             if (dt == FX_BF16) { if (out_f32) FX_DGRAD(__bf16, true); else FX_DGRAD(__bf16, false); }
@@ -565,14 +572,16 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
             const int64_t n_items = km->n_tiles * (int64_t)kGroupsPerTile * nslice;
             const unsigned grid = (unsigned)((n_items + kDgradWaves - 1) / kDgradWaves);
             ProfScope ps(kProfDgradStrided, st);
-#define FX_DGRAD(T, F32)                                                                                             \
-    k_dgrad_strided<T, F32><<<grid, 64 * kDgradWaves, 0, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,      \
+#define FX_DGRAD_W(T, F32, WHOLE)                                                                                    \
+    k_dgrad_strided<T, F32, WHOLE><<<grid, 64 * kDgradWaves, 0, st>>>(km->d_tile_hdr, km->d_tile_perm, km->d_tile_rows,      \
                                                                km->row_stride, km->d_tile_blocks, km->block_stride,  \
                                                                n_items, (const uint16_t*)d_src, (const uint16_t*)wp, \
                                                                C_contract, C_produce, d_dst)
+#define FX_DGRAD(T, F32) do { if (whole) FX_DGRAD_W(T, F32, true); else FX_DGRAD_W(T, F32, false); } while (0)
             if (dt == FX_BF16) { if (out_f32) FX_DGRAD(__bf16, true); else FX_DGRAD(__bf16, false); }
             else { if (out_f32) FX_DGRAD(_Float16, true); else FX_DGRAD(_Float16, false); }
 #undef FX_DGRAD
+#undef FX_DGRAD_W
             e = hipGetLastError();
         }
         dev_free(wp, st);
