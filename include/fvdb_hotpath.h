@@ -316,8 +316,8 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * map an input is shared by up to 8 outputs and the sum is gathered per input through the inverse map
  * (a tiled map of its own, built on the first such call and kept with km; no atomics, fixed order).
  * MFMA paths: FX_F16 / FX_BF16 on tiled maps (bwd_data: as the forward pass with the channel counts exchanged, on a
- * K = stride map with whole chunks and slices (C_out % 32 == 0, C_in % 64 == 0), or from 16 x 16 channels and 8 million
- * multiplications (20 million where the weights do not fit LDS) on with C_out % 8 == 0, C_in even and the same alignments;
+ * K = stride map with whole chunks and slices (C_out % 32 == 0, C_in % 64 == 0), or with C_out % 8 == 0, C_in even and the same
+ * alignments from 16 x 16 channels on, unless the products are few: some ten to twenty million over the slots of the map;
  * bwd_weight: C_in % 8 == 0 and C_out % 8 == 0); the kernels at up to 16 contracted channels (bwd_data: C_out;
  * bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as the forward pass; everything else takes
  * scalar kernels.  Non-finite values: where C_in % 32 == 0 and C_out % 64 == 0 the tile kernel of the weight gradient
@@ -350,8 +350,8 @@ fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_feat, const
  *        (symmetric map: the forward kernels over the mirrored offsets) and 3x3x3 stride 2 (gathered per
  *        input through the inverse map, built on first use).  Types, accumulation and
  *        rounding as fx_sparse_conv_fwd; MFMA path for K = stride: FX_F16 / FX_BF16, C_in % 32 == 0 and
- *        C_out % 64 == 0, or, from 20 million multiplications on, C_in % 8 == 0, C_out even, C_in * C_out >= 256, feat
- *        16-byte and out 4-byte aligned.
+ *        C_out % 64 == 0, or C_in % 8 == 0, C_out even, C_in * C_out >= 256, feat 16-byte and out 4-byte aligned and
+ *        more than 58 million products over the slots of the map (190 where the weights do not fit LDS).
  *   fx_pool2       km must be a (2,2) map.  out[o,c] = max (FX_POOL_MAX) or mean (FX_POOL_AVG) over the
  *                  ACTIVE children i = map(o,kappa) of feat[i,c]; the mean is the fp32 sum in offset
  *                  order divided by the number of active children (not by 8), rounded once to dt.

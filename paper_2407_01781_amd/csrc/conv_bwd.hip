@@ -524,17 +524,22 @@ fx_status strided_pair_product(const fx_kmap* km, const void* d_src, fx_dtype dt
     // produced channels, padded with zeros: every stored row is one pair's product, so padding reaches no result.  Against the
     // scalar kernels, (2,2) map of 221 k LiDAR voxels, bf16, input gradient / transposed convolution in us: 64 -> 32 844 / 193
     // -> 20 / 21, 128 -> 96 8890 / 1071 -> 38 / 38, 48 -> 48 969 / 300 -> 21 / 21, 40 -> 24 255 / 127 -> 19 / 20.
-    // Below 16 x 16 channels, and of few products at any, the scalar kernels, which need no packing launch, are the faster ones.  Scalar / matrix units in us, input
-    // gradient (whose weights the scalar kernel reads across the lanes): 24 -> 24 3.9 k voxels 11 / 15, 12 k 14 / 16; 40 -> 24
-    // 12 k 18 / 16; transposed: 24 -> 24 12 k 11 / 16, 31 k 13 / 16; 24 -> 32 31 k 16 / 16; and where the weights do not fit
-    // LDS either way: contracting 200 channels 1.4 k voxels 21 / 42, 3.9 k 38 / 41 and 24 / 42.
+    // Below 16 x 16 channels, and of few products at any, the scalar kernels, which need no packing launch, are the faster ones.
+    // They go over all slots of the map, with a child or without, so slots are counted and not inputs.  Scalar / matrix units in
+    // us, with millions of products: transposed, LiDAR-like and sheet grids 24 -> 24 35 M 13 / 16, 92 M 27 / 16, 16 -> 16 44 M
+    // 16 / 16, a sphere's shell 48 -> 48 55 M 15 / 17, 96 -> 96 57 M 15 / 18, 72 -> 40 69 M 20 / 18, solid bodies 48 -> 48 41 M 15 / 20,
+    // 128 -> 24 55 M 19 / 26, 24 -> 24 71 M 25 / 18, and where the weights do not fit LDS 136 -> 200 98 M 20 / 41, 167 M 35 / 41;
+    // input gradient (whose weights the scalar kernel reads across the lanes): contracting 16 17 M 20 / 15; 24 10 M 13 / 17, 14 M
+    // 11 / 16, 19 M 14 / 16, 35 M 21 / 16; 40 18 M 17 / 17; 48 14 M 23 / 15; 72 10 M 12 / 16, 18 M 19 / 17; 96 33 M 74 / 16; where
+    // the weights do not fit LDS, in products per input: contracting 200 channels 1.4 k voxels 21 / 42, 3.9 k 38 / 41 and 24 / 42.
     const int nslice = (C_produce + kCoutSlice - 1) / kCoutSlice, nchunk = (C_contract + kCinChunk - 1) / kCinChunk;
     const size_t lds = (size_t)km->K3 * nchunk * 4096 + (size_t)kDgradLdsWaves * km->K3 * kGroup * sizeof(int32_t);
     const bool lds_weights = lds <= 160 * 1024 && nchunk <= kDgradMaxChunks && km->K3 <= 27 && option(kOptGatherLds) != 0;
-    const int64_t products = km->n_in * C_contract * C_produce;
+    const bool dgrad = (mode & kWeightsTransposed) != 0;
+    const int64_t M = 1000 * 1000, products = (dgrad && !lds_weights ? km->n_in : km->n_out * km->K3) * C_contract * C_produce;
+    const bool few = products <= (dgrad ? (!lds_weights ? 20 : C_contract > 16 && C_contract <= 40 ? 20 : 12) : lds_weights ? 58 : 190) * M;
     const bool pieces = C_contract % 8 == 0 && C_produce % 2 == 0 && C_contract * C_produce >= 256 &&
-                        ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0 &&
-                        products > ((mode & kWeightsTransposed) && lds_weights ? 8 : 20) * 1000 * 1000;
+                        ((uintptr_t)d_src & 15) == 0 && ((uintptr_t)d_dst & 3) == 0 && !few;
     const bool whole = C_contract % kCinChunk == 0 && C_produce % kCoutSlice == 0;
     const bool mfma = dt != FX_F32 && km->n_tiles > 0 && (whole || pieces) && option(kOptForceScalar) != 1;
     if (mfma) {

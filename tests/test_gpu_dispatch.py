@@ -123,18 +123,22 @@ def test_split_weight_gradient_with_listed_tiles(dtype, c_in, c_out, corner, swi
 
 
 @pytest.mark.parametrize("op,kernel,stride,c_in,c_out,line", [
-    ("fwd", 1, 1, 24, 200, 6250), ("bwd_data", 1, 1, 200, 24, 6250), ("fwd", 2, 2, 24, 200, 7500), ("bwd_data", 2, 2, 40, 40, 5000),
-    ("bwd_data", 2, 2, 24, 200, 4166), ("transposed", 2, 2, 40, 40, 12500)])
+    ("fwd", 1, 1, 24, 200, 6250), ("bwd_data", 1, 1, 200, 24, 6250), ("fwd", 2, 2, 24, 200, 7500), ("bwd_data", 2, 2, 24, 200, 4166),
+    ("bwd_data of outputs", 2, 2, 40, 40, 1562), ("bwd_data of outputs", 2, 2, 48, 96, 325), ("bwd_data of outputs", 2, 2, 16, 16, 5859),
+    ("transposed of outputs", 2, 2, 40, 40, 4531), ("transposed of outputs", 2, 2, 40, 136, 4365)])
 @pytest.mark.parametrize("past", [0, 1])
 def test_partial_chunks_of_few_products_take_the_scalar_kernel(op, kernel, stride, c_in, c_out, line, past):
     # one offset a voxel, or one pair an input: up to a number of products the scalar kernel, which packs no weights, is the
-    # faster one; both sides of the line against the oracle
+    # faster one; both sides of the line, in inputs or in outputs, against the oracle
     rng = np.random.default_rng(71)
     pts = np.unique(rng.integers(-20, 20, size=(3 * line, 3)).astype(np.int32), axis=0)
     pts = pts[rng.permutation(pts.shape[0])[:line + past]]
+    if op.endswith(" of outputs"):                     # some of the children of every output
+        op, pts = op[:-len(" of outputs")], 2 * pts
+        pts = np.concatenate([pts, pts[::2] + 1, pts[::3] + np.array([0, 1, 0], np.int32)])
     g, og = H.both_grids(pts, np.array([[0, pts.shape[0]]]))
-    assert og.num_voxels == line + past
     km, ogo = fx.build_kernel_map(g, kernel, stride), O.output_grid(og, kernel, stride)
+    assert line + past in (og.num_voxels, ogo.num_voxels)
     feat, wt = G.features_and_weights(72, og.num_voxels, c_in, c_out, kernel ** 3, "bf16")
     gy = G.round_to_dtype(np.random.default_rng(73).standard_normal((ogo.num_voxels, c_out)).astype(np.float32), "bf16")
     wt_t = np.ascontiguousarray(wt.transpose(0, 2, 1))
