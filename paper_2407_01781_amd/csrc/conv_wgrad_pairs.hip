@@ -255,12 +255,20 @@ static int pairs_jobs(const fx_kmap* km, int C_in, int C_out) {
 
 int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out, int n_listed) {
     // one workgroup per compute unit; no range shorter than four column blocks (with two or three more partial sums than
-    // that saves, 7.8 k outputs 64 -> 128 26 and 23 us for 22; with eight 21, but 1.2 k outputs 64 -> 64 19 for 15), or, of a
-    // list, whose blocks are few and whose latency is what counts, than two and at most sixteen ranges
+    // that saves, 7.8 k outputs 64 -> 128 26 and 23 us for 22; with eight 21, but 1.2 k outputs 64 -> 64 19 for 15), or than eight
+    // where there would be more than 16 MB of partial sums, which are written and read once; or, of a list, whose blocks are
+    // few and whose latency is what counts, than two and at most sixteen ranges.  Four -> eight, us: (2,2) map 64 -> 128 and
+    // 128 -> 128 of 8.1 k outputs (17 and 34 MB) 22 -> 20, 27 -> 24, 128 -> 256 of 3 k (25 MB) 25 -> 23, 64 -> 64 of 20 k (20 MB)
+    // 23 -> 21, 64 -> 128 of 20 k (34 MB) 26 -> 25 and 24 -> 25; (3,2) map 64 -> 64 of 8.1 k (28 MB) 25 -> 22; but 128 -> 128 of
+    // 3 k (13 MB) 20.3 -> 21.2, 64 -> 64 of 15 k (16 MB) 21.2 -> 22.2.
     const int most = compute_units() / pairs_jobs(km, C_in, C_out);
     if (n_listed) return std::max(1, std::min(most, std::min(16, n_listed * (kGroupsPerTile / 2))));
-    const int n = (int)std::max<int64_t>(1, std::min<int64_t>((km->n_out + 4 * kGroup - 1) / (4 * kGroup), most));
-    return n > 8 ? n - n % 8 : n;        // see the block-to-XCD mapping in the kernel
+    auto ranges_of = [&](int blocks) {
+        const int n = (int)std::max<int64_t>(1, std::min<int64_t>((km->n_out + blocks * kGroup - 1) / (blocks * kGroup), most));
+        return n > 8 ? std::min((n + 3) / 8, std::max(most / 8, 1)) * 8 : n;        // see the block-to-XCD mapping in the kernel
+    };
+    const int n = ranges_of(4);
+    return (int64_t)n * km->K3 * C_in * C_out * 4 > 16 * 1000 * 1000 ? ranges_of(8) : n;
 }
 
 hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, float* part,
