@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfvdb_hotpath.so")
 SOURCES = ["conv_wgrad_bf16.hip", "conv_wgrad_f16.hip", "conv.hip", "conv_bwd.hip", "conv_leaf.hip", "conv_lowdepth.hip",
-           "grid.hip", "kmap.hip", "conv_wgrad_pairs.hip", "pool.hip", "lib.hip"]      # the ones that take longest first
+           "grid.hip", "kmap.hip", "conv_wgrad_pairs.hip", "conv_wgrad_lists.hip", "pool.hip", "lib.hip"]      # the ones that take longest first
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]

@@ -743,6 +743,8 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     }
     const fx_kmap* kmt = leaf_ranges ? km->mixed : km;      // the map whose tiles are walked
     mfma = mfma && kmt->n_tiles > 0;
+    if (mfma && !leaf_ranges && km->stride == 1 && wgrad_lists_pays(km, dt, C_in, C_out))
+        return wgrad_lists(km, d_feat, d_gout, dt, C_in, C_out, d_gw, out_dt, st);
     float* part = nullptr;
     hipError_t e = hipSuccess;
     int n_ranges = 1;

@@ -208,6 +208,11 @@ int wgrad_pairs_ranges(const fx_kmap* km, int C_in, int C_out, int n_listed);
 hipError_t launch_wgrad_pairs(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, float* part,
                               int n_ranges, int n_listed, hipStream_t st);
 
+// The same of wide layers as a matrix product per offset over the list of its pairs (conv_wgrad_lists.hip), reduction included.
+bool wgrad_lists_pays(const fx_kmap* km, fx_dtype dt, int C_in, int C_out);
+fx_status wgrad_lists(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, void* d_gw, fx_dtype out_dt,
+                      hipStream_t st);
+
 // Weight gradient of the 3x3x3 submanifold convolution from the leaf window (fp32 at low depth; f16 / bf16 at
 // C_in % 32 == 0 and C_out % 64 == 0), and the ordered
 // reduction of per-range partial sums part[n_ranges][total] into gw that all weight-gradient kernels end with
