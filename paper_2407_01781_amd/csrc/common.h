@@ -54,7 +54,7 @@ int compute_units();
 // When enabled (fx_profile_enable), every kernel launch of the library is bracketed by a pair
 // of hipEvents on the launch stream; fx_profile_read sums the elapsed times per slot.
 enum ProfSlot {
-    kProfBucketCount = 0, kProfBucketScan, kProfBucketScatter, kProfBucketLeaves, kProfVoxelsToLeaves, kProfFindTiles, kProfRankTiles, kProfInsertUpper, kProfScanUpper, kProfInsertLower, kProfScanLower,
+    kProfBucketSort = 0, kProfBucketLeaves, kProfVoxelsToLeaves, kProfFindTiles, kProfRankTiles, kProfInsertUpper, kProfScanUpper, kProfInsertLower, kProfScanLower,
     kProfInsertLeaf, kProfScanLeaf, kProfGridIjk, kProfNbmap, kProfLeafNeighbors, kProfBuildTiles,
     kProfPackWeights, kProfConvMfma, kProfConvGather, kProfConvLowdepth, kProfConvScalar, kProfMemset,
     kProfDgradStrided, kProfWgrad, kProfWgradReduce, kProfPool, kProfUpsample, kProfConvLeaf, kProfSmallGrid, kProfSlotCount
@@ -87,7 +87,7 @@ struct GridHeader {
     int32_t overflow;     // bit0: upper capacity, bit1: lower, bit2: leaf, bit3: tile limit, bit4: voxel count, bit5: leaf table full, bit6: a bucket's LDS table full, bit7: a scan's bounded wait expired, bit8: not a grid that the one-launch build holds
     int32_t n_leaf_raw;   // distinct leaves found by the voxel pass (may exceed capacity)
     int32_t n_bad;        // points whose cell is not representable (grids built from points)
-    int32_t wide_rows;    // some input row does not fit the build's packed 8-byte record
+    int32_t pad;
     int64_t n_voxels;
     int64_t n_voxels_dense;   // voxels in leaves that hold at least kDenseLeafVoxels of them (what the convolution's per-leaf dispatch goes by)
 };

@@ -68,14 +68,19 @@ __device__ __forceinline__ int find_batch(const BatchRanges& J, int B, int64_t r
 struct RowSource {
     const int32_t* ijk;
     const float* xyz;          // kPoints only
-    float o[3], s[3];
+    float o[3], s[3], inv_s[3];
 };
 
 // Cell of a coordinate.  Subtraction and division are the correctly rounded single-precision ones (no reciprocal, no
-// contraction), so that the cell of a point near a face is the same on every implementation.
-__device__ __forceinline__ int cell_of(float x, float o, float s, int& bad) {
-    const float t = floorf(__fdiv_rn(__fsub_rn(x, o), s));
-    const bool ok = isfinite(t) && t >= -1073741824.0f && t < 1073741824.0f;
+// contraction), so that the cell of a point near a face is the same on every implementation.  The division itself is only made
+// where it decides: the quotient times the rounded reciprocal is within 2^-22 of it (three roundings of 2^-24 and the
+// quotient's own), and unless a face lies within 2^-21 of its size both have the same floor.
+__device__ __forceinline__ int cell_of(float x, float o, float s, float inv_s, int& bad) {
+    const float d = __fsub_rn(x, o), near = __fmul_rn(d, inv_s), reach = __fmul_rn(fabsf(near), 4.76837158203125e-7f);
+    float t = floorf(near);
+    const float above = __fsub_rn(near, t);
+    if (!(above > reach && __fsub_rn(1.0f, above) > reach)) t = floorf(__fdiv_rn(d, s));     // NaN and infinities too
+    const bool ok = t >= -1073741824.0f && t < 1073741824.0f;
     bad += ok ? 0 : 1;
     return ok ? (int32_t)t : 0;
 }
@@ -83,8 +88,8 @@ __device__ __forceinline__ int cell_of(float x, float o, float s, int& bad) {
 template <bool kPoints>
 __device__ __forceinline__ int3 row_from_words(const RowSource& R, uint32_t w0, uint32_t w1, uint32_t w2, int& bad) {
     if (!kPoints) return make_int3((int)w0, (int)w1, (int)w2);
-    return make_int3(cell_of(__uint_as_float(w0), R.o[0], R.s[0], bad), cell_of(__uint_as_float(w1), R.o[1], R.s[1], bad),
-                     cell_of(__uint_as_float(w2), R.o[2], R.s[2], bad));
+    return make_int3(cell_of(__uint_as_float(w0), R.o[0], R.s[0], R.inv_s[0], bad), cell_of(__uint_as_float(w1), R.o[1], R.s[1], R.inv_s[1], bad),
+                     cell_of(__uint_as_float(w2), R.o[2], R.s[2], R.inv_s[2], bad));
 }
 
 template <bool kPoints>
@@ -169,6 +174,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
 struct LeafList {
     int4* key;           // [cap] (leaf i, leaf j, leaf k, grid): leaf coordinates = voxel coordinates >> 3
     int32_t* mask_idx;   // [cap] where the leaf's mask sits in `mask` (units of 8 words)
+    int32_t* node;       // [cap] the leaf's upper node, from the launch that numbers the lower ones on its lower node (-1: none)
     uint64_t* mask;
     int32_t cap;
 };
@@ -559,7 +565,7 @@ constexpr int kBucketSlots = 1024;                               // LDS leaf tab
 
 // A row on its way through the buckets is one 8-byte record when every coordinate of the input lies in [-2^19, 2^19)
 // and there are at most 16 grids (grid, i, j, k in 4 + 3 x 20 bits): half the bytes of four 32-bit words in the
-// scatter's writes and the leaf pass's reads.  Otherwise (GridHeader::wide_rows) it is two words, (i, j) and (k, grid).
+// row pass's writes and the leaf pass's reads.  Otherwise it is two words, (i, j) and (k, grid).
 __device__ __forceinline__ bool row_is_wide(const int3& v) {
     constexpr uint32_t half = 1u << 19;
     return (((uint32_t)v.x + half) | ((uint32_t)v.y + half) | ((uint32_t)v.z + half)) >= 2 * half;
@@ -576,13 +582,6 @@ __device__ __forceinline__ int4 unpack_row(uint64_t r) {
 }
 __device__ __forceinline__ uint64_t two_words(int a, int b) { return (uint64_t)(uint32_t)a | ((uint64_t)(uint32_t)b << 32); }
 
-// Workgroup b runs on XCD b % 8: consecutive pieces of the input go to one XCD, so that their adjacent runs of a
-// bucket meet in its L2 and leave as whole lines.
-__device__ __forceinline__ int part_piece() {
-    const int n = (int)gridDim.x, per = n >> 3, rest = n & 7, x = (int)blockIdx.x & 7;
-    return x * per + (x < rest ? x : rest) + ((int)blockIdx.x >> 3);
-}
-
 // What the first kernel of a build clears besides its own work: the head of the grid buffer (header, bases,
 // root table, child masks) and the head of the scratch buffer (scan tickets and block sums, root-tile table).
 // Nothing reads or updates either before the next launch.
@@ -591,139 +590,59 @@ struct ClearRanges {
     uint32_t n16[2];   // 16-byte units
 };
 
-// rows per (piece, bucket): hist[piece * n_buckets + bucket]; whether a row of the piece does not fit a packed record
+// One pass over the rows: a workgroup takes a piece of 4096 to 16384 of them, orders their records by bucket in LDS and writes
+// them behind one another, whole lines at a time; starts[piece][bucket] says where a bucket's run begins, [n_buckets] how many
+// rows the piece has in grids.  The leaf pass picks its bucket's runs out of all pieces.  (A counting pass, a scan over
+// (piece, bucket) and a scatter that gave every bucket one contiguous range of records read the rows twice: 10 M points
+// 52 + 14 + 81 us, now 75; 1 M rows 7 + 6 + 10, now 10.  The leaf pass takes 2 to 3 us more for its runs.)  info[piece]: 1 if some row does not fit a packed record (all records of the piece are
+// then two words), and twice the number of points whose cell is not representable.
 template <bool kPoints, int QUADS>
 __global__ void __launch_bounds__(kPartThreads)
-k_bucket_count(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B,
-               uint32_t bucket_mask, uint32_t* __restrict__ hist, int32_t* __restrict__ wide, ClearRanges clr) {
-    __shared__ uint32_t cnt[kMaxBuckets];
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-        for (uint32_t e = blockIdx.x * kPartThreads + threadIdx.x; e < clr.n16[c]; e += gridDim.x * kPartThreads)
-            clr.p[c][e] = make_uint4(0u, 0u, 0u, 0u);
-    for (uint32_t e = threadIdx.x; e <= bucket_mask; e += kPartThreads) cnt[e] = 0;
-    __syncthreads();
-    const int piece = part_piece();
-    bool is_wide = B > 16;
-    int ignored = 0;
-#pragma unroll
-    for (int c = 0; c < QUADS; ++c) {
-        const int64_t r = ((int64_t)piece * QUADS + c) * (4 * kPartThreads) + 4 * threadIdx.x;
-        int3 v[4];
-        const int n = load_four_rows<kPoints>(rows, n_rows, r, v, ignored);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int b = q < n ? find_batch(joff, B, r + q) : -1;
-            if (b < 0) continue;
-            is_wide |= row_is_wide(v[q]);
-            atomicAdd(&cnt[leaf_hash(b, v[q].x >> 3, v[q].y >> 3, v[q].z >> 3) & bucket_mask], 1u);
-        }
-    }
-    const int any_wide = __syncthreads_or(is_wide);
-    if (threadIdx.x == 0) wide[piece] = any_wide;
-    for (uint32_t e = threadIdx.x; e <= bucket_mask; e += kPartThreads) hist[(size_t)piece * (bucket_mask + 1) + e] = cnt[e];
-}
-
-// 64 buckets per workgroup, lane = bucket, the pieces cut into one run per wave: exclusive prefix over the pieces'
-// counts (in place) and the bucket totals.  Eight rows of counts in flight per wave; a wave reads 256 consecutive bytes.
-constexpr int kBucketScanThreads = 1024;
-__global__ void __launch_bounds__(kBucketScanThreads) k_bucket_scan(uint32_t* __restrict__ hist, int n_pieces, int n_buckets,
-                                                                    uint32_t* __restrict__ totals, const int32_t* __restrict__ wide,
-                                                                    GridHeader* hdr) {
-    constexpr int kWaves = kBucketScanThreads / 64;
-    __shared__ uint32_t run_sum[kWaves][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (blockIdx.x == 0) {
-        int w = 0;
-        for (int e = threadIdx.x; e < n_pieces; e += kBucketScanThreads) w |= wide[e];
-        w = __syncthreads_or(w);
-        if (threadIdx.x == 0) hdr->wide_rows = w;
-    }
-    const int p0 = (int)((int64_t)n_pieces * wave / kWaves), p1 = (int)((int64_t)n_pieces * (wave + 1) / kWaves);
-    uint32_t* col = hist + blockIdx.x * 64 + lane;
-    uint32_t sum = 0;
-    int p = p0;
-    for (; p + 8 <= p1; p += 8) {
-        uint32_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = col[(size_t)(p + u) * n_buckets];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
-    }
-    for (; p < p1; ++p) sum += col[(size_t)p * n_buckets];
-    run_sum[wave][lane] = sum;
-    __syncthreads();
-    uint32_t run = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        if (w == wave) run = all;
-        all += run_sum[w][lane];
-    }
-    p = p0;
-    for (; p + 8 <= p1; p += 8) {
-        uint32_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = col[(size_t)(p + u) * n_buckets];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { col[(size_t)(p + u) * n_buckets] = run; run += v[u]; }
-    }
-    for (; p < p1; ++p) { const uint32_t v = col[(size_t)p * n_buckets]; col[(size_t)p * n_buckets] = run; run += v; }
-    if (wave == 0) totals[blockIdx.x * 64 + lane] = all;
-}
-
-// scatter the rows into their buckets as records; the records of one workgroup are ordered by bucket in LDS first so
-// that each bucket receives one contiguous run
-template <bool kPoints, int QUADS>
-__global__ void __launch_bounds__(kPartThreads)
-k_bucket_scatter(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B,
-                 uint32_t bucket_mask, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals,
-                 uint32_t* __restrict__ bucket_start, uint64_t* __restrict__ records, GridHeader* hdr) {
+k_bucket_sort(const RowSource rows, int64_t n_rows, const BatchRanges joff, int B, uint32_t bucket_mask,
+              uint64_t* __restrict__ records, int64_t second_word, uint16_t* __restrict__ starts, int32_t* __restrict__ info, ClearRanges clr) {
     extern __shared__ __align__(16) unsigned char part_lds[];
     constexpr int kRows = 4 * QUADS * kPartThreads;
+    static_assert(kRows <= 1 << 16, "runs begin at 16-bit places");
     const uint32_t n_buckets = bucket_mask + 1;
     uint64_t* rec = reinterpret_cast<uint64_t*>(part_lds);                  // [kRows]
-    uint32_t* dest = reinterpret_cast<uint32_t*>(rec + kRows);              // [kRows]
-    uint32_t* cnt = dest + kRows;                                           // [n_buckets] rows of this workgroup
-    uint32_t* lstart = cnt + n_buckets;                                     // [n_buckets] first LDS slot
-    uint32_t* gbase = lstart + n_buckets;                                   // [n_buckets] first global record
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(rec + kRows);               // [n_buckets] rows of this piece, then the first LDS slot
     const int tid = threadIdx.x;
-    const int piece = part_piece();
-    // the rows are requested before the scan below waits for the totals
     int3 v[4 * QUADS];
     int b[4 * QUADS];
     int bad = 0;
+    bool is_wide = B > 16;
+    // nearly all pieces lie in one grid, which is then looked up once
+    const int64_t r0 = (int64_t)blockIdx.x * kRows, r_last = min(r0 + kRows, n_rows) - 1;
+    const int b_first = find_batch(joff, B, r0), b_all = b_first == find_batch(joff, B, r_last) ? b_first : -1;
 #pragma unroll
     for (int c = 0; c < QUADS; ++c) {
-        const int64_t r = ((int64_t)piece * QUADS + c) * (4 * kPartThreads) + 4 * tid;
+        const int64_t r = r0 + (int64_t)c * (4 * kPartThreads) + 4 * tid;
         int3 w[4];
         const int n = load_four_rows<kPoints>(rows, n_rows, r, w, bad);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             v[4 * c + q] = w[q];
-            b[4 * c + q] = q < n ? find_batch(joff, B, r + q) : -1;
+            b[4 * c + q] = q < n ? b_all : -1;
         }
     }
-    if (kPoints && bad) atomicAdd(&hdr->n_bad, bad);
-    // bucket starts = exclusive scan of the totals (every workgroup repeats it; the first one publishes it)
-    {
-        uint32_t t[2], sum = 0;
+    if (b_all < 0) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; t[q] = e < n_buckets ? totals[e] : 0u; sum += t[q]; }
-        uint32_t total;
-        uint32_t run = block_exclusive_scan(sum, &total);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t e = tid * 2 + q;
-            if (e < n_buckets) {
-                gbase[e] = run + hist[(size_t)piece * n_buckets + e];
-                if (blockIdx.x == 0) bucket_start[e] = run;
-            }
-            run += t[q];
+        for (int q = 0; q < 4 * QUADS; ++q) {
+            const int64_t r = r0 + (int64_t)(q >> 2) * (4 * kPartThreads) + 4 * tid + (q & 3);
+            b[q] = r < n_rows ? find_batch(joff, B, r) : -1;
         }
-        if (blockIdx.x == 0 && tid == 0) bucket_start[n_buckets] = total;
     }
+#pragma unroll
+    for (int q = 0; q < 4 * QUADS; ++q) is_wide |= b[q] >= 0 && row_is_wide(v[q]);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+        for (uint32_t e = blockIdx.x * kPartThreads + tid; e < clr.n16[c]; e += gridDim.x * kPartThreads)
+            clr.p[c][e] = make_uint4(0u, 0u, 0u, 0u);
+    __shared__ int n_bad;
+    if (tid == 0) n_bad = 0;
     for (uint32_t e = tid; e < n_buckets; e += kPartThreads) cnt[e] = 0;
-    __syncthreads();
+    is_wide = __syncthreads_or(is_wide);
+    if (kPoints && bad) atomicAdd(&n_bad, bad);
     uint32_t bucket[4 * QUADS], rank[4 * QUADS];
 #pragma unroll
     for (int q = 0; q < 4 * QUADS; ++q) {
@@ -731,40 +650,37 @@ k_bucket_scatter(const RowSource rows, int64_t n_rows, const BatchRanges joff, i
         rank[q] = b[q] >= 0 ? atomicAdd(&cnt[bucket[q]], 1u) : 0u;
     }
     __syncthreads();
-    // first LDS slot of every bucket = exclusive scan of this workgroup's counts
+    // first LDS slot of every bucket = exclusive scan of the counts, in place
+    uint32_t n_local;
     {
         uint32_t t[2], sum = 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) { const uint32_t e = tid * 2 + q; t[q] = e < n_buckets ? cnt[e] : 0u; sum += t[q]; }
-        uint32_t total;
-        uint32_t run = block_exclusive_scan(sum, &total);
+        uint32_t run = block_exclusive_scan(sum, &n_local);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const uint32_t e = tid * 2 + q;
-            if (e < n_buckets) lstart[e] = run;
+            if (e < n_buckets) cnt[e] = run;
             run += t[q];
         }
     }
+    if (tid == 0) info[blockIdx.x] = (is_wide ? 1 : 0) | 2 * n_bad;
     __syncthreads();
-    const bool is_wide = hdr->wide_rows != 0;
 #pragma unroll
-    for (int q = 0; q < 4 * QUADS; ++q) {
-        if (b[q] < 0) continue;
-        const uint32_t s = lstart[bucket[q]] + rank[q];
-        rec[s] = is_wide ? two_words(v[q].x, v[q].y) : pack_row(v[q], b[q]);
-        dest[s] = gbase[bucket[q]] + rank[q];
-    }
+    for (int q = 0; q < 4 * QUADS; ++q)
+        if (b[q] >= 0) rec[cnt[bucket[q]] + rank[q]] = is_wide ? two_words(v[q].x, v[q].y) : pack_row(v[q], b[q]);
+    uint16_t* my_starts = starts + (size_t)blockIdx.x * (n_buckets + 1);
+    for (uint32_t e = tid; e <= n_buckets; e += kPartThreads) my_starts[e] = (uint16_t)(e < n_buckets ? cnt[e] : n_local);
     __syncthreads();
-    // number of valid rows of this workgroup = last bucket's start + count
-    const uint32_t n_local = lstart[bucket_mask] + cnt[bucket_mask];
-    for (uint32_t s = tid; s < n_local; s += kPartThreads) records[dest[s]] = rec[s];
+    uint64_t* out = records + (int64_t)blockIdx.x * kRows;
+    for (uint32_t s = tid; s < n_local; s += kPartThreads) out[s] = rec[s];
     if (!is_wide) return;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 4 * QUADS; ++q)
-        if (b[q] >= 0) rec[lstart[bucket[q]] + rank[q]] = two_words(v[q].z, b[q]);
+        if (b[q] >= 0) rec[cnt[bucket[q]] + rank[q]] = two_words(v[q].z, b[q]);
     __syncthreads();
-    for (uint32_t s = tid; s < n_local; s += kPartThreads) records[n_rows + dest[s]] = rec[s];
+    for (uint32_t s = tid; s < n_local; s += kPartThreads) out[second_word + s] = rec[s];
 }
 
 // One workgroup per bucket: the bucket's distinct leaves and their masks, built in LDS.  The table's slots hold the
@@ -773,36 +689,67 @@ k_bucket_scatter(const RowSource rows, int64_t n_rows, const BatchRanges joff, i
 // of which takes the leaves of one class by two further bits of their hash; a class that is still too large is cut once
 // more by two.  A row that finds no slot within kBucketProbes steps (one longer each time) says so: rows that walked a
 // full table to its end read 1024 slots one after the other, in every round that came to nothing.
-constexpr int kBucketThreads = 1024, kBucketProbes = 64;
-__global__ void __launch_bounds__(kBucketThreads)
-k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint32_t* __restrict__ bucket_start, LeafList L, GridHeader* hdr) {
+// The bucket's rows are the runs that the pieces of the row pass have of it, four rows each on average at 10 M rows: their
+// starts, 1024 pieces at a time, and a scan of their lengths go to LDS, and every thread takes an equal share of consecutive
+// rows, whose run it finds by bisection -- input in the order of its voxels has all rows of a piece in few runs.  Workgroup b
+// runs on XCD b % 8: neighbouring buckets, whose runs and starts share lines, meet in one L2.
+constexpr int kBucketThreads = 1024, kBucketProbes = 64, kBucketBatch = 4;
+__global__ void __launch_bounds__(kBucketThreads, 8)
+k_bucket_leaves(const uint64_t* __restrict__ records, int64_t second_word, const uint16_t* __restrict__ starts, const int32_t* __restrict__ info,
+                int n_pieces, int piece_rows_log2, LeafList L, GridHeader* hdr) {
     __shared__ unsigned long long slot[kBucketSlots];     // 0 = empty
     __shared__ __align__(16) unsigned long long mask[kBucketSlots * 8];
+    __shared__ uint32_t run_first[kBucketThreads];        // rows of the bucket in the pieces before (of these 1024)
+    __shared__ uint16_t run_start[kBucketThreads];        // where the run begins in its piece
     __shared__ int32_t list_base;
     static_assert(kBucketSlots == kBucketThreads, "one table slot per thread in the listing step");
     const int tid = threadIdx.x;
-    const uint32_t begin = bucket_start[blockIdx.x], end = bucket_start[blockIdx.x + 1];
-    const bool is_wide = hdr->wide_rows != 0;
-    auto row_at = [&](uint32_t r) {
-        const uint64_t a = records[r];
-        if (!is_wide) return unpack_row(a);
-        const uint64_t c = records[n_rows + r];
-        return make_int4((int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)c, (int)(uint32_t)(c >> 32));
+    const uint32_t n_buckets = gridDim.x, bucket = (blockIdx.x & 7) * (n_buckets >> 3) + (blockIdx.x >> 3);
+    uint32_t n_run_rows = 0, from = 0, to = 0;
+    auto request_runs = [&](int p0) {                     // the runs of pieces p0 .. p0 + 1023
+        const uint16_t* s = starts + (size_t)min(p0 + tid, n_pieces - 1) * (n_buckets + 1) + bucket;
+        from = s[0];
+        to = s[1];
     };
-    uint32_t class_mask = 0, class_value = 0;             // this round's leaves: hash bits 24.. under the mask
-    while (true) {
+    auto place_runs = [&](int p0) {
+        const uint32_t first = block_exclusive_scan(p0 + tid < n_pieces ? to - from : 0u, &n_run_rows);
+        run_first[tid] = first;
+        run_start[tid] = (uint16_t)from;
+        __syncthreads();
+    };
+    auto clear = [&]() {
         slot[tid] = 0ull;
         for (int e = tid; e < kBucketSlots * 4; e += kBucketThreads) reinterpret_cast<ulonglong2*>(mask)[e] = make_ulonglong2(0ull, 0ull);
-        __syncthreads();
+    };
+    request_runs(0);
+    int all_info = 0;
+    for (int e = tid; e < n_pieces; e += kBucketThreads) {
+        const int i = info[e];
+        all_info |= i;
+        if (blockIdx.x == 0 && i > 1) atomicAdd(&hdr->n_bad, i >> 1);
+    }
+    clear();                                              // while those are under way
+    const bool is_wide = __syncthreads_or(all_info & 1);
+    if (n_pieces <= kBucketThreads) place_runs(0);
+    // a row by its place among the records; with wide rows a piece says whether its records are two words
+    auto unpack_at = [&](uint32_t r, uint64_t a) {
+        if (!is_wide || !(info[r >> piece_rows_log2] & 1)) return unpack_row(a);
+        const uint64_t c = records[second_word + r];
+        return make_int4((int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)(uint32_t)c, (int)(uint32_t)(c >> 32));
+    };
+    auto row_at = [&](uint32_t r) { return unpack_at(r, records[r]); };
+    uint32_t class_mask = 0, class_value = 0;             // this round's leaves: hash bits 24.. under the mask
+    for (bool first_round = true;; first_round = false) {
+        if (!first_round) { clear(); __syncthreads(); }
         bool full = false;
-        for (uint32_t r = begin + tid; r < end; r += kBucketThreads) {
-            const int4 v = row_at(r);
+        auto take_row = [&](uint32_t r, uint64_t record) {            // false: no slot found
+            const int4 v = unpack_at(r, record);
             const int li = v.x >> 3, lj = v.y >> 3, lk = v.z >> 3;
             const uint32_t hash = leaf_hash(v.w, li, lj, lk);
-            if (((hash >> 24) & class_mask) != class_value) continue;
+            if (((hash >> 24) & class_mask) != class_value) return true;
             uint32_t h = (hash >> 12) & (kBucketSlots - 1);   // other bits than the bucket's
             // the leaf as a nonzero word: biased coordinates of 17 bits, grid, a set top bit
-            const unsigned long long self = is_wide ? (unsigned long long)(r - begin) + 1ull
+            const unsigned long long self = is_wide ? (unsigned long long)r + 1ull
                 : (1ull << 63) | ((unsigned long long)(uint32_t)v.w << 51) | ((unsigned long long)(uint32_t)(li + (1 << 16)) << 34) |
                   ((unsigned long long)(uint32_t)(lj + (1 << 16)) << 17) | (unsigned long long)(uint32_t)(lk + (1 << 16));
             bool found = false;
@@ -815,13 +762,39 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
                 if (!is_wide) {
                     if (s == self) { found = true; break; }
                 } else {
-                    const int4 o = row_at(begin + (uint32_t)(s - 1ull));
+                    const int4 o = row_at((uint32_t)(s - 1ull));
                     if ((o.x >> 3) == li && (o.y >> 3) == lj && (o.z >> 3) == lk && o.w == v.w) { found = true; break; }
                 }
                 h = (h + probe + 1) & (kBucketSlots - 1);
             }
-            if (!found) { full = true; break; }
-            atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
+            if (found) atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
+            return found;
+        };
+        for (int p0 = 0; p0 < n_pieces; p0 += kBucketThreads) {
+            if (n_pieces > kBucketThreads) { __syncthreads(); request_runs(p0); place_runs(p0); }
+            const uint32_t share = (n_run_rows + kBucketThreads - 1) / kBucketThreads;
+            uint32_t r = tid * share;
+            const uint32_t end = min(r + share, n_run_rows);
+            if (r >= end) continue;
+            int run = 0;                                  // the last run that begins at or before row r
+#pragma unroll
+            for (int step = kBucketThreads / 2; step > 0; step >>= 1)
+                if (run_first[run + step] <= r) run += step;
+            while (r < end && !full) {
+                uint32_t at[kBucketBatch];
+                uint64_t rec[kBucketBatch];
+#pragma unroll
+                for (int u = 0; u < kBucketBatch; ++u) {  // past the share's end the last row again
+                    const uint32_t ru = min(r + u, end - 1);
+                    while (run + 1 < kBucketThreads && run_first[run + 1] <= ru) ++run;
+                    at[u] = ((uint32_t)(p0 + run) << piece_rows_log2) + run_start[run] + (ru - run_first[run]);
+                    rec[u] = records[at[u]];
+                }
+#pragma unroll
+                for (int u = 0; u < kBucketBatch; ++u)
+                    if (r + u < end && !full) full = !take_row(at[u], rec[u]);
+                r += kBucketBatch;
+            }
         }
         if (__syncthreads_or(full)) {
             // nothing of this class has been listed: take its first quarter instead.  A sixteenth of a bucket that still
@@ -839,7 +812,7 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t n_rows, const uint
         const int pos = list_base + (int)before;
         if (s != 0ull && pos < L.cap) {
             if (is_wide) {
-                const int4 v = row_at(begin + (uint32_t)(s - 1ull));
+                const int4 v = row_at((uint32_t)(s - 1ull));
                 L.key[pos] = make_int4(v.x >> 3, v.y >> 3, v.z >> 3, v.w);
             } else {
                 constexpr uint32_t m = (1u << 17) - 1;
@@ -879,32 +852,40 @@ __device__ __forceinline__ bool leaf_at(const LeafList& L, const GridHeader* hdr
 // hold a representative leaf (+1; 0 = empty).  Called by all threads of a workgroup together (`has`:
 // this thread holds leaf `idx` with key `key`).
 constexpr int kFindTilesThreads = 1024;
-constexpr int kTileRounds = 16;
+constexpr int kKnownTiles = 64;
 __device__ __forceinline__ void find_tile_item(const LeafList& L, GridHeader* hdr, int idx, bool has, const int4& key,
                                                int32_t* __restrict__ tile_slots, int32_t* __restrict__ rep_leaves) {
     const int4 tile = make_int4(key.x >> 9, key.y >> 9, key.z >> 9, key.w);   // leaf coordinate >> 9 = voxel >> 12
     auto same = [](const int4& a, const int4& b) { return a.x == b.x && a.y == b.y && a.z == b.z && a.w == b.w; };
     // One thread per distinct tile of the WORKGROUP goes to the table: accesses to one address from all over the
     // device queue up at memory (a coherent read of one slot from each of 600 waves took longer than the rest of
-    // this launch), and nearly all leaves share one tile.  In rounds, the first thread still waiting proposes its
-    // tile (the first waiting lane of every wave bids with an LDS atomic; same-address LDS atomics run lane by lane,
-    // so not every lane) and every thread with that tile is done: two barriers and no memory access per distinct tile.
-    __shared__ int leader[kTileRounds];
-    __shared__ int4 leader_tile[kTileRounds];
-    const int tid = (int)threadIdx.x;
+    // this launch), and nearly all leaves share a few tiles.  Every wave names the tiles of its leaves one after the other (the
+    // first lane still waiting, and all lanes with its tile are done), and the first wave that puts a tile into the table in
+    // LDS speaks for it; a wave that finds no place there speaks for itself.  (Rounds of the whole workgroup, two barriers
+    // for each distinct tile: 376 k leaves in eight tiles 19.7 -> 14.3 us, four indoor scenes 13.6 -> 10.2.)
+    __shared__ unsigned long long known[kKnownTiles];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    for (int e = tid; e < kKnownTiles; e += (int)blockDim.x) known[e] = 0ull;
+    __syncthreads();
     bool waiting = has, speaker = false;
-    for (int batch = 0; batch < (int)blockDim.x / kTileRounds + 1; ++batch) {
-        if (tid < kTileRounds) leader[tid] = INT32_MAX;
-        if (!__syncthreads_or(waiting)) break;
-        for (int r = 0; r < kTileRounds; ++r) {
-            const uint64_t bids = __ballot(waiting);
-            if (bids && (tid & 63) == __ffsll((long long)bids) - 1) atomicMin(&leader[r], tid);
-            __syncthreads();
-            const int l = leader[r];
-            if (l == INT32_MAX) break;
-            if (tid == l) { leader_tile[r] = tile; speaker = true; }
-            __syncthreads();
-            if (waiting && same(tile, leader_tile[r])) waiting = false;
+    for (uint64_t left = __ballot(waiting); left; left = __ballot(waiting)) {
+        const int first = __ffsll((long long)left) - 1;
+        const int4 t = make_int4(__builtin_amdgcn_readlane(tile.x, first), __builtin_amdgcn_readlane(tile.y, first),
+                                 __builtin_amdgcn_readlane(tile.z, first), __builtin_amdgcn_readlane(tile.w, first));
+        if (same(tile, t)) waiting = false;
+        if (lane == first) {
+            // a grid number of 15 bits and tile coordinates of 16 (voxels within 2^27); others speak for themselves
+            const bool fits = (((uint32_t)t.x + 0x8000u) | ((uint32_t)t.y + 0x8000u) | ((uint32_t)t.z + 0x8000u)) < 0x10000u && (uint32_t)t.w < 0x8000u;
+            const unsigned long long word = 1ull << 63 | (unsigned long long)(uint32_t)t.w << 48 | (unsigned long long)(t.x & 0xFFFF) << 32 |
+                                            (unsigned long long)(t.y & 0xFFFF) << 16 | (unsigned long long)(t.z & 0xFFFF);
+            speaker = true;
+            uint32_t h = mix32(mix32(mix32(0x811C9DC5u, (uint32_t)t.x ^ (uint32_t)t.w << 16), (uint32_t)t.y), (uint32_t)t.z) & (kKnownTiles - 1);
+            for (int probe = 0; probe < 4 && fits; ++probe) {
+                const unsigned long long old = atomicCAS(&known[h], 0ull, word);
+                if (old == 0ull) break;
+                if (old == word) { speaker = false; break; }
+                h = (h + 1) & (kKnownTiles - 1);
+            }
         }
     }
     if (!speaker) return;
@@ -978,22 +959,18 @@ __global__ void k_rank_tiles(LeafList L, const int32_t* __restrict__ rep_leaves,
 // cost some 0.3 us a thousand.
 constexpr int kInsertMaxBlocks = 1024;
 
-// lower node of a leaf, or -1
-__device__ __forceinline__ int lower_of(const GridPtrs& g, const int4& key) {
-    const int i = key.x << 3, j = key.y << 3, k = key.z << 3;   // the leaf's origin
-    const int u = find_upper_short(g.root_key, g.root_batch, g.hdr->n_upper, key.w, tile_key(i, j, k));
-    if (u < 0) return -1;
-    const int l = child_of(g.upper_mask + (size_t)u * kUpperWords, g.upper_prefix + (size_t)u * kUpperWords, upper_off(i, j, k));
-    return l < g.cap_lower ? l : -1;
-}
-
 // One thread per distinct leaf: its bit in the lower node's child mask (step 11.3)
 __global__ void k_insert_lower(LeafList L, GridPtrs g) {
     if (g.hdr->overflow) return;
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;; idx += (int64_t)gridDim.x * blockDim.x) {
         int4 key;
         if (!leaf_at(L, g.hdr, idx, &key)) return;
-        const int l = lower_of(g, key);
+        const int u = L.node[idx];
+        int l = -1;
+        if (u >= 0)
+            l = child_of(g.upper_mask + (size_t)u * kUpperWords, g.upper_prefix + (size_t)u * kUpperWords, upper_off(key.x << 3, key.y << 3, key.z << 3));
+        if (l >= g.cap_lower) l = -1;
+        L.node[idx] = l;
         if (l < 0) continue;
         const int off = lower_off(key.x << 3, key.y << 3, key.z << 3);
         atomicOr((unsigned long long*)(g.lower_mask + (size_t)l * kLowerWords + (off >> 6)), 1ull << (off & 63));
@@ -1004,6 +981,8 @@ __global__ void k_insert_lower(LeafList L, GridPtrs g) {
 // Listing 1, origin and grid; its voxel count goes to a compact array for the scan that follows.  Eight threads per
 // leaf, one per mask word, so that a leaf is read and written as 64 consecutive bytes (one thread per leaf: 64 lines
 // touched by every one of 12 store instructions of a wave; 376 k leaves 51 us here and 23 in the scan that re-read them).
+// The lower node comes from the launch before (LeafList::node): with the descent from the root made again, 376 k leaves took
+// 40 us, now 26, 38 k 8.2, now 6.5.
 __global__ void k_place_leaves(LeafList L, GridPtrs g, uint32_t* __restrict__ leaf_count) {
     if (g.hdr->overflow) return;
     const int w = threadIdx.x & 7;
@@ -1011,7 +990,7 @@ __global__ void k_place_leaves(LeafList L, GridPtrs g, uint32_t* __restrict__ le
         int4 key;
         if (!leaf_at(L, g.hdr, idx, &key)) return;           // the same for the eight threads of a leaf
         const uint64_t m = L.mask[(size_t)L.mask_idx[idx] * 8 + w];
-        const int l = lower_of(g, key);
+        const int l = L.node[idx];
         int f = -1;
         if (l >= 0)
             f = child_of(g.lower_mask + (size_t)l * kLowerWords, g.lower_prefix + (size_t)l * kLowerWords,
@@ -1101,6 +1080,7 @@ __global__ void __launch_bounds__(kInsertUpperThreads) k_insert_upper(LeafList L
     if (leaf_at(L, g.hdr, idx, &key)) {
         const int i = key.x << 3, j = key.y << 3, k = key.z << 3;
         const int u = find_upper_short(root_key, root_batch, n_upper, key.w, tile_key(i, j, k));
+        L.node[idx] = u;
         if (u >= 0) {
             const int off = upper_off(i, j, k);
             const int word = u * kUpperWords + (off >> 6);
@@ -1512,7 +1492,7 @@ k_small_grid(const RowSource rows, int n_rows, const BatchRanges joff, int B, Tr
     if (tid == 0) {
         GridHeader hdr;
         hdr.n_tiles_raw = n_upper; hdr.n_upper = n_upper; hdr.n_lower = n_lower; hdr.n_leaf = n_leaf;
-        hdr.overflow = overflow; hdr.n_leaf_raw = n_leaf; hdr.n_bad = n_bad; hdr.wide_rows = 0;
+        hdr.overflow = overflow; hdr.n_leaf_raw = n_leaf; hdr.n_bad = n_bad; hdr.pad = 0;
         hdr.n_voxels = n_vox; hdr.n_voxels_dense = (int64_t)dense;
         *g.hdr = hdr;
         *reinterpret_cast<GridHeader*>(host) = hdr;
@@ -1695,7 +1675,7 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     //   cleared by both paths:    [scan tickets and block words | tile table]
     //   cleared by the direct one [leaf table slots | leaf masks]
     //   not cleared:              [leaf keys | mask indices | tile representatives |
-    //                              partitioned path: leaf masks, bucket records, histogram, totals, bucket starts]
+    //                              partitioned path: leaf masks, records, runs of the buckets, pieces]
     const bool partition = !direct && n_rows >= kPartitionMinRows;
     const int64_t max_items = std::max<int64_t>((int64_t)g->cap_lower * kLowerWords / kWordChunk,
                                                 std::max<int64_t>((int64_t)g->cap_upper * kUpperWords / kWordChunk,
@@ -1716,9 +1696,9 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     // overflowed their tables (226 k points in 190 k leaves: 60 -> 21 us for the leaf pass).
     int n_buckets = 256;
     while (n_buckets < kMaxBuckets && (int64_t)n_buckets * kRowsPerBucket < n_rows) n_buckets <<= 1;
-    // Rows per workgroup of the two row passes: 4096, or 8192 once that still makes two workgroups per compute unit
-    // (longer runs per bucket, half the histogram).
-    const int quads = n_rows >= (int64_t)2 * 8192 * compute_units() ? 2 : 1;
+    // Rows of a piece: 4096, or 8192 and 16384 once that still makes two pieces per compute unit: fewer pieces are fewer, longer
+    // runs in the leaf pass (10 M points, pieces of 8192 / 16384: 77 / 80 us for the row pass, 110 / 85 for the leaf pass).
+    const int quads = n_rows >= (int64_t)2 * 16384 * compute_units() ? 4 : n_rows >= (int64_t)2 * 8192 * compute_units() ? 2 : 1;
     const int part_chunk = kPartThreads * 4 * quads;
     const int n_part_wg = (int)((n_rows + part_chunk - 1) / part_chunk);
     size_t off = 0;
@@ -1734,13 +1714,13 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     const size_t clear_bytes = partition ? clear_bytes_head : (whole_masks ? clear_bytes_slots : off);
     const size_t o_key = take(sizeof(int4) * (size_t)g->cap_leaf);
     const size_t o_midx = take(sizeof(int32_t) * (size_t)g->cap_leaf);
+    const size_t o_node = take(sizeof(int32_t) * (size_t)g->cap_leaf);
     const size_t o_lcnt = take(sizeof(uint32_t) * (size_t)g->cap_leaf);
     const size_t o_rep = take(sizeof(int32_t) * kMaxTiles);
-    const size_t o_rec = take(partition ? sizeof(int4) * (size_t)n_rows : 0);
-    const size_t o_hist = take(partition ? sizeof(uint32_t) * (size_t)n_buckets * n_part_wg : 0);
-    const size_t o_wide = take(partition ? sizeof(int32_t) * (size_t)n_part_wg : 0);
-    const size_t o_tot = take(partition ? sizeof(uint32_t) * n_buckets : 0);
-    const size_t o_bst = take(partition ? sizeof(uint32_t) * (n_buckets + 1) : 0);
+    const int64_t n_records = (int64_t)n_part_wg * part_chunk;
+    const size_t o_rec = take(partition ? sizeof(int4) * (size_t)n_records : 0);
+    const size_t o_starts = take(partition ? sizeof(uint16_t) * (size_t)(n_buckets + 1) * n_part_wg : 0);
+    const size_t o_info = take(partition ? sizeof(int32_t) * (size_t)n_part_wg : 0);
     void* scratch = nullptr;
     rc = dev_alloc(&scratch, off, st);
     if (rc != FX_OK) { fx_grid_destroy(g); return rc; }
@@ -1749,6 +1729,7 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     L.mask = (uint64_t*)(sp + o_mask);
     L.key = (int4*)(sp + o_key);
     L.mask_idx = (int32_t*)(sp + o_midx);
+    L.node = (int32_t*)(sp + o_node);
     L.cap = g->cap_leaf;
     int32_t* d_tile_slots = (int32_t*)(sp + o_tslot);
     int32_t* d_slots = (int32_t*)(sp + o_slots);
@@ -1759,10 +1740,8 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
         return ScanSync{base, base + 64};
     };
     uint64_t* d_records = (uint64_t*)(sp + o_rec);         // two words per row (the second: wide rows only)
-    uint32_t* d_hist = (uint32_t*)(sp + o_hist);
-    int32_t* d_wide = (int32_t*)(sp + o_wide);
-    uint32_t* d_totals = (uint32_t*)(sp + o_tot);
-    uint32_t* d_bucket_start = (uint32_t*)(sp + o_bst);
+    uint16_t* d_starts = (uint16_t*)(sp + o_starts);
+    int32_t* d_info = (int32_t*)(sp + o_info);
 
     auto fail = [&](fx_status s) { dev_free(scratch, st); fx_grid_destroy(g); return s; };
 #define FX_TRY_OR_FAIL(expr) do { hipError_t _e = (expr); if (_e != hipSuccess) { \
@@ -1785,29 +1764,20 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
         const unsigned nb_leaf_1024 = (unsigned)(((int64_t)g->cap_leaf + 1023) / 1024);
         if (partition) {
             const uint32_t bucket_mask = (uint32_t)n_buckets - 1;
-            const size_t lds = (sizeof(uint64_t) + sizeof(uint32_t)) * part_chunk + 3 * sizeof(uint32_t) * n_buckets;
+            const size_t lds = sizeof(uint64_t) * part_chunk + sizeof(uint32_t) * n_buckets;
             ClearRanges clr;
             clr.p[0] = (uint4*)g->buf; clr.n16[0] = (uint32_t)(grid_clear_bytes / 16);
             clr.p[1] = (uint4*)scratch; clr.n16[1] = (uint32_t)(clear_bytes / 16);
-#define FX_ROW_PASS(KERNEL, LDS, ...)                                                                                  \
-    do {                                                                                                               \
-        const void* f = rows.xyz ? (quads == 2 ? (const void*)KERNEL<true, 2> : (const void*)KERNEL<true, 1>)          \
-                                 : (quads == 2 ? (const void*)KERNEL<false, 2> : (const void*)KERNEL<false, 1>);       \
-        if ((LDS) > 64 * 1024) FX_TRY_OR_FAIL(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS))); \
-        if (rows.xyz && quads == 2) KERNEL<true, 2><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);              \
-        else if (rows.xyz) KERNEL<true, 1><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                       \
-        else if (quads == 2) KERNEL<false, 2><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                    \
-        else KERNEL<false, 1><<<n_part_wg, kPartThreads, (LDS), st>>>(__VA_ARGS__);                                    \
-    } while (0)
-            { ProfScope ps(kProfBucketCount, st);
-              FX_ROW_PASS(k_bucket_count, (size_t)0, rows, n_rows, d_joff, B, bucket_mask, d_hist, d_wide, clr); }
-            { ProfScope ps(kProfBucketScan, st);
-              k_bucket_scan<<<n_buckets / 64, kBucketScanThreads, 0, st>>>(d_hist, n_part_wg, n_buckets, d_totals, d_wide, g->d_hdr); }
-            { ProfScope ps(kProfBucketScatter, st);
-              FX_ROW_PASS(k_bucket_scatter, lds, rows, n_rows, d_joff, B, bucket_mask, d_hist, d_totals, d_bucket_start, d_records, g->d_hdr); }
+#define FX_SORT(POINTS, QUADS)                                                                                          \
+    if ((rows.xyz != nullptr) == POINTS && quads == QUADS) {                                                           \
+        if (lds > 64 * 1024) FX_TRY_OR_FAIL(hipFuncSetAttribute((const void*)k_bucket_sort<POINTS, QUADS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+        k_bucket_sort<POINTS, QUADS><<<n_part_wg, kPartThreads, lds, st>>>(rows, n_rows, d_joff, B, bucket_mask, d_records, n_records, d_starts, d_info, clr); \
+    }
+            { ProfScope ps(kProfBucketSort, st);
+              FX_SORT(true, 1) FX_SORT(true, 2) FX_SORT(true, 4) FX_SORT(false, 1) FX_SORT(false, 2) FX_SORT(false, 4) }
+#undef FX_SORT
             { ProfScope ps(kProfBucketLeaves, st);
-              k_bucket_leaves<<<n_buckets, kBucketThreads, 0, st>>>(d_records, n_rows, d_bucket_start, L, g->d_hdr); }
-#undef FX_ROW_PASS
+              k_bucket_leaves<<<n_buckets, kBucketThreads, 0, st>>>(d_records, n_records, d_starts, d_info, n_part_wg, quads == 4 ? 14 : quads == 2 ? 13 : 12, L, g->d_hdr); }
         } else {
             const unsigned nb_rows = (unsigned)((n_rows + kDirectThreads - 1) / kDirectThreads);
             // few fine leaves: more workgroups (15.8 k of them 10.1 us, 12.4 with 512 threads); many: fewer updates of the counter
@@ -2092,7 +2062,7 @@ extern "C" fx_status fx_build_index_grid_from_points(const float* d_xyz, int64_t
     if (n_rows > (int64_t)INT32_MAX) { set_error("more than 2^31-1 input rows"); return FX_ERANGE; }
     RowSource rows{};
     rows.xyz = d_xyz;
-    for (int a = 0; a < 3; ++a) { rows.o[a] = h_origin[a]; rows.s[a] = h_voxel_size[a]; }
+    for (int a = 0; a < 3; ++a) { rows.o[a] = h_origin[a]; rows.s[a] = h_voxel_size[a]; rows.inv_s[a] = 1.0f / h_voxel_size[a]; }
     fx_grid* g = nullptr;
     FX_TRY(build_index_grid_checked(rows, n_rows, h_joffsets, B, stream, &g));
     if (g->hdr.n_bad > 0) {
