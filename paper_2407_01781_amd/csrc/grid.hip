@@ -690,8 +690,8 @@ k_bucket_sort(const RowSource rows, int64_t n_rows, const BatchRanges joff, int 
 // more by two.  A row that finds no slot within kBucketProbes steps (one longer each time) says so: rows that walked a
 // full table to its end read 1024 slots one after the other, in every round that came to nothing.
 // The bucket's rows are the runs that the pieces of the row pass have of it, four rows each on average at 10 M rows: their
-// starts, 1024 pieces at a time, and a scan of their lengths go to LDS, and every thread takes an equal share of consecutive
-// rows, whose run it finds by bisection -- input in the order of its voxels has all rows of a piece in few runs.  Workgroup b
+// starts, 1024 pieces at a time, and a scan of their lengths go to LDS, and every thread takes up to four consecutive
+// rows at a time, whose run it finds by bisection -- input in the order of its voxels has all rows of a piece in few runs.  Workgroup b
 // runs on XCD b % 8: neighbouring buckets, whose runs and starts share lines, meet in one L2.
 constexpr int kBucketThreads = 1024, kBucketProbes = 64, kBucketBatch = 4;
 __global__ void __launch_bounds__(kBucketThreads, 8)
@@ -767,33 +767,41 @@ k_bucket_leaves(const uint64_t* __restrict__ records, int64_t second_word, const
                 }
                 h = (h + probe + 1) & (kBucketSlots - 1);
             }
-            if (found) atomicOr(&mask[h * 8 + (v.x & 7)], 1ull << (((v.y & 7) << 3) | (v.z & 7)));
-            return found;
+            if (!found) return false;
+            // rows of one voxel mostly find it there: updates of one word run one after the other
+            const unsigned long long bit = 1ull << (((v.y & 7) << 3) | (v.z & 7));
+            unsigned long long* const word = &mask[h * 8 + (v.x & 7)];
+            if (!(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit)) atomicOr(word, bit);
+            return true;
         };
         for (int p0 = 0; p0 < n_pieces; p0 += kBucketThreads) {
             if (n_pieces > kBucketThreads) { __syncthreads(); request_runs(p0); place_runs(p0); }
-            const uint32_t share = (n_run_rows + kBucketThreads - 1) / kBucketThreads;
-            uint32_t r = tid * share;
-            const uint32_t end = min(r + share, n_run_rows);
-            if (r >= end) continue;
+            const uint32_t per = min((n_run_rows + kBucketThreads - 1) / kBucketThreads, (uint32_t)kBucketBatch);
+            uint32_t r = tid * per;
+            if (r >= n_run_rows) continue;
             int run = 0;                                  // the last run that begins at or before row r
 #pragma unroll
             for (int step = kBucketThreads / 2; step > 0; step >>= 1)
                 if (run_first[run + step] <= r) run += step;
-            while (r < end && !full) {
+            for (; r < n_run_rows && !full; r += kBucketThreads * per) {
+                const uint32_t n = min(per, n_run_rows - r);
                 uint32_t at[kBucketBatch];
                 uint64_t rec[kBucketBatch];
 #pragma unroll
-                for (int u = 0; u < kBucketBatch; ++u) {  // past the share's end the last row again
-                    const uint32_t ru = min(r + u, end - 1);
-                    while (run + 1 < kBucketThreads && run_first[run + 1] <= ru) ++run;
+                for (int u = 0; u < kBucketBatch; ++u) {  // past the n-th the last row again
+                    const uint32_t ru = r + min((uint32_t)u, n - 1);
+                    if (run + 1 < kBucketThreads && run_first[run + 1] <= ru) ++run;
+                    if (run + 1 < kBucketThreads && run_first[run + 1] <= ru) {       // over the empty runs between
+#pragma unroll 1
+                        for (int step = kBucketThreads / 2; step > 0; step >>= 1)
+                            if (run + step < kBucketThreads && run_first[run + step] <= ru) run += step;
+                    }
                     at[u] = ((uint32_t)(p0 + run) << piece_rows_log2) + run_start[run] + (ru - run_first[run]);
                     rec[u] = records[at[u]];
                 }
 #pragma unroll
                 for (int u = 0; u < kBucketBatch; ++u)
-                    if (r + u < end && !full) full = !take_row(at[u], rec[u]);
-                r += kBucketBatch;
+                    if (u < (int)n && !full) full = !take_row(at[u], rec[u]);
             }
         }
         if (__syncthreads_or(full)) {
