@@ -445,6 +445,15 @@ __global__ void __launch_bounds__(64 * kReduceWaves) k_wgrad_reduce_waves(const 
     }
 }
 
+static hipError_t launch_reduce_waves(const float* part, int n_ranges, int64_t total, void* gw, fx_dtype out_dt, hipStream_t st) {
+    ProfScope ps(kProfWgradReduce, st);
+    const unsigned nb = (unsigned)((total / 4 + 63) / 64);
+    if (out_dt == FX_F32) k_wgrad_reduce_waves<FX_F32><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, gw);
+    else if (out_dt == FX_F16) k_wgrad_reduce_waves<FX_F16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, gw);
+    else k_wgrad_reduce_waves<FX_BF16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, gw);
+    return hipGetLastError();
+}
+
 // Scalar weight gradient: one thread per element of gw and per range of outputs, fp32 FMA in
 // output order; the ranges are added by k_wgrad_reduce.
 template <int DT>
@@ -667,12 +676,17 @@ extern "C" fx_status fx_sparse_conv_bwd_data(const fx_kmap* km, const void* d_go
     return strided_pair_product(km, d_gout, dt, d_w, C_out, C_in, d_gin, out_dt, st, kWeightsTransposed);
 }
 
-// Adds the ranges of part[n_ranges][total] in ascending order into gw; above 192 ranges in two levels (groups of
-// 64, then the groups), so that the first level runs at full occupancy.  The bracketing depends on n_ranges only.
+// Adds the ranges of part[n_ranges][total] in ascending order into gw; above 192 ranges by eight waves of a workgroup that meet in
+// LDS, if there are at most 512 ranges of at most 128 k elements, else in two levels (groups of 64, then the groups), so that the
+// first level runs at full occupancy.  The bracketing depends on n_ranges and total only.  Two launches -> eight waves, us: 256 ranges
+// of 27 x 32 x 32 elements 12.5 -> 6.6, of 27 x 4 x 32 11.4 -> 6.4, 384 of 27 x 64 x 64 23.7 -> 17.9; 144 ranges of that size take
+// 10.9 in one launch of either kind.
 fx_status fx::wgrad_reduce_ranges(const float* part, int n_ranges, int64_t total, void* gw, fx_dtype out_dt, hipStream_t st) {
     constexpr int kReduceGroup = 64;
     hipError_t e;
-    if (n_ranges > 3 * kReduceGroup) {
+    if (n_ranges > 3 * kReduceGroup && n_ranges <= 8 * kReduceGroup && total <= 128 * 1024 && total % 4 == 0) {
+        e = launch_reduce_waves(part, n_ranges, total, gw, out_dt, st);
+    } else if (n_ranges > 3 * kReduceGroup) {
         float* part2 = nullptr;
         const int n_groups = (n_ranges + kReduceGroup - 1) / kReduceGroup;
         FX_TRY(dev_alloc((void**)&part2, sizeof(float) * (size_t)total * n_groups, st));
@@ -809,12 +823,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // the strided maps' ranges are many and short; below 24 of them one thread's chain is as fast, and tensors of more than
     // 128 k elements fill the chip with one thread each
     if (e == hipSuccess && mfma && km->stride == 2 && n_ranges >= 24 && total <= 128 * 1024) {
-        ProfScope ps(kProfWgradReduce, st);
-        const unsigned nb = (unsigned)((total / 4 + 63) / 64);
-        if (out_dt == FX_F32) k_wgrad_reduce_waves<FX_F32><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
-        else if (out_dt == FX_F16) k_wgrad_reduce_waves<FX_F16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
-        else k_wgrad_reduce_waves<FX_BF16><<<nb, 64 * kReduceWaves, 0, st>>>(part, n_ranges, total, d_gw);
-        e = hipGetLastError();
+        e = launch_reduce_waves(part, n_ranges, total, d_gw, out_dt, st);
     } else if (e == hipSuccess) rc_red = wgrad_reduce_ranges(part, n_ranges + (mfma ? leaf_ranges : 0), total, d_gw, out_dt, st);
     dev_free(part, st);
     if (e != hipSuccess) { set_error("weight-gradient launch failed: %s", hipGetErrorString(e)); return FX_EDEVICE; }
