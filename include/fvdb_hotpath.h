@@ -261,9 +261,9 @@ void fx_kmap_destroy(fx_kmap* km);
  *     for FX_F32 with C_in not a multiple of 16) and whose shape fx_sparse_conv_leaf_fwd serves: the
  *     leaf-window kernels;
  *   - per-leaf dispatch (16-bit types, shapes of the leaf-window kernel): a sparser grid of which at least 10 % of
- *     the voxels sit in locally dense leaves (>= 205 of 512 voxels) is split inside the call -- those leaves go to
- *     the leaf-window kernel, all other outputs to the tile kernel over a second copy of the map, built on the
- *     first such call and kept with the map;
+ *     the voxels sit in locally dense leaves (>= 205 of 512 voxels) is split inside the call -- leaves with >= 144
+ *     voxels go to the leaf-window kernel, all other outputs to the tile kernel over a second copy of the map, built
+ *     on the first such call and kept with the map;
  *   - everything else: a scalar kernel (fp32 FMA in offset-then-channel order).
  * Infinite and NaN weights: the tile, gather and leaf-window kernels multiply a missing neighbour as a row of zeros, so
  * such a weight makes NaN of its column in every row they multiply it for; the wave-per-16-voxels kernel, the kernels at

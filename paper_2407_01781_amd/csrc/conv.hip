@@ -1734,7 +1734,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         // Per-leaf dispatch: a grid that mixes locally dense leaves (solid bodies) with sparse ones (thin surfaces,
-        // scan lines) is split inside this one call -- the leaves with at least kDenseLeafVoxels voxels go to the
+        // scan lines) is split inside this one call -- the leaves with at least kSplitLeafVoxels voxels go to the
         // leaf-window kernel, the outputs of all other leaves to the tile kernel over a copy of the map that leaves
         // the dense leaves' outputs out.  Taken when the grid as a whole is too sparse for the leaf-window kernel
         // (mean occupancy below 0.40) but at least 10 % of its voxels sit in dense leaves; leaf_dispatch = 2 forces it.

@@ -1,0 +1,128 @@
+"""Tiles that need about as many, and more, input rows than the tile kernels stage (816, and two buffers of them), and grids
+whose thinner leaves (144 to 204 of 512 voxels) go to the leaf-window kernels, against sums in 64 bits over the dense map,
+which other tests compare with the oracle.
+
+Tolerance: a product of two 16-bit numbers is exact in fp32; a sum of N of them in any order is off by at most 2^-24 sqrt(N)
+of its size times a small factor, N <= 27 * 128 for a row and 2e5 for a weight: 3.5e-6 of a row's norm and 2.7e-5 of an
+offset's, taken four times; results rounded to 16 bits add half a unit in the last place, at most 2^-8 (bf16) or 2^-11 (f16) of a value."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_common as H
+import paper_2407_01781_amd as fx
+
+pytestmark = pytest.mark.gpu
+
+CAP = 816
+
+
+def _index(pts):
+    return fx.build_index_grid(torch.from_numpy(np.ascontiguousarray(pts.astype(np.int32))).cuda(), np.array([[0, pts.shape[0]]]))
+
+
+def _norm_ok(y, ref, rel):
+    return bool(((y.double() - ref).flatten(1).norm(dim=1) <= rel * ref.flatten(1).norm(dim=1) + 1e-30).all())
+
+
+def _check(km, dtype, c_in, c_out):
+    half = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda").to(H.TORCH_DT[dtype])
+    x, w, gy = rand(km.g_in.num_voxels, c_in), rand(27, c_in, c_out), rand(km.n_out, c_out)
+    t = km.dense().long()
+    ref_y = torch.zeros((km.n_out, c_out), dtype=torch.float64, device="cuda")
+    ref_x = torch.zeros((x.shape[0], c_in), dtype=torch.float64, device="cuda")
+    ref_w = torch.zeros((27, c_in, c_out), dtype=torch.float64, device="cuda")
+    for k in range(27):
+        o = (t[:, k] >= 0).nonzero()[:, 0]
+        i = t[o, k]
+        ref_y[o] += x[i].double() @ w[k].double()
+        ref_x[i] += gy[o].double() @ w[k].double().t()         # an input meets an offset at most once
+        ref_w[k] = x[i].double().t() @ gy[o].double()
+    y = fx.sparse_conv_fwd(km, x, w, out=H.nan_filled(ref_y.shape, H.TORCH_DT[dtype]))
+    assert _norm_ok(y, ref_y, 1.4e-5 + half)
+    y32 = fx.sparse_conv_fwd(km, x, w, out_dtype=torch.float32, out=H.nan_filled(ref_y.shape, torch.float32))
+    assert _norm_ok(y32, ref_y, 1.4e-5) and torch.equal(y32.to(y.dtype), y)
+    assert _norm_ok(fx.sparse_conv_bwd_data(km, gy, w, out_dtype=torch.float32), ref_x, 1.4e-5)
+    assert _norm_ok(fx.sparse_conv_bwd_weight(km, x, gy, out_dtype=torch.float32), ref_w, 1.1e-4)
+
+
+def _tile_rows(km):
+    t = km.dense()
+    return [int(torch.unique(t[s:s + 512][t[s:s + 512] >= 0]).numel()) for s in range(0, km.n_out, 512)]
+
+
+def _inputs_for(g_out, rows, rng):
+    """Input voxels such that tile t of outputs two apart reads rows[t % len(rows)] different ones of its surroundings."""
+    out = g_out.ijk()[0].cpu().numpy()
+    d = np.stack(np.meshgrid(*[np.arange(-1, 2)] * 3, indexing="ij"), axis=-1).reshape(1, 27, 3)
+    have = {}
+    for t, s in enumerate(range(0, out.shape[0], 512)):
+        cells = np.unique((out[s:s + 512, None, :] + d).reshape(-1, 3), axis=0)
+        keys = [tuple(c) for c in cells]
+        want = min(rows[t % len(rows)], len(keys)) - sum(have.get(k, False) for k in keys)
+        free = [k for k in keys if k not in have]
+        for n, f in enumerate(rng.permutation(len(free))):
+            have[free[f]] = n < want                # cells that are refused stay empty, those of earlier tiles stay what they are
+    return np.array([k for k, v in have.items() if v])
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
+@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [2 * CAP - 1, 2 * CAP, 2 * CAP + 1], [2 * CAP, 100, CAP], [2500, 1200, 300, CAP + 16, 815]])
+def test_rows_of_a_tile(rows, dtype, c_in, c_out):
+    rng = np.random.default_rng(len(rows) * 1000 + rows[0])
+    lattice = np.stack(np.meshgrid(np.arange(40), np.arange(8), np.arange(56), indexing="ij"), axis=-1).reshape(-1, 3) * 2
+    g_out = _index(lattice[:17_700])
+    km = fx.build_kernel_map_onto(_index(_inputs_for(g_out, rows, rng)), g_out, 3)
+    seen = _tile_rows(km)
+    assert all(seen.count(r) >= 1 for r in rows if r <= 2 * CAP + 1), (rows, sorted(set(seen)))
+    _check(km, dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 64, 128)])
+@pytest.mark.parametrize("p", [0.24, 0.285, 0.33])
+def test_long_tiles_of_a_thin_block(p, dtype, c_in, c_out):
+    a = np.stack(np.meshgrid(np.arange(64), np.arange(48), np.arange(40), indexing="ij"), axis=-1).reshape(-1, 3)
+    km = fx.build_kernel_map(_index(a[np.random.default_rng(7).random(a.shape[0]) < p]), 3, 1)
+    assert p < 0.3 or max(_tile_rows(km)) > CAP
+    _check(km, dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 64, 128)])
+@pytest.mark.parametrize("thin", [143, 144, 204])
+def test_grid_split_with_thin_leaves(thin, dtype, c_in, c_out):
+    """Full leaves, leaves with exactly `thin` voxels and sheets through leaves, side by side: tiles that keep all, some and none
+    of their outputs."""
+    rng = np.random.default_rng(thin)
+    cell = np.stack(np.meshgrid(*[np.arange(8)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = []
+    for b, org in enumerate(np.stack(np.meshgrid(np.arange(8), np.arange(6), np.arange(7), indexing="ij"), axis=-1).reshape(-1, 3)):
+        kind = rng.integers(0, 4)
+        pick = cell if kind == 0 else cell[rng.permutation(512)[:thin]] if kind < 3 else cell[cell[:, 1] == b % 8]
+        pts.append(pick + 8 * org)
+    pts.append(np.unique(rng.integers(80, 400, size=(60_000, 3)), axis=0))       # so that the mean leaf is not dense
+    g = _index(np.concatenate(pts))
+    km = fx.build_kernel_map(g, 3, 1)
+    fx.profile_enable(True)
+    fx.profile_reset()
+    fx.sparse_conv_fwd(km, torch.zeros((g.num_voxels, c_in), device="cuda", dtype=H.TORCH_DT[dtype]),
+                       torch.zeros((27, c_in, c_out), device="cuda", dtype=H.TORCH_DT[dtype]))
+    torch.cuda.synchronize()
+    slots = fx.profile_read()
+    fx.profile_enable(False)
+    assert "k_conv_leaf" in slots and "k_conv_mfma" in slots
+    _check(km, dtype, c_in, c_out)
+
+
+def _reduction_grid(n, seed):
+    rng = np.random.default_rng(seed)
+    side = int(round(4.5 * n ** (1 / 3)))
+    return _index(np.unique(rng.integers(0, side, size=(n, 3)), axis=0))
+
+
+@pytest.mark.parametrize("n,dtype,c_in,c_out", [(98_500, "f16", 4, 32), (104_000, "f16", 4, 32), (104_000, "bf16", 32, 32), (140_000, "bf16", 64, 64),
+                                                (140_000, "f16", 8, 32), (140_000, "bf16", 32, 160)])
+def test_partial_sums_of_a_small_weight_gradient(n, dtype, c_in, c_out):
+    """192, 200 and 256 ranges: above 192 a small tensor's sums are added by eight waves."""
+    _check(fx.build_kernel_map(_reduction_grid(n, n), 3, 1), dtype, c_in, c_out)
