@@ -49,7 +49,7 @@ constexpr int32_t kTilePartial = 4;          // some outputs of the tile are lef
 // r*64 + ((q ^ ((r >> 2) & 3)) << 4); row kRowCap is all zeros.
 constexpr int kCinChunk = 32;               // input channels staged in LDS at a time (one MFMA k-step)
 constexpr int kRowBytes = kCinChunk * 2;
-constexpr int kRowCap = 792;                // LDS rows per tile
+constexpr int kRowCap = 816;                // LDS rows per tile: what 160 KB hold twice beside the id blocks (see ConvLds)
 __host__ __device__ constexpr uint32_t lds_row_code(uint32_t row) { return row * kRowBytes | (((row >> 2) & 3u) << 4); }
 constexpr int kIdBlockElems = kGroup * kGroupsPerWave;   // ids of one block (2 bytes each)
 
