@@ -370,6 +370,7 @@ struct Item {
     int slice;
     int win_lo, win_n, n_list, n_blocks, n_valid, n_staged;
     bool general, all_rows;
+    bool both_halves;      // rows that fill more than one half of the row buffer, and no more than both
 };
 
 __device__ __forceinline__ int64_t slot_work(const MetaSlot& M) {
@@ -384,11 +385,22 @@ __device__ __forceinline__ Item item_of(const MetaSlot& M, int64_t work, int nsl
     I.win_lo = uni(M.hdr.win_lo); I.win_n = uni(M.hdr.win_n); I.n_list = uni(M.hdr.n_list);
     I.n_blocks = uni(M.hdr.n_blocks); I.n_valid = uni(M.hdr.n_out);
     const int flags = uni(M.hdr.flags);
-    I.n_staged = (flags & kTileDirect) ? 0 : min(I.win_n + I.n_list, kRowCap);
+    const int n_rows = (flags & kTileDirect) ? 0 : I.win_n + I.n_list;
+    I.both_halves = n_rows > kRowCap && n_rows <= 2 * kRowCap;
+    I.n_staged = I.both_halves ? n_rows : min(n_rows, kRowCap);
     I.general = !(flags & kTileLdsOffsets);
     I.all_rows = !(flags & kTilePartial);
     return I;
 }
+
+// Phases of an item.  One whose rows need both halves of the row buffer takes turns: the producers fill both, the consumers
+// multiply, chunk after chunk, and in a last phase the producers start the next item.  The sums are the same, in the same order,
+// as when the rows past the first half were read from global memory by the lanes that need them, one dependent load ahead of
+// every multiply; bf16 64 -> 64 on 24 k voxels of a sphere shell with one such tile 39.5 -> 30.3 us (21 where no tile has as many
+// rows), 116 k LiDAR voxels 47.6 -> 38.7, 88 k / 531 k of bodies, surfaces and scan lines 114.3 -> 102.5 / 198 -> 190.  Filling the first half
+// in the item before measured the same; 16 channels a phase, pipelined like the others, 36.4 / 43.7 / 107 / 190: twice the
+// phases, each with the loads of ids and weights in front.
+__device__ __forceinline__ int item_phases(const Item& I, int nchunk) { return I.both_halves ? 2 * nchunk + 1 : nchunk; }
 
 // word e of a lane's id entry (a scalar when a wave has two groups, a vector otherwise)
 __device__ __forceinline__ uint32_t id_word(uint32_t v, int) { return v; }
@@ -405,9 +417,13 @@ __device__ __forceinline__ uint32_t id_word(const V& v, int e) { return v[e]; }
 // The pipeline runs across calls: the last two steps fetch the fragments at offsets w_after0 and
 // w_after1 -- the first two offsets of whatever this wave multiplies next -- into wa and wb, and
 // wa_at / wb_at record what the two sets hold, so that a call normally starts with both in
-// flight (and fetches them itself if a call in between was skipped).  GENERAL adds the fallback
-// for rows that are not staged in LDS.
-template <typename T, bool GENERAL, int NT, bool PARTIAL>
+// flight (and fetches them itself if a call in between was skipped).
+enum class RowsAt {
+    OneHalf,               // all rows staged in one half of the row buffer: ids are LDS offsets
+    BothHalves,            // all rows staged, in both halves: ids are row numbers
+    Anywhere,              // rows that are not staged are read from global memory
+};
+template <typename T, RowsAt ROWS, int NT, bool PARTIAL>
 __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, const unsigned char* lds_blocks,
                                              f32x16 (&acc)[kGroupsPerWave][NT],
                                              const uint32_t (&gmask)[kGroupsPerWave], uint32_t wave_mask,
@@ -449,9 +465,14 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
         // issues the same number of LDS instructions and the compiler waits for exactly the
         // fragments it needs; behind uniform branches it assumed the worst and drained the freshly
         // issued prefetch before every multiply.
-        if (GENERAL && !((gmask[gi] >> kappa) & 1u)) return;
+        if (ROWS == RowsAt::Anywhere && !((gmask[gi] >> kappa) & 1u)) return;
         const uint32_t id = (id_word(ids, gi >> 1) >> (16 * (gi & 1))) & 0xFFFFu;
-        if (GENERAL) {
+        if (ROWS == RowsAt::BothHalves) {                    // row kRowCap is the zero row; the second half's rows follow it
+            const bool staged = id < (uint32_t)n_staged;
+            const uint32_t a0 = (staged ? lds_row_code(id) + (id >= (uint32_t)kRowCap ? kRowBytes : 0) : lds_row_code(kRowCap)) ^ hsel;
+            bf[0] = *reinterpret_cast<const vec8*>(lds_rows + a0);
+            bf[1] = *reinterpret_cast<const vec8*>(lds_rows + (a0 ^ 32u));
+        } else if (ROWS == RowsAt::Anywhere) {
             const bool staged = id < (uint32_t)n_staged;
             const int row = staged ? (int)id : kRowCap;
             bf[0] = *reinterpret_cast<const vec8*>(lds_rows + lds_row_offset(row, h));
@@ -521,14 +542,14 @@ __device__ __forceinline__ void offsets_loop(const unsigned char* lds_rows, cons
 // are the same for all its chunks, so only the first chunk pays the dependent load of the halo list.
 constexpr int kSlabsPerProducer = ((kRowCap + 15) / 16 + kProducerWaves - 1) / kProducerWaves;
 
-__device__ __forceinline__ void resolve_rows(int32_t (&gr)[kSlabsPerProducer], const Item& I, int pwave, int lane,
+__device__ __forceinline__ void resolve_rows(int32_t (&gr)[kSlabsPerProducer], const Item& I, int first_row, int pwave, int lane,
                                              const int32_t* __restrict__ tile_rows, int row_stride) {
     const int32_t* my_rows = tile_rows + I.tile * (int64_t)row_stride;
 #pragma unroll
     for (int j = 0; j < kSlabsPerProducer; ++j) {
-        const int r = 16 * (pwave + kProducerWaves * j) + (lane >> 2);
+        const int at = 16 * (pwave + kProducerWaves * j) + (lane >> 2), r = first_row + at;
         gr[j] = -1;
-        if (r < I.n_staged) gr[j] = r < I.win_n ? I.win_lo + r : my_rows[r - I.win_n];
+        if (at < kRowCap && r < I.n_staged) gr[j] = r < I.win_n ? I.win_lo + r : my_rows[r - I.win_n];
     }
 }
 
@@ -635,7 +656,7 @@ __device__ __forceinline__ int first_offset(uint32_t mask) { return mask ? __ffs
 // across items: the last steps of an item already fetch the first weights of the next one (MN
 // is its slot), ahead of the write-back stores -- loads and stores retire in order, and weights
 // requested after the stores would have to wait for them.
-template <typename T, bool OUT_F32, bool GENERAL, int NT, bool PARTIAL>
+template <typename T, bool OUT_F32, RowsAt ROWS, int NT, bool PARTIAL>
 __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, const MetaSlot& MN, const Item& I, int phase,
                                              int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                              const int32_t* __restrict__ tile_rows, int row_stride,
@@ -663,6 +684,7 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
             for (int v = 0; v < 16; ++v) acc[gi][mt][v] = 0.f;
 
     for (int c = 0; c < nchunk; ++c) {
+        if (ROWS == RowsAt::BothHalves) __syncthreads();     // the producers fill both halves
         // where this wave's weights come from after this chunk
         int w_after0, w_after1;
         {
@@ -680,7 +702,7 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
         }
         if (wave_mask) {
             FX_CYCLES_BEGIN();
-            offsets_loop<T, GENERAL, NT, PARTIAL>(L.rows[(phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
+            offsets_loop<T, ROWS, NT, PARTIAL>(L.rows[ROWS == RowsAt::BothHalves ? 0 : (phase + c) & 1], L.blocks[mb], acc, gmask, wave_mask, wave_block0,
                                      reinterpret_cast<const vec8*>(wp), (uint32_t)lane * 16u,
                                      w_frag<NT>(nslice, w_kappa_stride, I.slice, c, 0), w_kappa_stride, wa, wb, wa_at, wb_at,
                                      w_after0, w_after1, n, h, I.n_staged, I.win_lo, I.win_n, my_rows, feat, pitch, c);
@@ -722,10 +744,10 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
     FX_CYCLES_ADD(tm[2]);
 }
 
-// Items whose rows are not all staged in LDS take this path: a real call, so that its registers
-// are allocated apart from the main loop's.
+// Items with more rows than one half holds take this path: a real call, so that its registers are allocated apart from the
+// main loop's.  Returns the item's phases.
 template <typename T, bool OUT_F32, int NT, bool PARTIAL>
-__device__ __noinline__ void consume_item_general(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
+__device__ __noinline__ int consume_long_item(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                                   const int32_t* __restrict__ tile_rows, int row_stride,
                                                   const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
                                                   int64_t pitch, int C_out, void* __restrict__ out, const PairArgs* again) {
@@ -737,8 +759,15 @@ __device__ __noinline__ void consume_item_general(int slot, int phase, int mb, i
     vec8 wa[2 * NT], wb[2 * NT];
     int wa_at = -1, wb_at = -1;
     unsigned long long tm[4] = {0, 0, 0, 0};
-    consume_item<T, OUT_F32, true, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane, tile_rows,
-                                   row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
+    if (I.both_halves) {
+        consume_item<T, OUT_F32, RowsAt::BothHalves, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane,
+                                   tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
+        __syncthreads();                                     // the producers fill a half for the next item
+    } else {
+        consume_item<T, OUT_F32, RowsAt::Anywhere, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane,
+                                   tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
+    }
+    return item_phases(I, nchunk);
 }
 
 // Persistent workgroups, one per compute unit.  Work items (tile of 512 consecutive outputs x
@@ -820,8 +849,10 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         if (slot_work(L.meta[0]) >= 0) {       // a workgroup whose static item is another's start may find nothing left
             const Item cur = item_of(L.meta[0], slot_work(L.meta[0]), nslice);
             produce_meta(L.blocks[0], L.perm[0], cur, pwave, lane, tile_perm, tile_blocks, block_stride);
-            resolve_rows(gr, cur, pwave, lane, tile_rows, row_stride);
-            produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, 0);
+            if (!cur.both_halves) {
+                resolve_rows(gr, cur, 0, pwave, lane, tile_rows, row_stride);
+                produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, 0);
+            }
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -831,22 +862,38 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             const int64_t work = slot_work(M);
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
-            for (int c = 0; c < nchunk; ++c, ++phase) {
+            const int n_phases = item_phases(cur, nchunk);
+            int32_t gr2[kSlabsPerProducer];
+            if (cur.both_halves) {
+                resolve_rows(gr, cur, 0, pwave, lane, tile_rows, row_stride);
+                resolve_rows(gr2, cur, kRowCap, pwave, lane, tile_rows, row_stride);
+            }
+            for (int p = 0; p < n_phases; ++p, ++phase) {
                 const int rb = (phase + 1) & 1;
-                if (c != nchunk - 1) produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
+                const bool last = p == n_phases - 1;
+                if (cur.both_halves) {
+                    if (!last && !(p & 1)) {
+                        produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, p >> 1);
+                        produce_rows_resolved<PARTIAL>(L.rows[1], gr2, pwave, lane, feat, pitch, p >> 1);
+                    }
+                } else if (!last) {
+                    produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, p + 1);
+                }
                 // At one chunk an item two chains of dependent loads side by side: the next item's row numbers and the claim of
                 // the item that starts two phases from now, then the rows and that item's header.  (One after the other they were longer than a
                 // phase's multiplies at one chunk an item: f16 32 -> 32 on 221 k voxels 36.0 -> 34.7 us, on 980 k 72 -> 71.)
-                const int64_t nwork = c == nchunk - 1 ? slot_work(L.meta[(item_no + 1) % kMetaSlots]) : -1;
-                if (nwork >= 0) resolve_rows(gr, item_of(L.meta[(item_no + 1) % kMetaSlots], nwork, nslice), pwave, lane, tile_rows, row_stride);
-                const bool claims = pwave == 0 && (phase + 2) % nchunk == 0;
+                const MetaSlot& MN = L.meta[(item_no + 1) % kMetaSlots];
+                const int64_t nwork = last ? slot_work(MN) : -1;
+                const bool next_rows = nwork >= 0 && !item_of(MN, nwork, nslice).both_halves;      // else they are staged by the next item
+                if (next_rows) resolve_rows(gr, item_of(MN, nwork, nslice), 0, pwave, lane, tile_rows, row_stride);
+                const bool claims = pwave == 0 && p == (nchunk == 1 ? 0 : n_phases - (cur.both_halves ? 3 : 2));   // ahead of the phase that looks at it
                 const int64_t claimed = claims ? take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, n_orphans, open_lists) : -1;
                 if (nwork >= 0) {
-                    const Item nxt = item_of(L.meta[(item_no + 1) % kMetaSlots], nwork, nslice);
-                    produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
-                    produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], nxt, pwave, lane, tile_perm, tile_blocks, block_stride);
+                    if (next_rows) produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
+                    produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], item_of(MN, nwork, nslice), pwave, lane, tile_perm,
+                                 tile_blocks, block_stride);
                 }
-                if (claims) announce_claimed(L.meta[((phase + 2) / nchunk) % kMetaSlots], claimed);
+                if (claims) announce_claimed(L.meta[(item_no + (nchunk == 1 ? 2 : 1)) % kMetaSlots], claimed);
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();
             }
@@ -872,22 +919,23 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         }
         __syncthreads();
         int phase = 0, n_items = 0;
-        for (int item_no = 0;; ++item_no, phase += nchunk) {
+        for (int item_no = 0;; ++item_no) {
             const int slot = item_no % kMetaSlots;
             const MetaSlot& M = L.meta[slot];
             const int64_t work = slot_work(M);
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
             if (cur.general) {
-                consume_item_general<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows, row_stride,
-                                                 feat, wp, pitch, C_out, out, again);
+                phase += consume_long_item<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows,
+                                                                    row_stride, feat, wp, pitch, C_out, out, again);
                 wa_at = wb_at = -1;       // nothing is handed over a call
 #pragma unroll
                 for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
             } else {
-                consume_item<T, OUT_F32, false, NT, PARTIAL>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
+                consume_item<T, OUT_F32, RowsAt::OneHalf, NT, PARTIAL>(L, M, L.meta[(item_no + 1) % kMetaSlots], cur, phase, item_no & 1, item_no % 3, nchunk, nslice,
                                                 wave, lane, tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at,
                                                 wb_at, again, tm);
+                phase += nchunk;
             }
             ++n_items;
         }
