@@ -43,8 +43,9 @@ __device__ __forceinline__ typename Elem<T>::vec8 pack8(const f32x16& t, int fir
 //      (channels 32cb + lane % 32) and accumulates
 //      gw[kappa][ci][co] += sum_voxel feat[voxel][ci] * gout[voxel][co].
 // A voxel of the block without that tap reads the zero row and adds nothing; a slot past the end
-// of the last tile has a zero gout row.  Tiles whose rows are not all staged in LDS keep the older form
-// of step 1: the lane reads the row of voxel lane % 32 (from LDS or from global memory), and a product with
+// of the last tile has a zero gout row.  A tile of 817 to 1022 rows (more than a half of the forward kernel's buffer, so that the
+// map holds row numbers for it) is staged like the others and its ids become LDS offsets once they are staged.  Tiles whose rows do
+// not fit keep the older form of step 1: the lane reads the row of voxel lane % 32 (from LDS or from global memory), and a product with
 // the identity on the matrix unit leaves the block in the accumulator layout, which is the operand layout
 // with voxels along k; rounding back to the storage type is exact.
 // Partial sums go to part[range][kappa][ci][co] (fp32); k_wgrad_reduce adds the ranges in
@@ -53,23 +54,26 @@ constexpr int kGoutRowBytes = kWgCo * 2;    // one slot of the staged gout tile
 constexpr int kGoutSlabs = kTileT * kGoutRowBytes / 1024;     // 1 KB slabs: 8 slots each
 
 struct WgradLds {
-    unsigned char rows[kRowBufBytes];
+    unsigned char rows[(kWgRowCap + 1) * kRowBytes];       // rows kWgRowCap and, for ids made by the map, kRowCap are all zeros
     unsigned char blocks[kBlockBufBytes];
     unsigned char gt[kTileT * kGoutRowBytes];
 };
 static_assert(sizeof(WgradLds) <= 160 * 1024, "LDS budget of one compute unit");
 static_assert(kGroupsPerWave == 4 && kTileWaves == 4, "id blocks of four column blocks, 8 bytes per voxel");
 
-// Which tiles a launch takes.  Tiles whose rows are all staged in LDS (kTileLdsOffsets; all but one or two of a
-// sparse grid's) need neither the identity fragments nor the fallback loads of the older form: without that code the
+// Which tiles a launch takes.  Tiles whose rows are all staged in LDS (wgrad_stages; all of most submanifold maps') need
+// neither the identity fragments nor the fallback loads of the older form: without that code the
 // kernel fits 128 registers, runs sixteen waves with two offsets each -- four waves per SIMD to cover each other's
 // LDS latencies -- and took 150 us where the eight-wave kernel with both forms took 204 (1 M-voxel LiDAR grid,
 // 64 -> 64); 30 us of those 204 were one workgroup's single tile of the other kind, which costs as much as four
 // staged ones.  When the map has at most kMaxListedTiles such tiles (counted once per map), kWgStaged (16 waves)
 // takes the staged tiles of the ranges, and k_wgrad_pairs the listed ones, a wave per offset.  Other maps (between two
-// grids, dense grids, whose tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of
+// grids, whose tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of
 // kWgAll (8 waves, both forms, every tile of the range).  Either way a partial sum is made of the same terms in a
-// fixed order.
+// fixed order.  With 816 rows staged, tiles above went to the pairs or, from 0.20 mean leaf occupancy on, the map to kWgAll; with
+// 1022, bf16 64 -> 64, us: 24 k voxels of a sphere shell 38.8 -> 27.3, 116 k of LiDAR 48 -> 39, 195 k of sheets 61 -> 52, 88 k / 531 k of
+// bodies, surfaces and scan lines 86 -> 74 / 235 -> 214; random voxels of a cube, 239 k at 0.18 of its volume 89.8 -> 65.6, 399 k at 0.30
+// 191 -> 105.5; 40 -> 40 on 505 k at 0.38 303 -> 134.
 enum WgradMode { kWgAll = 0, kWgStaged = 1 };
 
 //
@@ -109,7 +113,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     const int ci_n = kMasked ? C_in - cib * kWgCi : kWgCi, co_n = kMasked ? C_out - cob * kWgCo : kWgCo;
     const int64_t t0 = n_tiles * range / n_ranges, t1 = n_tiles * (range + 1) / n_ranges;
 
-    if (tid < kRowBytes / 16) reinterpret_cast<u32x4*>(L.rows + kRowCap * kRowBytes)[tid] = u32x4{0, 0, 0, 0};
+    if (tid < kRowBytes / 16) reinterpret_cast<u32x4*>(L.rows + kWgRowCap * kRowBytes)[tid] = u32x4{0, 0, 0, 0};
 
     // identity fragments: element e of lane (n, h) in k-step ks is row k = 8h + e, column n of [I16 at columns 16ks..]
     vec8 ident[2];
@@ -138,13 +142,13 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     // what this lane's address contributes to a transposing read: voxel jv of four, channels 16*g1 + 4*q .. + 3
     const int q = lane & 3, jv = (lane >> 2) & 3, g1 = (lane >> 4) & 1;
     const uint32_t a_piece = (uint32_t)(2 * g1 + (q >> 1)) << 4, half8 = (uint32_t)(q & 1) << 3;
-    constexpr int kWgSlabs = ((kRowCap + 15) / 16 + kWgWaves - 1) / kWgWaves;   // 1 KB row slabs per wave
+    constexpr int kWgSlabs = ((kWgRowCap + 15) / 16 + kWgWaves - 1) / kWgWaves;   // 1 KB row slabs per wave
     int32_t nx_gr[kWgSlabs];
     int nx_local[kGoutSlabsPerWave];      // output row (inside the tile) of the slot this lane stages in each of its slabs
     auto resolve = [&](int64_t t) {
         const TileHeader* Ht = tile_hdr + t;
         const int fl = uni(Ht->flags), wl = uni(Ht->win_lo), wn = uni(Ht->win_n), nl = uni(Ht->n_list);
-        const int ns = (fl & kTileDirect) ? 0 : min(wn + nl, kRowCap);
+        const int ns = (fl & kTileDirect) ? 0 : min(wn + nl, kWgRowCap);
         const int32_t* rows_t = tile_rows + t * (int64_t)row_stride;
 #pragma unroll
         for (int j = 0; j < kWgSlabs; ++j) {
@@ -158,7 +162,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
     // the tiles that this workgroup takes, in order: those of its range (kWgStaged: the staged ones among them)
     auto next_mine = [&](int64_t c) {
         if (MODE == kWgStaged)
-            while (c < t1 && !(uni(tile_hdr[c].flags) & kTileLdsOffsets)) ++c;
+            while (c < t1 && !wgrad_stages(uni(tile_hdr[c].flags), uni(tile_hdr[c].win_n), uni(tile_hdr[c].n_list))) ++c;
         return c;
     };
     int64_t cur = next_mine(t0);
@@ -169,8 +173,9 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         const TileHeader* H = tile_hdr + tile;
         const int flags = uni(H->flags), win_lo = uni(H->win_lo), win_n = uni(H->win_n), n_list = uni(H->n_list);
         const int n_blocks = uni(H->n_blocks), n_valid = uni(H->n_out);
-        const int n_staged = (flags & kTileDirect) ? 0 : min(win_n + n_list, kRowCap);
-        const bool general = MODE == kWgStaged ? false : !(flags & kTileLdsOffsets);
+        const int n_staged = (flags & kTileDirect) ? 0 : min(win_n + n_list, kWgRowCap);
+        const bool general = MODE == kWgStaged ? false : !wgrad_stages(flags, win_n, n_list);
+        const bool row_ids = !general && !(flags & kTileLdsOffsets);
         const int32_t* my_rows = tile_rows + tile * (int64_t)row_stride;
         uint32_t wmask[kTileWaves], gmask[kGroupsPerTile];
         int block0[kTileWaves];
@@ -218,10 +223,20 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 const int off = s * 1024 + lane * 16;
                 if (off < bytes) __builtin_amdgcn_global_load_lds(bsrc + off, (lds_ptr_t)(L.blocks + s * 1024), 16, 0, 0);
             }
+            // the zero row that the map's LDS offsets name; a tile of row numbers may have put a row there
+            if ((flags & kTileLdsOffsets) && tid < kRowBytes / 16) reinterpret_cast<u32x4*>(L.rows + kRowCap * kRowBytes)[tid] = u32x4{0, 0, 0, 0};
             if (cur_next < t1) resolve(cur_next);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        if (row_ids) {          // row numbers -> LDS offsets, two to a word
+            uint32_t* words = reinterpret_cast<uint32_t*>(L.blocks);
+            for (int i = tid; i < n_blocks * kIdBlockElems / 2; i += 64 * W) {
+                const uint32_t v = words[i];
+                words[i] = lds_row_code(min(v & 0xFFFFu, (uint32_t)kWgRowCap)) | lds_row_code(min(v >> 16, (uint32_t)kWgRowCap)) << 16;
+            }
+            __syncthreads();
+        }
 
         // ---- multiply
 #pragma unroll
@@ -254,12 +269,12 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                             if (!((gmask[tile_group_of(fw, gj)] >> kappa) & 1u)) continue;
                             const uint32_t id = (ids[gj >> 1] >> (16 * (gj & 1))) & 0xFFFFu;
                             const bool staged = id < (uint32_t)n_staged;
-                            const int row = staged ? (int)id : kRowCap;
+                            const int row = staged ? (int)id : kWgRowCap;
                             // pieces h and h + 2 of the row; a piece beyond the row's end is zero (the identity product
                             // below sums over all 32 channels)
                             const bool has0 = h * 8 < ci_n, has1 = h * 8 + 16 < ci_n;
-                            ga[gj & 1][0] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has0 ? row : kRowCap, h));
-                            ga[gj & 1][1] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has1 ? row : kRowCap, h + 2));
+                            ga[gj & 1][0] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has0 ? row : kWgRowCap, h));
+                            ga[gj & 1][1] = *reinterpret_cast<const vec8*>(L.rows + lds_row_offset(has1 ? row : kWgRowCap, h + 2));
                             if (!staged && id != kNoRow) {
                                 const int64_t gr = id < (uint32_t)win_n ? (int64_t)win_lo + id : (int64_t)my_rows[id - win_n];
                                 const uint16_t* src = feat + gr * C_in + cib * kWgCi + h * 8;

@@ -77,6 +77,14 @@ struct TileHeader {
     uint32_t wave_block0[kTileWaves];       // first id block of each wave
 };
 
+// Rows of a tile that the weight-gradient kernel holds: its LDS takes one buffer of them, not two, and its ids become 16-bit
+// LDS offsets there.
+constexpr int kWgRowCap = 1022;
+static_assert(lds_row_code(kWgRowCap) < 65536 - kRowBytes, "16-bit LDS offsets");
+__host__ __device__ inline bool wgrad_stages(int flags, int win_n, int n_list) {
+    return (flags & kTileLdsOffsets) || (!(flags & kTileDirect) && win_n + n_list <= kWgRowCap);
+}
+
 }  // namespace fx
 
 struct fx_kmap {
@@ -105,7 +113,7 @@ struct fx_kmap {
     int32_t row_stride = 0, block_stride = 0;
     int64_t* d_stats = nullptr;             // [4 + K3]: MFMA rows issued, staged rows, direct tiles, tiled bytes, pairs per offset
     void* d_alloc = nullptr;                // single allocation backing all of the above
-    // Tiles whose rows are not all staged in LDS (no kTileLdsOffsets): their number (-1: not counted yet) and the
+    // Tiles whose rows the weight-gradient kernel does not hold (see wgrad_stages): their number (-1: not counted yet) and the
     // first kMaxListedTiles of them in ascending order; counted on the first weight gradient over the map.
     int32_t h_n_unstaged = -1;
     int32_t* d_unstaged_list = nullptr;

@@ -1202,7 +1202,7 @@ fx_status fx::kmap_ensure_mixed(fx_kmap* km, hipStream_t st) {
     return build_map(km->gin, km->gout, 3, 1, false, st, &km->mixed, kSplitLeafVoxels);
 }
 
-// One workgroup: the tiles without kTileLdsOffsets, counted and (the first `cap`) listed in ascending order; the count
+// One workgroup: the tiles whose rows the weight-gradient kernel does not hold, counted and (the first `cap`) listed in ascending order; the count
 // goes to pinned host memory, then the ticket.
 __global__ void __launch_bounds__(1024) k_list_unstaged_tiles(const TileHeader* __restrict__ tile_hdr, int64_t n_tiles,
                                                               int32_t* __restrict__ list, int cap, int32_t* __restrict__ host_count,
@@ -1212,7 +1212,7 @@ __global__ void __launch_bounds__(1024) k_list_unstaged_tiles(const TileHeader* 
     uint32_t base = 0;
     for (int64_t t0 = 0; t0 < n_tiles; t0 += 1024) {
         const int64_t t = t0 + tid;
-        const bool hit = t < n_tiles && !(tile_hdr[t].flags & kTileLdsOffsets);
+        const bool hit = t < n_tiles && !wgrad_stages(tile_hdr[t].flags, tile_hdr[t].win_n, tile_hdr[t].n_list);
         const uint64_t votes = __ballot(hit);
         if (lane == 0) wave_count[wave] = (uint32_t)__popcll(votes);
         __syncthreads();

@@ -1,4 +1,5 @@
-"""Tiles that need about as many, and more, input rows than the tile kernels stage (816, and two buffers of them), and grids
+"""Tiles that need about as many, and more, input rows than the tile kernels stage (816, two buffers of them, 1022 for the
+weight gradient), and grids
 whose thinner leaves (144 to 204 of 512 voxels) go to the leaf-window kernels, against sums in 64 bits over the dense map,
 which other tests compare with the oracle.
 
@@ -69,7 +70,7 @@ def _inputs_for(g_out, rows, rng):
 
 
 @pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
-@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [2 * CAP - 1, 2 * CAP, 2 * CAP + 1], [2 * CAP, 100, CAP], [2500, 1200, 300, CAP + 16, 815]])
+@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [2 * CAP - 1, 2 * CAP, 2 * CAP + 1], [2 * CAP, 100, CAP], [1021, 1022, 500, 1023, 400], [2500, 1200, 300, CAP + 16, 815]])
 def test_rows_of_a_tile(rows, dtype, c_in, c_out):
     rng = np.random.default_rng(len(rows) * 1000 + rows[0])
     lattice = np.stack(np.meshgrid(np.arange(40), np.arange(8), np.arange(56), indexing="ij"), axis=-1).reshape(-1, 3) * 2
