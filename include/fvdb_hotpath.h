@@ -257,13 +257,14 @@ void fx_kmap_destroy(fx_kmap* km);
  *     v_mfma_f32_16x16x4_f32, true fp32 products as well; few tiles of any other fp32 shape: the scalar kernel;
  *   - FX_F16 / FX_BF16 with C_in <= 16 on maps with a dense table: v_mfma_f32_32x32x16 with (offset, channel) as the
  *     contracted dimension;
- *   - on a 3x3x3 stride-1 submanifold map whose grid is locally dense (mean leaf occupancy >= 0.40, or >= 0.08
+ *   - on a 3x3x3 stride-1 submanifold map whose grid is locally dense (mean leaf occupancy >= 0.40, of the 16-bit
+ *     types >= 0.60 from 16 k voxels on, or >= 0.08
  *     for FX_F32 with C_in not a multiple of 16) and whose shape fx_sparse_conv_leaf_fwd serves: the
  *     leaf-window kernels;
- *   - per-leaf dispatch (16-bit types, shapes of the leaf-window kernel): a sparser grid of which at least 10 % of
- *     the voxels sit in locally dense leaves (>= 205 of 512 voxels) is split inside the call -- leaves with >= 144
- *     voxels go to the leaf-window kernel, all other outputs to the tile kernel over a second copy of the map, built
- *     on the first such call and kept with the map;
+ *   - per-leaf dispatch (16-bit types, shapes of the leaf-window kernel): a grid of mean occupancy below 0.40 of which
+ *     at least 55 % of the voxels sit in locally dense leaves (>= 205 of 512 voxels) is split inside the call -- those
+ *     leaves go to the leaf-window kernel, all other outputs to the tile kernel over a second copy of the map, built on
+ *     the first such call and kept with the map;
  *   - everything else: a scalar kernel (fp32 FMA in offset-then-channel order).
  * Infinite and NaN weights: the tile, gather and leaf-window kernels multiply a missing neighbour as a row of zeros, so
  * such a weight makes NaN of its column in every row they multiply it for; the wave-per-16-voxels kernel, the kernels at

@@ -75,12 +75,6 @@ constexpr int kUpperWords = 32 * 32 * 32 / 64;  // 512 child-mask words per uppe
 constexpr int kLowerWords = 16 * 16 * 16 / 64;  // 64 child-mask words per lower node
 // a leaf counts as locally dense from 40 % occupancy on (Sec. 3.5: the dense-window operators win from there)
 constexpr int kDenseLeafVoxels = 205;
-// In a grid that is split per leaf (see conv_apply) the leaf-window kernels take leaves from here on: a leaf of 144 to 204
-// voxels is mostly a piece of a body's surface, whose tiles need more rows than the tile kernel's LDS holds.  bf16, from 205 / 160 /
-// 144 / 128 / 112 / 96 voxels on, us, 64 -> 64 on 531 k voxels of bodies, surfaces and scan lines, forward 217 / 215 / 200 / 202 /
-// 203 / 200, weight gradient 262 / 243 / 238 / 252 / 272 / 281; on 245 k 151 / 145 / 134 / 134 / 129 / 133, 145 / 143 / 143 / 143 / 141 / 156;
-// 128 -> 128 on 72 k 294 / 273 / 270 / 276 / 267 / 218, 131 / 129 / 129 / 130 / 135 / 135.
-constexpr int kSplitLeafVoxels = 144;
 constexpr int kMaxTiles = 65536;                // root tiles per batch (documented limit)
 constexpr int kTileHashSlots = 1 << 17;
 

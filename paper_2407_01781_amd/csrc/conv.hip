@@ -1774,7 +1774,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
     const bool force_scalar = option(kOptForceScalar) == 1;
     // Locally dense grids (Sec. 3.5 scenarios 1-2): on a 3x3x3 stride-1 map the leaf-window kernels compute the same
     // sum from the grid alone and are faster once the leaves are full enough -- the tiles of such a map need more
-    // rows than the tile kernel's LDS holds -- and, at fp32 depths that the tile kernel does not take, almost
+    // rows than the tile kernel's LDS holds twice -- and, at fp32 depths that the tile kernel does not take, almost
     // everywhere.  Option leaf_dispatch = 0 keeps the kernel-map kernels, = 1 takes the leaf kernels whenever
     // they serve the shape.
     if (km->K == 3 && km->stride == 1 && km->gin == km->gout && (mode == kWeightsForward || mode == kWeightsMirrored) &&
@@ -1782,13 +1782,19 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         // Per-leaf dispatch: a grid that mixes locally dense leaves (solid bodies) with sparse ones (thin surfaces,
-        // scan lines) is split inside this one call -- the leaves with at least kSplitLeafVoxels voxels go to the
+        // scan lines) is split inside this one call -- the leaves with at least kDenseLeafVoxels voxels go to the
         // leaf-window kernel, the outputs of all other leaves to the tile kernel over a copy of the map that leaves
         // the dense leaves' outputs out.  Taken when the grid as a whole is too sparse for the leaf-window kernel
-        // (mean occupancy below 0.40) but at least 10 % of its voxels sit in dense leaves; leaf_dispatch = 2 forces it.
+        // (mean occupancy below 0.40) and most of its voxels (55 %) sit in dense leaves; leaf_dispatch = 2 forces it.
+        // bf16 64 -> 64, split / tiles alone, us: a full cube of 885 k voxels and a thin cloud, 70 % of the voxels in the cube 323 / 328,
+        // 90 % 290 / 292 (128 -> 128 994 / 1045, 892 / 936), 50 % 383 / 379; bodies, surfaces and scan lines, 245 k (45 % in dense
+        // leaves) 118 / 84, 531 k (48 %) 190 / 128, though also 168 k (58 %) 122 / 69 and 697 k (62 %) 220 / 190.
+        // From 0.40 on the leaf-window kernel takes the whole of a small grid (below 16 k voxels), and of any from 0.60 on (tiles /
+        // leaf window: random voxels of a cube, 97 k at 0.37 46 / 74, 119 k at 0.45 50 / 76, 732 k at 0.52 241 / 260, 865 k at 0.62 294 / 277,
+        // 1.33 M at 0.96 464 / 340; small solid cubes of 33 k and 111 k 32 / 42 and 46 / 81).
         if (in_dt != FX_F32 && !km->is_inverse) {
             const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
-            if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.10)) {
+            if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.55)) {
                 fx_kmap* kmw = const_cast<fx_kmap*>(km);
                 FX_TRY(kmap_ensure_mixed(kmw, st));
                 void* wp = nullptr;
@@ -1801,7 +1807,8 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
             }
         }
         const bool scalar_otherwise = in_dt == FX_F32 && C_in % 16 != 0;
-        const bool take = ld >= 0 ? ld >= 1 : occupancy >= (scalar_otherwise ? 0.08 : 0.40);
+        const double line = scalar_otherwise ? 0.08 : in_dt != FX_F32 && km->n_in >= 16384 ? 0.60 : 0.40;
+        const bool take = ld >= 0 ? ld >= 1 : occupancy >= line;
         if (take)
             return leaf_apply("sparse convolution (leaf-window kernels)", km->gin, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt,
                               st, mode);

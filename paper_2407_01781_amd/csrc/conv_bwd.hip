@@ -720,14 +720,19 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     }
     // fp32 at low depth on a 3x3x3 submanifold map: the leaf-window kernel sums on the matrix units straight from
     // the grid, where everything below would take the scalar kernel (option leaf_dispatch = 0 keeps that one)
-    // The 16-bit types at depth >= 32 take it on locally dense grids only (mean leaf occupancy of 0.40 and above, the
-    // forward pass's rule): there the tiles of the map need more rows than the tile kernel's LDS holds
-    // (option leaf_dispatch = 1 takes it on any grid).
+    // The 16-bit types at depth >= 32 take it on locally dense grids only (mean leaf occupancy of 0.40 and above): there the
+    // tiles of the map need more rows than the tile kernel's LDS holds.  Below 0.60, where all but a few of the map's tiles
+    // are staged, the tiles are faster (bf16 64 -> 64, tiles / leaf window, us: random voxels of a cube, 119 k at 0.45 of its leaves,
+    // many tiles not staged, 71 / 71, 598 k at 0.43, all staged, 170 / 253).  Option leaf_dispatch = 1 takes it on any grid.
     if (km->K == 3 && km->stride == 1 && km->gin == km->gout && leaf_wgrad_shape_supported(dt, C_in, C_out) &&
         !force_scalar()) {
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
-        const bool take = dt == FX_F32 ? ld != 0 : (ld >= 0 ? ld == 1 : occupancy >= 0.40);
+        bool take = dt == FX_F32 ? ld != 0 : (ld >= 0 ? ld == 1 : occupancy >= 0.40);
+        if (take && dt != FX_F32 && ld < 0 && occupancy < 0.60) {
+            FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
+            take = km->n_tiles == 0 || km->h_n_unstaged > kMaxListedTiles;
+        }
         if (take)
             return leaf_wgrad("sparse convolution weight gradient (leaf-window kernel)", km->gin, d_feat, d_gout, dt, C_in,
                               C_out, d_gw, out_dt, st);
@@ -744,13 +749,20 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // Per-leaf dispatch, as in the forward pass: on a grid that mixes locally dense leaves with sparse ones the pairs
     // of the dense leaves' outputs are summed by the leaf-window kernel (over the list of those leaves) and all
     // others by the tile kernel over the copy of the map that leaves those outputs out; both write partial sums of
-    // the same form and one ordered reduction adds them.  leaf_dispatch = 2 forces it.
+    // the same form and one ordered reduction adds them.  Not where all but a few of the whole map's tiles are staged (bf16 64 -> 64,
+    // split / tiles alone, us: a full cube and a thin cloud of 1.26 M voxels 477 / 305; bodies, surfaces and scan lines of 531 k, four
+    // in ten tiles not staged, 226 / 261).  leaf_dispatch = 2 forces it.
     int leaf_ranges = 0;
     if (mfma && km->K == 3 && km->stride == 1 && km->gin == km->gout && !km->is_inverse && leaf_wgrad_shape_supported(dt, C_in, C_out)) {
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
-        if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.10)) {
+        bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10;
+        if (split) {
+            FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
+            split = km->h_n_unstaged > kMaxListedTiles;
+        }
+        if (ld == 2 || split) {
             FX_TRY(kmap_ensure_mixed(const_cast<fx_kmap*>(km), st));
             leaf_ranges = leaf_wgrad16_ranges(km->gin, C_in, C_out);
         }

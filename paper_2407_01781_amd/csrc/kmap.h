@@ -101,7 +101,7 @@ struct fx_kmap {
     // outputs of locally dense leaves left out, and the list of those leaves for the leaf-window kernel.  Built on
     // the first convolution that splits the grid; `mixed` owns the list.
     fx_kmap* mixed = nullptr;
-    int32_t* d_dense_leaves = nullptr;      // [n_leaf] leaf ids with at least kSplitLeafVoxels voxels (first *d_n_dense entries)
+    int32_t* d_dense_leaves = nullptr;      // [n_leaf] leaf ids with at least kDenseLeafVoxels voxels (first *d_n_dense entries)
     int32_t* d_n_dense = nullptr;
     // tiled form
     int64_t n_tiles = 0;

@@ -1199,7 +1199,7 @@ fx_status fx::kmap_ensure_mixed(fx_kmap* km, hipStream_t st) {
         return FX_EUNSUPPORTED;
     }
     fx_grid_retain(km->gout);                  // build_map takes over one reference to the grid of the produced rows
-    return build_map(km->gin, km->gout, 3, 1, false, st, &km->mixed, kSplitLeafVoxels);
+    return build_map(km->gin, km->gout, 3, 1, false, st, &km->mixed, kDenseLeafVoxels);
 }
 
 // One workgroup: the tiles whose rows the weight-gradient kernel does not hold, counted and (the first `cap`) listed in ascending order; the count

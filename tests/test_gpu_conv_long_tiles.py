@@ -1,7 +1,6 @@
 """Tiles that need about as many, and more, input rows than the tile kernels stage (816, two buffers of them, 1022 for the
-weight gradient), and grids
-whose thinner leaves (144 to 204 of 512 voxels) go to the leaf-window kernels, against sums in 64 bits over the dense map,
-which other tests compare with the oracle.
+weight gradient), grids split between the tile and leaf-window kernels, and the lines between those kernels, against sums in 64
+bits over the dense map, which other tests compare with the oracle.
 
 Tolerance: a product of two 16-bit numbers is exact in fp32; a sum of N of them in any order is off by at most 2^-24 sqrt(N)
 of its size times a small factor, N <= 27 * 128 for a row and 2e5 for a weight: 3.5e-6 of a row's norm and 2.7e-5 of an
@@ -91,10 +90,11 @@ def test_long_tiles_of_a_thin_block(p, dtype, c_in, c_out):
 
 
 @pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 64, 128)])
-@pytest.mark.parametrize("thin", [143, 144, 204])
-def test_grid_split_with_thin_leaves(thin, dtype, c_in, c_out):
+@pytest.mark.parametrize("thin", [144, 204, 205])
+def test_grid_split_with_thin_leaves(thin, dtype, c_in, c_out, fx_opt):
     """Full leaves, leaves with exactly `thin` voxels and sheets through leaves, side by side: tiles that keep all, some and none
     of their outputs."""
+    fx_opt("leaf_dispatch", 2)
     rng = np.random.default_rng(thin)
     cell = np.stack(np.meshgrid(*[np.arange(8)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
     pts = []
@@ -127,3 +127,21 @@ def _reduction_grid(n, seed):
 def test_partial_sums_of_a_small_weight_gradient(n, dtype, c_in, c_out):
     """192, 200 and 256 ranges: above 192 a small tensor's sums are added by eight waves."""
     _check(fx.build_kernel_map(_reduction_grid(n, n), 3, 1), dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("p,thick,dtype,c_in,c_out", [(0.38, 28, "bf16", 64, 64), (0.47, 24, "bf16", 64, 64), (0.47, 48, "f16", 32, 64), (0.57, 40, "bf16", 96, 64),
+                                                      (0.62, 40, "bf16", 64, 64), (1.0, 20, "f16", 64, 64), (1.0, 40, "bf16", 64, 128)])
+def test_either_side_of_the_lines_of_dense_grids(p, thick, dtype, c_in, c_out):
+    """Random voxels of a cube of whole leaves and solid cubes across them: mean occupancies below 0.40, to 0.60 and above, of fewer
+    and more than 16 k voxels, weight gradients with few and with many tiles that are not staged."""
+    a = np.stack(np.meshgrid(*[np.arange(thick)] * 3, indexing="ij"), axis=-1).reshape(-1, 3) - 4 * (thick % 16 != 0)
+    _check(fx.build_kernel_map(_index(a[np.random.default_rng(8).random(a.shape[0]) < p]), 3, 1), dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("share", [0.5, 0.6])
+def test_either_side_of_the_line_of_a_split(share):
+    """Full leaves with half and with six tenths of a grid's voxels."""
+    rng = np.random.default_rng(9)
+    cloud = np.unique(rng.integers(100, 300, size=(int(13_824 * (1 - share) / share), 3)), axis=0)
+    cube = np.stack(np.meshgrid(*[np.arange(24)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    _check(fx.build_kernel_map(_index(np.concatenate([cube, cloud])), 3, 1), "bf16", 64, 64)
