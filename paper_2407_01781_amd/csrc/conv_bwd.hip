@@ -731,7 +731,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         bool take = dt == FX_F32 ? ld != 0 : (ld >= 0 ? ld == 1 : occupancy >= 0.40);
         if (take && dt != FX_F32 && ld < 0 && occupancy < 0.60) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
-            take = km->n_tiles == 0 || km->h_n_unstaged > kMaxListedTiles;
+            take = km->n_tiles == 0 || !kmap_few_unstaged(km);
         }
         if (take)
             return leaf_wgrad("sparse convolution weight gradient (leaf-window kernel)", km->gin, d_feat, d_gout, dt, C_in,
@@ -760,7 +760,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10;
         if (split) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
-            split = km->h_n_unstaged > kMaxListedTiles;
+            split = !kmap_few_unstaged(km);
         }
         if (ld == 2 || split) {
             FX_TRY(kmap_ensure_mixed(const_cast<fx_kmap*>(km), st));
@@ -793,7 +793,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         bool split = km->stride == 1 && km->gin == km->gout && !km->is_inverse;
         if (split) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
-            split = km->h_n_unstaged <= kMaxListedTiles;
+            split = kmap_few_unstaged(km);
         }
         const int n_listed = split ? km->h_n_unstaged : 0;
         const int list_ranges = n_listed > 0 ? wgrad_pairs_ranges(km, C_in, C_out, n_listed) : 0;

@@ -145,6 +145,8 @@ fx_status kmap_ensure_mixed(fx_kmap* km, hipStream_t st);
 // host copies of the map's statistics (pairs per offset, tiling figures); synchronises the build stream once
 fx_status kmap_fetch_stats(fx_kmap* km);
 constexpr int kMaxListedTiles = 16;
-// km->h_n_unstaged / d_unstaged_list, counting (one small kernel and a wait for its result) on first use
+// km->h_n_unstaged / d_unstaged_list, counting (one small kernel and a wait for its result) on first use; a stream under capture
+// leaves the number unknown (-1)
 fx_status kmap_unstaged_tiles(fx_kmap* km, hipStream_t st);
+inline bool kmap_few_unstaged(const fx_kmap* km) { return km->h_n_unstaged >= 0 && km->h_n_unstaged <= kMaxListedTiles; }
 }
