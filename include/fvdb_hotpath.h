@@ -323,14 +323,16 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * bwd_weight: C_in, with any C_out) on maps with a dense table; FX_F32 bwd_data as the forward pass; everything else takes
  * scalar kernels.  Non-finite values: where C_in % 32 == 0 and C_out % 64 == 0 the tile kernel of the weight gradient
  * multiplies a missing pair as zeros, so an infinite or NaN value of gout makes its column of gw NaN for every offset that one
- * of the 32 voxels of its column block has, and a tile whose input rows do not all fit the kernel's local memory has its
- * operand transposed by a multiplication with the identity (on dense grids, between two grids, and on sparse maps with more than
+ * of the 32 voxels of its column block has, and a tile whose input rows do not all fit the kernel's local memory (1022 rows) has its
+ * operand transposed by a multiplication with the identity (between two grids, and on maps of one grid with more than
  * 16 such tiles; 16 or fewer are summed over existing pairs), so that such a value in feat makes the whole 32-channel block of
  * gw that it touches NaN rather than only its own row.  All other
- * shapes, and all on strided maps, sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
- * the leaf-window kernels: at those shapes a locally dense grid (mean leaf occupancy >= 0.40) is summed leaf by
- * leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a grid that mixes dense and sparse leaves is split per
- * leaf between that kernel and the tile kernel inside the call (option leaf_dispatch as for the forward pass).
+ * shapes, all on strided maps, and layers of both counts a multiple of 256 that are summed from lists of pairs (from 24 k outputs x
+ * 256 x 256 blocks on) sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for
+ * the leaf-window kernels: at those shapes a locally dense grid (mean leaf occupancy >= 0.60; >= 0.40 where more than 16 tiles
+ * need more than 1022 rows) is summed leaf by
+ * leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a sparser grid with as many such tiles and at least 10 % of its voxels in
+ * dense leaves is split per leaf between that kernel and the tile kernel inside the call (option leaf_dispatch as for the forward pass).
  */
 fx_status fx_sparse_conv_bwd_data(const fx_kmap* km, const void* d_gout, fx_dtype dt, const void* d_w,
                                   int32_t C_in, int32_t C_out, void* d_gin, fx_dtype out_dt, void* stream);

@@ -818,7 +818,7 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         if (pwave == 0) {
             const int n_long = long_tiles_first(n_work, gridDim.x) ? uni(counters[8]) : 0;              // in flight beside the first header
             flags = announce(L.meta[0], first, nslice, tile_hdr, lane);
-            // Items of long tiles (rows gathered from global memory: two to four times a staged item) would end the launch
+            // Items of long tiles (rows in both halves of the row buffer, or gathered from global memory: two to four times another item) would end the launch
             // alone if they were claimed last.  When all of them are listed the first workgroups start with one each, claims
             // pass them over, and the static items of those workgroups are claimed like the others (at most the lower half
             // of every XCD's workgroups, all of which have a static item: see long_tiles_first).  bf16 on 195 k voxels of sheets (four long tiles of 381), 128 -> 128

@@ -136,7 +136,7 @@ enum WeightMode { kWeightsForward = 0, kWeightsTransposed = 1, kWeightsFlipped =
 
 // Packs the weights (C_in = contracted channels, C_out = produced channels, in the sense of the
 // mode) and zeroes the eight work-list counters behind them.  With tile_long it also lists the long tiles (whose rows
-// are not all staged in LDS): their number goes to counters[8], the first kMaxLongTiles of them behind it (kConvWorkInts in
+// do not fit one row buffer): their number goes to counters[8], the first kMaxLongTiles of them behind it (kConvWorkInts in
 // all).
 // n_nt = 1: slices of 32 produced channels, column m of the one n-tile = channel m.  `again` goes to counters[kPairArgsAt]
 // if it is set.  Contracted channels are padded with zeros to whole 64-byte chunks.

@@ -20,7 +20,7 @@ namespace fx {
 //     r >= win_n            -> global row rows[r - win_n]     (the halo: distinct rows outside
 //                              the window, ascending)
 //     r == kNoRow           -> no input (multiplies a zero row, or the block is skipped)
-// When all rows of a tile fit the convolution's LDS budget (flag kTileLdsOffsets) the id blocks
+// When all rows of a tile fit one of the convolution's two row buffers (flag kTileLdsOffsets) the id blocks
 // hold lds_row_code(r) instead of r (kNoRow -> the zero row), so the multiply loop needs no
 // address arithmetic beyond one XOR.
 // A tile flagged kTileDirect keeps no window and lists one row per active pair (no
@@ -106,7 +106,7 @@ struct fx_kmap {
     // tiled form
     int64_t n_tiles = 0;
     fx::TileHeader* d_tile_hdr = nullptr;   // [n_tiles]
-    uint8_t* d_tile_long = nullptr;         // [n_tiles, rounded up to 4 with zeros] 1: the tile's rows are not all staged (no kTileLdsOffsets)
+    uint8_t* d_tile_long = nullptr;         // [n_tiles, rounded up to 4 with zeros] 1: the tile's rows need more than one row buffer (no kTileLdsOffsets)
     uint16_t* d_tile_perm = nullptr;        // [n_tiles][kTileT] output slot -> local output (0..T-1)
     int32_t* d_tile_rows = nullptr;         // [n_tiles][row_stride] global input rows (halo / direct)
     uint16_t* d_tile_blocks = nullptr;      // [n_tiles][block_stride][16][8] local row ids (id blocks)
