@@ -45,6 +45,11 @@ __device__ __forceinline__ void to_lds4(const void* src, uint32_t lds) {
 
 __device__ __forceinline__ int units_of(int pairs) { return (pairs + kListUnit - 1) / kListUnit; }
 
+// Runs that the units are cut into: no more than there are units, so that every run from the first to the last of an offset has units
+// of it and writes the partial sum that the reduction reads.  (The map of one grid has a unit per 32 outputs at its centre offset alone;
+// a map between two grids that hardly touch has any number, down to none.)
+__device__ __forceinline__ int runs_with_units(int n_units, int n_runs) { return max(1, min(n_units, n_runs)); }
+
 }  // namespace
 
 // The pairs of every (tile, offset), packed: list[tile][kappa][0 .. n-1] = input row << 9 | output inside the tile, in the
@@ -114,7 +119,7 @@ k_pair_lists(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
 
 // gw[kappa] = sum over the pairs of kappa of feat[in]^T gout[out], the pairs as the contracted dimension.  A workgroup owns 256 x 256
 // channels, a wave 64 x 64 of them, and a run of units (32 pairs of one tile and offset), one of `n_runs` equal ones
-// of all units in order of offset and tile; where a run passes from one offset to the next it ends one partial sum and starts another.
+// of all units in order of offset and tile (fewer if there are fewer units: the last workgroups then have none); where a run passes from one offset to the next it ends one partial sum and starts another.
 template <typename T>
 __global__ void __launch_bounds__(64 * kListWaves)
 k_wgrad_lists(const uint16_t* __restrict__ counts, int n_tiles, int tiles_pad, const uint32_t* __restrict__ list, int K3, int n_runs,
@@ -155,7 +160,8 @@ k_wgrad_lists(const uint16_t* __restrict__ counts, int n_tiles, int tiles_pad, c
     const int n_units = __builtin_amdgcn_readlane(upto, K3 - 1);
     if (blockIdx.x == 0 && tid < K3) unit_base[1 + tid] = upto;
     if (blockIdx.x == 0 && tid == 0) unit_base[0] = 0;
-    const int u0 = (int)((int64_t)n_units * run / n_runs), u1 = (int)((int64_t)n_units * (run + 1) / n_runs);
+    const int runs = runs_with_units(n_units, n_runs);
+    const int u0 = (int)((int64_t)n_units * min(run, runs) / runs), u1 = (int)((int64_t)n_units * min(run + 1, runs) / runs);
 
     // ---- this wave's part of a stage: slab `wave` of either side
     const int wi = wave % kListSide, wo = wave / kListSide;
@@ -293,8 +299,9 @@ __global__ void __launch_bounds__(256) k_wgrad_lists_reduce(const float* __restr
     const int64_t n = unit_base[K3], f = unit_base[k], l = (int64_t)unit_base[k + 1] - 1;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (f <= l) {
-        // run r holds units n r / n_runs (rounded down) and on: that of unit u is the last r with n r / n_runs <= u
-        const int r0 = (int)(((f + 1) * n_runs - 1) / n), r1 = (int)(((l + 1) * n_runs - 1) / n);
+        // run r holds units n r / runs (rounded down) and on: that of unit u is the last r with n r / runs <= u
+        const int runs = runs_with_units((int)n, n_runs);
+        const int r0 = (int)(((f + 1) * runs - 1) / n), r1 = (int)(((l + 1) * runs - 1) / n);
         const float* p = part + ((size_t)job * (n_runs + K3) + r0 + k) * (kListBlk * kListBlk) + (ci % kListBlk) * kListBlk + co % kListBlk;
         const int cnt = r1 - r0 + 1;
         for (int r = 0; r < cnt; r += 8) {

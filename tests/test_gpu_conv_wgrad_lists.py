@@ -3,6 +3,9 @@ the same sums in 64 bits: torch on the dense map, which other tests compare with
 
 Tolerance: a sum of N exact products in fp32, in any order, is off by about 2^-24 sqrt(N) of its size; N is at most 2e5
 here, which gives 2.7e-5 of an offset's norm, and the bar is four times that."""
+import ctypes as C
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -68,6 +71,46 @@ def test_other_maps():
     g = _grid(30_000, 5)
     _check(fx.build_kernel_map(g, 1, 1), "bf16", 256, 256)                  # one offset, every run has units of it
     _check(fx.build_kernel_map_onto(g, g.pad(1), 3), "f16", 256, 256)
+
+
+@pytest.fixture
+def nan_scratch():
+    """The library's device memory from one arena of NaNs that is handed out once, so that what no kernel wrote shows."""
+    arena, at = torch.full((100 << 20,), float("nan"), device="cuda"), [256]
+
+    def take(nbytes, stream, ctx):
+        at[0] += (nbytes + 255) // 256 * 256
+        return arena.data_ptr() + at[0] - (nbytes + 255) // 256 * 256 if at[0] <= 4 * arena.numel() else None
+
+    alloc = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p)(take)
+    free = C.CFUNCTYPE(None, C.c_void_p, C.c_void_p, C.c_void_p)(lambda p, stream, ctx: None)
+    fx.binding._check(fx.binding.lib.fx_set_allocator(C.cast(alloc, C.c_void_p), C.cast(free, C.c_void_p), None))
+    yield lambda: at[0]
+    gc.collect()                                                            # maps and grids of the test go back before the arena does
+    torch.cuda.synchronize()
+    fx.binding._check(fx.binding.lib.fx_set_allocator(None, None, None))
+
+
+@pytest.mark.parametrize("kernel,c_in,c_out", [(3, 256, 256), (1, 256, 256), (3, 512, 256)])
+@pytest.mark.parametrize("touched", [0, 1, 2, 4, 5, 9, 10, 57])
+def test_fewer_units_than_runs(touched, kernel, c_in, c_out, nan_scratch):
+    """Two grids that meet in a few places only: inputs in the neighbourhood of `touched` of the output's 59 tiles, so that the pairs
+    make fewer units than there are workgroups, or just as many."""
+    out = np.stack(np.meshgrid(np.arange(62), np.arange(62), np.arange(8), indexing="ij"), axis=-1).reshape(-1, 3)[:30_000] * 2
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a.astype(np.int32))).cuda()
+    g_out = fx.build_index_grid(dev(out), np.array([[0, out.shape[0]]]))
+    at = g_out.ijk()[0].cpu().numpy()[512 * np.arange(touched) + 17]        # an output of each of those tiles, its neighbours, and something far off
+    d = np.stack(np.meshgrid(*[np.arange(-1, 2)] * 3, indexing="ij"), axis=-1).reshape(1, 27, 3)
+    pts = np.concatenate([np.unique((at[:, None] + d).reshape(-1, 3), axis=0), np.arange(-3000, -2000, 100)[:, None].repeat(3, axis=1)])
+    km = fx.build_kernel_map_onto(fx.build_index_grid(dev(pts), np.array([[0, pts.shape[0]]])), g_out, kernel)
+    t = (km.dense() >= 0).cpu().numpy()
+    pairs = np.array([t[s:s + 512].sum(0) for s in range(0, t.shape[0], 512)])
+    assert (pairs.sum(1) > 0).sum() >= touched and (touched or not pairs.any())
+    runs = torch.cuda.get_device_properties(0).multi_processor_count // ((c_in // 256) * (c_out // 256))
+    assert touched > 9 or kernel == 3 or ((pairs + 31) // 32).sum() < runs
+    before = nan_scratch()
+    _check(km, "bf16", c_in, c_out)
+    assert nan_scratch() - before >= 3 * 4 * kernel ** 3 * c_in * c_out     # its scratch came from the arena
 
 
 def test_pieces_longer_than_the_table():
