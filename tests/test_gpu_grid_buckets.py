@@ -74,6 +74,21 @@ def test_batches_with_rows_between_the_grids(B):
     _check(fx.build_index_grid(rows, joff), rows, joff)
 
 
+@pytest.mark.parametrize("B,far", [(16, False), (16, True), (17, False), (40, False)])
+@pytest.mark.parametrize("n", [150_000, 1_200_000])
+def test_scattered_rows_of_many_grids(n, B, far):
+    """Nearly as many leaves as rows, more than a bucket's table holds: several rounds over runs of records of one word, of two in some
+    pieces (coordinates beyond 2^19), and of two in all (more than 16 grids)."""
+    rows = _rows(n, 700, n + B)
+    if far:
+        rows[n // 3: n // 2, 2] += 600_000
+    cut = np.sort(np.random.default_rng(B).integers(0, n, B + 1))
+    joff = np.stack([cut[:-1], cut[1:]], axis=1)
+    g = fx.build_index_grid(rows, joff)
+    assert g.counts()[0] > 0.9 * (cut[-1] - cut[0])
+    _check(g, rows, joff)
+
+
 @pytest.mark.parametrize("size", [1.0, 0.05, 0.3, 7.7, 1e-3])
 @pytest.mark.parametrize("n", [3_000, 40_000, 90_000])
 def test_cells_of_points_near_faces(size, n):
