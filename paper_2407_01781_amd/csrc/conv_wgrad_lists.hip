@@ -320,16 +320,28 @@ __global__ void __launch_bounds__(256) k_wgrad_lists_reduce(const float* __restr
     }
 }
 
-// Whether the lists serve a stride-1 map and pay.  Their listing launch and the partial sums (74 MB at 256 -> 256) cost 50 us
-// whatever the map; the tile kernel stages every row once per block of 32 x 64 channels.  bf16, tile kernel / lists, whole
-// call, us, 256 -> 256: spheres of 9.9 k voxels 49 / 65, 24 k 97 / 84, 41 k 115 / 105; indoor 10.5 k 46 / 64, 21 k 67 / 76, 88 k
-// 178 / 159; sheets 13 k 66 / 68, 24 k 98 / 77, 57 k 166 / 114, 195 k 534 / 281; LiDAR 85 k 194 / 157, 269 k 587 / 396; 256 -> 512 on
-// 9.9 k 70 / 78, 41 k 208 / 155; 512 -> 512 on 140 k 1224 / 710.  Blocks of 128 x 128 channels, which fetch every row twice as
-// often for its products, were measured too: 128 -> 128 on 195 k voxels of sheets 158 / 153, LiDAR 269 k 155 / 218, 980 k 538 / 635.
+// Whether the lists serve a stride-1 map and pay.  Their listing launch and the partial sums (74 MB at 256 -> 256) cost 20 to 60 us
+// whatever the map; the tile kernel stages every row once per block of 32 x 64 channels.  The line is in outputs x blocks of 256 x 256.
+// bf16, tile kernel / lists, whole call, us, 256 -> 256:
+//   24 k from 8 voxels a leaf on: sheets 13 k voxels 66 / 68, 25 k 100 / 76, 57 k 166 / 114, 195 k 534 / 281; spheres 9.9 k 49 / 65,
+//     26 k 102 / 85, 41 k 115 / 105; indoor 10.5 k 46 / 64, 21 k 67 / 76, 88 k 178 / 159; random voxels, 24 a leaf, 23.7 k 74 / 75, 27 k
+//     82 / 64, 14 a leaf, 24.6 k 61 / 62, 29 k 69 / 64, 10 a leaf, 24.6 k 58 / 62, 26.5 k 62 / 62, 29 k 68 / 62; LiDAR 85 k 194 / 157, 269 k 587 / 396; 256 -> 512 on 9.9 k 70 / 78, 41 k 208 / 155; 512 -> 512 on 140 k 1224 / 710
+//   32 k where a leaf has few voxels, and a voxel few pairs: random voxels, 1 to 7 a leaf, 24 k 50..54 / 60..62, 28 k 55..61 / 61..62,
+//     33 k 62..68 / 62..64, 56 k 88..99 / 65..70; 512 -> 512 on 6.3 k 54..58 / 59..61, 8.4 k 65..70 / 60..62
+//   40 k for the one pair a voxel of a 1x1x1 map: 24 k 32 / 49, 30 k 43 / 50, 38 k 52 / 51, 50 k 66 / 53, 393 k 552 / 129; 512 -> 512 on
+//     8.1 k 45 / 41
+//   24 k between two grids, whose tiles list a row per pair: 32 k outputs, 3x3x3, input all of them 275 / 85, half 117 / 68, hardly any
+//     43 / 40; 1x1x1, half 124 / 47, hardly any 25 / 22; 1.03 M of a padded grid 2587 / 365
+// Blocks of 128 x 128 channels, which fetch every row twice as often for its products, were measured too: 128 -> 128 on 195 k
+// voxels of sheets 158 / 153, LiDAR 269 k 155 / 218, 980 k 538 / 635.
 bool wgrad_lists_pays(const fx_kmap* km, fx_dtype dt, int C_in, int C_out) {
-    return dt != FX_F32 && C_in % kListBlk == 0 && C_out % kListBlk == 0 &&
-           km->n_out * (C_in / kListBlk) * (C_out / kListBlk) >= 24000 && km->n_in < (1 << kListRowBits) - 1 &&
-           km->n_tiles > 0 && km->n_tiles <= kListMaxTiles;
+    if (dt == FX_F32 || C_in % kListBlk != 0 || C_out % kListBlk != 0 || km->n_in >= (1 << kListRowBits) - 1 || km->n_tiles <= 0 ||
+        km->n_tiles > kListMaxTiles)
+        return false;
+    const int64_t work = km->n_out * (C_in / kListBlk) * (C_out / kListBlk);
+    if (km->gin != km->gout) return work >= 24000;
+    if (km->K == 1) return work >= 40000;
+    return work >= (km->n_in >= (int64_t)8 * km->gin->hdr.n_leaf ? 24000 : 32000);
 }
 
 fx_status wgrad_lists(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, void* d_gw, fx_dtype out_dt,

@@ -57,7 +57,7 @@ def _check(km, dtype, c_in, c_out, spoil=False):
     assert torch.equal(low.view(torch.int16), gw.to(H.TORCH_DT[dtype]).view(torch.int16)) or spoil
 
 
-# 6 k outputs at four blocks and 24 k at one are the smallest sizes that come here; the last tile holds one voxel and more
+# 24 k outputs x blocks and little more, where these grids, of more than 8 voxels a leaf, start to come here
 @pytest.mark.parametrize("n,dtype,c_in,c_out", [(27_000, "bf16", 256, 256), (30_000, "f16", 256, 256), (14_500, "bf16", 256, 512), (7_000, "f16", 512, 512),
                                                 (60_000, "bf16", 512, 256)])
 @pytest.mark.parametrize("thick", [0, 24])
@@ -111,6 +111,29 @@ def test_fewer_units_than_runs(touched, kernel, c_in, c_out, nan_scratch):
     before = nan_scratch()
     _check(km, "bf16", c_in, c_out)
     assert nan_scratch() - before >= 3 * 4 * kernel ** 3 * c_in * c_out     # its scratch came from the arena
+
+
+@pytest.mark.parametrize("kernel,spread,line,c_in,c_out", [(1, 3.0, 40_000, 256, 256), (1, 3.0, 10_000, 512, 512), (3, 6.0, 32_000, 256, 256),
+                                                           (3, 6.0, 8_000, 512, 512), (3, 2.2, 24_000, 256, 256)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_either_side_of_the_line(kernel, spread, line, c_in, c_out, past, nan_scratch):
+    """A voxel fewer than the line, and as many: 1x1x1 maps, some two voxels a leaf, and some forty.  The lists show by the size
+    of their scratch memory, which the tile kernel's partial sums stay below."""
+    n = line - 1 + past
+    rng = np.random.default_rng(line + past)
+    pts = np.unique(rng.integers(0, int(spread * n ** (1 / 3)), size=(2 * n, 3)), axis=0)
+    pts = np.ascontiguousarray(rng.permutation(pts)[:n].astype(np.int32))
+    g = fx.build_index_grid(torch.from_numpy(pts).cuda(), np.array([[0, n]]))
+    assert g.num_voxels == n and (n >= 8 * g.counts()[0]) == (spread < 4)
+    km = fx.build_kernel_map(g, kernel, 1)
+    x, gy = (torch.ones((n, c), dtype=torch.bfloat16, device="cuda") for c in (c_in, c_out))
+    fx.sparse_conv_bwd_weight(km, x, gy)                                    # what the map keeps is there now
+    before = nan_scratch()
+    gw = fx.sparse_conv_bwd_weight(km, x, gy, out_dtype=torch.float32)
+    jobs = (c_in // 256) * (c_out // 256)
+    runs = torch.cuda.get_device_properties(0).multi_processor_count // jobs // 8 * 8
+    assert (nan_scratch() - before >= 4 * jobs * (runs + kernel ** 3) * 256 * 256) == bool(past)
+    assert torch.equal(gw, (km.dense() >= 0).sum(0).float()[:, None, None].expand_as(gw))
 
 
 def test_pieces_longer_than_the_table():
