@@ -324,8 +324,9 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * scalar kernels.  Non-finite values: where C_in % 32 == 0 and C_out % 64 == 0 the tile kernel of the weight gradient
  * multiplies a missing pair as zeros, so an infinite or NaN value of gout makes its column of gw NaN for every offset that one
  * of the 32 voxels of its column block has, and a tile whose input rows do not all fit the kernel's local memory (1022 rows) has its
- * operand transposed by a multiplication with the identity (between two grids, and on maps of one grid with more than
- * 16 such tiles; 16 or fewer are summed over existing pairs), so that such a value in feat makes the whole 32-channel block of
+ * operand transposed by a multiplication with the identity (between two grids, unless it is a 3x3x3 map onto
+ * one of twice the input's voxels or more, and on those and maps of one grid with more than 16 such tiles; 16 or fewer are summed
+ * over existing pairs), so that such a value in feat makes the whole 32-channel block of
  * gw that it touches NaN rather than only its own row.  All other
  * shapes, all on strided maps, and layers of both counts a multiple of 256 that are summed from lists of pairs (from 24 k outputs x
  * 256 x 256 blocks on; 32 k on 3x3x3 maps of one grid with fewer than 8 voxels a leaf, 40 k on 1x1x1 maps of one grid) sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for

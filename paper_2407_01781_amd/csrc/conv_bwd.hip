@@ -787,10 +787,10 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         const int n_cblk = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
         n_ranges = (int)std::max<int64_t>(1, std::min<int64_t>(km->n_tiles, compute_units() / n_cblk));
         if (n_ranges > 8) n_ranges -= n_ranges % 8;   // see the block-to-XCD mapping in the kernel
-        // Submanifold maps with at most a few tiles that are not staged in LDS: the sixteen-wave launch for the
-        // staged tiles and, if there are others, k_wgrad_pairs over the list of those (see WgradMode).  Other maps: one launch that
-        // takes every tile.  (With a per-leaf split the tiles walked are those of the map without the dense leaves.)
-        bool split = km->stride == 1 && km->gin == km->gout && !km->is_inverse;
+        // Submanifold maps, and maps onto a larger grid whose tiles hold their rows once each, with at most a few tiles that are not
+        // staged in LDS: the sixteen-wave launch for the staged tiles and, if there are others, k_wgrad_pairs over the list of those
+        // (see WgradMode).  Other maps: one launch that takes every tile.  (With a per-leaf split the tiles walked are those of the map without the dense leaves.)
+        bool split = km->stride == 1 && !km->is_inverse && (km->gin == km->gout || (km->K == 3 && map_shares_rows(km)));
         if (split) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
             split = kmap_few_unstaged(km);

@@ -67,8 +67,9 @@ static_assert(kGroupsPerWave == 4 && kTileWaves == 4, "id blocks of four column 
 // LDS latencies -- and took 150 us where the eight-wave kernel with both forms took 204 (1 M-voxel LiDAR grid,
 // 64 -> 64); 30 us of those 204 were one workgroup's single tile of the other kind, which costs as much as four
 // staged ones.  When the map has at most kMaxListedTiles such tiles (counted once per map), kWgStaged (16 waves)
-// takes the staged tiles of the ranges, and k_wgrad_pairs the listed ones, a wave per offset.  Other maps (between two
-// grids, whose tiles mostly list one row per pair; strided maps go to k_wgrad_pairs) take one launch of
+// takes the staged tiles of the ranges, and k_wgrad_pairs the listed ones, a wave per offset.  The same for a 3x3x3 map onto a grid of
+// twice the input's voxels and more (kWgAll / this, us: 1.72 M voxels of a padded grid 64 -> 64 352 / 246, 4.7 k 37.8 / 25.0).  Other
+// maps (onto another grid, a row per pair; strided maps go to k_wgrad_pairs) take one launch of
 // kWgAll (8 waves, both forms, every tile of the range).  Either way a partial sum is made of the same terms in a
 // fixed order.  With 816 rows staged, tiles above went to the pairs or, from 0.20 mean leaf occupancy on, the map to kWgAll; with
 // 1022, bf16 64 -> 64, us: 24 k voxels of a sphere shell 38.8 -> 27.3, 116 k of LiDAR 48 -> 39, 195 k of sheets 61 -> 52, 88 k / 531 k of
@@ -229,11 +230,20 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (row_ids) {          // row numbers -> LDS offsets, two to a word
+        // Row numbers -> LDS offsets, two to a word.  kWgStaged: an id block per wave at a time, a scalar loop, 1 to 5 % less of launches of
+        // which no tile takes it (1x1x1 map of 940 k voxels, 128 -> 128, 359 -> 341 us); in kWgAll, where tiles listed pair by pair are
+        // most of the work, that form was 3 to 5 % slower (map from a padded grid of 1.03 M, 128 -> 128, 484 / 499).
+        if (row_ids) {
+            static_assert(kIdBlockElems == 2 * 64, "a word of an id block per lane");
             uint32_t* words = reinterpret_cast<uint32_t*>(L.blocks);
-            for (int i = tid; i < n_blocks * kIdBlockElems / 2; i += 64 * W) {
+            auto convert = [&](int i) {
                 const uint32_t v = words[i];
                 words[i] = lds_row_code(min(v & 0xFFFFu, (uint32_t)kWgRowCap)) | lds_row_code(min(v >> 16, (uint32_t)kWgRowCap)) << 16;
+            };
+            if (MODE == kWgStaged) {
+                for (int b = uni(wave); b < n_blocks; b += W) convert(b * 64 + lane);
+            } else {
+                for (int i = tid; i < n_blocks * 64; i += 64 * W) convert(i);
             }
             __syncthreads();
         }

@@ -68,15 +68,37 @@ def _inputs_for(g_out, rows, rng):
     return np.array([k for k, v in have.items() if v])
 
 
-@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
-@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [2 * CAP - 1, 2 * CAP, 2 * CAP + 1], [2 * CAP, 100, CAP], [1021, 1022, 500, 1023, 400], [2500, 1200, 300, CAP + 16, 815]])
-def test_rows_of_a_tile(rows, dtype, c_in, c_out):
-    rng = np.random.default_rng(len(rows) * 1000 + rows[0])
+def _between(rows, tiles, shared):
+    """A map onto a grid whose first tiles read rows[t % len(rows)] inputs each; `shared`: onto a grid at least twice the input's
+    size, by outputs far off, whose tiles hold every row once."""
     lattice = np.stack(np.meshgrid(np.arange(40), np.arange(8), np.arange(56), indexing="ij"), axis=-1).reshape(-1, 3) * 2
-    g_out = _index(lattice[:17_700])
-    km = fx.build_kernel_map_onto(_index(_inputs_for(g_out, rows, rng)), g_out, 3)
+    out = lattice[:512 * tiles - 220]
+    pts = _inputs_for(_index(out), rows, np.random.default_rng(len(rows) * 1000 + rows[0]))
+    if shared:
+        side = int(np.ceil((2 * len(pts)) ** (1 / 3)))
+        out = np.concatenate([out, 4000 + 3 * np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)])
+    g_in, g_out = _index(pts), _index(out)
+    assert (g_out.num_voxels >= 2 * g_in.num_voxels) == shared
+    return fx.build_kernel_map_onto(g_in, g_out, 3)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
+@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [1023, 1024, 100, CAP], [1021, 1022, 500, 1023, 400], [2500, 1200, 300, CAP + 16, 815]])
+def test_rows_of_a_tile(rows, dtype, c_in, c_out):
+    """Staged in one half and in both (to 1024 rows, what a tile between two grids holds once each), and a row per pair beyond."""
+    km = _between(rows, 35, True)
     seen = _tile_rows(km)
-    assert all(seen.count(r) >= 1 for r in rows if r <= 2 * CAP + 1), (rows, sorted(set(seen)))
+    assert all(seen.count(r) >= 1 for r in rows if r <= 1024), (rows, sorted(set(seen)))
+    _check(km, dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 160), ("bf16", 40, 24)])
+@pytest.mark.parametrize("rows,tiles,shared,some", [([1022, 1000, 300], 24, True, 0), ([1024, 1022, 900], 24, True, 1), ([1024, 1023, 1400], 24, True, 17), ([900], 24, False, 17)])
+def test_weight_gradient_between_two_grids(rows, tiles, shared, some, dtype, c_in, c_out):
+    """All tiles staged by the weight gradient, up to 16 that are not and are listed, more than 16, and a map whose tiles list a row per pair."""
+    km = _between(rows, tiles, shared)
+    n = sum(r > 1022 for r in _tile_rows(km)) if shared else km.n_out // 512
+    assert n == 0 if some == 0 else n > 16 if some > 16 else 1 <= n <= 16
     _check(km, dtype, c_in, c_out)
 
 
