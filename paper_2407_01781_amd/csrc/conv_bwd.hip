@@ -749,16 +749,22 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // Per-leaf dispatch, as in the forward pass: on a grid that mixes locally dense leaves with sparse ones the pairs
     // of the dense leaves' outputs are summed by the leaf-window kernel (over the list of those leaves) and all
     // others by the tile kernel over the copy of the map that leaves those outputs out; both write partial sums of
-    // the same form and one ordered reduction adds them.  Not where all but a few of the whole map's tiles are staged (bf16 64 -> 64,
-    // split / tiles alone, us: a full cube and a thin cloud of 1.26 M voxels 477 / 305; bodies, surfaces and scan lines of 531 k, four
-    // in ten tiles not staged, 226 / 261).  leaf_dispatch = 2 forces it.
+    // the same form and one ordered reduction adds them.  Where all but a few of the whole map's tiles are staged the tiles alone are
+    // mostly faster, but their ranges hold equal numbers of tiles, and those of a solid body, which cost the most, are neighbours and
+    // fall into a few ranges: the launch waits for them, the longer the smaller their share and the fewer the ranges beside the
+    // channel blocks.  bf16, tiles / split, us, a full cube and a thin cloud, dense share 0.11: 64 -> 64 on 296 k voxels 82 / 90, 578 k 133 / 131,
+    // 998 k 251 / 210, 2.4 M 545 / 416; 128 -> 128 on 125 k 106 / 107, 296 k 223 / 209, 998 k 822 / 613; share 0.2: 64 -> 64 on 550 k 137 / 149,
+    // 1.9 M 445 / 393, 128 -> 128 on 318 k 249 / 258, 873 k 729 / 640; share 0.3: 128 -> 128 on 869 k 719 / 727; share 0.45 503 / 602 on 580 k.
+    // Over 630 calls (cubes of 16, 24 and 48 voxels, one and many, and slabs, 37 k to 2.4 M voxels) the line is at most 12 % behind the
+    // faster side, tiles alone wherever few are not staged up to 43 %.  Bodies, surfaces and scan lines of 531 k, four in ten tiles not staged, 64 -> 64 226 split / 261.  leaf_dispatch = 2 forces it.
     int leaf_ranges = 0;
     if (mfma && km->K == 3 && km->stride == 1 && km->gin == km->gout && !km->is_inverse && leaf_wgrad_shape_supported(dt, C_in, C_out)) {
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
         bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10;
-        if (split) {
+        const int64_t blocks = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
+        if (split && (0.30 - dense) * (double)(km->n_out * blocks) < (double)(1 << 18)) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
             split = !kmap_few_unstaged(km);
         }

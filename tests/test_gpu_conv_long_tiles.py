@@ -167,3 +167,25 @@ def test_either_side_of_the_line_of_a_split(share):
     cloud = np.unique(rng.integers(100, 300, size=(int(13_824 * (1 - share) / share), 3)), axis=0)
     cube = np.stack(np.meshgrid(*[np.arange(24)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
     _check(fx.build_kernel_map(_index(np.concatenate([cube, cloud])), 3, 1), "bf16", 64, 64)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out,split", [("bf16", 64, 64, False), ("f16", 128, 128, True), ("bf16", 32, 64, False), ("bf16", 128, 192, True)])
+def test_weight_gradient_split_by_size(dtype, c_in, c_out, split):
+    """A solid cube with 11 % of the voxels, all tiles staged: alone where few blocks of channels share them, split per leaf from
+    (0.30 - share) x outputs x blocks of 32 x 64 channels = 2^18 on."""
+    cloud = np.unique(np.random.default_rng(12).integers(200, 460, size=(269_000, 3)), axis=0)
+    cube = np.stack(np.meshgrid(*[np.arange(32)] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    km = fx.build_kernel_map(_index(np.concatenate([cube, cloud])), 3, 1)
+    share = 32768 / km.n_out
+    assert 0.10 < share < 0.12 and max(_tile_rows(km)) <= 1022
+    assert ((0.30 - share) * km.n_out * (c_in // 32) * (c_out // 64) >= 2 ** 18) == split
+    x = torch.zeros((km.n_out, c_in), device="cuda", dtype=H.TORCH_DT[dtype])
+    gy = torch.zeros((km.n_out, c_out), device="cuda", dtype=H.TORCH_DT[dtype])
+    fx.profile_enable(True)
+    fx.profile_reset()
+    fx.sparse_conv_bwd_weight(km, x, gy)
+    torch.cuda.synchronize()
+    slots = fx.profile_read()
+    fx.profile_enable(False)
+    assert slots["k_wgrad"][1] == (2 if split else 1)               # the dense leaves' kernel and the tiles', or the tiles' alone
+    _check(km, dtype, c_in, c_out)
