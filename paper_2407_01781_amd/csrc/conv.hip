@@ -1786,12 +1786,19 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         // leaf-window kernel, the outputs of all other leaves to the tile kernel over a copy of the map that leaves
         // the dense leaves' outputs out.  Taken when the grid as a whole is too sparse for the leaf-window kernel
         // (mean occupancy below 0.40) and most of its voxels (55 %) sit in dense leaves; leaf_dispatch = 2 forces it.
-        // bf16 64 -> 64, split / tiles alone, us: a full cube of 885 k voxels and a thin cloud, 70 % of the voxels in the cube 323 / 328,
-        // 90 % 290 / 292 (128 -> 128 994 / 1045, 892 / 936), 50 % 383 / 379; bodies, surfaces and scan lines, 245 k (45 % in dense
-        // leaves) 118 / 84, 531 k (48 %) 190 / 128, though also 168 k (58 %) 122 / 69 and 697 k (62 %) 220 / 190.
-        // From 0.40 on the leaf-window kernel takes the whole of a small grid (below 16 k voxels), and of any from 0.60 on (tiles /
-        // leaf window: random voxels of a cube, 97 k at 0.37 46 / 74, 119 k at 0.45 50 / 76, 732 k at 0.52 241 / 260, 865 k at 0.62 294 / 277,
-        // 1.33 M at 0.96 464 / 340; small solid cubes of 33 k and 111 k 32 / 42 and 46 / 81).
+        // bf16, split / tiles alone, us.  What the split gains it gains on whole solid bodies of some million voxels, with 75 % and more
+        // of the voxels in them: a full cube and a thin cloud, 982 k, 90 % in the cube, 64 -> 64 303 / 318, 128 -> 128 874 / 939; a
+        // ball, 979 k, 75 %, 294 / 306, 835 / 933.  Smaller grids lose by it, the more the smaller they are: the leaf-window kernel walks a
+        // leaf in 80 us at 64 -> 64 and 230 at 128 -> 128 however few there are (114 k, 56 % in a cube, 90 / 47, 252 / 118; 414 k,
+        // 90 %, 173 / 138, 487 / 406; cubes of 24, 998 k, 90 %, 318 / 240; bodies, surfaces and scan lines, 168 k (58 %) 122 / 69, 697 k (62 %)
+        // 220 / 190).  Below 55 % it lost everywhere (245 k (45 %) 118 / 84, 531 k (48 %) 190 / 128; cube, 400 k, 50 %, 383 / 379), and there it is not
+        // taken any more; the line does not yet ask for the size, which is what decides above.
+        // From 0.40 on the leaf-window kernel takes the whole of a small grid (below 16 k voxels), and of any from 0.60 on, from 0.54 on above
+        // 2^20 voxels at up to 192 contracted channels.  Tiles / leaf window, us: random voxels of a cube, 64 -> 64, 97 k at 0.37 46 / 74, 119 k
+        // at 0.45 50 / 76, 732 k at 0.52 241 / 260, 513 k at 0.58 186 / 195, 865 k at 0.62 294 / 277, 1.17 M at 0.56 460 / 426, 2.8 M at
+        // 0.59 1002 / 898, 1.33 M at 0.96 464 / 340; 128 -> 128, 1.17 M at 0.56 1297 / 1221, 1.11 M at 0.53 1177 / 1172; 256 -> 256, 1.17 M at 0.56 4446 / 4745.
+        // The size decides here as well, and the line asks for it only so far: 152 k at 0.58 88 / 79, and solid cubes of 33 k and
+        // 111 k 32 / 41 and 47 / 79, of 14 k 31 / 40 (128 -> 128 53 / 128).
         if (in_dt != FX_F32 && !km->is_inverse) {
             const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
             if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.55)) {
@@ -1807,7 +1814,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
             }
         }
         const bool scalar_otherwise = in_dt == FX_F32 && C_in % 16 != 0;
-        const double line = scalar_otherwise ? 0.08 : in_dt != FX_F32 && km->n_in >= 16384 ? 0.60 : 0.40;
+        const double line = scalar_otherwise ? 0.08 : in_dt == FX_F32 || km->n_in < 16384 ? 0.40 : km->n_in < (1 << 20) || C_in > 192 ? 0.60 : 0.54;
         const bool take = ld >= 0 ? ld >= 1 : occupancy >= line;
         if (take)
             return leaf_apply("sparse convolution (leaf-window kernels)", km->gin, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt,

@@ -189,3 +189,31 @@ def test_weight_gradient_split_by_size(dtype, c_in, c_out, split):
     fx.profile_enable(False)
     assert slots["k_wgrad"][1] == (2 if split else 1)               # the dense leaves' kernel and the tiles', or the tiles' alone
     _check(km, dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("p,n_more,c_in,leaf", [(0.53, True, 64, False), (0.55, True, 64, True), (0.55, True, 192, True), (0.55, True, 224, False), (0.55, False, 64, False),
+                                                (0.61, False, 64, True)])
+def test_line_of_large_dense_grids(p, n_more, c_in, leaf):
+    """Random voxels of a block of leaves, as many as 2^20 or one fewer: the leaf window from 0.54 on at up to 192 channels, or
+    from 0.60 on."""
+    n = 2 ** 20 - (0 if n_more else 1)
+    cells = np.random.default_rng(13).permutation(512 * int(n / (512 * p)))[:n]
+    g = _index(8 * np.stack(np.unravel_index(cells // 512, (16,) * 3), axis=1) + np.stack(np.unravel_index(cells % 512, (8,) * 3), axis=1))
+    occupancy = n / (512 * g.counts()[0])
+    assert abs(occupancy - p) < 0.001 and (occupancy >= (0.54 if n_more and c_in <= 192 else 0.60)) == leaf
+    km = fx.build_kernel_map(g, 3, 1)
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    x = torch.randn((n, c_in), generator=gen, device="cuda").bfloat16()
+    w = torch.randn((27, c_in, 64), generator=gen, device="cuda").bfloat16()
+    fx.profile_enable(True)
+    fx.profile_reset()
+    y = fx.sparse_conv_fwd(km, x, w, out_dtype=torch.float32, out=H.nan_filled((n, 64), torch.float32))
+    torch.cuda.synchronize()
+    slots = fx.profile_read()
+    fx.profile_enable(False)
+    assert ("k_conv_leaf" in slots) == leaf
+    at = torch.cat([torch.arange(s, s + 512, device="cuda") for s in (0, n // 2, n - 512)])
+    t, ref = km.dense()[at].long(), 0.0
+    for k in range(27):
+        ref = ref + torch.where((t[:, k] >= 0)[:, None], x[t[:, k].clamp(min=0)].double(), 0.0) @ w[k].double()
+    assert _norm_ok(y[at], ref, 1.4e-5 * 2)                          # 27 * 224 products a sum, where 27 * 128 give 1.4e-5
