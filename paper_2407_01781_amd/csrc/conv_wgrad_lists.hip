@@ -34,14 +34,17 @@ static_assert(kListSlabRows * kListWaves == kListUnit, "a slab of either side pe
 
 // Loads straight from global memory to LDS (16 or 4 bytes a lane, to lds + 16 or 4 * lane), written out: behind the builtin the
 // compiler lets no LDS read pass before all such loads have arrived, and the next three stages' would be waited for with this
-// one's.  They are counted by hand.
+// one's.  They are counted by hand; m0, which holds the LDS address, is the only register that they write.
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_ptr_t)p; }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // that m0 is not preserved is what the list says
 __device__ __forceinline__ void to_lds16(const void* src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
 __device__ __forceinline__ void to_lds4(const void* src, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 __device__ __forceinline__ int units_of(int pairs) { return (pairs + kListUnit - 1) / kListUnit; }
 
