@@ -50,6 +50,9 @@ fx_status host_staging(void** p, size_t bytes, int area = 0);
 // compute units of the current device (256 on an MI355X; 256 if the query fails)
 int compute_units();
 
+// whether launches on the stream are being recorded into a graph: what they write is not there after the call
+bool stream_captures(hipStream_t st);
+
 // ------------------------------------------------------------------ per-kernel timing
 // When enabled (fx_profile_enable), every kernel launch of the library is bracketed by a pair
 // of hipEvents on the launch stream; fx_profile_read sums the elapsed times per slot.

@@ -1801,7 +1801,8 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         // 111 k 32 / 41 and 47 / 79, of 14 k 31 / 40 (128 -> 128 53 / 128).
         if (in_dt != FX_F32 && !km->is_inverse) {
             const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
-            if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.55)) {
+            // (a second map that a captured call built would not be there for the next call that is not replayed)
+            if (ld == 2 || (ld < 0 && occupancy < 0.40 && dense >= 0.55 && (km->mixed || !stream_captures(st)))) {
                 fx_kmap* kmw = const_cast<fx_kmap*>(km);
                 FX_TRY(kmap_ensure_mixed(kmw, st));
                 void* wp = nullptr;

@@ -762,7 +762,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         const int ld = option(kOptLeafDispatch);
         const double occupancy = (double)km->n_in / (512.0 * (double)std::max<int64_t>(1, km->gin->hdr.n_leaf));
         const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
-        bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10;
+        bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10 && (km->mixed || !stream_captures(st));      // see the forward pass
         const int64_t blocks = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
         if (split && (0.30 - dense) * (double)(km->n_out * blocks) < (double)(1 << 18)) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));

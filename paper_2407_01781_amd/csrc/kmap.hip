@@ -1233,9 +1233,7 @@ __global__ void __launch_bounds__(1024) k_list_unstaged_tiles(const TileHeader* 
 fx_status fx::kmap_unstaged_tiles(fx_kmap* km, hipStream_t st) {
     if (km->h_n_unstaged >= 0) return FX_OK;
     if (km->n_tiles == 0) { km->h_n_unstaged = 0; return FX_OK; }
-    // a captured launch writes no count to wait for: the number stays unknown
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (st && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return FX_OK;
+    if (stream_captures(st)) return FX_OK;      // a captured launch writes no count to wait for: the number stays unknown
     if (!km->d_unstaged_list) FX_TRY(dev_alloc((void**)&km->d_unstaged_list, sizeof(int32_t) * kMaxListedTiles, st));
     void* stage = nullptr;
     FX_TRY(host_staging(&stage, 128));      // the area of read-backs that the host waits for

@@ -189,6 +189,11 @@ int compute_units() {
     return n_cu;
 }
 
+bool stream_captures(hipStream_t st) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone;
+}
+
 // ---------------------------------------------------------------------------------- profiler
 struct ProfRec { int slot; hipEvent_t a, b; };
 static std::atomic<bool> g_prof_on{false};
