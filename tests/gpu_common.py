@@ -63,3 +63,30 @@ def conv_tolerance_check(y: np.ndarray, ref: np.ndarray, dtype: str, k3: int, c_
     rel = (num / den).max() if y.size else 0.0
     assert rel <= 2e-2, rel
     return rel
+
+
+def box(dims, at=(0, 0, 0)) -> np.ndarray:
+    """All integer points of a box, in coordinate order."""
+    return np.stack(np.meshgrid(*[np.arange(d) + a for d, a in zip(dims, at)], indexing="ij"), axis=-1).reshape(-1, 3)
+
+
+def facing_sheets(rows) -> np.ndarray:
+    """Voxels of a grid whose tile 8 m' + t (m' depends on the sheets before) of 512 voxels reads exactly rows[m][t] rows (512 to
+    2417), its own among them: 128^3 cells per m, in which a plane of every second voxel, eight tiles, faces a plane of as many
+    voxels next to each tile's as it is to read, 4096 rows behind it and more; filled up to whole tiles by voxels without neighbours."""
+    parts = []
+    for m, counts in enumerate(rows):
+        assert len(counts) == 8 and all(512 <= c <= 512 + 15 * 127 for c in counts)
+        plane = np.stack(np.meshgrid([7], np.arange(0, 128, 2), np.arange(0, 128, 2), indexing="ij"), axis=-1).reshape(-1, 3)
+        rng = np.random.default_rng(100 + m)
+        sheet = [box((1, 15, 127), (8, 16 * t, 0))[np.sort(rng.permutation(15 * 127)[:c - 512])] for t, c in enumerate(counts)]
+        n_sheet = sum(len(s) for s in sheet)
+        alone = np.stack(np.meshgrid([20], np.arange(0, 128, 4), np.arange(0, 128, 4), indexing="ij"), axis=-1).reshape(-1, 3)[:-n_sheet % 512]
+        parts.append(np.concatenate([plane] + sheet + [alone]) + [0, 0, 128 * m])
+    return np.concatenate(parts)
+
+
+def tile_row_counts(table: np.ndarray) -> np.ndarray:
+    """Rows that every tile of 512 outputs of a submanifold map holds: its own and all that it reads."""
+    own = np.arange(512)
+    return np.array([np.union1d(table[s:s + 512][table[s:s + 512] >= 0], own[:len(table) - s] + s).size for s in range(0, len(table), 512)])

@@ -435,14 +435,14 @@ def test_long_tiles_first_every_row(dtype, c_in, c_out, cloud, corner, fx_opt):
     fx_opt("leaf_dispatch", "0")
     rng = np.random.default_rng(520 + cloud)
     pts = rng.integers(-300, 300, size=(cloud, 3)).astype(np.int32)
-    ax = [np.arange(d, dtype=np.int32) + corner for d in (40, 24, 8)]
+    # (behind a cloud the block's tiles straddle its leaves and need more rows)
+    ax = [np.arange(d, dtype=np.int32) + corner for d in ((40, 24, 16) if corner < 0 else (40, 24, 8))]
     pts = np.concatenate([pts, np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)])
     g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
     n, km = og.num_voxels, fx.build_kernel_map(g, 3, 1)
-    # the call is on the path: tiles whose rows (their own and the neighbours outside) are more than fit in LDS
-    table, own = km.dense().cpu().numpy(), np.arange(512)
-    n_tiles = (n + 511) // 512
-    n_long = sum(np.union1d(table[512 * t:512 * t + 512].ravel(), own + 512 * t).size - 1 > 792 for t in range(n_tiles))
+    # the call is on the path: tiles whose rows (their own and the neighbours outside) are more than one half of the row buffer holds
+    counts = H.tile_row_counts(km.dense().cpu().numpy())
+    n_tiles, n_long = counts.size, int((counts > 816).sum())
     n_slices, half = (c_out + (31 if c_out <= 32 else 63)) // (32 if c_out <= 32 else 64), torch.cuda.get_device_properties(0).multi_processor_count // 2
     assert 0 < n_long <= 32 and n_long * n_slices <= half < 2 * half < n_tiles * n_slices
     feat, wt = G.features_and_weights(33, n, c_in, c_out, 27, dtype)

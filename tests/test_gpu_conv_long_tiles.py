@@ -102,6 +102,36 @@ def test_weight_gradient_between_two_grids(rows, tiles, shared, some, dtype, c_i
     _check(km, dtype, c_in, c_out)
 
 
+SHEETS = [[1631, 815, 816, 817, 1021, 1022, 1023, 700], [1632, 1500, 512, 1000, 1536, 900, 600, 1100], [1633, 1200, 1300, 2000, 850, 816, 1400, 513],
+          [2048, 817, 1022, 1023, 2400, 1536, 1537, 800]]
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64), ("bf16", 160, 32)])
+@pytest.mark.parametrize("sheets", [SHEETS[:1], SHEETS[1:3], SHEETS])
+def test_rows_of_a_tile_of_one_grid(sheets, dtype, c_in, c_out):
+    """One half of the row buffer, both to the last row, one row more, and tiles of a row per pair (more than 1024 rows far off), in turn."""
+    km = fx.build_kernel_map(_index(H.facing_sheets(sheets)), 3, 1)
+    counts = H.tile_row_counts(km.dense().cpu().numpy()).tolist()
+    assert all(counts[i:i + 8] == s for s, i in zip(sheets, [counts.index(s[0]) for s in sheets]))
+    _check(km, dtype, c_in, c_out)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 96, 128)])
+@pytest.mark.parametrize("last", [False, True])
+def test_long_tiles_of_every_kind_first(last, dtype, c_in, c_out):
+    """Few enough long tiles beside others that all are started first: both halves filled, rows beyond them, a row per pair."""
+    side = -1 if last else 1
+    cloud = np.unique(np.random.default_rng(15).integers(0, 500, size=(200_000, 3)), axis=0)[:199_680] + side * 4096
+    short = [[1631, 512, 600, 700, 512, 640, 512, 650], [2048, 513, 1700, 512, 1500, 512, 700, 512]]
+    km = fx.build_kernel_map(_index(np.concatenate([H.facing_sheets(short), cloud])), 3, 1)
+    counts = H.tile_row_counts(km.dense().cpu().numpy())
+    n_slices = (c_out + (31 if c_out <= 32 else 63)) // (32 if c_out <= 32 else 64)
+    half = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    assert 5 <= (counts > CAP).sum() <= 32 and (counts > CAP).sum() * n_slices <= half < 2 * half < counts.size * n_slices
+    assert ((counts > CAP) & (counts <= 2 * CAP)).any() and (counts > 2 * CAP).any()
+    _check(km, dtype, c_in, c_out)
+
+
 @pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 64, 128)])
 @pytest.mark.parametrize("p", [0.24, 0.285, 0.33])
 def test_long_tiles_of_a_thin_block(p, dtype, c_in, c_out):
