@@ -745,9 +745,9 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
 }
 
 // Items with more rows than one half holds take this path: a real call, so that its registers are allocated apart from the
-// main loop's.  Returns the item's phases.
+// main loop's.
 template <typename T, bool OUT_F32, int NT, bool PARTIAL>
-__device__ __noinline__ int consume_long_item(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
+__device__ __noinline__ void consume_long_item(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                                   const int32_t* __restrict__ tile_rows, int row_stride,
                                                   const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
                                                   int64_t pitch, int C_out, void* __restrict__ out, const PairArgs* again) {
@@ -767,7 +767,6 @@ __device__ __noinline__ int consume_long_item(int slot, int phase, int mb, int p
         consume_item<T, OUT_F32, RowsAt::Anywhere, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane,
                                    tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
     }
-    return item_phases(I, nchunk);
 }
 
 // Persistent workgroups, one per compute unit.  Work items (tile of 512 consecutive outputs x
@@ -859,41 +858,58 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         int phase = 0;
         for (int item_no = 0;; ++item_no) {
             const MetaSlot& M = L.meta[item_no % kMetaSlots];
+            const MetaSlot& MN = L.meta[(item_no + 1) % kMetaSlots];
             const int64_t work = slot_work(M);
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
-            const int n_phases = item_phases(cur, nchunk);
-            int32_t gr2[kSlabsPerProducer];
+            MetaSlot& claim_slot = L.meta[(item_no + (nchunk == 1 ? 2 : 1)) % kMetaSlots];       // of the item that is claimed during this one
+            // Items in both halves in a loop of their own.  The claim goes with the last chunk: with the first, 257 items of these on 256
+            // workgroups took 77 us for 67, whoever claimed first was not who would be done first.
             if (cur.both_halves) {
+                int32_t gr2[kSlabsPerProducer];
                 resolve_rows(gr, cur, 0, pwave, lane, tile_rows, row_stride);
                 resolve_rows(gr2, cur, kRowCap, pwave, lane, tile_rows, row_stride);
-            }
-            for (int p = 0; p < n_phases; ++p, ++phase) {
-                const int rb = (phase + 1) & 1;
-                const bool last = p == n_phases - 1;
-                if (cur.both_halves) {
-                    if (!last && !(p & 1)) {
-                        produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, p >> 1);
-                        produce_rows_resolved<PARTIAL>(L.rows[1], gr2, pwave, lane, feat, pitch, p >> 1);
-                    }
-                } else if (!last) {
-                    produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, p + 1);
+                for (int c = 0; c < nchunk; ++c) {
+                    produce_rows_resolved<PARTIAL>(L.rows[0], gr, pwave, lane, feat, pitch, c);
+                    produce_rows_resolved<PARTIAL>(L.rows[1], gr2, pwave, lane, feat, pitch, c);
+                    if (c == nchunk - 1 && pwave == 0) announce_next(claim_slot);
+                    __builtin_amdgcn_s_waitcnt(0);
+                    __syncthreads();
+                    __syncthreads();                         // the consumers have multiplied
                 }
+                phase += 2 * nchunk;
+                const int64_t nwork = slot_work(MN);
+                if (nwork >= 0) {
+                    const Item nxt = item_of(MN, nwork, nslice);
+                    if (!nxt.both_halves) {
+                        resolve_rows(gr, nxt, 0, pwave, lane, tile_rows, row_stride);
+                        produce_rows_resolved<PARTIAL>(L.rows[(phase + 1) & 1], gr, pwave, lane, feat, pitch, 0);
+                    }
+                    produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], nxt, pwave, lane, tile_perm, tile_blocks, block_stride);
+                }
+                __builtin_amdgcn_s_waitcnt(0);
+                __syncthreads();
+                ++phase;
+                continue;
+            }
+            for (int c = 0; c < nchunk; ++c, ++phase) {
+                const int rb = (phase + 1) & 1;
+                const bool last = c == nchunk - 1;
+                if (!last) produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, c + 1);
                 // At one chunk an item two chains of dependent loads side by side: the next item's row numbers and the claim of
                 // the item that starts two phases from now, then the rows and that item's header.  (One after the other they were longer than a
                 // phase's multiplies at one chunk an item: f16 32 -> 32 on 221 k voxels 36.0 -> 34.7 us, on 980 k 72 -> 71.)
-                const MetaSlot& MN = L.meta[(item_no + 1) % kMetaSlots];
                 const int64_t nwork = last ? slot_work(MN) : -1;
-                const bool next_rows = nwork >= 0 && !item_of(MN, nwork, nslice).both_halves;      // else they are staged by the next item
-                if (next_rows) resolve_rows(gr, item_of(MN, nwork, nslice), 0, pwave, lane, tile_rows, row_stride);
-                const bool claims = pwave == 0 && p == (nchunk == 1 ? 0 : n_phases - (cur.both_halves ? 3 : 2));   // ahead of the phase that looks at it
+                const Item nxt = nwork >= 0 ? item_of(MN, nwork, nslice) : cur;
+                const bool next_rows = nwork >= 0 && !nxt.both_halves;      // else they are staged by the next item
+                if (next_rows) resolve_rows(gr, nxt, 0, pwave, lane, tile_rows, row_stride);
+                const bool claims = pwave == 0 && c == max(nchunk - 2, 0);             // ahead of the phase that looks at it
                 const int64_t claimed = claims ? take_work(counters, xcd, per_xcd, wg_per_xcd, n_work, lane, n_orphans, open_lists) : -1;
                 if (nwork >= 0) {
                     if (next_rows) produce_rows_resolved<PARTIAL>(L.rows[rb], gr, pwave, lane, feat, pitch, 0);
-                    produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], item_of(MN, nwork, nslice), pwave, lane, tile_perm,
-                                 tile_blocks, block_stride);
+                    produce_meta(L.blocks[(item_no + 1) & 1], L.perm[(item_no + 1) % 3], nxt, pwave, lane, tile_perm, tile_blocks, block_stride);
                 }
-                if (claims) announce_claimed(L.meta[(item_no + (nchunk == 1 ? 2 : 1)) % kMetaSlots], claimed);
+                if (claims) announce_claimed(claim_slot, claimed);
                 __builtin_amdgcn_s_waitcnt(0);
                 __syncthreads();
             }
@@ -926,8 +942,13 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
             if (cur.general) {
-                phase += consume_long_item<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows,
-                                                                    row_stride, feat, wp, pitch, C_out, out, again);
+                consume_long_item<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows,
+                                                           row_stride, feat, wp, pitch, C_out, out, again);
+                // What the call saved is read back before the next item, with a wait of its own: among the other items' the wait for it
+                // was one for their weights and stores too, and every launch took 1 to 3 % longer, with such items or without (this and the
+                // producers' loop for them, us: 96 -> 96 on 98 k voxels 58.5 -> 57.7, 256 -> 256 on 393 k 657 -> 646).
+                __builtin_amdgcn_s_waitcnt(0);
+                phase += item_phases(cur, nchunk);
                 wa_at = wb_at = -1;       // nothing is handed over a call
 #pragma unroll
                 for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
