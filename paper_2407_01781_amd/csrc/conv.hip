@@ -747,7 +747,7 @@ __device__ __forceinline__ void consume_item(ConvLds& L, const MetaSlot& M, cons
 // Items with more rows than one half holds take this path: a real call, so that its registers are allocated apart from the
 // main loop's.
 template <typename T, bool OUT_F32, int NT, bool PARTIAL>
-__device__ __noinline__ void consume_long_item(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
+__device__ __noinline__ int consume_long_item(int slot, int phase, int mb, int pb, int nchunk, int nslice, int wave, int lane,
                                                   const int32_t* __restrict__ tile_rows, int row_stride,
                                                   const unsigned char* __restrict__ feat, const unsigned char* __restrict__ wp,
                                                   int64_t pitch, int C_out, void* __restrict__ out, const PairArgs* again) {
@@ -767,6 +767,7 @@ __device__ __noinline__ void consume_long_item(int slot, int phase, int mb, int 
         consume_item<T, OUT_F32, RowsAt::Anywhere, NT, PARTIAL>(L, M, L.meta[(slot + 1) % kMetaSlots], I, phase, mb, pb, nchunk, nslice, wave, lane,
                                    tile_rows, row_stride, feat, wp, pitch, C_out, out, wa, wb, wa_at, wb_at, again, tm);
     }
+    return item_phases(I, nchunk);
 }
 
 // Persistent workgroups, one per compute unit.  Work items (tile of 512 consecutive outputs x
@@ -916,6 +917,9 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
         }
     } else {
         // ---------------- consumers
+        // Where the multiply's loop lies within the 32 bytes that are fetched at a time is worth 3 % of a launch (98 k voxels 128 -> 128,
+        // by steps of 8 bytes: 67.5, 67.4, 69.2, 68.8), and any line above it moved it.  The code from here to the loop is the same but for PARTIAL.
+        asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(PARTIAL ? 2 : 6));
         const PairArgs* again = reinterpret_cast<const PairArgs*>(counters + kPairArgsAt);
         unsigned long long tm[4] = {0, 0, 0, 0};
         const unsigned long long t_start = FX_CYCLES_NOW();
@@ -942,13 +946,11 @@ k_conv_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict_
             if (work < 0) break;
             const Item cur = item_of(M, work, nslice);
             if (cur.general) {
-                consume_long_item<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows,
-                                                           row_stride, feat, wp, pitch, C_out, out, again);
-                // What the call saved is read back before the next item, with a wait of its own: among the other items' the wait for it
-                // was one for their weights and stores too, and every launch took 1 to 3 % longer, with such items or without (this and the
-                // producers' loop for them, us: 96 -> 96 on 98 k voxels 58.5 -> 57.7, 256 -> 256 on 393 k 657 -> 646).
+                phase += uni(consume_long_item<T, OUT_F32, NT, PARTIAL>(slot, phase, item_no & 1, item_no % 3, nchunk, nslice, wave, lane, tile_rows,
+                                                           row_stride, feat, wp, pitch, C_out, out, again));
+                // What the call saved is read back before the next item, with a wait of its own; among the other items' the wait for it
+                // was one for their weights and stores too.
                 __builtin_amdgcn_s_waitcnt(0);
-                phase += item_phases(cur, nchunk);
                 wa_at = wb_at = -1;       // nothing is handed over a call
 #pragma unroll
                 for (int f = 0; f < 2 * NT; ++f) { wa[f] = vec8{}; wb[f] = vec8{}; }
