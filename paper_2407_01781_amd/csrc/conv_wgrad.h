@@ -230,9 +230,10 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        // Row numbers -> LDS offsets, two to a word.  kWgStaged: an id block per wave at a time, a scalar loop, 1 to 5 % less of launches of
-        // which no tile takes it (1x1x1 map of 940 k voxels, 128 -> 128, 359 -> 341 us); in kWgAll, where tiles listed pair by pair are
-        // most of the work, that form was 3 to 5 % slower (map from a padded grid of 1.03 M, 128 -> 128, 484 / 499).
+        // Row numbers -> LDS offsets, two to a word.  kWgStaged on whole blocks: an id block per wave at a time, a scalar loop, 1 to 5 %
+        // less of launches of which no tile takes it (1x1x1 map of 940 k voxels, 128 -> 128, 359 -> 341 us).  Elsewhere that form cost
+        // registers: kWgAll, where tiles listed pair by pair are most of the work, 3 to 5 % slower (map from a padded grid of 1.03 M,
+        // 128 -> 128, 484 / 499), partial blocks 2 to 7 % (96 -> 96 on 200 k scattered voxels 83 / 89).
         if (row_ids) {
             static_assert(kIdBlockElems == 2 * 64, "a word of an id block per lane");
             uint32_t* words = reinterpret_cast<uint32_t*>(L.blocks);
@@ -240,7 +241,7 @@ k_wgrad_mfma(const TileHeader* __restrict__ tile_hdr, const uint16_t* __restrict
                 const uint32_t v = words[i];
                 words[i] = lds_row_code(min(v & 0xFFFFu, (uint32_t)kWgRowCap)) | lds_row_code(min(v >> 16, (uint32_t)kWgRowCap)) << 16;
             };
-            if (MODE == kWgStaged) {
+            if (MODE == kWgStaged && SHAPE == kWgFull) {
                 for (int b = uni(wave); b < n_blocks; b += W) convert(b * 64 + lane);
             } else {
                 for (int i = tid; i < n_blocks * 64; i += 64 * W) convert(i);
