@@ -333,8 +333,9 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for the leaf-window kernels: at those
  * shapes a locally dense grid (mean leaf occupancy >= 0.60; >= 0.40 where more than 16 tiles need more than 1022 rows) is summed leaf
  * by leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a sparser grid with at least 10 % of its voxels in dense leaves is
- * split per leaf between that kernel and the tile kernel inside the call where as many tiles need so many rows, or
- * (0.30 - that share) x outputs x blocks of 32 x 64 channels is at least 2^18 (option leaf_dispatch as for the forward pass).
+ * split per leaf between that kernel and the tile kernel inside the call where as many tiles need so many rows, or, of layers that
+ * are not summed from lists, (0.30 - that share) x outputs x blocks of 32 x 64 channels is at least 2^18 (option leaf_dispatch as
+ * for the forward pass).
  */
 fx_status fx_sparse_conv_bwd_data(const fx_kmap* km, const void* d_gout, fx_dtype dt, const void* d_w,
                                   int32_t C_in, int32_t C_out, void* d_gin, fx_dtype out_dt, void* stream);

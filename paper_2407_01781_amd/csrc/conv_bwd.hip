@@ -756,7 +756,9 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // 998 k 251 / 210, 2.4 M 545 / 416; 128 -> 128 on 125 k 106 / 107, 296 k 223 / 209, 998 k 822 / 613; share 0.2: 64 -> 64 on 550 k 137 / 149,
     // 1.9 M 445 / 393, 128 -> 128 on 318 k 249 / 258, 873 k 729 / 640; share 0.3: 128 -> 128 on 869 k 719 / 727; share 0.45 503 / 602 on 580 k.
     // Over 630 calls (cubes of 16, 24 and 48 voxels, one and many, and slabs, 37 k to 2.4 M voxels) the line is at most 12 % behind the
-    // faster side, tiles alone wherever few are not staged up to 43 %.  Bodies, surfaces and scan lines of 531 k, four in ten tiles not staged, 64 -> 64 226 split / 261.  leaf_dispatch = 2 forces it.
+    // faster side, tiles alone wherever few are not staged up to 43 %.  Bodies, surfaces and scan lines of 531 k, four in ten tiles not staged, 64 -> 64 226 split / 261.
+    // Layers that the pair lists serve have no ranges of tiles: the line is not asked there (256 -> 256, lists / split, share 0.11: 125 k 127 / 303,
+    // 998 k 775 / 2140; share 0.2, 550 k 617 / 1424).  leaf_dispatch = 2 forces it.
     int leaf_ranges = 0;
     if (mfma && km->K == 3 && km->stride == 1 && km->gin == km->gout && !km->is_inverse && leaf_wgrad_shape_supported(dt, C_in, C_out)) {
         const int ld = option(kOptLeafDispatch);
@@ -764,7 +766,7 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
         bool split = ld < 0 && occupancy < 0.40 && dense >= 0.10 && (km->mixed || !stream_captures(st));      // see the forward pass
         const int64_t blocks = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
-        if (split && (0.30 - dense) * (double)(km->n_out * blocks) < (double)(1 << 18)) {
+        if (split && (wgrad_lists_pays(km, dt, C_in, C_out) || (0.30 - dense) * (double)(km->n_out * blocks) < (double)(1 << 18))) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
             split = !kmap_few_unstaged(km);
         }
