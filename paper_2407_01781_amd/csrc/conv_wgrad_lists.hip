@@ -17,7 +17,7 @@ constexpr int kListTable = 3072;                   // units of a piece in the LD
 constexpr int kListLds = kListRing * (kListStageBytes + kListEntryBytes) + kListTable * 4 + 256;
 constexpr uint32_t kNoPair = 0xFFFFFFFFu;
 constexpr int kListRowBits = 32 - 9;               // of an entry: input row, output inside the tile
-constexpr int kListMaxTiles = 4096;                // 226 MB of lists
+constexpr int kListMaxTiles = 4096;                // 226 MB of lists (what the bound costs beyond: sheets, 256 -> 256, 1.99 M voxels 2.80 ms, 2.10 M 5.13)
 static_assert(kTileT == 512 && kListLds <= 160 * 1024, "entry format; LDS budget");
 static_assert(kListSlabRows * kListWaves == kListUnit, "a slab of either side per wave");
 
@@ -330,7 +330,9 @@ __global__ void __launch_bounds__(256) k_wgrad_lists_reduce(const float* __restr
 //     26 k 102 / 85, 41 k 115 / 105; indoor 10.5 k 46 / 64, 21 k 67 / 76, 88 k 178 / 159; random voxels, 24 a leaf, 23.7 k 74 / 75, 27 k
 //     82 / 64, 14 a leaf, 24.6 k 61 / 62, 29 k 69 / 64, 10 a leaf, 24.6 k 58 / 62, 26.5 k 62 / 62, 29 k 68 / 62; LiDAR 85 k 194 / 157, 269 k 587 / 396; 256 -> 512 on 9.9 k 70 / 78, 41 k 208 / 155; 512 -> 512 on 140 k 1224 / 710
 //   32 k where a leaf has few voxels, and a voxel few pairs: random voxels, 1 to 7 a leaf, 24 k 50..54 / 60..62, 28 k 55..61 / 61..62,
-//     33 k 62..68 / 62..64, 56 k 88..99 / 65..70; 512 -> 512 on 6.3 k 54..58 / 59..61, 8.4 k 65..70 / 60..62
+//     33 k 62..68 / 62..64, 56 k 88..99 / 65..70; 512 -> 512 on 6.3 k 54..58 / 59..61, 8.4 k 65..70 / 60..62; but with full leaves among
+//     them, whose tiles the tile kernel has side by side in one range, 24 k again: 7 voxels a leaf, 24 k with 2 % in full leaves 60 / 62, 4 %
+//     64 / 63, 8 % 73 / 64, 17 % in one body 89 / 68
 //   40 k for the one pair a voxel of a 1x1x1 map: 24 k 32 / 49, 30 k 43 / 50, 38 k 52 / 51, 50 k 66 / 53, 393 k 552 / 129; 512 -> 512 on
 //     8.1 k 45 / 41
 //   24 k between two grids, whose tiles list a row per pair: 32 k outputs, 3x3x3, input all of them 275 / 85, half 117 / 68, hardly any
@@ -344,7 +346,7 @@ bool wgrad_lists_pays(const fx_kmap* km, fx_dtype dt, int C_in, int C_out) {
     const int64_t work = km->n_out * (C_in / kListBlk) * (C_out / kListBlk);
     if (km->gin != km->gout) return work >= 24000;
     if (km->K == 1) return work >= 40000;
-    return work >= (km->n_in >= (int64_t)8 * km->gin->hdr.n_leaf ? 24000 : 32000);
+    return work >= (km->n_in >= (int64_t)8 * km->gin->hdr.n_leaf || 32 * km->gin->hdr.n_voxels_dense >= km->n_in ? 24000 : 32000);
 }
 
 fx_status wgrad_lists(const fx_kmap* km, const void* d_feat, const void* d_gout, fx_dtype dt, int C_in, int C_out, void* d_gw, fx_dtype out_dt,

@@ -113,16 +113,18 @@ def test_fewer_units_than_runs(touched, kernel, c_in, c_out, nan_scratch):
     assert nan_scratch() - before >= 3 * 4 * kernel ** 3 * c_in * c_out     # its scratch came from the arena
 
 
-@pytest.mark.parametrize("kernel,spread,line,c_in,c_out", [(1, 3.0, 40_000, 256, 256), (1, 3.0, 10_000, 512, 512), (3, 6.0, 32_000, 256, 256),
-                                                           (3, 6.0, 8_000, 512, 512), (3, 2.2, 24_000, 256, 256)])
+@pytest.mark.parametrize("kernel,spread,full,line,c_in,c_out", [(1, 3.0, 0, 40_000, 256, 256), (1, 3.0, 0, 10_000, 512, 512), (3, 6.0, 0, 32_000, 256, 256),
+                                                                (3, 6.0, 0, 8_000, 512, 512), (3, 2.2, 0, 24_000, 256, 256), (3, 6.0, 1, 32_000, 256, 256),
+                                                                (3, 6.0, 2, 24_000, 256, 256)])
 @pytest.mark.parametrize("past", [0, 1])
-def test_either_side_of_the_line(kernel, spread, line, c_in, c_out, past, nan_scratch):
-    """A voxel fewer than the line, and as many: 1x1x1 maps, some two voxels a leaf, and some forty.  The lists show by the size
-    of their scratch memory, which the tile kernel's partial sums stay below."""
+def test_either_side_of_the_line(kernel, spread, full, line, c_in, c_out, past, nan_scratch):
+    """A voxel fewer than the line, and as many: 1x1x1 maps, some two voxels a leaf, and some forty; full leaves with less and more
+    than one voxel in 32.  The lists show by the size of their scratch memory, which the tile kernel's partial sums stay below."""
     n = line - 1 + past
     rng = np.random.default_rng(line + past)
     pts = np.unique(rng.integers(0, int(spread * n ** (1 / 3)), size=(2 * n, 3)), axis=0)
-    pts = np.ascontiguousarray(rng.permutation(pts)[:n].astype(np.int32))
+    leaves = np.stack(np.meshgrid(-17 - np.arange(8 * full), np.arange(8), np.arange(8), indexing="ij"), axis=-1).reshape(-1, 3)
+    pts = np.ascontiguousarray(np.concatenate([leaves, rng.permutation(pts)[:n - len(leaves)]]).astype(np.int32))
     g = fx.build_index_grid(torch.from_numpy(pts).cuda(), np.array([[0, n]]))
     assert g.num_voxels == n and (n >= 8 * g.counts()[0]) == (spread < 4)
     km = fx.build_kernel_map(g, kernel, 1)
