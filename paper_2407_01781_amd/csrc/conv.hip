@@ -21,8 +21,8 @@
 
 namespace fx {
 
-// Whether the tile kernel starts with the items of long tiles, whose rows are gathered from global memory (k_conv_mfma): there
-// are more items than workgroups, and the lower half of the last XCD's workgroups has static items (those of the workgroups
+// Whether the tile kernel starts with the items of long tiles, whose rows fill both halves of the row buffer or are gathered from
+// global memory (k_conv_mfma): there are more items than workgroups, and the lower half of the last XCD's workgroups has static items (those of the workgroups
 // that start with long tiles are claimed like the others).  However many items a workgroup takes, a long one claimed last ends
 // the launch alone; where none is claimed late, starting with them costs a percent.  bf16, in the order of the list -> long
 // tiles first, us: 269 k LiDAR voxels 256 -> 256 (8.2 items a workgroup) 516 -> 446; 988 k with a solid block among the last
@@ -1811,8 +1811,8 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         // (mean occupancy below 0.40) and most of its voxels (55 %) sit in dense leaves; leaf_dispatch = 2 forces it.
         // bf16, split / tiles alone, us.  What the split gains it gains on whole solid bodies of some million voxels, with 75 % and more
         // of the voxels in them: a full cube and a thin cloud, 982 k, 90 % in the cube, 64 -> 64 303 / 318, 128 -> 128 874 / 939; a
-        // ball, 979 k, 75 %, 294 / 306, 835 / 933.  Smaller grids lose by it, the more the smaller they are: the leaf-window kernel walks a
-        // leaf in 80 us at 64 -> 64 and 230 at 128 -> 128 however few there are (114 k, 56 % in a cube, 90 / 47, 252 / 118; 414 k,
+        // ball, 979 k, 75 %, 294 / 306, 835 / 933.  Smaller grids lose by it, the more the smaller they are: its two launches run one after the other, and
+        // the leaf-window kernel alone takes 33 to 40 us at 64 -> 64 and 102 to 130 at 128 -> 128 however few leaves there are (114 k, 56 % in a cube, 90 / 47, 252 / 118; 414 k,
         // 90 %, 173 / 138, 487 / 406; cubes of 24, 998 k, 90 %, 318 / 240; bodies, surfaces and scan lines, 168 k (58 %) 122 / 69, 697 k (62 %)
         // 220 / 190).  Below 55 % it lost everywhere (245 k (45 %) 118 / 84, 531 k (48 %) 190 / 128; cube, 400 k, 50 %, 383 / 379), and there it is not
         // taken any more; the line does not yet ask for the size, which is what decides above.
@@ -1820,7 +1820,7 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         // 2^20 voxels at up to 192 contracted channels.  Tiles / leaf window, us: random voxels of a cube, 64 -> 64, 97 k at 0.37 46 / 74, 119 k
         // at 0.45 50 / 76, 732 k at 0.52 241 / 260, 513 k at 0.58 186 / 195, 865 k at 0.62 294 / 277, 1.17 M at 0.56 460 / 426, 2.8 M at
         // 0.59 1002 / 898, 1.33 M at 0.96 464 / 340; 128 -> 128, 1.17 M at 0.56 1297 / 1221, 1.11 M at 0.53 1177 / 1172; 256 -> 256, 1.17 M at 0.56 4446 / 4745.
-        // The size decides here as well, and the line asks for it only so far: 152 k at 0.58 88 / 79, and solid cubes of 33 k and
+        // The size decides here as well, and the line asks for it only so far: 144 k at 0.55 87 / 72, 152 k at 0.58 88 / 79, and solid cubes of 33 k and
         // 111 k 32 / 41 and 47 / 79, of 14 k 31 / 40 (128 -> 128 53 / 128).
         if (in_dt != FX_F32 && !km->is_inverse) {
             const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);

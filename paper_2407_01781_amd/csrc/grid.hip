@@ -64,7 +64,7 @@ __device__ __forceinline__ int find_batch(const BatchRanges& J, int B, int64_t r
 }
 
 // What the build's rows are: voxel coordinates, or points that are turned into the cells they lie in as they are read
-// (each of the two row passes reads the points; a pass of its own that writes the cells cost 85 us for 10 M points).
+// (by the one row pass; a pass of its own that writes the cells cost 85 us for 10 M points).
 struct RowSource {
     const int32_t* ijk;
     const float* xyz;          // kPoints only
@@ -1704,7 +1704,7 @@ static fx_status build_attempt(const RowSource& rows, int64_t n_rows, const Batc
     const size_t n_masks = partition ? (size_t)g->cap_leaf
                          : no_table ? 8 * (size_t)n_rows : n_slots + (from.kind == LeafSource::kPad ? (size_t)n_rows : 0);
     if (n_masks > 0x7FFFFFFFull) { fx_grid_destroy(g); set_error("grid build: too many leaves"); return FX_ERANGE; }
-    // Buckets of 1500 to 3000 rows from 800 k rows on: fewer, fuller buckets give the scatter pass longer runs per bucket and the
+    // Buckets of 1500 to 3000 rows from 800 k rows on: fewer, fuller buckets give the row pass longer runs per bucket and the
     // leaf pass fewer workgroups that each clear a 64 KB table (1 M rows: 98 us with ~1000 rows per bucket, 90 with
     // ~2000, 91 with ~4000, 107 with ~8000, which leaves half the compute units without a bucket; four grids of
     // 1.07 M rows: 140 / 123 / 117 / 111 us for ~500 / 1000 / 2000 / 4000).
