@@ -435,9 +435,36 @@ def test_long_tiles_first_every_row(dtype, c_in, c_out, cloud, corner, fx_opt):
     fx_opt("leaf_dispatch", "0")
     rng = np.random.default_rng(520 + cloud)
     pts = rng.integers(-300, 300, size=(cloud, 3)).astype(np.int32)
-    # (behind a cloud the block's tiles straddle its leaves and need more rows)
-    ax = [np.arange(d, dtype=np.int32) + corner for d in ((40, 24, 16) if corner < 0 else (40, 24, 8))]
+    ax = [np.arange(d, dtype=np.int32) + corner for d in (40, 24, 8)]
     pts = np.concatenate([pts, np.stack(np.meshgrid(*ax, indexing="ij"), axis=-1).reshape(-1, 3)])
+    g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
+    n, km = og.num_voxels, fx.build_kernel_map(g, 3, 1)
+    # the call is on the path: tiles whose rows (their own and the neighbours outside) are more than fit in LDS
+    table, own = km.dense().cpu().numpy(), np.arange(512)
+    n_tiles = (n + 511) // 512
+    n_long = sum(np.union1d(table[512 * t:512 * t + 512].ravel(), own + 512 * t).size - 1 > 792 for t in range(n_tiles))
+    n_slices, half = (c_out + (31 if c_out <= 32 else 63)) // (32 if c_out <= 32 else 64), torch.cuda.get_device_properties(0).multi_processor_count // 2
+    assert 0 < n_long <= 32 and n_long * n_slices <= half < 2 * half < n_tiles * n_slices
+    feat, wt = G.features_and_weights(33, n, c_in, c_out, 27, dtype)
+    d_x, d_w = H.to_device_storage(feat, dtype), H.to_device_storage(wt, dtype)
+    y = fx.sparse_conv_fwd(km, d_x, d_w, out_dtype=torch.float32, out=H.nan_filled((n, c_out), torch.float32))
+    fx_opt("force_scalar", "1")
+    ref = fx.sparse_conv_fwd(km, d_x, d_w, out_dtype=torch.float32)
+    # both sum the same products in 32 bits, of a sum with unit variance: 27 * c_in roundings of partial sums below 8 each
+    assert ((y - ref).abs().amax(1) <= 2 * 27 * c_in * 2.0 ** -24 * 8).all()
+    for s in [0] + list(range(20000, n - 300, 60000)) + [n - 300]:
+        H.conv_tolerance_check(y[s:s + 300].cpu().numpy(), O.conv(og, og, 3, 1, feat, wt, s, s + 300)[s:s + 300], "f32" if dtype == "f32" else dtype, 27, c_in)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out,cloud", [("bf16", 32, 512, 40000), ("bf16", 96, 320, 40000), ("f32", 32, 320, 40000), ("bf16", 48, 320, 40000),
+                                                    ("f16", 32, 32, 180000), ("bf16", 40, 24, 180000), ("f16", 64, 128, 660000)])
+def test_long_tiles_of_a_block_before_a_cloud_first(dtype, c_in, c_out, cloud, fx_opt):
+    # the same of tiles of more than 816 rows, which one half of the row buffer does not hold: in front of a cloud it takes a larger block,
+    # behind one the block's tiles straddle its leaves.  Every row against the scalar kernel, the first, last and some other rows against the oracle.
+    fx_opt("leaf_dispatch", "0")
+    rng = np.random.default_rng(520 + cloud)
+    pts = rng.integers(-300, 300, size=(cloud, 3)).astype(np.int32)
+    pts = np.concatenate([pts, H.box((40, 24, 16), (-2000,) * 3).astype(np.int32)])
     g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
     n, km = og.num_voxels, fx.build_kernel_map(g, 3, 1)
     # the call is on the path: tiles whose rows (their own and the neighbours outside) are more than one half of the row buffer holds

@@ -68,6 +68,18 @@ def _inputs_for(g_out, rows, rng):
     return np.array([k for k, v in have.items() if v])
 
 
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
+@pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [2 * CAP - 1, 2 * CAP, 2 * CAP + 1], [2 * CAP, 100, CAP], [1021, 1022, 500, 1023, 400], [2500, 1200, 300, CAP + 16, 815]])
+def test_rows_of_a_tile(rows, dtype, c_in, c_out):
+    rng = np.random.default_rng(len(rows) * 1000 + rows[0])
+    lattice = np.stack(np.meshgrid(np.arange(40), np.arange(8), np.arange(56), indexing="ij"), axis=-1).reshape(-1, 3) * 2
+    g_out = _index(lattice[:17_700])
+    km = fx.build_kernel_map_onto(_index(_inputs_for(g_out, rows, rng)), g_out, 3)
+    seen = _tile_rows(km)
+    assert all(seen.count(r) >= 1 for r in rows if r <= 2 * CAP + 1), (rows, sorted(set(seen)))
+    _check(km, dtype, c_in, c_out)
+
+
 def _between(rows, tiles, shared):
     """A map onto a grid whose first tiles read rows[t % len(rows)] inputs each; `shared`: onto a grid at least twice the input's
     size, by outputs far off, whose tiles hold every row once."""
@@ -84,7 +96,7 @@ def _between(rows, tiles, shared):
 
 @pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 32, 32), ("bf16", 128, 96), ("f16", 40, 64)])
 @pytest.mark.parametrize("rows", [[CAP - 1], [CAP, CAP + 1], [CAP + 1], [1023, 1024, 100, CAP], [1021, 1022, 500, 1023, 400], [2500, 1200, 300, CAP + 16, 815]])
-def test_rows_of_a_tile(rows, dtype, c_in, c_out):
+def test_rows_of_a_tile_between_two_grids(rows, dtype, c_in, c_out):
     """Staged in one half and in both (to 1024 rows, what a tile between two grids holds once each), and a row per pair beyond."""
     km = _between(rows, 35, True)
     seen = _tile_rows(km)

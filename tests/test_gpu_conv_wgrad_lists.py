@@ -57,7 +57,7 @@ def _check(km, dtype, c_in, c_out, spoil=False):
     assert torch.equal(low.view(torch.int16), gw.to(H.TORCH_DT[dtype]).view(torch.int16)) or spoil
 
 
-# 24 k outputs x blocks and little more, where these grids, of more than 8 voxels a leaf, start to come here
+# 6 k outputs at four blocks and 24 k at one are the smallest sizes that come here; the last tile holds one voxel and more
 @pytest.mark.parametrize("n,dtype,c_in,c_out", [(27_000, "bf16", 256, 256), (30_000, "f16", 256, 256), (14_500, "bf16", 256, 512), (7_000, "f16", 512, 512),
                                                 (60_000, "bf16", 512, 256)])
 @pytest.mark.parametrize("thick", [0, 24])

@@ -96,6 +96,36 @@ def test_full_size_mixed_grid_every_row():
 @pytest.mark.parametrize("corner", [-2000, 1000])
 @pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 96, 128)])
 def test_split_weight_gradient_with_listed_tiles(dtype, c_in, c_out, corner, switch, fx_opt):
+    # full leaves for the leaf-window kernel, a sparse cloud whose tiles are staged, and a block at a third of its voxels, below
+    # the line of a dense leaf, whose few tiles are not staged: one sum of three kernels' partial sums, the first or the last tiles
+    if switch is not None:
+        fx_opt("leaf_dispatch", switch)
+    rng = np.random.default_rng(91)
+    box = lambda dims, at: np.stack(np.meshgrid(*[np.arange(d, dtype=np.int64) + at for d in dims], indexing="ij"), axis=-1).reshape(-1, 3)
+    third = box((32, 32, 24), corner)
+    pts = np.concatenate([rng.integers(-300, 300, size=(30000, 3)), box((32, 32, 16), corner + 512), third[rng.random(third.shape[0]) < 0.34]]).astype(np.int32)
+    g, og = H.both_grids(pts[rng.permutation(pts.shape[0])], np.array([[0, pts.shape[0]]]))
+    n, km = og.num_voxels, fx.build_kernel_map(g, 3, 1)
+    cnt = np.diff(np.append(g.leaf_table()["offset"], n))
+    sparse_out = np.repeat(cnt < 205, cnt)
+    assert (cnt == 512).sum() == 32 and n / (512 * cnt.size) < 0.20 and 0.1 < cnt[cnt >= 205].sum() / n < 0.5
+    # tiles without their dense leaves' outputs: some whose rows do not fit (792), no more than are listed (16)
+    table, tiles = km.dense().cpu().numpy(), range((n + 511) // 512)
+    rows = [np.unique(table[512 * t:512 * t + 512][sparse_out[512 * t:512 * t + 512]]) for t in tiles]
+    assert 1 <= sum(r.size - 1 > 792 for r in rows) and sum(np.union1d(r, np.arange(512) + 512 * t).size - 1 > 792 for t, r in enumerate(rows)) <= 16
+    feat, _ = G.features_and_weights(92, n, c_in, c_out, 27, dtype)
+    gy = G.round_to_dtype(np.random.default_rng(93).standard_normal((n, c_out)).astype(np.float32), dtype)
+    gw = H.nan_filled((27, c_in, c_out), torch.float32)
+    fx.sparse_conv_bwd_weight(km, H.to_device_storage(feat, dtype), H.to_device_storage(gy, dtype), out_dtype=torch.float32, out=gw)
+    ref = O.conv_bwd_weight(og, og, 3, 1, feat, gy)
+    num = np.sqrt(((gw.cpu().numpy().astype(np.float64) - ref) ** 2).sum(axis=(1, 2)))
+    assert (num / np.maximum(np.sqrt((ref ** 2).sum(axis=(1, 2))), 1e-3 * np.sqrt(c_in * c_out))).max() <= 2e-3
+
+
+@pytest.mark.parametrize("switch", [None, 2])
+@pytest.mark.parametrize("corner", [-2000, 1000])
+@pytest.mark.parametrize("dtype,c_in,c_out", [("bf16", 64, 64), ("f16", 96, 128)])
+def test_automatic_split_weight_gradient_with_listed_tiles(dtype, c_in, c_out, corner, switch, fx_opt):
     # full leaves for the leaf-window kernel, whose tiles in the whole map are too long for the weight gradient to stage (more than are
     # listed, so that the automatic rule splits), a sparse cloud whose tiles are staged, and sheets that face one another, of some
     # voxels a leaf, with a few tiles that are not staged: one sum of three kernels' partial sums, the first or the last tiles
