@@ -1817,11 +1817,12 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         // 220 / 190).  Below 55 % it lost everywhere (245 k (45 %) 118 / 84, 531 k (48 %) 190 / 128; cube, 400 k, 50 %, 383 / 379), and there it is not
         // taken any more; the line does not yet ask for the size, which is what decides above.
         // From 0.40 on the leaf-window kernel takes the whole of a small grid (below 16 k voxels), and of any from 0.60 on, from 0.54 on above
-        // 2^20 voxels at up to 192 contracted channels.  Tiles / leaf window, us: random voxels of a cube, 64 -> 64, 97 k at 0.37 46 / 74, 119 k
+        // 2^20 voxels at up to 192 contracted channels, or 2^19 at 32 where more than 64 are produced.  Tiles / leaf window, us: random voxels of a cube, 64 -> 64, 97 k at 0.37 46 / 74, 119 k
         // at 0.45 50 / 76, 732 k at 0.52 241 / 260, 513 k at 0.58 186 / 195, 865 k at 0.62 294 / 277, 1.17 M at 0.56 460 / 426, 2.8 M at
-        // 0.59 1002 / 898, 1.33 M at 0.96 464 / 340; 128 -> 128, 1.17 M at 0.56 1297 / 1221, 1.11 M at 0.53 1177 / 1172; 256 -> 256, 1.17 M at 0.56 4446 / 4745.
-        // The size decides here as well, and the line asks for it only so far: 144 k at 0.55 87 / 72, 152 k at 0.58 88 / 79, and solid cubes of 33 k and
-        // 111 k 32 / 41 and 47 / 79, of 14 k 31 / 40 (128 -> 128 53 / 128).
+        // 0.59 1002 / 898, 1.33 M at 0.96 464 / 340; 128 -> 128, 1.17 M at 0.56 1297 / 1221, 1.11 M at 0.53 1177 / 1172; 256 -> 256, 1.17 M at 0.56 4446 / 4745; 32 -> 192, 566 k at
+        // 0.59 325 / 281, 770 k at 0.59 442 / 362, 952 k at 0.55 534 / 468 (32 -> 128 216 / 201, 318 / 260, 376 / 335), balls of 578 k at 0.56 341 / 323 (231 / 249).
+        // The size decides here as well, and the line asks for it only so far: solid cubes of 33 k and 111 k 32 / 41 and 47 / 79, of 14 k 31 / 40
+        // (128 -> 128 53 / 128), and just past a round of tiles up to 7 % the other way (141 k at 0.54 80 / 76).
         if (in_dt != FX_F32 && !km->is_inverse) {
             const double dense = (double)km->gin->hdr.n_voxels_dense / (double)std::max<int64_t>(1, km->n_in);
             // (a second map that a captured call built would not be there for the next call that is not replayed)
@@ -1838,8 +1839,18 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
             }
         }
         const bool scalar_otherwise = in_dt == FX_F32 && C_in % 16 != 0;
-        const double line = scalar_otherwise ? 0.08 : in_dt == FX_F32 || km->n_in < 16384 ? 0.40 : km->n_in < (1 << 20) || C_in > 192 ? 0.60 : 0.54;
-        const bool take = ld >= 0 ? ld >= 1 : occupancy >= line;
+        const int64_t large = C_in <= 32 && C_out > 64 ? 1 << 19 : 1 << 20;      // several slices of one chunk stage every row once per slice
+        const double line = scalar_otherwise ? 0.08 : in_dt == FX_F32 || km->n_in < 16384 ? 0.40 : km->n_in < large || C_in > 192 ? 0.60 : 0.54;
+        // Layers of one chunk, and of two at up to 64 produced channels, take whole rounds of either kernel's workgroups: one a compute
+        // unit of the tile kernel, two of the leaf window's.  With three or four rounds of tiles but fewer of leaves (from 0.50 mean occupancy on) the
+        // leaf window is faster, or as fast.  Tiles / leaf window, us: random voxels of a cube, 267 k at 0.58 (523 tiles, 900 leaves) 32 -> 64
+        // 86 / 67, 32 -> 128 126 / 108, 64 -> 64 111 / 105; 302 k at 0.59 (589, 999) 87 / 70, 136 / 112, 132 / 110; 409 k at 0.55 (799, 1452)
+        // 107 / 93, 164 / 155, 155 / 146; a shell of 268 k (523, 982) 91 / 88, 137 / 132, 131 / 129; a slab of 288 k (563, 1000) 83 / 83, 125 / 132,
+        // 123 / 127.  As many rounds of leaves: 309 k at 0.55 (605, 1100) 87 / 85, 133 / 138, 128 / 136, balls of 347 k (678, 1205) 92 / 105.  Two rounds of
+        // tiles over one of leaves gain at 32 -> 64 only (55 / 55 to 56 / 52; 64 -> 64 67 / 81), five and more are uneven (balls of 578 k 146 / 157).
+        const int64_t cu = compute_units(), rounds = (km->n_tiles + cu - 1) / cu, leaf_rounds = (km->gin->hdr.n_leaf + 2 * cu - 1) / (2 * cu);
+        const bool fewer_rounds = in_dt != FX_F32 && (C_in <= 32 || (C_in <= 64 && C_out <= 64)) && (rounds == 3 || rounds == 4) && leaf_rounds < rounds;
+        const bool take = ld >= 0 ? ld >= 1 : occupancy >= line || fewer_rounds;
         if (take)
             return leaf_apply("sparse convolution (leaf-window kernels)", km->gin, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt,
                               st, mode);

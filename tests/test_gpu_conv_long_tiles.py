@@ -260,3 +260,37 @@ def test_line_of_large_dense_grids(p, n_more, c_in, leaf):
     for k in range(27):
         ref = ref + torch.where((t[:, k] >= 0)[:, None], x[t[:, k].clamp(min=0)].double(), 0.0) @ w[k].double()
     assert _norm_ok(y[at], ref, 1.4e-5 * 2)                          # 27 * 224 products a sum, where 27 * 128 give 1.4e-5
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out,tiles,leaves,leaf", [
+    ("bf16", 32, 64, 513, 1024, True), ("bf16", 32, 64, 513, 1025, False), ("f16", 32, 64, 512, 1024, False), ("f16", 64, 64, 1024, 1800, False),
+    ("bf16", 64, 64, 880, 1536, True), ("bf16", 64, 64, 880, 1537, False), ("bf16", 64, 64, 1025, 2000, False), ("f16", 32, 192, 590, 1000, True),
+    ("f16", 64, 128, 590, 1000, False), ("bf16", 96, 64, 590, 1000, False), ("bf16", 32, 128, 1024, 1860, True), ("bf16", 32, 64, 1024, 1860, False),
+    ("bf16", 32, 128, 1023, 1860, False)])
+def test_rounds_of_tiles_and_leaves(dtype, c_in, c_out, tiles, leaves, leaf):
+    """Random voxels of a block of leaves between the lines: three or four rounds of tiles against fewer of leaves, as many, and at 32
+    channels 2^19 voxels.  Forward pass and, where the counts allow it, the input gradient."""
+    n = 512 * tiles
+    assert (torch.cuda.get_device_properties(0).multi_processor_count, 0.40 < tiles / leaves) == (256, True)
+    cells = np.random.default_rng(tiles).permutation(512 * leaves)[:n]
+    g = _index(8 * np.stack(np.unravel_index(cells // 512, (16,) * 3), axis=1) + np.stack(np.unravel_index(cells % 512, (8,) * 3), axis=1))
+    assert g.num_voxels == n and g.counts()[0] == leaves
+    km = fx.build_kernel_map(g, 3, 1)
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    x = torch.randn((n, c_in), generator=gen, device="cuda").to(H.TORCH_DT[dtype])
+    w = torch.randn((27, c_in, c_out), generator=gen, device="cuda").to(H.TORCH_DT[dtype])
+    at = torch.cat([torch.arange(s, s + 512, device="cuda") for s in (0, n // 2, n - 512)])
+    t = km.dense()[at].long()
+    for back in ([False, True] if c_in == c_out else [False]):
+        fx.profile_enable(True)
+        fx.profile_reset()
+        y = (fx.sparse_conv_bwd_data if back else fx.sparse_conv_fwd)(km, x, w, out_dtype=torch.float32, out=H.nan_filled((n, c_out), torch.float32))
+        torch.cuda.synchronize()
+        slots = fx.profile_read()
+        fx.profile_enable(False)
+        assert ("k_conv_leaf" in slots) == leaf
+        ref = 0.0
+        for k in range(27):                                          # an input is the neighbour at the opposite offset of its outputs
+            m = t[:, 26 - k] if back else t[:, k]
+            ref = ref + torch.where((m >= 0)[:, None], x[m.clamp(min=0)].double(), 0.0) @ (w[k].double().t() if back else w[k].double())
+        assert _norm_ok(y[at], ref, 1.4e-5)
