@@ -333,7 +333,8 @@ fx_status fx_sparse_conv_fwd_noalloc(const fx_kmap* km, const void* d_feat, fx_d
  * shapes, all on strided maps, and layers of both counts a multiple of 256 that are summed from lists of pairs (from 24 k outputs x
  * 256 x 256 blocks on; 32 k on 3x3x3 maps of one grid with fewer than 8 voxels a leaf and less than 1/32 of them in dense leaves, 40 k
  * on 1x1x1 maps of one grid) sum over existing pairs only.  On the (3,1) map of one grid bwd_weight follows the forward pass's rule for the leaf-window kernels: at those
- * shapes a locally dense grid (mean leaf occupancy >= 0.60; >= 0.40 where more than 16 tiles need more than 1022 rows) is summed leaf
+ * shapes a locally dense grid (mean leaf occupancy >= 0.60; >= 0.40 where more than 16 tiles need more than 1022 rows, or
+ * more than one in layers of one block of 32 x 64 channels, or of up to four with outputs x blocks below 200 k) is summed leaf
  * by leaf without the map (fx_sparse_conv_leaf_bwd_weight), and a sparser grid with at least 10 % of its voxels in dense leaves is
  * split per leaf between that kernel and the tile kernel inside the call where as many tiles need so many rows, or, of layers that
  * are not summed from lists, (0.30 - that share) x outputs x blocks of 32 x 64 channels is at least 2^18 (option leaf_dispatch as

@@ -723,7 +723,11 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
     // The 16-bit types at depth >= 32 take it on locally dense grids only (mean leaf occupancy of 0.40 and above): there the
     // tiles of the map need more rows than the tile kernel's LDS holds.  Below 0.60, where all but a few of the map's tiles
     // are staged, the tiles are faster (bf16 64 -> 64, tiles / leaf window, us: random voxels of a cube, 119 k at 0.45 of its leaves,
-    // many tiles not staged, 71 / 71, 598 k at 0.43, all staged, 170 / 253).  Option leaf_dispatch = 1 takes it on any grid.
+    // many tiles not staged, 71 / 71, 598 k at 0.43, all staged, 170 / 253).  Two and more that are listed are a second launch, which
+    // layers of one block of 32 x 64 channels, and small ones of up to four, take longer for than what the staged ones gain (random
+    // voxels of a cube, 32 -> 64, 103 k at 0.59 68 / 52, 64 -> 64, 76 k at 0.59 71 / 52, 64 -> 128, 38 k at 0.59 62 / 51; beyond, 32 -> 192 on
+    // 96 k at 0.55 72 / 82, 64 -> 128 75 / 96, 128 -> 128 on 38 k 76 / 75, on 83 k 112 / 143): over 120 of these grids the line is at most 17 %
+    // behind the faster side, tiles wherever few are listed up to 42 %.  Option leaf_dispatch = 1 takes it on any grid.
     if (km->K == 3 && km->stride == 1 && km->gin == km->gout && leaf_wgrad_shape_supported(dt, C_in, C_out) &&
         !force_scalar()) {
         const int ld = option(kOptLeafDispatch);
@@ -731,7 +735,9 @@ extern "C" fx_status fx_sparse_conv_bwd_weight(const fx_kmap* km, const void* d_
         bool take = dt == FX_F32 ? ld != 0 : (ld >= 0 ? ld == 1 : occupancy >= 0.40);
         if (take && dt != FX_F32 && ld < 0 && occupancy < 0.60) {
             FX_TRY(kmap_unstaged_tiles(const_cast<fx_kmap*>(km), st));
-            take = km->n_tiles == 0 || !kmap_few_unstaged(km);
+            const int64_t blocks = ((C_in + kWgCi - 1) / kWgCi) * ((C_out + kWgCo - 1) / kWgCo);
+            const bool lists_cost = km->h_n_unstaged >= 2 && blocks <= 4 && (blocks == 1 || blocks * km->n_out < 200000);
+            take = km->n_tiles == 0 || !kmap_few_unstaged(km) || lists_cost;
         }
         if (take)
             return leaf_wgrad("sparse convolution weight gradient (leaf-window kernel)", km->gin, d_feat, d_gout, dt, C_in,

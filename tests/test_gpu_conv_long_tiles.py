@@ -294,3 +294,26 @@ def test_rounds_of_tiles_and_leaves(dtype, c_in, c_out, tiles, leaves, leaf):
             m = t[:, 26 - k] if back else t[:, k]
             ref = ref + torch.where((m >= 0)[:, None], x[m.clamp(min=0)].double(), 0.0) @ (w[k].double().t() if back else w[k].double())
         assert _norm_ok(y[at], ref, 1.4e-5)
+
+
+@pytest.mark.parametrize("dtype,c_in,c_out,n,p,listed,leaf", [
+    ("bf16", 64, 64, 20_000, 0.59, 1, False), ("bf16", 64, 64, 24_000, 0.58, 2, True), ("f16", 64, 128, 24_000, 0.58, 2, True),
+    ("bf16", 96, 128, 24_000, 0.58, 2, False), ("f16", 32, 64, 100_000, 0.53, 3, True), ("bf16", 64, 64, 90_000, 0.55, 2, True),
+    ("f16", 64, 64, 100_000, 0.53, 3, False), ("bf16", 64, 128, 90_000, 0.55, 2, False)])
+def test_dense_grids_with_few_listed_tiles(dtype, c_in, c_out, n, p, listed, leaf, fx_opt):
+    """The weight gradient between 0.40 and 0.60 mean occupancy: one tile that is not staged, and more on either side of the sizes
+    at which their launch is worth it.  Which kernel ran shows in the bits."""
+    side = int(round((n / p) ** (1 / 3) / 8)) * 8
+    depth = int(round(n / p / (side * side) / 8)) * 8
+    g = _index(np.argwhere(np.random.default_rng(n).random((side, side, depth)) < p))
+    km = fx.build_kernel_map(g, 3, 1)
+    assert 0.40 <= km.n_out / (512 * g.counts()[0]) < 0.60 and (H.tile_row_counts(km.dense().cpu().numpy()) > 1022).sum() == listed
+    assert (listed >= 2 and (c_in * c_out == 32 * 64 or c_in * c_out <= 4 * 32 * 64 and c_in * c_out * km.n_out < 32 * 64 * 200_000)) == leaf
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    x, gy = (torch.randn((km.n_out, c), generator=gen, device="cuda").to(H.TORCH_DT[dtype]) for c in (c_in, c_out))
+    gw = fx.sparse_conv_bwd_weight(km, x, gy, out_dtype=torch.float32)
+    for switch in (0, 1):
+        fx_opt("leaf_dispatch", switch)
+        assert torch.equal(gw, fx.sparse_conv_bwd_weight(km, x, gy, out_dtype=torch.float32)) == (switch == int(leaf))
+    fx_opt("leaf_dispatch", -1)
+    _check(km, dtype, c_in, c_out)
