@@ -259,7 +259,7 @@ void fx_kmap_destroy(fx_kmap* km);
  *     contracted dimension;
  *   - on a 3x3x3 stride-1 submanifold map whose grid is locally dense (mean leaf occupancy >= 0.40, of the 16-bit
  *     types >= 0.60 from 16 k voxels on, or 0.54 from 2^20 voxels on with C_in <= 192 (2^19 with C_in <= 32, C_out > 64), or,
- *     with C_in <= 32 or both counts <= 64, where 3 or 4 rounds of tiles (512 voxels, one a compute unit) stand against
+ *     with C_in <= 32 or C_out <= 64, where 3 or 4 rounds of tiles (512 voxels, one a compute unit) stand against
  *     fewer rounds of leaves (two a compute unit); >= 0.08
  *     for FX_F32 with C_in not a multiple of 16) and whose shape fx_sparse_conv_leaf_fwd serves: the
  *     leaf-window kernels;

@@ -1841,15 +1841,16 @@ fx_status fx::conv_apply(const fx_kmap* km, const void* d_feat, fx_dtype in_dt, 
         const bool scalar_otherwise = in_dt == FX_F32 && C_in % 16 != 0;
         const int64_t large = C_in <= 32 && C_out > 64 ? 1 << 19 : 1 << 20;      // several slices of one chunk stage every row once per slice
         const double line = scalar_otherwise ? 0.08 : in_dt == FX_F32 || km->n_in < 16384 ? 0.40 : km->n_in < large || C_in > 192 ? 0.60 : 0.54;
-        // Layers of one chunk, and of two at up to 64 produced channels, take whole rounds of either kernel's workgroups: one a compute
+        // Layers of one chunk or of one slice of 64 produced channels take whole rounds of either kernel's workgroups: one a compute
         // unit of the tile kernel, two of the leaf window's.  With three or four rounds of tiles but fewer of leaves (from 0.50 mean occupancy on) the
         // leaf window is faster, or as fast.  Tiles / leaf window, us: random voxels of a cube, 267 k at 0.58 (523 tiles, 900 leaves) 32 -> 64
         // 86 / 67, 32 -> 128 126 / 108, 64 -> 64 111 / 105; 302 k at 0.59 (589, 999) 87 / 70, 136 / 112, 132 / 110; 409 k at 0.55 (799, 1452)
         // 107 / 93, 164 / 155, 155 / 146; a shell of 268 k (523, 982) 91 / 88, 137 / 132, 131 / 129; a slab of 288 k (563, 1000) 83 / 83, 125 / 132,
-        // 123 / 127.  As many rounds of leaves: 309 k at 0.55 (605, 1100) 87 / 85, 133 / 138, 128 / 136, balls of 347 k (678, 1205) 92 / 105.  Two rounds of
+        // 123 / 127; 96, 128, 192 -> 64 on 302 k 173 / 146, 211 / 178, 298 / 248, the slab 168 / 174, 197 / 217, 281 / 311 (64 -> 128 206 / 184 and 189 / 219,
+        // even on the whole).  As many rounds of leaves: 309 k at 0.55 (605, 1100) 87 / 85, 133 / 138, 128 / 136, balls of 347 k (678, 1205) 92 / 105.  Two rounds of
         // tiles over one of leaves gain at 32 -> 64 only (55 / 55 to 56 / 52; 64 -> 64 67 / 81), five and more are uneven (balls of 578 k 146 / 157).
         const int64_t cu = compute_units(), rounds = (km->n_tiles + cu - 1) / cu, leaf_rounds = (km->gin->hdr.n_leaf + 2 * cu - 1) / (2 * cu);
-        const bool fewer_rounds = in_dt != FX_F32 && (C_in <= 32 || (C_in <= 64 && C_out <= 64)) && (rounds == 3 || rounds == 4) && leaf_rounds < rounds;
+        const bool fewer_rounds = in_dt != FX_F32 && (C_in <= 32 || C_out <= 64) && (rounds == 3 || rounds == 4) && leaf_rounds < rounds;
         const bool take = ld >= 0 ? ld >= 1 : occupancy >= line || fewer_rounds;
         if (take)
             return leaf_apply("sparse convolution (leaf-window kernels)", km->gin, d_feat, in_dt, d_w, C_in, C_out, d_out, out_dt,

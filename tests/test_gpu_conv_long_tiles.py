@@ -265,7 +265,7 @@ def test_line_of_large_dense_grids(p, n_more, c_in, leaf):
 @pytest.mark.parametrize("dtype,c_in,c_out,tiles,leaves,leaf", [
     ("bf16", 32, 64, 513, 1024, True), ("bf16", 32, 64, 513, 1025, False), ("f16", 32, 64, 512, 1024, False), ("f16", 64, 64, 1024, 1800, False),
     ("bf16", 64, 64, 880, 1536, True), ("bf16", 64, 64, 880, 1537, False), ("bf16", 64, 64, 1025, 2000, False), ("f16", 32, 192, 590, 1000, True),
-    ("f16", 64, 128, 590, 1000, False), ("bf16", 96, 64, 590, 1000, False), ("bf16", 32, 128, 1024, 1860, True), ("bf16", 32, 64, 1024, 1860, False),
+    ("f16", 64, 128, 590, 1000, False), ("bf16", 96, 64, 590, 1000, True), ("bf16", 96, 128, 590, 1000, False), ("bf16", 32, 128, 1024, 1860, True), ("bf16", 32, 64, 1024, 1860, False),
     ("bf16", 32, 128, 1023, 1860, False)])
 def test_rounds_of_tiles_and_leaves(dtype, c_in, c_out, tiles, leaves, leaf):
     """Random voxels of a block of leaves between the lines: three or four rounds of tiles against fewer of leaves, as many, and at 32
