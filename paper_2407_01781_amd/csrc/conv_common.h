@@ -135,7 +135,7 @@ enum WeightMode { kWeightsForward = 0, kWeightsTransposed = 1, kWeightsFlipped =
 // the 32 lanes of a half-wave store one whole row slice.
 
 // Packs the weights (C_in = contracted channels, C_out = produced channels, in the sense of the
-// mode) and zeroes the eight work-list counters behind them.  With tile_long it also lists the long tiles (whose rows
+// mode) and zeroes the eight work-list counters behind them, or n_clear (at most 64) words.  With tile_long it also lists the long tiles (whose rows
 // do not fit one row buffer): their number goes to counters[8], the first kMaxLongTiles of them behind it (kConvWorkInts in
 // all).
 // n_nt = 1: slices of 32 produced channels, column m of the one n-tile = channel m.  `again` goes to counters[kPairArgsAt]
@@ -154,7 +154,7 @@ static_assert(9 + kMaxLongTiles + 1 <= kPairArgsAt && kPairArgsAt * 4 + sizeof(P
               "counters, count, list, one more counter, pair arguments");
 void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out, int elem_bytes, int32_t* counters,
                          int mode, hipStream_t st, const uint8_t* tile_long = nullptr, int64_t n_tiles = 0, int n_nt = 2,
-                         const PairArgs& again = PairArgs{});
+                         const PairArgs& again = PairArgs{}, int n_clear = 8);
 
 // The forward multiply-accumulate over a map with the weights read in the given mode: d_out[o,:]
 // = sum over kappa of d_feat[map(o,kappa),:] . Wmode[kappa], C_in channels in, C_out channels out.

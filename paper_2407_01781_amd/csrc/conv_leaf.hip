@@ -1087,16 +1087,11 @@ fx_status fx::leaf_apply(const char* who, const fx_grid* g, const void* d_src, f
         if (g->hdr.n_voxels == 0) return FX_OK;
         void* wpk = nullptr;
         const size_t wbytes = packed_weight_bytes(27, C_contract, C_produce, 2);
-        // behind the packed weights: 32 bytes that the memset and the packing kernel clear (the first four are the
-        // leaf kernel's work counter), then a 64-byte row of zeros
+        // behind the packed weights 24 words that the packing launch clears: the leaf kernel's work counter is the first, a
+        // 64-byte row of zeros the last sixteen.  (A memset was 1 to 2 us more, and a memset node in a caller's graph.)
         FX_TRY(dev_alloc(&wpk, wbytes + 96, st));
         const void* zero_row = (const char*)wpk + wbytes + 32;
-        if (hipMemsetAsync((char*)wpk + wbytes, 0, 96, st) != hipSuccess) {
-            dev_free(wpk, st);
-            set_error("%s: memset failed", who);
-            return FX_EDEVICE;
-        }
-        launch_pack_weights(d_w, wpk, 27, C_contract, C_produce, 2, reinterpret_cast<int32_t*>((char*)wpk + wbytes), mode, st);
+        launch_pack_weights(d_w, wpk, 27, C_contract, C_produce, 2, reinterpret_cast<int32_t*>((char*)wpk + wbytes), mode, st, nullptr, 0, 2, PairArgs{}, 24);
         fx_status rc;
         if (dt == FX_BF16)
             rc = out_dt == FX_F32 ? launch_leaf16<__bf16, true>(g, d_src, wpk, d_dst, C_contract, C_produce, (char*)wpk + wbytes, zero_row, leaf_list, n_list, st)

@@ -42,6 +42,7 @@ def _thinned(box, p):
 GRIDS = {
     "cloud": lambda: _cloud(30_000, 90, 1),
     "tiles that are not staged": lambda: _thinned(_box(64, 48, 40), 0.37),
+    "occupancy 0.7": lambda: _thinned(_box(48, 48, 48), 0.7),
     "occupancy 0.47": lambda: _thinned(_box(48, 48, 48), 0.47),
     "a cube with a ninth of the voxels": lambda: np.concatenate([_box(32, 32, 32), 200 + _cloud(269_000, 260, 12)]),
     "a cube with most of the voxels": lambda: np.concatenate([_box(32, 32, 32), 200 + _cloud(15_000, 100, 2)]),
@@ -51,7 +52,7 @@ GRIDS = {
 @pytest.mark.parametrize("called_before", [True, False])
 @pytest.mark.parametrize("name,c_in,c_out", [("cloud", 64, 64), ("cloud", 256, 256), ("tiles that are not staged", 64, 64), ("occupancy 0.47", 64, 128),
                                              ("a cube with a ninth of the voxels", 128, 128), ("a cube with most of the voxels", 64, 64),
-                                             ("padded cloud", 64, 64)])
+                                             ("padded cloud", 64, 64), ("occupancy 0.7", 64, 64)])
 def test_replays_of_a_layer(name, c_in, c_out, called_before):
     g = _index(GRIDS[name.replace("padded ", "")]())
     onto = name.startswith("padded")
