@@ -42,8 +42,8 @@ __host__ __device__ inline bool long_tiles_first(int64_t n_work, int wgs) {
 // and the 32 lanes of a half-wave store one whole output row.  With one n-tile (n_nt = 1) a slice is 32
 // channels and column n is channel n of it.
 template <typename E>   // uint16_t or uint32_t: the bits of one element
-__global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out,
-                               int32_t* __restrict__ counters, int mode, int n_nt, const uint8_t* __restrict__ tile_long, int64_t n_tiles, PairArgs again, int n_clear) {
+__global__ void k_pack_weights(const E* __restrict__ w, E* __restrict__ wp, int K3, int C_in, int C_out, int n_clear,
+                               int32_t* __restrict__ counters, int mode, int n_nt, const uint8_t* __restrict__ tile_long, int64_t n_tiles, PairArgs again) {
     if (blockIdx.x == 0 && (int)threadIdx.x < n_clear) counters[threadIdx.x] = 0;   // the convolution's work-list counters
     if (again.hdr && blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<PairArgs*>(counters + kPairArgsAt) = again;
     if (tile_long && blockIdx.x == gridDim.x - 1) {
@@ -115,9 +115,9 @@ void launch_pack_weights(const void* d_w, void* wp, int K3, int C_in, int C_out,
     const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + bs - 1) / bs, 4096)) + (tile_long ? 1 : 0);
     ProfScope ps(kProfPackWeights, st);
     if (elem_bytes == 2)
-        k_pack_weights<uint16_t><<<nb, bs, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_long, n_tiles, again, n_clear);
+        k_pack_weights<uint16_t><<<nb, bs, 0, st>>>((const uint16_t*)d_w, (uint16_t*)wp, K3, C_in, C_out, n_clear, counters, mode, n_nt, tile_long, n_tiles, again);
     else
-        k_pack_weights<uint32_t><<<nb, bs, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, counters, mode, n_nt, tile_long, n_tiles, again, n_clear);
+        k_pack_weights<uint32_t><<<nb, bs, 0, st>>>((const uint32_t*)d_w, (uint32_t*)wp, K3, C_in, C_out, n_clear, counters, mode, n_nt, tile_long, n_tiles, again);
 }
 
 // Write-back of one column block computed with the features as the A operand: register v of
